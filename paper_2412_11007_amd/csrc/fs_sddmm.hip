@@ -5,58 +5,135 @@
 // masked by the sparsity pattern, straight into the value layout fs_spmm reads
 // (the role the paper gives its Algorithm 1).
 //
-// The contraction runs over the feature dimension d, which is contiguous in
-// the rows of both X and Y (the alignment the paper points out at the end of
-// Section 3.4), so every lane loads 16 contiguous bytes directly in matrix-core
-// operand layout: the operands need no LDS staging.  As in SpMM the operands are swapped
-// (Section 3.2): gathered Y rows are the left operand (16 vectors x 32 features),
-// the window's X rows the right operand (32 features x 16 rows, rows >= V zero).
+// As in SpMM the operands are swapped (Section 3.2): gathered Y rows are the left operand (16 vectors x 32
+// features), the window's X rows the right operand (32 features x 16 rows, rows >= V zero).
 // Vector c of a block is placed on row 8*(i/4)+4t+(i%4) -> i of tile t, so that
 // after both tiles a lane holds the eight consecutive vectors 8g..8g+7 of one
 // window row: exactly 16 contiguous bytes of the row-major value tile.
+//
+// The contraction runs over the feature dimension d, which is contiguous in the rows of both X and Y (the
+// alignment the paper points out at the end of Section 3.4), so the matrix-core operand can be loaded
+// straight from memory, 16 bytes per lane.  In operand layout neighbouring lanes read different rows, and the
+// vector-memory unit then takes a cycle per lane: 64-70 cycles per wave-wide load, 9 TB/s over the chip, however
+// often the rows hit a cache.  With neighbouring lanes on one row a load takes 18-24 cycles.  So for d > 32
+// the rows are gathered row by row like those of SpMM and turned into operand layout in LDS (R-MAT of 65 k rows,
+// d = 128: 38 -> 23.5 us; lognormal graph of 262 k rows, d = 256: 560 -> 421 us, 6.4 TB/s of rows that miss the
+// L2s).  For d <= 32 a row is half a cache line at most, the loads are few and the L2s set the time; the detour
+// costs 2-5 % there and is left out.
 #include <algorithm>
 #include <cstdlib>
 
 #include "fs_common.h"
-
-// Wavefronts per workgroup.  The wavefronts of a workgroup share nothing, and a workgroup keeps its slots
-// until its slowest wavefront is done: one per workgroup measured best (cfg 5: 122 us against 128 us with
-// four, cfg 1 and cfg 2 unchanged).
-#ifndef FS_SDDMM_WPB
-#define FS_SDDMM_WPB 1
-#endif
+#include "fs_tile.h"
 
 namespace {
 
-// One 32-vector block (all fields are wave-uniform).
-struct BlockDesc {
-    int s;   // first vector
-    int kb;  // vectors in the block, 0..32 (0: block slot of an empty window, or past the end)
-    int w;   // window
-};
+// The scores of one block, masked by the pattern, to memory.  Lane (j, g): acc[t][e] is the score of window row
+// j and vector 8g + 4t + e; msk is the occupancy mask of vector `lane` (zero past the width), rbase the CSR position
+// of row j's first entry in the block, blk the block's place in the value array (null: CSR order only).
+template <int DT, int V, bool CSR>
+__device__ __forceinline__ void fs_store_scores(const fs_f4 (&acc)[2], uint32_t msk, int kb, int rbase, int lane, uint16_t *tile,
+                                                uint16_t *__restrict__ blk, uint16_t *__restrict__ out_csr)
+{
+    const int j = lane & 15, g = lane >> 4;
+    fs_frag o;
+    o.u.x = fs_pack2<DT>(acc[0][0], acc[0][1]);
+    o.u.y = fs_pack2<DT>(acc[0][2], acc[0][3]);
+    o.u.z = fs_pack2<DT>(acc[1][0], acc[1][1]);
+    o.u.w = fs_pack2<DT>(acc[1][2], acc[1][3]);
+    // bit c of `bits`: vector c of the block stores window row j.  Wave-wide ballots over the
+    // per-vector occupancy masks, one per window row, instead of eight cross-lane reads.
+    uint32_t bits = 0;
+#pragma unroll
+    for (int r = 0; r < V; r++) {
+        const uint32_t has = (uint32_t)__ballot((msk >> r) & 1u);
+        bits = (j == r) ? has : bits;
+    }
+    const uint32_t mine = bits >> (8 * g);  // bit x: vector 8g + x
+    uint32_t keep[4];  // 0xFFFF per stored position, else 0: sign-extended single bits
+#pragma unroll
+    for (int p = 0; p < 4; p++)
+        keep[p] = ((uint32_t)__builtin_amdgcn_sbfe((int)mine, 2 * p, 1) & 0xFFFFu) |
+                  ((uint32_t)__builtin_amdgcn_sbfe((int)mine, 2 * p + 1, 1) & 0xFFFF0000u);
+    o.u.x &= keep[0]; o.u.y &= keep[1]; o.u.z &= keep[2]; o.u.w &= keep[3];
+    if constexpr (CSR) {
+        if (j < V) {
+            // CSR order: the entries of row j inside this block are consecutive positions, in vector order
+            int pos = rbase + __popc(bits & ((1u << (8 * g)) - 1u));
+#pragma unroll
+            for (int x = 0; x < 8; x++) {
+                if ((mine >> x) & 1u) out_csr[pos++] = o.e[x];
+            }
+        }
+        if (!blk) return;
+    }
+    if (kb == 32) {
+        if (j < V) *reinterpret_cast<fs_u4 *>(blk + j * 32 + 8 * g) = o.u;
+    } else {
+        // narrow last block of the window (row stride kb): gather the V x kb tile in LDS,
+        // then store its V*kb contiguous values 16 bytes per lane
+        if (j < V) {
+#pragma unroll
+            for (int x = 0; x < 8; x++) {
+                const int c = 8 * g + x;
+                if (c < kb) tile[j * kb + c] = o.e[x];
+            }
+        }
+        FS_WAVE_SYNC();
+        if (lane * 8 + 8 <= V * kb)
+            *reinterpret_cast<fs_u4 *>(blk + 8 * lane) = *reinterpret_cast<const fs_u4 *>(tile + 8 * lane);
+        else if (V == 4 && lane * 8 < V * kb)  // V = 4, odd width: the last piece holds four values
+            *reinterpret_cast<uint2 *>(blk + 8 * lane) = *reinterpret_cast<const uint2 *>(tile + 8 * lane);
+        FS_WAVE_SYNC();
+    }
+}
 
-// KS = 32-feature steps of the contraction (d <= 32*KS), BB = blocks handled per round.  A block of
-// scores depends on nothing but its own descriptor, so the work is cut into units of G consecutive
-// block slots straight from the block table (G <= 64), whatever windows they belong to.
+// Which block slots a wavefront takes; false: none.  With `items`, those of a work item, in the launch order of
+// SpMM: parts of hub windows by column, placed per XCD, so that they share rows of Y in L2 (R-MAT of 262 k rows,
+// d = 128: 132 -> 105 us).  Without, G consecutive slots straight from the block table, whatever windows they
+// belong to -- a block of scores depends on nothing but its own descriptor, and the item record would be one
+// more dependent load.  One wavefront per workgroup: wavefronts share nothing, and a workgroup keeps its slots
+// until its slowest wavefront is done.
+__device__ __forceinline__ bool fs_sddmm_unit(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n_blocks, int G,
+                                              int &first, int &nblk)
+{
+    if (items) {
+        const int turn = fs_launch_turn<1>(blockIdx.x, slice, n_swz);
+        if (turn >= n_items) return false;
+        const int4 it = items[turn];
+        first = it.x;
+        nblk = it.y;
+        return nblk > 0;
+    }
+    first = blockIdx.x * G;
+    nblk = min(G, n_blocks - first);
+    return nblk > 0;
+}
+
+// d > 32.  KS = 32-feature steps of the contraction per chunk of 32 * KS features (one chunk for d <= 32 * KS, else d is
+// walked in several); BB = blocks per step, BB * KS = 4: a step gathers its rows in eight wave-wide loads.
 // CSR: also (or only) write the scores in CSR order; kept out of the plain instantiation, whose registers it
-// would cost (d <= 32: 88 -> 101, one wavefront per SIMD fewer, 13.8 -> 15 us on cfg 2).
-template <int DT, int V, int KS, int BB, int WPB, bool BIG, bool CSR>  // BIG: X or Y spans 4 GiB or more
-__global__ void __launch_bounds__(64 * WPB)
-k_sddmm(int n_blocks, int G, const int4 *__restrict__ blk_desc,
-        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ vec_mask,
+// would cost.  BIG: X or Y spans 4 GiB or more.
+template <int DT, int V, int KS, int BB, bool CHUNKS, bool BIG, bool CSR>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n_blocks, int G, const int4 *__restrict__ blk_desc,
+        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ vec_mask, int nvec,
         const uint16_t *__restrict__ X, int64_t ldx, const uint16_t *__restrict__ Y, int64_t ldy, int d,
         uint16_t *__restrict__ out, int64_t M, uint16_t *__restrict__ out_csr, const int32_t *__restrict__ row_base)
 {
-    // 1 KB per wave: re-lays the scores of a narrow block before they are stored
-    __shared__ __attribute__((aligned(16))) uint16_t lds_all[WPB][512];
+    constexpr int LPR = 4 * KS;       // lanes that share one gathered row (16 bytes each)
+    constexpr int RPI = 64 / LPR;     // rows per wave-wide load
+    constexpr int LPB = 32 / RPI;     // wave-wide loads per block
+    constexpr int NLD = BB * LPB;     // ... and per step
+    constexpr int NF = 32 * KS;       // features per chunk
+    constexpr int RS = NF * 2 + 16;   // LDS row stride: an odd number of 16-byte pieces, so that the sixteen rows of
+                                      // an operand read start in sixteen different groups of four banks
+    __shared__ __attribute__((aligned(16))) unsigned char lds[BB * 32 * RS];
+    __shared__ __attribute__((aligned(16))) uint16_t tile[V * 32];  // re-lays the scores of a narrow block before they are stored
 
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int unit = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + wave);  // wave-uniform
-    const int first = unit * G;  // first block slot of this wavefront
-    if (first >= n_blocks) return;
-    const int nblk = min(G, n_blocks - first);
-    const int b_lo = 0, b_hi = nblk;
-    uint16_t *lds = lds_all[wave];
+    const int lane = threadIdx.x;
+    int first, nblk;  // first block slot of this wavefront, and how many
+    if (!fs_sddmm_unit(items, n_items, slice, n_swz, n_blocks, G, first, nblk)) return;
     const int j = lane & 15, g = lane >> 4;
     const unsigned char *Xb = reinterpret_cast<const unsigned char *>(X);
     const unsigned char *Yb = reinterpret_cast<const unsigned char *>(Y);
@@ -64,44 +141,196 @@ k_sddmm(int n_blocks, int G, const int4 *__restrict__ blk_desc,
 
     // descriptors of the unit's blocks (at most 64), one per lane
     const int4 my_desc = blk_desc[first + min(lane, nblk - 1)];
-    auto block = [&](int i) -> BlockDesc {  // i-th block of the unit; blocks past its end are empty
-        BlockDesc dsc;
-        const int ic = min(i, nblk - 1);
-        dsc.s = __builtin_amdgcn_readlane(my_desc.x, ic);
-        dsc.kb = i < b_hi ? (__builtin_amdgcn_readlane(my_desc.y, ic) & 255) : 0;
-        dsc.w = __builtin_amdgcn_readlane(my_desc.z, ic);
-        return dsc;
+
+    // Gather geometry.  LDS row p of a block's tile holds vector 8*((p%16)/4) + 4*(p/16) + p%4: the sixteen rows
+    // of an operand tile are then neighbours.  Lane l of load k serves LDS row k*RPI + l/LPR.
+    const int g_row = lane / LPR, g_piece = lane % LPR;
+    auto vector_of = [](int p) -> int { return 8 * ((p & 15) >> 2) + 4 * (p >> 4) + (p & 3); };
+    unsigned char *lds_wr = lds + g_row * RS + g_piece * 16;        // + k*RPI*RS per load
+    const unsigned char *lds_rd = lds + j * RS + g * 16;            // + (b*32 + 16*t)*RS + 64*ks per read
+    // features past d: the lane does not read past the row (it repeats the row's last piece), and LDS holds zeros there
+    const int n_chunks = CHUNKS ? (d + NF - 1) / NF : 1;
+    if (!CHUNKS && d < NF) {  // zero what no lane will write
+        for (int o = lane * 16; o < BB * 32 * RS; o += 64 * 16) *reinterpret_cast<fs_u4 *>(lds + o) = fs_u4{0u, 0u, 0u, 0u};
+        FS_WAVE_SYNC();
+    }
+
+    // With sixteen lanes per row every group of 16 lanes wants one index per load: lane i of a group holds the
+    // index for load i and a DPP move hands it out.  Shorter rows keep the indices one per vector.
+    // Both loads take a scalar base and a small lane offset.  Lanes past the block's width repeat its last vector;
+    // the slot of an empty window reads some valid element.
+    const uint32_t v_byte = 4 * (LPR == 16 ? vector_of(((lane & 15) * RPI + g_row) & 31) : (lane & 31));
+    auto load_cols = [&](const BlockDesc &b) -> int {
+        const char *base = reinterpret_cast<const char *>(vec_col + min(b.s, nvec - 1));
+        return *reinterpret_cast<const int32_t *>(base + min(v_byte, 4u * (uint32_t)(max(b.kb, 1) - 1)));
+    };
+    auto load_mask = [&](const BlockDesc &b) -> uint32_t {
+        const char *base = reinterpret_cast<const char *>(vec_mask + min(b.s, nvec - 1));
+        const uint32_t m = *reinterpret_cast<const uint32_t *>(base + min(4u * (uint32_t)lane, 4u * (uint32_t)(max(b.kb, 1) - 1)));
+        return lane < b.kb ? m : 0u;
+    };
+    fs_u4 stage[NLD];
+    uint32_t grow[NLD];  // byte offsets of the rows this lane gathers in a step (row numbers if BIG)
+    auto rows_of = [&](const int (&cols)[BB]) {
+        fs_for_each_index([&](auto k_) {
+            constexpr int k = decltype(k_)::value, b = k / LPB, l = k % LPB;
+            int idx;
+            if constexpr (LPR == 16) idx = fs_row_bcast<l>(cols[b]);
+            else idx = __shfl(cols[b], vector_of(l * RPI + g_row), 64);
+            grow[k] = BIG ? (uint32_t)idx : __umul24((uint32_t)idx, ldy2);
+        }, std::make_integer_sequence<int, NLD>{});
+    };
+    auto gather = [&](int f_base) {
+        const int f = max(min(f_base + g_piece * 8, d - 8), 0);
+#pragma unroll
+        for (int k = 0; k < NLD; k++)
+            stage[k] = *reinterpret_cast<const fs_u4 *>(Yb + (BIG ? (uint64_t)grow[k] * ldy2 : (uint64_t)grow[k]) + 2 * (uint32_t)f);
+    };
+    // X operand of a block: lane (j, g) holds X[w*V + j][f_base + 32*ks + 8g .. +7]; rows past V or M are zero
+    auto load_x = [&](int w, int f_base, fs_frag (&x)[KS]) {
+        const int64_t row = (int64_t)w * V + j;
+        const bool ok = j < V && row < M;
+        const uint64_t off = BIG ? (uint64_t)row * ldx2 : (uint64_t)__umul24((uint32_t)row, ldx2);
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) {
+            const int f = f_base + 32 * ks + 8 * g;
+            x[ks].u = fs_u4{0u, 0u, 0u, 0u};
+            if (ok && f < d) x[ks].u = *reinterpret_cast<const fs_u4 *>(Xb + off + 2 * (uint32_t)f);
+        }
     };
 
-    for (int b0 = b_lo; b0 < b_hi; b0 += BB) {
+    const int n_steps = (nblk + BB - 1) / BB;
+    BlockDesc cur[BB], nxt[BB];
+    int col[BB];
+    uint32_t msk[BB], msk_n[BB];
+    fs_frag xf[BB][KS];
+    auto load_xs = [&](const BlockDesc (&blk)[BB], int f_base) {
+#pragma unroll
+        for (int b = 0; b < BB; b++) load_x(blk[b].w, f_base, xf[b]);
+    };
+    // the indices and masks of a later step, loaded ahead
+    auto look_ahead = [&](int st) {
+#pragma unroll
+        for (int b = 0; b < BB; b++) {
+            nxt[b] = fs_item_block(my_desc, st * BB + b, nblk);
+            col[b] = load_cols(nxt[b]);
+            msk_n[b] = load_mask(nxt[b]);
+        }
+    };
+#pragma unroll
+    for (int b = 0; b < BB; b++) {
+        cur[b] = fs_item_block(my_desc, b, nblk);
+        col[b] = load_cols(cur[b]);
+        msk[b] = load_mask(cur[b]);
+    }
+    rows_of(col);
+    gather(0);
+    if constexpr (!CHUNKS) load_xs(cur, 0);
+    look_ahead(1);
+    for (int st = 0; st < n_steps; st++) {
+        const bool more = st + 1 < n_steps;
+        fs_f4 acc[BB][2];
+#pragma unroll
+        for (int b = 0; b < BB; b++)
+#pragma unroll
+            for (int t = 0; t < 2; t++) acc[b][t] = fs_f4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < n_chunks; c++) {
+            if constexpr (CHUNKS) load_xs(cur, c * NF);
+            // the gathered rows go to LDS (this is where the wave waits for the gather), and the next gather starts
+            if (c * NF + g_piece * 8 < d) {
+#pragma unroll
+                for (int k = 0; k < NLD; k++) *reinterpret_cast<fs_u4 *>(lds_wr + k * RPI * RS) = stage[k];
+            } else if (CHUNKS) {
+#pragma unroll
+                for (int k = 0; k < NLD; k++) *reinterpret_cast<fs_u4 *>(lds_wr + k * RPI * RS) = fs_u4{0u, 0u, 0u, 0u};
+            }
+            if (CHUNKS && c + 1 < n_chunks) gather((c + 1) * NF);
+            else if (more) {
+                rows_of(col);
+                gather(0);
+            }
+            FS_WAVE_SYNC();
+#pragma unroll
+            for (int b = 0; b < BB; b++)
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+#pragma unroll
+                    for (int ks = 0; ks < KS; ks++) {
+                        fs_frag y;
+                        y.u = *reinterpret_cast<const fs_u4 *>(lds_rd + (b * 32 + 16 * t) * RS + 64 * ks);
+                        acc[b][t] = fs_mfma_16x16x32<DT>(y, xf[b][ks], acc[b][t]);
+                    }
+            FS_WAVE_SYNC();
+        }
+#pragma unroll
+        for (int u = 0; u < BB; u++) {
+            const int kb = cur[u].kb;
+            if (kb <= 0) continue;
+            int rbase = 0;
+            if constexpr (CSR) rbase = j < V ? row_base[(int64_t)(first + st * BB + u) * V + j] : 0;
+            fs_store_scores<DT, V, CSR>(acc[u], msk[u], kb, rbase, lane, tile, out ? out + (int64_t)V * cur[u].s : nullptr, out_csr);
+        }
+        if (more) {
+#pragma unroll
+            for (int b = 0; b < BB; b++) {
+                // blocks of one window keep its rows of X (in operand layout, so a load of half a step's gather)
+                if (!CHUNKS && nxt[b].w != cur[b].w) load_x(nxt[b].w, 0, xf[b]);
+                cur[b] = nxt[b];
+                msk[b] = msk_n[b];
+            }
+            look_ahead(st + 2);
+        }
+    }
+}
+
+// d <= 32: a round of four blocks loads every block's indices, masks and rows of X, then every row of Y, straight
+// in operand layout (see above), so that it costs two memory round trips however many blocks it holds.
+template <int DT, int V, bool BIG, bool CSR>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CSR ? 5 : 6)))
+k_sddmm_short(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n_blocks, int G, const int4 *__restrict__ blk_desc,
+        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ vec_mask, int,
+        const uint16_t *__restrict__ X, int64_t ldx, const uint16_t *__restrict__ Y, int64_t ldy, int d,
+        uint16_t *__restrict__ out, int64_t M, uint16_t *__restrict__ out_csr, const int32_t *__restrict__ row_base)
+{
+    constexpr int BB = 4;  // blocks per round
+    __shared__ __attribute__((aligned(16))) uint16_t lds[V * 32];  // re-lays the scores of a narrow block before they are stored
+
+    const int lane = threadIdx.x;
+    int first, nblk;
+    if (!fs_sddmm_unit(items, n_items, slice, n_swz, n_blocks, G, first, nblk)) return;
+    const int j = lane & 15, g = lane >> 4;
+    const unsigned char *Xb = reinterpret_cast<const unsigned char *>(X);
+    const unsigned char *Yb = reinterpret_cast<const unsigned char *>(Y);
+    const uint32_t ldx2 = (uint32_t)ldx * 2, ldy2 = (uint32_t)ldy * 2;  // bytes between rows
+
+    // descriptors of the unit's blocks (at most 64), one per lane
+    const int4 my_desc = blk_desc[first + min(lane, nblk - 1)];
+
+    for (int b0 = 0; b0 < nblk; b0 += BB) {
         // round of up to BB blocks: first every block's indices, masks and X rows, then every Y row,
         // so that a round costs two memory round trips however many blocks it holds
         BlockDesc dsc[BB];
         int col[BB];
         uint32_t msk[BB];
         int rbase[BB];  // CSR position of window row j's first entry in the block (CSR-order output only)
-        fs_frag xf[BB][KS];
+        fs_frag xf[BB];
 #pragma unroll
         for (int u = 0; u < BB; u++) {
-            dsc[u] = block(b0 + u);
+            dsc[u] = fs_item_block(my_desc, b0 + u, nblk);
             col[u] = (lane < dsc[u].kb) ? vec_col[dsc[u].s + lane] : -1;
             msk[u] = (lane < dsc[u].kb) ? vec_mask[dsc[u].s + lane] : 0u;
             rbase[u] = 0;
-            if constexpr (CSR) rbase[u] = (j < V && b0 + u < b_hi) ? row_base[(int64_t)(first + b0 + u) * V + j] : 0;
-            // X operand: lane (j, g) holds X[w*V + j][32*ks + 8g .. +7]; rows past V or M are zero
+            if constexpr (CSR) rbase[u] = (j < V && b0 + u < nblk) ? row_base[(int64_t)(first + b0 + u) * V + j] : 0;
+            // X operand: lane (j, g) holds X[w*V + j][8g .. 8g+7]; rows past V or M are zero
             const int64_t xrow = (int64_t)dsc[u].w * V + j;
             const bool x_ok = dsc[u].kb > 0 && j < V && xrow < M;
             const uint64_t xoff = BIG ? (uint64_t)xrow * ldx2 : (uint64_t)__umul24((uint32_t)xrow, ldx2);
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++) {
-                const int f0 = 32 * ks + 8 * g;
-                xf[u][ks].u = fs_u4{0u, 0u, 0u, 0u};
-                if (x_ok && f0 < d) xf[u][ks].u = *reinterpret_cast<const fs_u4 *>(Xb + xoff + 2 * f0);
-            }
+            xf[u].u = fs_u4{0u, 0u, 0u, 0u};
+            if (x_ok && 8 * g < d) xf[u].u = *reinterpret_cast<const fs_u4 *>(Xb + xoff + 16 * g);
         }
         // Y operand: matrix row j of tile t is vector 8*(j/4) + 4t + (j%4) of the block; vectors past the
         // block's width re-read its first row and are masked out below
-        fs_frag yf[BB][2][KS];
+        fs_frag yf[BB][2];
 #pragma unroll
         for (int u = 0; u < BB; u++) {
             const int first = max(__builtin_amdgcn_readfirstlane(col[u]), 0);
@@ -110,12 +339,8 @@ k_sddmm(int n_blocks, int G, const int4 *__restrict__ blk_desc,
                 int yrow = __shfl(col[u], 8 * (j >> 2) + 4 * t + (j & 3), 64);
                 yrow = yrow < 0 ? first : yrow;
                 const uint64_t yoff = BIG ? (uint64_t)yrow * ldy2 : (uint64_t)__umul24((uint32_t)yrow, ldy2);
-#pragma unroll
-                for (int ks = 0; ks < KS; ks++) {
-                    const int f0 = 32 * ks + 8 * g;
-                    yf[u][t][ks].u = *reinterpret_cast<const fs_u4 *>(Yb + yoff + 2 * (f0 < d ? f0 : 0));
-                    if (f0 >= d) yf[u][t][ks].u = fs_u4{0u, 0u, 0u, 0u};
-                }
+                yf[u][t].u = *reinterpret_cast<const fs_u4 *>(Yb + yoff + (8 * g < d ? 16 * g : 0));
+                if (8 * g >= d) yf[u][t].u = fs_u4{0u, 0u, 0u, 0u};
             }
         }
 #pragma unroll
@@ -124,126 +349,8 @@ k_sddmm(int n_blocks, int G, const int4 *__restrict__ blk_desc,
             if (kb <= 0) continue;
             fs_f4 acc[2];
 #pragma unroll
-            for (int t = 0; t < 2; t++) {
-                acc[t] = fs_f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KS; ks++) acc[t] = fs_mfma_16x16x32<DT>(yf[u][t][ks], xf[u][ks], acc[t]);
-            }
-            // lane (j, g): acc[t][e] is the score of window row j and vector 8g + 4t + e
-            fs_frag o;
-            o.u.x = fs_pack2<DT>(acc[0][0], acc[0][1]);
-            o.u.y = fs_pack2<DT>(acc[0][2], acc[0][3]);
-            o.u.z = fs_pack2<DT>(acc[1][0], acc[1][1]);
-            o.u.w = fs_pack2<DT>(acc[1][2], acc[1][3]);
-            // bit c of `bits`: vector c of the block stores window row j.  Wave-wide ballots over the
-            // per-vector occupancy masks, one per window row, instead of eight cross-lane reads.
-            uint32_t bits = 0;
-#pragma unroll
-            for (int r = 0; r < V; r++) {
-                const uint32_t has = (uint32_t)__ballot((msk[u] >> r) & 1u);
-                bits = (j == r) ? has : bits;
-            }
-            const uint32_t mine = bits >> (8 * g);  // bit x: vector 8g + x
-            uint32_t keep[4];  // 0xFFFF per stored position, else 0
-#pragma unroll
-            for (int p = 0; p < 4; p++)
-                keep[p] = (((mine >> (2 * p)) & 1u) ? 0xFFFFu : 0u) | (((mine >> (2 * p + 1)) & 1u) ? 0xFFFF0000u : 0u);
-            o.u.x &= keep[0]; o.u.y &= keep[1]; o.u.z &= keep[2]; o.u.w &= keep[3];
-            if constexpr (CSR) {
-                if (j < V) {
-                    // CSR order: the entries of row j inside this block are consecutive positions, in vector order
-                    int pos = rbase[u] + __popc(bits & ((1u << (8 * g)) - 1u));
-#pragma unroll
-                    for (int x = 0; x < 8; x++) {
-                        if ((mine >> x) & 1u) out_csr[pos++] = o.e[x];
-                    }
-                }
-                if (!out) continue;
-            }
-            uint16_t *blk = out + (int64_t)V * dsc[u].s;
-            if (kb == 32) {
-                if (j < V) *reinterpret_cast<fs_u4 *>(blk + j * 32 + 8 * g) = o.u;
-            } else {
-                // narrow last block of the window (row stride kb): gather the V x kb tile in LDS,
-                // then store its V*kb contiguous values 16 bytes per lane
-                if (j < V) {
-#pragma unroll
-                    for (int x = 0; x < 8; x++) {
-                        const int c = 8 * g + x;
-                        if (c < kb) lds[j * kb + c] = o.e[x];
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                if (lane * 8 + 8 <= V * kb)
-                    *reinterpret_cast<fs_u4 *>(blk + 8 * lane) = *reinterpret_cast<const fs_u4 *>(lds + 8 * lane);
-                else if (V == 4 && lane * 8 < V * kb)  // V = 4, odd width: the last piece holds four values
-                    *reinterpret_cast<uint2 *>(blk + 8 * lane) = *reinterpret_cast<const uint2 *>(lds + 8 * lane);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
-        }
-    }
-}
-
-// Generic fallback for long feature dimensions (d > 128): one block at a time, the contraction in
-// 32-feature steps with both operands loaded per step.
-template <int DT, int V, int WPB>
-__global__ void __launch_bounds__(64 * WPB)
-k_sddmm_long(int n_blocks, int G, const int4 *__restrict__ blk_desc,
-             const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ vec_mask,
-             const uint16_t *__restrict__ X, int64_t ldx, const uint16_t *__restrict__ Y, int64_t ldy, int d,
-             uint16_t *__restrict__ out, int64_t M, uint16_t *__restrict__ out_csr, const int32_t *__restrict__ row_base)
-{
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int unit = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + wave);
-    const int first = unit * G;
-    if (first >= n_blocks) return;
-    const int nblk = min(G, n_blocks - first);
-    const int j = lane & 15, g = lane >> 4;
-    const int nsteps = (d + 31) / 32;
-    for (int step = 0; step < nblk; step++) {
-        const int4 dsc = blk_desc[first + step];
-        const int s = dsc.x, kb = dsc.y & 255, w = dsc.z;
-        if (kb > 0) {
-            const int my_col = (lane < kb) ? vec_col[s + lane] : -1;
-            const uint32_t my_mask = (lane < kb) ? vec_mask[s + lane] : 0u;
-            const int64_t xrow = (int64_t)w * V + j;
-            const bool x_ok = j < V && xrow < M;
-            fs_f4 acc[2];
-#pragma unroll
-            for (int t = 0; t < 2; t++) {
-                acc[t] = fs_f4{0.f, 0.f, 0.f, 0.f};
-                const int64_t yrow = __shfl(my_col, 8 * (j >> 2) + 4 * t + (j & 3), 64);
-                for (int ks = 0; ks < nsteps; ks++) {
-                    const int f0 = 32 * ks + 8 * g;
-                    fs_frag yf, xx;
-                    yf.u = fs_u4{0u, 0u, 0u, 0u};
-                    xx.u = fs_u4{0u, 0u, 0u, 0u};
-                    if (yrow >= 0 && f0 < d) yf.u = *reinterpret_cast<const fs_u4 *>(Y + yrow * ldy + f0);
-                    if (x_ok && f0 < d) xx.u = *reinterpret_cast<const fs_u4 *>(X + xrow * ldx + f0);
-                    acc[t] = fs_mfma_16x16x32<DT>(yf, xx, acc[t]);
-                }
-            }
-            (void)my_mask;
-            if (j < V) {
-                uint16_t *blk = out ? out + (int64_t)V * s : nullptr;
-                int pos = out_csr ? row_base[(int64_t)(first + step) * V + j] : 0;
-                for (int c = 0; c < 8 * g && out_csr; c++) pos += (c < kb && ((vec_mask[s + c] >> j) & 1u)) ? 1 : 0;
-#pragma unroll
-                for (int x = 0; x < 8; x++) {
-                    const int c = 8 * g + x;
-                    if (c < kb) {
-                        const uint32_t m = vec_mask[s + c];
-                        const bool stored = (m >> j) & 1u;
-                        const uint16_t v = stored ? fs_round_bits<DT>(acc[x >> 2][x & 3]) : (uint16_t)0;
-                        if (blk) blk[j * kb + c] = v;
-                        if (out_csr && stored) out_csr[pos++] = v;
-                    }
-                }
-            }
+            for (int t = 0; t < 2; t++) acc[t] = fs_mfma_16x16x32<DT>(yf[u][t], xf[u], fs_f4{0.f, 0.f, 0.f, 0.f});
+            fs_store_scores<DT, V, CSR>(acc, msk[u], kb, rbase[u], lane, lds, out ? out + (int64_t)V * dsc[u].s : nullptr, out_csr);
         }
     }
 }
@@ -254,10 +361,12 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
 {
     if (f->n_blocks == 0) return FS_OK;
     const int n_blocks = (int)f->n_blocks;
-    constexpr int WPB = FS_SDDMM_WPB;
-    // blocks per wavefront: whole rounds, 4 to 16 blocks, about 16384 wavefronts on large matrices
-    // (measured: 4 to 8 blocks are best from 30 thousand to 180 thousand blocks, 16 and more lose 5-15 %)
-    int G = (int)std::min<int64_t>(std::max<int64_t>(((n_blocks + 16383) / 16384 + 3) / 4 * 4, 4), 16);
+    // The launch order pays where hub windows hold a good part of the work and Y is more than one XCD's L2 holds
+    // (R-MAT, d = 32: 47 -> 44 us with 16 MB of Y, 12.7 -> 13.0 us with 4 MB); otherwise four block slots per
+    // wavefront (4 to 8 measured best from 30 thousand to 200 thousand blocks, 16 and more lose 5-15 %).
+    const bool ordered = f->n_cut_items * 8 >= f->n_items && f->K * ldy * 2 > ((int64_t)4 << 20);
+    const int4 *items = ordered ? (const int4 *)f->items_by_cost : nullptr;
+    int G = 4;
 #ifdef FS_TUNING_ENV  // tuning builds only (-DFS_TUNING_ENV): the shipped library reads no environment
     if (const char *e = getenv("FS_SDDMM_G")) G = std::min(std::max(atoi(e), 1), 64);
 #endif
@@ -265,23 +374,23 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
     const bool big = f->K >= ((int64_t)1 << 24) || f->M >= ((int64_t)1 << 24) || ldx * 2 >= ((int64_t)1 << 24) ||
                      ldy * 2 >= ((int64_t)1 << 24) || f->K * ldy * 2 >= ((int64_t)1 << 32) ||
                      (f->M + 32) * ldx * 2 >= ((int64_t)1 << 32);
-    const int64_t units = ((int64_t)n_blocks + G - 1) / G;
-    const dim3 grid((unsigned)((units + WPB - 1) / WPB)), block(64 * WPB);
-#define FS_SDDMM_ARGS n_blocks, G, (const int4 *)f->blk_desc, f->vec_col, f->vec_mask, X, ldx, Y, ldy, (int)d, out, f->M, out_csr, f->blk_row_base
-#define FS_SDDMM_LAUNCH(KS, BB)                                                                           \
+    const fs_launch_geometry geo = fs_launch_geometry_for(f, 1);
+    const dim3 grid(ordered ? (unsigned)geo.nbx : (unsigned)(((int64_t)n_blocks + G - 1) / G)), block(64);
+#define FS_SDDMM_ARGS items, (int)f->n_items, geo.slice, geo.n_swz, n_blocks, G, (const int4 *)f->blk_desc, f->vec_col, f->vec_mask, (int)f->nvec, X, ldx, Y, ldy, (int)d, out, f->M, out_csr, f->blk_row_base
+#define FS_SDDMM_LAUNCH(...)  /* the kernel and its first template arguments */                         \
     {                                                                                                     \
         if (out_csr) {                                                                                    \
-            if (big) k_sddmm<DT, V, KS, BB, WPB, true, true><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);      \
-            else k_sddmm<DT, V, KS, BB, WPB, false, true><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);         \
+            if (big) __VA_ARGS__, true, true><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);                     \
+            else __VA_ARGS__, false, true><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);                        \
         } else {                                                                                          \
-            if (big) k_sddmm<DT, V, KS, BB, WPB, true, false><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);     \
-            else k_sddmm<DT, V, KS, BB, WPB, false, false><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);        \
+            if (big) __VA_ARGS__, true, false><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);                    \
+            else __VA_ARGS__, false, false><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);                       \
         }                                                                                                 \
     }
-    if (d <= 32) FS_SDDMM_LAUNCH(1, 4)
-    else if (d <= 64) FS_SDDMM_LAUNCH(2, 2)
-    else if (d <= 128) FS_SDDMM_LAUNCH(4, 1)
-    else k_sddmm_long<DT, V, WPB><<<grid, block, 0, st>>>(FS_SDDMM_ARGS);
+    if (d <= 32) FS_SDDMM_LAUNCH(k_sddmm_short<DT, V)
+    else if (d <= 64) FS_SDDMM_LAUNCH(k_sddmm<DT, V, 2, 2, false)
+    else if (d <= 128) FS_SDDMM_LAUNCH(k_sddmm<DT, V, 4, 1, false)
+    else FS_SDDMM_LAUNCH(k_sddmm<DT, V, 4, 1, true)
 #undef FS_SDDMM_LAUNCH
 #undef FS_SDDMM_ARGS
     FS_LAUNCH_CHECK();
