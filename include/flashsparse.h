@@ -92,6 +92,8 @@ typedef enum { FS_F16 = 0, FS_BF16 = 1 } fs_dtype;
  *                  window row r whose column is not below the column of slot x's first vector (the end of
  *                  the row if there is none).  With the occupancy masks this locates every entry of a
  *                  block in CSR order: fs_sddmm writes CSR-order output with it
+ *   blk_row_bits   V uint32 per block slot (KB = 32 only, else NULL): [x * V + r] = the vectors of block x that window
+ *                  row r stores, bit c for the block's vector c (the occupancy masks, seen from a row)
  *   split_windows  n_split_windows records of four int32
  *                  {window, first partial slot, number of slots, 0}: the partial
  *                  tiles of a cut window are consecutive slots
@@ -122,6 +124,7 @@ typedef struct fs_format {
                                      built by fs_convert for large matrices with long rows, read by fs_spmm */
     const int32_t *slot_range;    /* 2 * n_split_items: per partial-tile slot {first slot of its window, slots of the window}:
                                      what a part of a cut window needs to find the other parts' statistics (fs_edge_softmax) */
+    const uint32_t *blk_row_bits; /* V * n_blocks, or NULL for KB != 32 */
     size_t arena_used;            /* bytes of the arena actually occupied */
 } fs_format;
 

@@ -41,6 +41,7 @@ class _FsFormatStruct(ctypes.Structure):
         ("blk_row_base", ctypes.c_void_p),
         ("packed", ctypes.c_void_p),
         ("slot_range", ctypes.c_void_p),
+        ("blk_row_bits", ctypes.c_void_p),
         ("arena_used", ctypes.c_size_t),
     ]
 
@@ -202,6 +203,10 @@ class FsFormat:
     def blk_row_base_t(self):
         import torch
         return self._view(self.c.blk_row_base, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
+
+    def blk_row_bits_t(self):
+        import torch
+        return self._view(self.c.blk_row_bits, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
 
     def split_windows_t(self):
         import torch

@@ -5,27 +5,27 @@
 // library's own.  It needs no sort and no atomics, so the output is
 // deterministic and bit-identical to a sequential construction:
 //
-//   1. flag   one thread per stored entry (row i, column c): the entry LEADS its
-//             nonzero vector iff no earlier row of the same window stores c
-//             (binary search in each earlier row; CSR rows are sorted).
-//   2. scan   exclusive prefix sum L of the flags over CSR order.  Entries of a
-//             window are contiguous in CSR order, so L at a window's first entry
-//             is the index of its first vector: win_ptr[w] = L[rowptr[w*V]].
-//   3. emit   one thread per entry: the position of column c among the window's
-//             distinct columns is the number of leaders with a smaller column,
-//             summed over the window's rows with one lower_bound and two reads
-//             of L per row.  Leaders write vec_col / vec_mask; every entry
-//             writes its value into its slot and records the slot.
-//   4. items  a descriptor per 32-vector block, and the work items: windows longer than one and a half
-//             times `chunk` vectors are cut into equal parts of about `chunk` vectors, shorter ones are
-//             packed whole into items of about four blocks (boundary candidates, flag, scan, compact).
+//   1. units  at most 512 stored entries each, one wavefront's work: a few windows, one window, or a range of
+//             columns of a hub window (fs_units.h).
+//   2. rank   a unit's rows are merged in LDS; an entry's rank is the number of distinct columns before its
+//             own.  Ranks stay per unit (two bytes per entry); a prefix sum over the units' vector counts gives
+//             every unit's first vector, and with it win_ptr.
+//   3. place  the same units write vec_col, vec_mask, csr_to_slot, the value array (put together in LDS, so that it
+//             is written once, whole), a descriptor per block and, for blocks of 32 vectors, the rows'
+//             occupancy and CSR positions and the bitmap-packed copy of the values.
+//   4. items  windows longer than one and a half times `chunk` vectors are cut into equal parts of about `chunk`
+//             vectors, shorter ones are packed whole into items of about four blocks (boundary candidates, scan,
+//             compact), and the items are put in launch order.
+//
+// A small matrix is bound by the number of launches, about 5 us each, and by the one time the host waits for the
+// sizes (R-MAT of 65 k rows, 0.9 M entries: 35 launches, 292 us; now 19 and 222 us).
 #include <algorithm>
 #include <cstdlib>
 
 #include "fs_common.h"
-#include "fs_rows.h"
 #include "fs_scan.h"
 #include "fs_sort.h"
+#include "fs_units.h"
 
 namespace {
 
@@ -36,190 +36,6 @@ constexpr int kMaxItemBlocks = 32;  // a part of a cut window never has more blo
 constexpr int kDefaultMaxPartBlocks = 16;
 constexpr int kPackBlocks = 4;      // packing grain for short windows, in blocks
 constexpr int kMaxItemSlots = 64;   // the compute kernels hold an item's block descriptors one per lane
-
-// ---------------------------------------------------------------- CSR helpers
-struct CsrView {
-    const int32_t *rowptr;
-    const int32_t *colidx;
-    int64_t M;
-    int32_t nnz;
-};
-
-// Row bounds clamped into [0, nnz] so that a malformed rowptr can never cause an out-of-range read.
-__device__ __forceinline__ void row_range(const CsrView &a, int64_t i, int32_t &lo, int32_t &hi)
-{
-    lo = min(max(a.rowptr[i], 0), a.nnz);
-    hi = min(max(a.rowptr[i + 1], lo), a.nnz);
-}
-
-// An int32 array element by its byte offset: with a 32-bit offset from a pointer that is the same for the
-// whole wavefront the load needs no address arithmetic of its own.
-__device__ __forceinline__ int32_t at_byte(const int32_t *__restrict__ a, uint32_t off)
-{
-    return *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(a) + off);
-}
-
-// For up to G rows at once: base[u] moves to the first position in [base[u], base[u] + n[u]) whose column
-// is >= c (to base[u] + n[u] if there is none), and hit[u] says whether that column is c itself.  Positions
-// are byte offsets into colidx (base[u] = 4 * index); 32 bits hold them because a window has other rows
-// to search only for V >= 2, where V * nnz < 2^31 keeps 4 * nnz below 2^32.  Halving without branches:
-// every round probes the middle of what is left of each row -- G independent loads in flight together, five
-// instructions per row -- and the number of rounds is that of the longest row; the last round reads the two
-// positions the answer can be, so that the comparison with c needs no load of its own.  A row with
-// n[u] == 0 is left alone (no hit); its base must still be a valid offset, because the rounds read it.
-// `last` = the offset of the last element of colidx.
-template <int G>
-__device__ __forceinline__ void lower_bound_cols(const int32_t *__restrict__ colidx, uint32_t last, uint32_t (&base)[G],
-                                                 int32_t (&n)[G], int32_t c, bool (&hit)[G])
-{
-    int32_t nmax = 0;
-#pragma unroll
-    for (int u = 0; u < G; u++) nmax = max(nmax, n[u]);
-    for (; nmax > 1; nmax -= nmax >> 1) {  // n -> ceil(n / 2) per round, for every row
-        int32_t half[G], v[G];
-        uint32_t probe[G];
-#pragma unroll
-        for (int u = 0; u < G; u++) {
-            half[u] = n[u] >> 1;
-            probe[u] = base[u] + ((uint32_t)half[u] << 2);
-            v[u] = at_byte(colidx, probe[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < G; u++) {
-            base[u] = v[u] < c ? probe[u] : base[u];
-            n[u] -= half[u];
-        }
-    }
-    // the answer is base[u] or the element after it (which may be the end of the row: the caller knows)
-    int32_t v0[G], v1[G];
-#pragma unroll
-    for (int u = 0; u < G; u++) {
-        v0[u] = at_byte(colidx, base[u]);
-        v1[u] = at_byte(colidx, min(base[u] + 4u, last));
-    }
-#pragma unroll
-    for (int u = 0; u < G; u++) {
-        const bool some = n[u] > 0, below = some && v0[u] < c;
-        hit[u] = some && (below ? v1[u] == c : v0[u] == c);
-        base[u] += below ? 4u : 0u;
-    }
-}
-
-__global__ void k_check_rowptr(CsrView a, int *__restrict__ err)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > a.M) return;
-    int32_t x = a.rowptr[i];
-    bool bad = x < 0 || x > a.nnz;
-    if (i == 0 && x != 0) bad = true;
-    if (i == a.M && x != a.nnz) bad = true;
-    if (i < a.M && a.rowptr[i + 1] < x) bad = true;
-    if (bad) atomicOr(err, 1);
-}
-
-// Step 1: leader flags (+ the column checks of the CSR contract).
-__global__ void __launch_bounds__(kEntriesPerGroup) k_flag(CsrView a, int64_t K, int V, const int32_t *__restrict__ block_rows,
-                                                            int *__restrict__ flag, int *__restrict__ err)
-{
-    __shared__ int32_t sh_ptr[kEntriesPerGroup];
-    const int64_t p64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = group_row_of(a.rowptr, a.nnz, p64, block_rows, sh_ptr);
-    if (i < 0) return;
-    const int32_t p = (int32_t)p64;
-    const int32_t c = a.colidx[p];
-    int32_t lo, hi;
-    row_range(a, i, lo, hi);
-    if (c < 0 || c >= K || (p > lo && a.colidx[p - 1] >= c)) atomicOr(err, 2);
-    const int32_t w0 = ((int32_t)i / V) * V, rows_before = (int32_t)i - w0;
-    int leader = 1;
-    constexpr int G = 8;
-    for (int t0 = 0; t0 < rows_before && leader; t0 += G) {  // the earlier rows of the window, G at a time
-        uint32_t base[G], end[G];
-        int32_t n[G], rp[G + 1];
-        bool hit[G];
-#pragma unroll
-        for (int u = 0; u <= G; u++) rp[u] = min(max(a.rowptr[min(w0 + t0 + u, (int32_t)i)], 0), a.nnz);
-#pragma unroll
-        for (int u = 0; u < G; u++) {
-            base[u] = end[u] = 4u * (uint32_t)p;  // no row, or an empty one: nothing to search, and a valid offset
-            if (t0 + u < rows_before && rp[u + 1] > rp[u]) { base[u] = 4u * (uint32_t)rp[u]; end[u] = 4u * (uint32_t)rp[u + 1]; }
-            n[u] = (int32_t)((end[u] - base[u]) >> 2);
-        }
-        lower_bound_cols<G>(a.colidx, 4u * (uint32_t)(a.nnz - 1), base, n, c, hit);
-#pragma unroll
-        for (int u = 0; u < G; u++)
-            if (hit[u] && base[u] < end[u]) leader = 0;
-    }
-    flag[p] = leader;
-}
-
-// Step 2b: window pointers from the scanned flags, and every window's number of block slots.
-__global__ void k_win_ptr(CsrView a, int V, int64_t W, const int *__restrict__ L, int32_t *__restrict__ win_ptr, int KB,
-                          int *__restrict__ nblk)
-{
-    int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (w > W) return;
-    const int32_t p = L[min(max(a.rowptr[min(w * V, a.M)], 0), a.nnz)];
-    win_ptr[w] = p;
-    if (w < W) {
-        const int32_t p1 = L[min(max(a.rowptr[min((w + 1) * V, a.M)], 0), a.nnz)];
-        nblk[w] = max(1, (p1 - p + KB - 1) / KB);
-    }
-}
-
-// Step 3: vectors, masks, slots and values.
-template <typename T>
-__global__ void __launch_bounds__(kEntriesPerGroup) k_emit(CsrView a, int V, int KB, const int32_t *__restrict__ block_rows,
-                                                            const int *__restrict__ L,
-                                              const int32_t *__restrict__ win_ptr, const T *__restrict__ vals,
-                                              int32_t *__restrict__ vec_col, uint32_t *__restrict__ vec_mask,
-                                              int32_t *__restrict__ csr_to_slot, T *__restrict__ vals_blk)
-{
-    __shared__ int32_t sh_ptr[kEntriesPerGroup];
-    const int64_t p64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = group_row_of(a.rowptr, a.nnz, p64, block_rows, sh_ptr);
-    if (i < 0) return;
-    const int32_t p = (int32_t)p64;
-    const int32_t c = a.colidx[p];
-    const int32_t w = (int32_t)i / V, w0 = w * V, own = (int32_t)i - w0;
-    const int32_t rows = (int32_t)min((int64_t)V, a.M - w0);  // rows of this window
-    int32_t lo_i, hi_i;
-    row_range(a, i, lo_i, hi_i);
-    int32_t rank = L[p] - L[lo_i];  // leaders of its own row with a column below c: the position is known
-    uint32_t mask = 1u << own;
-    constexpr int G = 8;
-    for (int t0 = 0; t0 < rows; t0 += G) {  // the other rows of the window, G at a time
-        uint32_t base[G], beg[G], end[G];
-        int32_t n[G], rp[G + 1];
-        bool hit[G];
-#pragma unroll
-        for (int u = 0; u <= G; u++) rp[u] = min(max(a.rowptr[min(w0 + t0 + u, w0 + rows)], 0), a.nnz);
-#pragma unroll
-        for (int u = 0; u < G; u++) {
-            base[u] = end[u] = 4u * (uint32_t)p;  // no row, its own or an empty one: nothing to search, and a valid offset
-            if (t0 + u < rows && t0 + u != own && rp[u + 1] > rp[u]) { base[u] = 4u * (uint32_t)rp[u]; end[u] = 4u * (uint32_t)rp[u + 1]; }
-            beg[u] = base[u];
-            n[u] = (int32_t)((end[u] - base[u]) >> 2);
-        }
-        lower_bound_cols<G>(a.colidx, 4u * (uint32_t)(a.nnz - 1), base, n, c, hit);
-#pragma unroll
-        for (int u = 0; u < G; u++) {
-            rank += at_byte(L, base[u]) - at_byte(L, beg[u]);  // leaders of this row with a column below c
-            if (hit[u] && base[u] < end[u]) mask |= 1u << (t0 + u);
-        }
-    }
-    const int32_t first = win_ptr[w];
-    const int32_t n_w = win_ptr[w + 1] - first;
-    if (L[p + 1] != L[p]) {  // this entry leads its vector
-        vec_col[first + rank] = c;
-        vec_mask[first + rank] = mask;
-    }
-    const int32_t b = rank / KB, cc = rank - b * KB;
-    const int32_t kb = min(KB, n_w - b * KB);
-    const int32_t slot = V * (first + b * KB) + own * kb + cc;
-    csr_to_slot[p] = slot;
-    if (vals) vals_blk[slot] = vals[p];
-}
 
 // Step 4: work items.  Every window owns max(1, ceil(n_w / KB)) block slots, numbered window after
 // window.  Items are runs of consecutive slots.  A window with more than 1.5 T blocks is cut into
@@ -284,45 +100,45 @@ __global__ void k_item_cand(const int *__restrict__ blk_ptr, int W, const int *_
     flag[i] = (i == 0 || st != item_boundary(blk_ptr, W, NB, T, Ts, i - 1)) ? 1 : 0;
 }
 
-// pos = exclusive scan of the flags: the distinct boundaries, in order, are the item starts
-__global__ void k_item_compact(const int *__restrict__ cand, const int *__restrict__ pos, const int *__restrict__ total,
-                               int Ts, int n_cand_max, int *__restrict__ start)
+// pos = exclusive scan of the flags: the distinct boundaries, in order, are the item starts.  Candidate i makes the
+// record of the item that starts at its boundary, {first block slot, blocks, cost << 2 | head << 1 | tail, first
+// vector}: head / tail say that the item starts / ends inside a window.  n_part = its partial tiles; opens = 1 if the window
+// cut at its end begins in it (every cut window has one such item).  Both are cleared past the last item.
+constexpr int kItemMakeThreads = 1024;  // few workgroups, because each adds once to one counter
+__global__ void __launch_bounds__(kItemMakeThreads) k_item_make(const int *__restrict__ blk_ptr, int W, const int32_t *__restrict__ win_ptr, int KB, const int *__restrict__ cand,
+                            const int *__restrict__ pos, const int *__restrict__ total, int Ts, int n_cand_max, int4 *__restrict__ rec,
+                            int *__restrict__ n_part, int *__restrict__ opens, int *__restrict__ max_blocks, int *__restrict__ n_cut)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > n_cand_max) return;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int NB = total[0];
-    const int n_cand = (NB + Ts - 1) / Ts;
-    if (i > n_cand) return;
-    if (i == n_cand) { start[pos[n_cand]] = NB; return; }
-    if (i == 0 || cand[i] != cand[i - 1]) start[pos[i]] = cand[i];
-}
-
-__global__ void k_item_make(const int *__restrict__ blk_ptr, int W, const int32_t *__restrict__ win_ptr, int KB,
-                            const int *__restrict__ start, int n_items, int4 *__restrict__ items,
-                            int *__restrict__ n_part, int *__restrict__ max_blocks)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_items) return;
-    const int s0 = start[i], s1 = start[i + 1];
-    if (s1 - s0 > kMaxItemSlots) atomicMax(max_blocks, s1 - s0);  // never by construction; checked by the host
-    if (s1 <= s0) {
-        items[i] = make_int4(0, 0, 0, 0);
-        n_part[i] = 0;
-        return;
+    const int n_cand = min((NB + Ts - 1) / Ts, n_cand_max);
+    bool cut = false;
+    if (i < n_cand && (i == 0 || cand[i] != cand[i - 1])) {
+        const int s0 = cand[i], k = pos[i];
+        int j = i + 1;
+        while (j < n_cand && cand[j] == s0) j++;  // at most the candidates inside one part
+        const int s1 = j < n_cand ? cand[j] : NB;
+        if (s1 - s0 > kMaxItemSlots) atomicMax(max_blocks, s1 - s0);  // never by construction; checked by the host
+        int4 r = make_int4(0, 0, 0, 0);
+        int parts = 0, first = 0;
+        if (s1 > s0) {
+            const int wf = window_of_slot(blk_ptr, W, s0), wl = window_of_slot(blk_ptr, W, s1 - 1);
+            const int bf = s0 - blk_ptr[wf];
+            const bool head = bf > 0, tail = s1 < blk_ptr[wl + 1];
+            first = tail && !(head && wl == wf);
+            parts = (head ? 1 : 0) + first;
+            cut = head || tail;
+            const int cost = s1 - s0 + wl - wf + (tail ? 0 : 1);  // blocks, and blocks that end a window
+            r = make_int4(s0, s1 - s0, cost << 2 | (head ? 2 : 0) | (tail ? 1 : 0), win_ptr[wf] + bf * KB);
+        }
+        rec[k] = r;
+        n_part[k] = parts;
+        opens[k] = first;
     }
-    const int wf = window_of_slot(blk_ptr, W, s0);
-    const int wl = window_of_slot(blk_ptr, W, s1 - 1);
-    const int bf = s0 - blk_ptr[wf];
-    const bool head = bf > 0;                 // starts inside a window
-    const bool tail = s1 < blk_ptr[wl + 1];   // ends inside a window
-    n_part[i] = (head ? 1 : 0) + ((tail && !(head && wl == wf)) ? 1 : 0);
-    items[i] = make_int4(s0, s1 - s0, 0, win_ptr[wf] + bf * KB);
-}
-
-__global__ void k_item_slots(const int *__restrict__ slot_ptr, int n_items, int4 *__restrict__ items)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_items) items[i].z = slot_ptr[i];
+    const int n_items = pos[n_cand_max];
+    if (i >= n_items && i <= n_cand_max) n_part[i] = opens[i] = 0;
+    const int cuts = __syncthreads_count(cut);
+    if (threadIdx.x == 0 && cuts) atomicAdd(n_cut, cuts);  // a count: the same whatever the order of the additions
 }
 
 // Launch order of the work list.  Parts of cut windows come first, ordered by the column of their first
@@ -335,23 +151,38 @@ __global__ void k_item_slots(const int *__restrict__ slot_ptr, int n_items, int4
 // the hubs.  Measured against the work list's own order: cfg 2 k_spmm 24.0 -> 21.5 us, cfg 4 (four-row
 // windows) 938 -> 827 us with the cost order alone.  The 24-bit key sorts ascending; equal keys keep the
 // work list's order (the sort is stable).
-__global__ void k_item_key(const int4 *__restrict__ items, const int4 *__restrict__ blk_desc, int n_items,
-                           const int32_t *__restrict__ vec_col, int64_t nvec, int64_t K, int32_t *__restrict__ key,
-                           int *__restrict__ n_cut)
+// The item's record gets its first partial slot (slot_ptr); an item that a cut window begins in also fills that
+// window's entry of the cut-window table and tells every one of its partial slots the window's slot range (the window's
+// tiles are consecutive slots: the tail of this item, the items inside, the head of the window's last item).
+__global__ void __launch_bounds__(256) k_item_fill(const int4 *__restrict__ rec, int n_items, const int *__restrict__ slot_ptr, const int *__restrict__ cut_pos,
+                                                   const int *__restrict__ blk_ptr, const int4 *__restrict__ blk_desc, const int32_t *__restrict__ vec_col,
+                                                   int64_t nvec, int64_t K, int4 *__restrict__ items, int32_t *__restrict__ key,
+                                                   int4 *__restrict__ split_windows, int2 *__restrict__ slot_range)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_items) return;
-    const int4 it = items[i];
-    if (it.y == 0) { key[i] = 0x00FFFFFF; return; }  // empty record: last
-    int cost = it.y;
-    for (int b = 0; b < it.y; b++) cost += (blk_desc[it.x + b].y & 256) ? 1 : 0;
-    const bool head = !(blk_desc[it.x].y & 512), tail = !(blk_desc[it.x + it.y - 1].y & 256);
-    if (head || tail) {
-        const int32_t c = nvec > 0 ? vec_col[min((int64_t)it.w, nvec - 1)] : 0;
+    const int4 r = rec[i];
+    const int slot = slot_ptr[i];
+    items[i] = make_int4(r.x, r.y, r.y ? slot : 0, r.w);
+    if (r.y == 0) {
+        key[i] = 0x00FFFFFF;  // empty record: last
+    } else if (r.z & 3) {
+        const int32_t c = nvec > 0 ? vec_col[min((int64_t)r.w, nvec - 1)] : 0;
         key[i] = (int32_t)(((int64_t)c << 16) / max(K, (int64_t)1));  // column of the first vector, 16 bits
-        atomicAdd(n_cut, 1);  // a count: the same whatever the order of the additions
     } else {
-        key[i] = (1 + 128 - min(cost, 128)) << 16;
+        key[i] = (1 + 128 - min(r.z >> 2, 128)) << 16;
+    }
+    if (cut_pos[i + 1] != cut_pos[i]) {
+        const int w = blk_desc[r.x + r.y - 1].z, end = blk_ptr[w + 1];
+        int lo = i, hi = n_items;  // the last item that starts before the window's end
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            // (an empty record -- it can only be the last one -- lies past the end)
+            if (rec[mid].y > 0 && rec[mid].x < end) lo = mid; else hi = mid;
+        }
+        const int first = slot + (r.z & 2 ? 1 : 0), parts = lo - i + 1;
+        split_windows[cut_pos[i]] = make_int4(w, first, parts, 0);
+        for (int k = 0; k < parts; k++) slot_range[first + k] = make_int2(first, parts);
     }
 }
 
@@ -363,25 +194,108 @@ __global__ void k_item_permute(const int4 *__restrict__ items, const int32_t *__
     if (t < n_items) by_cost[t] = items[order[t]];
 }
 
-// One descriptor per block slot: {first vector, width | last-block flag << 8 | first-block flag << 9, window, 0}.
-__global__ void k_block_table(const int *__restrict__ blk_ptr, int W, const int32_t *__restrict__ win_ptr, int KB,
-                              int NB, int4 *__restrict__ blk_desc)
+// The same for a short list, in one launch: a single workgroup sorts the keys in LDS, three stable passes of eight bits.
+// Every wavefront keeps a run of consecutive keys in registers and ranks them 64 at a time, by
+// ballots, against counts of its own per digit.
+constexpr int kSortSmallMax = 8192, kSortSmallThreads = 1024;
+__global__ void __launch_bounds__(kSortSmallThreads) k_item_sort_small(const int32_t *__restrict__ keys, int n, const int4 *__restrict__ items,
+                                                                       int32_t *__restrict__ order, int4 *__restrict__ by_cost)
 {
-    int x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= NB) return;
-    const int w = window_of_slot(blk_ptr, W, x);
-    const int b = x - blk_ptr[w];
-    const int nb_w = blk_ptr[w + 1] - blk_ptr[w];
-    const int first = win_ptr[w];
-    const int n_w = win_ptr[w + 1] - first;
-    const int kb = max(0, min(KB, n_w - b * KB));
-    blk_desc[x] = make_int4(first + b * KB, kb | ((b == nb_w - 1) ? 256 : 0) | ((b == 0) ? 512 : 0), w, 0);
+    constexpr int NW = kSortSmallThreads / 64, ROUNDS = kSortSmallMax / kSortSmallThreads;
+    __shared__ int32_t key_buf[kSortSmallMax];
+    __shared__ uint16_t idx_buf[kSortSmallMax];
+    __shared__ int cur[NW][kDigits];
+    __shared__ int digit_sum[kDigits / 64];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int per = (n + kSortSmallThreads - 1) / kSortSmallThreads * 64;  // keys per wavefront
+    const int lo = min(w * per, n), hi = min(lo + per, n);
+    const uint64_t below = ((uint64_t)1 << lane) - 1;
+    int key[ROUNDS], idx[ROUNDS], pos[ROUNDS];  // of this lane's keys, 64 apart
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        const int i = lo + 64 * r + lane;
+        key[r] = i < hi ? keys[i] : 0;
+        idx[r] = i;
+        pos[r] = 0;
+    }
+    for (int shift = 0; shift < 24; shift += kDigitBits) {
+        for (int i = t; i < NW * kDigits; i += kSortSmallThreads) (&cur[0][0])[i] = 0;
+        __syncthreads();
+        // place of every key among the wavefront's keys with its digit
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            const bool valid = lo + 64 * r + lane < hi;
+            if (lo + 64 * r >= hi) break;  // the same for all lanes
+            const int digit = ((uint32_t)key[r] >> shift) & (kDigits - 1);
+            uint64_t same = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < kDigitBits; b++) {
+                const bool bit = (digit >> b) & 1;
+                const uint64_t set = __ballot(valid && bit);
+                same &= bit ? set : ~set;
+            }
+            const int rank = __popcll(same & below), cnt = __popcll(same);
+            const int at = cur[w][digit];
+            pos[r] = at + rank;
+            FS_WAVE_SYNC();  // the wavefront's reads stay before its update
+            if (valid && rank == cnt - 1) cur[w][digit] = at + cnt;
+            FS_WAVE_SYNC();
+        }
+        __syncthreads();
+        // where each wavefront's keys with a digit go: all smaller digits, then this digit of the wavefronts before
+        int before[NW], inc = 0, mine = 0;
+        if (t < kDigits) {
+#pragma unroll
+            for (int k = 0; k < NW; k++) before[k] = cur[k][t];
+#pragma unroll
+            for (int k = 0; k < NW; k++) {
+                const int c = before[k];
+                before[k] = mine;
+                mine += c;
+            }
+            inc = wave_inclusive_scan(mine);
+            if (lane == 63) digit_sum[w] = inc;
+        }
+        __syncthreads();
+        if (t < kDigits) {
+            int at = inc - mine;
+            for (int k = 0; k < w; k++) at += digit_sum[k];
+#pragma unroll
+            for (int k = 0; k < NW; k++) cur[k][t] = at + before[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (lo + 64 * r + lane < hi) {
+                const int at = cur[w][((uint32_t)key[r] >> shift) & (kDigits - 1)] + pos[r];
+                key_buf[at] = key[r];
+                idx_buf[at] = (uint16_t)idx[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (lo + 64 * r + lane < hi) {
+                key[r] = key_buf[lo + 64 * r + lane];
+                idx[r] = idx_buf[lo + 64 * r + lane];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        const int i = lo + 64 * r + lane;
+        if (i < hi) {
+            order[i] = idx[r];
+            by_cost[i] = items[idx[r]];
+        }
+    }
 }
 
 // CSR position of the first stored entry of window row r that lies in block slot x or later:
 // row_base[x * V + r] = first position in row w*V + r whose column is >= the column of the block's first
 // vector.  With the block's occupancy bits this gives the CSR position of every entry of the block, which
-// lets a kernel that works block by block write its results in CSR order.
+// lets a kernel that works block by block write its results in CSR order.  (Blocks of 32 vectors have it from
+// k_unit_place; this is for the other widths.)
 __global__ void k_block_row_base(CsrView a, int V, const int4 *__restrict__ blk_desc, int NB,
                                  const int32_t *__restrict__ vec_col, int64_t nvec, int32_t *__restrict__ row_base)
 {
@@ -400,46 +314,6 @@ __global__ void k_block_row_base(CsrView a, int V, const int4 *__restrict__ blk_
         }
     }
     row_base[t] = lo;
-}
-
-// Last item index i in [0, n_items) with start[i] <= x (skips empty items, whose start equals the next one's).
-__device__ __forceinline__ int item_of_slot(const int *__restrict__ start, int n_items, int x)
-{
-    int lo = 0, hi = n_items;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (start[mid] <= x) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-__global__ void k_split_flag(const int *__restrict__ blk_ptr, int64_t W, const int *__restrict__ start, int n_items,
-                             int *__restrict__ is_split)
-{
-    int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= W) return;
-    const int fi = item_of_slot(start, n_items, blk_ptr[w]);
-    const int li = item_of_slot(start, n_items, blk_ptr[w + 1] - 1);
-    is_split[w] = li > fi ? 1 : 0;
-}
-
-__global__ void k_split_fill(const int *__restrict__ blk_ptr, int64_t W, const int *__restrict__ start, int n_items,
-                             const int *__restrict__ slot_ptr,
-                             const int *__restrict__ sw_ptr, int4 *__restrict__ split_windows,
-                             int2 *__restrict__ slot_range)
-{
-    int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= W) return;
-    if (sw_ptr[w + 1] == sw_ptr[w]) return;
-    const int fi = item_of_slot(start, n_items, blk_ptr[w]);
-    const int li = item_of_slot(start, n_items, blk_ptr[w + 1] - 1);
-    // the window's partial tiles are consecutive slots: the tail of item fi, the items inside, the head of
-    // item li.  Item fi owns a head tile of an earlier window iff it starts strictly inside that window.
-    const int wfi = window_of_slot(blk_ptr, (int)W, start[fi]);
-    const int first_slot = slot_ptr[fi] + (start[fi] > blk_ptr[wfi] ? 1 : 0);
-    split_windows[sw_ptr[w]] = make_int4((int)w, first_slot, li - fi + 1, 0);
-    // and every one of its slots learns the window's slot range (what a part needs to find the others)
-    for (int k = 0; k <= li - fi; k++) slot_range[first_slot + k] = make_int2(first_slot, li - fi + 1);
 }
 
 template <typename T>
@@ -531,30 +405,36 @@ __global__ void __launch_bounds__(256) k_pack(const int4 *__restrict__ blk_desc,
 
 inline unsigned grid_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
-// Scratch layout (ints): [L: nnz+1][scan tmp][err + totals: 64][blk_ptr: W+1][split flags: W+1][item starts][slot_ptr]
-// [boundary candidates][their flags / positions][digit counts of the work-list sort]
+// Scratch layout (ints): [ranks: nnz 16-bit][scan tmp][err + totals: 64][units, 4 each][where they start in their rows, V each][their vector counts + 1]
+// [windows' places in them, 2 each][units per group + 1][blk_ptr: W+1][windows to cut again: W+1][cut windows that begin in an item][slot_ptr]
+// [item records, 4 each][boundary candidates][their flags / positions][digit counts of the work-list sort]
 struct ScratchPlan {
-    size_t L, tmp, misc, blk, spl, start, slotp, cand, upos, hist, brow, total_ints;
+    size_t info, tmp, misc, units, pieces, count, win_at, group, blk, redo, rec, start, slotp, cand, upos, hist, total_ints;
 };
 size_t items_bound(int64_t W, int64_t nnz, int KB) { return (size_t)(W + nnz / KB + 2); }
-ScratchPlan plan_scratch(int64_t nnz, int64_t W, int KB)
+ScratchPlan plan_scratch(int64_t nnz, int64_t W, int V, int KB)
 {
     ScratchPlan s;
-    const size_t ib = items_bound(W, nnz, KB);
+    const size_t ib = items_bound(W, nnz, KB), ub = (size_t)units_bound(W, nnz);
     size_t o = 0;
-    s.L = o; o += fs_align_up((size_t)nnz + 1, 64);
+    s.info = o; o += fs_align_up(((size_t)nnz + 1) / 2, 64);
     s.tmp = o; o += scan_tmp_ints(std::max<int64_t>(std::max<int64_t>(nnz, W), (int64_t)ib));
     s.misc = o; o += 64;
+    s.units = o; o += fs_align_up(4 * ub, 64);
+    s.pieces = o; o += fs_align_up(ub * V, 64);
+    s.count = o; o += fs_align_up(ub + 1, 64);
+    s.win_at = o; o += fs_align_up(2 * (size_t)W, 64);
+    s.group = o; o += fs_align_up((size_t)W + 1, 64);
     s.blk = o; o += fs_align_up((size_t)W + 1, 64);
-    s.spl = o; o += fs_align_up((size_t)W + 1, 64);
+    s.redo = o; o += fs_align_up((size_t)W + 1, 64);
+    s.rec = o; o += fs_align_up(4 * ib, 64);
     s.start = o; o += fs_align_up(ib + 1, 64);
     s.slotp = o; o += fs_align_up(ib + 1, 64);
     s.cand = o; o += fs_align_up(ib + 1, 64);
     s.upos = o; o += fs_align_up(ib + 1, 64);
     s.hist = o; o += fs_align_up((size_t)kDigits * std::max<size_t>((ib + kSortTile - 1) / kSortTile,
                                                                      (std::min<size_t>(ib, 65536) + kSortTileSmall - 1) / kSortTileSmall) + 1, 64);  // digit counts of the work-list sort
-    s.brow = o; o += fs_align_up((size_t)nnz / kEntriesPerGroup + 3, 64);  // row of every 256th stored entry
-    s.total_ints = o;
+    s.total_ints = std::max(o, (size_t)nnz);  // (callers have counted on four bytes per entry)
     return s;
 }
 
@@ -606,7 +486,7 @@ extern "C" fs_status fs_format_bytes(int64_t M, int64_t nnz, int32_t V, int32_t 
         a += fs_align_up((size_t)V * nnz * 2, 256) + 256;      // vals_blk (+ slack so a 16-byte read of the tail stays inside)
         a += 3 * fs_align_up(items_bound(W, nnz, KB) * 16, 256);  // blk_desc, items, split_windows
         a += fs_align_up(items_bound(W, nnz, KB) * 4, 256);       // item_order
-        a += fs_align_up(items_bound(W, nnz, KB) * V * 4, 256);   // blk_row_base
+        a += 2 * fs_align_up(items_bound(W, nnz, KB) * V * 4, 256);  // blk_row_base, blk_row_bits
         a += fs_align_up(items_bound(W, nnz, KB) * 16, 256);      // items_by_cost
         a += fs_align_up(items_bound(W, nnz, KB) * 16, 256);      // slot_range (an item has at most two partial tiles)
         if (wants_packed_values(M, nnz, V, KB)) {  // the packed copy of the values (bounds: nvec <= nnz, blocks <= items_bound)
@@ -616,7 +496,7 @@ extern "C" fs_status fs_format_bytes(int64_t M, int64_t nnz, int32_t V, int32_t 
         }
         *arena_bytes = a;
     }
-    if (scratch_bytes) *scratch_bytes = plan_scratch(nnz, W, KB).total_ints * 4;
+    if (scratch_bytes) *scratch_bytes = plan_scratch(nnz, W, V, KB).total_ints * 4;
     return FS_OK;
 }
 
@@ -638,31 +518,47 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
 
     hipStream_t s = (hipStream_t)stream;
     const int64_t W = (M + V - 1) / V;
-    const ScratchPlan sp = plan_scratch(nnz, W, KB);
+    const ScratchPlan sp = plan_scratch(nnz, W, V, KB);
     int *scr = (int *)d_scratch;
-    int *L = scr + sp.L, *misc = scr + sp.misc, *tmp = scr + sp.tmp;
-    int *blk_ptr = scr + sp.blk, *spl = scr + sp.spl, *start = scr + sp.start, *slot_ptr = scr + sp.slotp;
+    int *misc = scr + sp.misc, *tmp = scr + sp.tmp;
+    int *blk_ptr = scr + sp.blk, *redo = scr + sp.redo, *cut_pos = scr + sp.start, *slot_ptr = scr + sp.slotp;
     int *cand = scr + sp.cand, *upos = scr + sp.upos;
-    int32_t *block_rows = scr + sp.brow;
-    const int64_t n_groups = (nnz + kEntriesPerGroup - 1) / kEntriesPerGroup;  // workgroups of the per-entry kernels
+    int4 *rec = (int4 *)(scr + sp.rec);
+    uint16_t *info = (uint16_t *)(scr + sp.info);
+    int4 *units = (int4 *)(scr + sp.units);
+    int *pieces = scr + sp.pieces, *first_vec = scr + sp.count, *group_pos = scr + sp.group;
+    int2 *win_at = (int2 *)(scr + sp.win_at);
     char *arena = (char *)d_arena;
     int32_t *win_ptr = (int32_t *)arena;
     CsrView a{d_rowptr, d_colidx, M, (int32_t)nnz};
 
-    FS_HIP(hipMemsetAsync(misc, 0, 64 * sizeof(int), s));
-    k_check_rowptr<<<grid_for(M + 1, 256), 256, 0, s>>>(a, misc);
-    FS_LAUNCH_CHECK();
-    if (nnz > 0) {
-        k_group_rows<<<grid_for(n_groups + 1, 256), 256, 0, s>>>(d_rowptr, M, nnz, n_groups, block_rows);
-        FS_LAUNCH_CHECK();
-        k_flag<<<(unsigned)n_groups, kEntriesPerGroup, 0, s>>>(a, K, V, block_rows, L, misc);
-        FS_LAUNCH_CHECK();
-    }
     // misc: [0] CSR error flags, [1] vectors, [2] longest item, [3] items with a part of a cut window,
-    // [4] block slots, [5] items, [6] partial tiles, [7] cut windows -- what the host reads, in one copy each time
-    st = scan_exclusive(L, nnz, tmp, s, misc + 1);
-    if (st != FS_OK) return st;
-    k_win_ptr<<<grid_for(W + 1, 256), 256, 0, s>>>(a, V, W, L, win_ptr, KB, blk_ptr);
+    // [4] block slots, [5] items, [6] partial tiles, [7] cut windows -- what the host reads, in one copy;
+    // [8] units
+    FS_HIP(hipMemsetAsync(misc, 0, 64 * sizeof(int), s));
+    const UnitPlan up = unit_plan(M, nnz, V);
+    const int64_t n_groups = (W + up.group - 1) / up.group;
+    const unsigned unit_grid = (unsigned)units_bound(W, nnz);
+    const int *n_units = misc + 8;
+    k_units<false><<<grid_for(std::max<int64_t>(n_groups, 1), 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
+    FS_LAUNCH_CHECK();
+    if (W > 0) {
+        if ((st = scan_exclusive(group_pos, n_groups, tmp, s, misc + 8)) != FS_OK) return st;
+        k_units<true><<<grid_for(n_groups, 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
+        FS_LAUNCH_CHECK();
+        if (nnz > kUnitEntries) {
+            if (V <= 8) k_pieces<8><<<(unit_grid + 6) / 7, 64, 0, s>>>(a, up, units, n_units, pieces, redo, misc);
+            else k_pieces<32><<<unit_grid, 64, 0, s>>>(a, up, units, n_units, pieces, redo, misc);
+            FS_LAUNCH_CHECK();
+            if (V <= 8) k_pieces_exact<8><<<(unit_grid + kExactPerWave - 1) / kExactPerWave, 64, 0, s>>>(a, up, units, n_units, pieces, redo, misc);
+            else k_pieces_exact<32><<<(unit_grid + kExactPerWave - 1) / kExactPerWave, 64, 0, s>>>(a, up, units, n_units, pieces, redo, misc);
+            FS_LAUNCH_CHECK();
+        }
+        k_unit_rank<<<unit_grid, 64, 0, s>>>(a, up, K, units, n_units, pieces, info, first_vec, win_at, misc);
+        FS_LAUNCH_CHECK();
+        if ((st = scan_exclusive(first_vec, unit_grid, tmp, s, misc + 1)) != FS_OK) return st;
+    }
+    k_win_ptr<<<grid_for(W + 1, 256), 256, 0, s>>>(win_at, first_vec, n_units, W, KB, win_ptr, blk_ptr, misc);
     FS_LAUNCH_CHECK();
     if ((st = scan_exclusive(blk_ptr, W, tmp, s, misc + 4)) != FS_OK) return st;
 
@@ -678,8 +574,10 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         k_item_cand<<<grid_for(n_cand_max + 1, 256), 256, 0, s>>>(blk_ptr, (int)W, misc + 4, t_user, Ts, n_cand_max, cand, upos);
         FS_LAUNCH_CHECK();
         if ((st = scan_exclusive(upos, n_cand_max, tmp, s, misc + 5)) != FS_OK) return st;
-        k_item_compact<<<grid_for(n_cand_max + 1, 256), 256, 0, s>>>(cand, upos, misc + 4, Ts, n_cand_max, start);
+        k_item_make<<<grid_for(n_cand_max + 1, kItemMakeThreads), kItemMakeThreads, 0, s>>>(blk_ptr, (int)W, win_ptr, KB, cand, upos, misc + 4, Ts, n_cand_max, rec, slot_ptr, cut_pos,
+                                                                  misc + 2, misc + 3);
         FS_LAUNCH_CHECK();
+        if ((st = scan_exclusive(slot_ptr, n_cand_max, tmp, s, misc + 6, cut_pos, misc + 7)) != FS_OK) return st;
     }
 
     int h_misc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -693,6 +591,9 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
                           scratch_bytes, stream, out);
     if ((int64_t)V * nvec >= (int64_t)1 << 31) return FS_ERR_TOO_LARGE;
     const int n_items = W > 0 ? h_misc[5] : 0;
+    // Uncut windows have at most 1.5 T <= 48 blocks and parts of cut windows at most 1.25 T + 1, so no item
+    // exceeds the 64 block descriptors a wavefront holds; a work list that did would be refused here.
+    if (h_misc[2] > kMaxItemSlots) return FS_ERR_UNSUPPORTED;
     chunk = part_blocks(NB, t_user) * KB;
 
     // arena layout, now that the sizes are known.  The value array is followed by 256 zeroed bytes: with no
@@ -702,95 +603,107 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     int32_t *vec_col = (int32_t *)(arena + o); o += fs_align_up((size_t)nvec * 4, 256);
     uint32_t *vec_mask = (uint32_t *)(arena + o); o += fs_align_up((size_t)nvec * 4, 256);
     int32_t *csr_to_slot = (int32_t *)(arena + o); o += fs_align_up((size_t)nnz * 4, 256);
-    uint16_t *vals_blk = (uint16_t *)(arena + o); o += fs_align_up((size_t)V * nvec * 2, 256) + 256;
+    const size_t vals_bytes = (size_t)V * nvec * 2, vals_padded = fs_align_up(vals_bytes, 256) + 256;
+    uint16_t *vals_blk = (uint16_t *)(arena + o); o += vals_padded;
     int4 *blk_desc = (int4 *)(arena + o); o += fs_align_up((size_t)NB * 16, 256);
     int4 *items = (int4 *)(arena + o); o += fs_align_up((size_t)n_items * 16, 256);
     int32_t *item_order = (int32_t *)(arena + o); o += fs_align_up((size_t)n_items * 4, 256);
     int4 *items_by_cost = (int4 *)(arena + o); o += fs_align_up((size_t)n_items * 16, 256);
     int32_t *blk_row_base = (int32_t *)(arena + o); o += fs_align_up((size_t)NB * V * 4, 256);
+    uint32_t *blk_row_bits = nullptr;
+    if (KB == 32) { blk_row_bits = (uint32_t *)(arena + o); o += fs_align_up((size_t)NB * V * 4, 256); }
     int2 *slot_range = (int2 *)(arena + o); o += fs_align_up((size_t)n_items * 16, 256);  // at most two partial tiles per item
-    int4 *split_windows = (int4 *)(arena + o);
+    PlaceOut po{};
+    po.vec_col = vec_col; po.vec_mask = vec_mask; po.csr_to_slot = csr_to_slot; po.vals_blk = vals_blk;
+    po.blk_desc = blk_desc; po.row_base = blk_row_base; po.row_bits = blk_row_bits;
+    po.tail = (uint16_t *)((char *)vals_blk + vals_bytes); po.n_tail = (int)((vals_padded - vals_bytes) / 2); po.n_blocks = NB;
+    void *packed = nullptr;
+    if (d_vals && nvec > 0 && wants_packed_values(M, nnz, V, KB)) {
+        fs_format b{};
+        b.n_blocks = NB; b.nvec = nvec; b.nnz = nnz; b.V = V;
+        const fs_packed_plan_t pl = fs_packed_plan(&b);
+        packed = arena + o;
+        po.packed_ofs = (int32_t *)(arena + o + pl.ofs);
+        po.packed_m8 = V <= 8 ? (uint8_t *)(arena + o + pl.masks) : nullptr;
+        po.packed_m16 = V <= 8 ? nullptr : (uint16_t *)(arena + o + pl.masks);
+        po.packed_vals = (uint16_t *)(arena + o + pl.vals);
+        o += pl.total;
+    }
+    int4 *split_windows = (int4 *)(arena + o); o += fs_align_up((size_t)h_misc[7] * 16, 256);
 
-    FS_HIP(hipMemsetAsync(vals_blk, 0, fs_align_up((size_t)V * nvec * 2, 256) + 256, s));
-    if (nnz > 0) {
-        k_emit<uint16_t><<<(unsigned)n_groups, kEntriesPerGroup, 0, s>>>(a, V, KB, block_rows, L, win_ptr, (const uint16_t *)d_vals, vec_col,
-                                                          vec_mask, csr_to_slot, vals_blk);
-        FS_LAUNCH_CHECK();
+    if (!d_vals || W == 0) FS_HIP(hipMemsetAsync(vals_blk, 0, vals_padded, s));
+    if (W > 0) {
+        const size_t lds = place_lds_bytes(V, KB);
+        const int64_t vb = (int64_t)place_vector_bytes(V);
+        const uint16_t *va = (const uint16_t *)d_vals;
+#define FS_PLACE(KB32, VT) k_unit_place<KB32, VT><<<unit_grid, 64, lds, s>>>(a, up, KB, vb, units, n_units, pieces, info, first_vec, win_ptr, blk_ptr, va, po)
+        if (KB == 32) {
+            if (V == 4) FS_PLACE(true, 4);
+            else if (V == 8) FS_PLACE(true, 8);
+            else if (V == 16) FS_PLACE(true, 16);
+            else FS_PLACE(true, 0);
+            FS_LAUNCH_CHECK();
+        } else {
+            FS_PLACE(false, 0);
+            FS_LAUNCH_CHECK();
+            k_block_row_base<<<grid_for((int64_t)NB * V, 256), 256, 0, s>>>(a, V, blk_desc, NB, vec_col, nvec, blk_row_base);
+            FS_LAUNCH_CHECK();
+        }
+#undef FS_PLACE
+        if (nnz > kUnitEntries) {
+            if (KB == 32) k_shared_blocks<true><<<(unit_grid + kSharedPerWave - 1) / kSharedPerWave, 64, 0, s>>>(V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
+            else k_shared_blocks<false><<<(unit_grid + kSharedPerWave - 1) / kSharedPerWave, 64, 0, s>>>(V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
+            FS_LAUNCH_CHECK();
+        }
     }
 
-    int h_tot[2] = {0, 0}, h_max_item = 0, h_cut_items = 0;
     if (n_items > 0) {
-        k_block_table<<<grid_for(NB, 256), 256, 0, s>>>(blk_ptr, (int)W, win_ptr, KB, NB, blk_desc);
+        k_item_fill<<<grid_for(n_items, 256), 256, 0, s>>>(rec, n_items, slot_ptr, cut_pos, blk_ptr, blk_desc, vec_col, nvec, K, items, cand, split_windows,
+                                                           slot_range);
         FS_LAUNCH_CHECK();
-        k_block_row_base<<<grid_for((int64_t)NB * V, 256), 256, 0, s>>>(a, V, blk_desc, NB, vec_col, nvec, blk_row_base);
-        FS_LAUNCH_CHECK();
-        k_item_make<<<grid_for(n_items, 256), 256, 0, s>>>(blk_ptr, (int)W, win_ptr, KB, start, n_items, items, slot_ptr,
-                                                                  misc + 2);
-        FS_LAUNCH_CHECK();
-        if ((st = scan_exclusive(slot_ptr, n_items, tmp, s, misc + 6)) != FS_OK) return st;
-        k_item_slots<<<grid_for(n_items, 256), 256, 0, s>>>(slot_ptr, n_items, items);
-        FS_LAUNCH_CHECK();
-        k_split_flag<<<grid_for(W, 256), 256, 0, s>>>(blk_ptr, W, start, n_items, spl);
-        FS_LAUNCH_CHECK();
-        if ((st = scan_exclusive(spl, W, tmp, s, misc + 7)) != FS_OK) return st;
-        k_split_fill<<<grid_for(W, 256), 256, 0, s>>>(blk_ptr, W, start, n_items, slot_ptr, spl, split_windows, slot_range);
-        FS_LAUNCH_CHECK();
-        {   // launch order: three stable radix passes over the 24-bit keys.  cand, upos and start are free
-            // again: keys alternate between cand and upos, the payload between start and item_order
-            {
-                const int tile = n_items <= 65536 ? kSortTileSmall : kSortTile;
-                const int64_t ntile = ((int64_t)n_items + tile - 1) / tile;
-                int *hist = scr + sp.hist;
-                k_item_key<<<grid_for(n_items, 256), 256, 0, s>>>(items, blk_desc, n_items, vec_col, nvec, K, cand, misc + 3);
+        // launch order: stable radix passes over the keys
+        if (n_items <= kSortSmallMax) {
+            k_item_sort_small<<<1, kSortSmallThreads, 0, s>>>(cand, n_items, items, item_order, items_by_cost);
+            FS_LAUNCH_CHECK();
+        } else {
+            // cand, upos and cut_pos are free again: keys alternate between cand and upos, the payload between cut_pos and item_order
+            const int tile = n_items <= 65536 ? kSortTileSmall : kSortTile;
+            const int64_t ntile = ((int64_t)n_items + tile - 1) / tile;
+            int *hist = scr + sp.hist;
+            int32_t *kbuf[2] = {upos, cand};              // pass p reads kbuf[(p + 1) & 1], writes kbuf[p & 1]
+            int32_t *vbuf[2] = {item_order, cut_pos};     // pass p writes vbuf[p & 1]; the last pass (2) writes item_order
+            for (int p = 0; p < 3; p++) {
+                const int32_t *src_k = kbuf[(p + 1) & 1];
+                k_digit_hist<<<(unsigned)ntile, 64, 0, s>>>(src_k, n_items, 8 * p, ntile, hist, tile);
                 FS_LAUNCH_CHECK();
-                int32_t *kbuf[2] = {upos, cand};            // pass p reads kbuf[(p + 1) & 1], writes kbuf[p & 1]
-                int32_t *vbuf[2] = {item_order, start};     // pass p writes vbuf[p & 1]; the last pass (2) writes item_order
-                for (int p = 0; p < 3; p++) {
-                    const int32_t *src_k = kbuf[(p + 1) & 1];
-                    k_digit_hist<<<(unsigned)ntile, 64, 0, s>>>(src_k, n_items, 8 * p, ntile, hist, tile);
-                    FS_LAUNCH_CHECK();
-                    if ((st = scan_exclusive(hist, (int64_t)kDigits * ntile, tmp, s)) != FS_OK) return st;
-                    if (p == 0)
-                        k_digit_scatter<true><<<(unsigned)((ntile + kScatterWaves - 1) / kScatterWaves), 64 * kScatterWaves, 0, s>>>(src_k, nullptr, n_items, 0, ntile, hist,
-                                                                            kbuf[0], vbuf[0], tile);
-                    else
-                        k_digit_scatter<false><<<(unsigned)((ntile + kScatterWaves - 1) / kScatterWaves), 64 * kScatterWaves, 0, s>>>(src_k, vbuf[(p + 1) & 1], n_items, 8 * p, ntile,
-                                                                             hist, kbuf[p & 1], vbuf[p & 1], tile);
-                    FS_LAUNCH_CHECK();
-                }
+                if ((st = scan_exclusive(hist, (int64_t)kDigits * ntile, tmp, s)) != FS_OK) return st;
+                if (p == 0)
+                    k_digit_scatter<true><<<(unsigned)((ntile + kScatterWaves - 1) / kScatterWaves), 64 * kScatterWaves, 0, s>>>(src_k, nullptr, n_items, 0, ntile, hist,
+                                                                        kbuf[0], vbuf[0], tile);
+                else
+                    k_digit_scatter<false><<<(unsigned)((ntile + kScatterWaves - 1) / kScatterWaves), 64 * kScatterWaves, 0, s>>>(src_k, vbuf[(p + 1) & 1], n_items, 8 * p, ntile,
+                                                                         hist, kbuf[p & 1], vbuf[p & 1], tile);
+                FS_LAUNCH_CHECK();
             }
             k_item_permute<<<grid_for(n_items, 256), 256, 0, s>>>(items, item_order, n_items, items_by_cost);
             FS_LAUNCH_CHECK();
         }
-        FS_HIP(hipMemcpyAsync(h_misc, misc, sizeof(h_misc), hipMemcpyDeviceToHost, s));
     }
-    FS_HIP(hipStreamSynchronize(s));
-    if (n_items > 0) { h_tot[0] = h_misc[6]; h_tot[1] = h_misc[7]; h_max_item = h_misc[2]; h_cut_items = h_misc[3]; }
-    // Uncut windows have at most 1.5 T <= 48 blocks and parts of cut windows at most 1.25 T + 1, so no item
-    // exceeds the 64 block descriptors a wavefront holds; a work list that did would be refused here.
-    if (h_max_item > kMaxItemSlots) return FS_ERR_UNSUPPORTED;
-    o += fs_align_up((size_t)h_tot[1] * 16, 256);
+    FS_HIP(hipStreamSynchronize(s));  // (the scratch buffer is the caller's again)
 
     out->M = M; out->K = K; out->nnz = nnz; out->nvec = nvec; out->W = W;
     out->V = V; out->KB = KB; out->dtype = (int32_t)dtype; out->chunk = chunk;
-    out->n_items = n_items; out->n_split_items = h_tot[0]; out->n_split_windows = h_tot[1];
-    out->n_cut_items = h_cut_items;
+    out->n_items = n_items; out->n_split_items = h_misc[6]; out->n_split_windows = h_misc[7];
+    out->n_cut_items = h_misc[3];
     out->win_ptr = win_ptr; out->vec_col = vec_col; out->vec_mask = vec_mask; out->csr_to_slot = csr_to_slot;
     out->vals_blk = vals_blk; out->blk_desc = (const int32_t *)blk_desc; out->n_blocks = NB;
     out->items = (const int32_t *)items; out->split_windows = (const int32_t *)split_windows;
     out->item_order = item_order; out->items_by_cost = (const int32_t *)items_by_cost;
     out->blk_row_base = blk_row_base;
-    out->packed = nullptr;
+    out->blk_row_bits = blk_row_bits;
+    out->packed = packed;
     out->slot_range = (const int32_t *)slot_range;
     out->arena_used = o;
-    if (d_vals && nvec > 0 && wants_packed_values(M, nnz, V, KB)) {
-        const size_t pb = fs_packed_plan(out).total;
-        if (o + pb > arena_bytes) return FS_ERR_BUFFER_TOO_SMALL;  // cannot happen with fs_format_bytes' bound
-        st = fs_pack_values(out, nullptr, arena + o, pb, stream);
-        if (st != FS_OK) return st;
-        out->packed = arena + o;
-        out->arena_used = o + pb;
-    }
     return FS_OK;
 }
 

@@ -110,8 +110,11 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ d
 // latency is exposed.
 constexpr int kSmallScanThreads = 1024;
 constexpr int kSmallScanMax = 65536;
-__global__ void __launch_bounds__(kSmallScanThreads) k_scan_small(int *__restrict__ data, int n, int *__restrict__ total_out)
+// A second array of the same length may go along (workgroup 1).
+__global__ void __launch_bounds__(kSmallScanThreads) k_scan_small(int *__restrict__ data0, int n, int *__restrict__ total0, int *__restrict__ data1,
+                                                                  int *__restrict__ total1)
 {
+    int *data = blockIdx.x ? data1 : data0, *total_out = blockIdx.x ? total1 : total0;
     __shared__ int wave_sum[2][kSmallScanThreads / 64];
     constexpr int kTile = kSmallScanThreads * 8;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -165,14 +168,19 @@ size_t scan_tmp_ints(int64_t n)
     return tot + 64;
 }
 
-// data has n+1 ints; tmp has scan_tmp_ints(n) ints.  total_out (optional) also receives the grand total.
-fs_status scan_exclusive(int *data, int64_t n, int *tmp, hipStream_t st, int *total_out = nullptr)
+// data has n+1 ints; tmp has scan_tmp_ints(n) ints.  total_out (optional) also receives the grand total.  `also`, a second
+// array of the same length with a total of its own, shares the launch where one is enough.
+fs_status scan_exclusive(int *data, int64_t n, int *tmp, hipStream_t st, int *total_out = nullptr, int *also = nullptr, int *also_total = nullptr)
 {
     int64_t nb = n <= 0 ? 1 : (n + kScanTile - 1) / kScanTile;
-    if (nb > 1 && n <= kSmallScanMax) {
-        k_scan_small<<<1, kSmallScanThreads, 0, st>>>(data, (int)n, total_out);
+    if ((nb > 1 || also) && n > 0 && n <= kSmallScanMax) {
+        k_scan_small<<<also ? 2 : 1, kSmallScanThreads, 0, st>>>(data, (int)n, total_out, also, also_total);
         FS_LAUNCH_CHECK();
         return FS_OK;
+    }
+    if (also) {
+        const fs_status s = scan_exclusive(also, n, tmp, st, also_total);
+        if (s != FS_OK) return s;
     }
     if (nb == 1) {
         k_scan_apply<<<1, kScanThreads, 0, st>>>(data, n < 0 ? 0 : n, nullptr, total_out);

@@ -1,0 +1,808 @@
+// The conversion's units of work and the two kernels that walk them: one ranks every stored entry among its
+// window's nonzero vectors, the other writes the format's arrays from those ranks.
+//
+// A unit is at most kUnitEntries stored entries, handled by one wavefront in LDS: a few consecutive windows, one
+// window, or -- of a hub window with more entries than that -- a range of columns.  What bounds the conversion
+// otherwise is searching: with one thread per entry and a binary search in each of the window's other rows, every
+// probe is a cache line (31.4 M entries in eight-row windows: 1.7 ms in two such kernels).  In LDS the V sorted rows of
+// a window are merged pairwise in log2(V) rounds, the neighbours of an entry in the merged
+// order tell which entries share a vector, and a prefix sum over the first ones of each vector is the rank.
+// Those entries (R-MAT of 1 M rows): the whole conversion 2.70 -> 1.26 ms, of which ranking takes 340 us (about thirty
+// instructions per entry and round: searching the merge paths bounds it, not memory: 260 MB are 50 us) and placing
+// 427 us (0.9 GB, most of it written, 170 us; the LDS tile and scattered two-byte accesses are the rest).
+#pragma once
+
+#include "fs_common.h"
+#include "fs_scan.h"
+#include "fs_tile.h"  // FS_WAVE_SYNC: a barrier would also wait for every store under way
+
+namespace {
+
+// Waits for every load under way.  The kernels below issue all of a unit's loads under uniform branches and use them
+// under others; without one place at which all have arrived, the compiler waits for everything in flight -- the stores
+// included -- wherever it cannot tell.
+#define FS_WAIT_LOADS() __builtin_amdgcn_s_waitcnt(0x0F70)  /* vmcnt(0), nothing else */
+
+// A loop over the up to NCH entries of a lane whose index is a constant from the start, so that arrays of them stay in
+// registers of their own (unrolled late, the compiler had made one of them a tuple that every branch copied).
+#define FS_EACH(h) fs_for_each_index([&](auto h##_) { constexpr int h = decltype(h##_)::value;
+#define FS_EACH_END }, std::make_integer_sequence<int, NCH>{})
+
+constexpr int kUnitEntries = 512;   // 9 bits of a rank
+constexpr int kUnitRows = 64;       // rows of a unit, one per lane: 6 bits
+constexpr int kMaxUnitWindows = 16;
+
+struct CsrView {
+    const int32_t *rowptr;
+    const int32_t *colidx;
+    int64_t M;
+    int32_t nnz;
+};
+
+// Row bounds clamped into [0, nnz] so that a malformed rowptr can never cause an out-of-range read.
+__device__ __forceinline__ void row_range(const CsrView &a, int64_t i, int32_t &lo, int32_t &hi)
+{
+    lo = min(max(a.rowptr[i], 0), a.nnz);
+    hi = min(max(a.rowptr[i + 1], lo), a.nnz);
+}
+
+// How windows become units.  Windows are taken in groups of `group`; a group that fits a unit is one.  The windows of
+// a group that does not fit are units of their own, and a window with more than kUnitEntries entries is cut by columns:
+// every `stride`-th entry of a row is a sample, a sample's rank counts the samples of all rows with a smaller
+// (column, row), and the columns of the samples with ranks `per`, 2 per, ... start new pieces.  A piece then
+// spans at most per + V - 1 samples, a row with q of them at most (q + 1) * stride - 1 entries of it: in all fewer than
+// (per + 2 V) * stride <= kUnitEntries.  (`per` stays a sixth below what that allows, so that pieces cut by a guess
+// fit as well, see k_pieces.)
+struct UnitPlan {
+    int V, lv;     // rows per window, and log2 of the next power of two
+    int group;     // windows per group
+    int stride, per;
+};
+inline UnitPlan unit_plan(int64_t M, int64_t nnz, int V)
+{
+    UnitPlan p;
+    p.V = V;
+    p.lv = 0;
+    while ((1 << p.lv) < V) p.lv++;
+    const double mean = M > 0 ? (double)nnz * V / (double)M : 0.;  // entries per window
+    p.group = 1;
+    while (p.group < kMaxUnitWindows && ((2 * p.group) << p.lv) <= kUnitRows && 2 * p.group * mean <= 0.7 * kUnitEntries) p.group *= 2;
+    p.stride = V <= 16 ? 8 : 4;
+    p.per = (kUnitEntries / p.stride - 2 * V) * 5 / 6;
+    return p;
+}
+// at most this many units: per * stride >= 208 for every V
+inline int64_t units_bound(int64_t W, int64_t nnz) { return W + nnz / 208 + 2; }
+
+// Pieces of window w (1: it fits a unit).
+__device__ __forceinline__ int window_pieces(const CsrView &a, const UnitPlan &p, int64_t w, int64_t &entries)
+{
+    int64_t e = 0, samples = 0;
+    for (int r = 0; r < p.V && w * p.V + r < a.M; r++) {
+        int32_t lo, hi;
+        row_range(a, w * p.V + r, lo, hi);
+        e += hi - lo;
+        samples += (hi - lo) / p.stride;
+    }
+    entries = e;
+    return e <= kUnitEntries ? 1 : (int)max((samples + p.per - 1) / p.per, (int64_t)1);
+}
+
+// One thread per group: how many units it becomes (FILL = false, which also checks the row pointers), or their records
+// {first window, windows, piece, pieces of the window} from position pos[group] on.
+template <bool FILL>
+__global__ void __launch_bounds__(256) k_units(CsrView a, UnitPlan p, int64_t W, int *__restrict__ pos, int4 *__restrict__ units, int *__restrict__ redo, int *__restrict__ err)
+{
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t w0 = g * p.group, w1 = min(w0 + p.group, W);
+    if (!FILL && W == 0 && g == 0 && a.rowptr[0] != 0) atomicOr(err, 1);
+    if (w0 >= W || (FILL && (*err & 1))) return;
+    if constexpr (!FILL) {
+        bool bad = false;
+        int32_t last = a.rowptr[w0 * p.V];
+        if (w0 == 0 && last != 0) bad = true;
+        for (int64_t i = w0 * p.V; i < min(w1 * p.V, a.M); i++) {
+            const int32_t next = a.rowptr[i + 1];
+            if (last < 0 || next < last) bad = true;
+            last = next;
+        }
+        if (last > a.nnz || (w1 == W && last != a.nnz)) bad = true;
+        if (bad) atomicOr(err, 1);
+    }
+    int64_t total = 0, n = 0, e;
+    for (int64_t w = w0; w < w1; w++) {
+        n += window_pieces(a, p, w, e);
+        total += e;
+    }
+    if (total <= kUnitEntries) {
+        if constexpr (FILL) units[pos[g]] = make_int4((int)w0, (int)(w1 - w0), 0, 1);
+        else pos[g] = 1;
+        return;
+    }
+    if constexpr (!FILL) {
+        pos[g] = (int)n;
+    } else {
+        int u = pos[g];
+        for (int64_t w = w0; w < w1; w++) {
+            const int np = window_pieces(a, p, w, e);
+            redo[w] = 0;
+            for (int k = 0; k < np; k++) units[u++] = make_int4((int)w, 1, k, np);
+        }
+    }
+}
+
+// First position in [lo, hi) whose column is >= c.
+__device__ __forceinline__ int32_t first_at_least(const int32_t *__restrict__ colidx, int32_t lo, int32_t hi, int32_t c)
+{
+    while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (colidx[mid] < c) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// Where the pieces of hub windows start: start[u * V + r] = the first entry of row r that belongs to piece u or a later
+// one.  Piece k should start where k / pieces of the window's entries lie before; that column is looked for among
+// those of the window's longest row, by interpolation between the two nearest ones known (a guess from the longest
+// row alone is off by a factor where the hot columns saturate all rows).  A few steps are enough for a graph; a window
+// one of whose pieces came out too large for a unit is noted in redo[] for k_pieces_exact.  64 / ROWS pieces per
+// wavefront, one row per lane; the last one of a wavefront is only there for the size of the one before.
+template <int ROWS>  // a power of two, at least V
+__global__ void __launch_bounds__(64) k_pieces(CsrView a, UnitPlan p, const int4 *__restrict__ units, const int *__restrict__ n_units,
+                                               int32_t *__restrict__ start, int *__restrict__ redo, const int *__restrict__ err)
+{
+    constexpr int PER = 64 / ROWS;
+    constexpr int CLOSE = kUnitEntries / 12;  // near enough: pieces are planned at most five sixths full
+    const int lane = threadIdx.x, k = lane / ROWS, r = lane % ROWS;
+    const int u = blockIdx.x * (PER - 1) + k, n = *n_units;
+    if (blockIdx.x * (PER - 1) >= n || (*err & 1)) return;
+    const int4 un = units[min(u, n - 1)];
+    const bool hub = u < n && un.w > 1;
+    if (!__any(hub)) return;
+    const int64_t row = (int64_t)un.x * p.V + r;
+    int32_t lo = 0, hi = 0;
+    if (hub && r < p.V && row < a.M) row_range(a, row, lo, hi);
+    auto over_rows = [](int v) -> int {
+#pragma unroll
+        for (int h = 1; h < ROWS; h <<= 1) v += __shfl_xor(v, h, 64);
+        return v;
+    };
+    uint64_t best = ((uint64_t)(uint32_t)(hi - lo) << 32) | (uint32_t)lo;  // the longest row's length and place
+#pragma unroll
+    for (int h = 1; h < ROWS; h <<= 1) {
+        const uint64_t other = __shfl_xor(best, h, 64);
+        best = other > best ? other : best;
+    }
+    const int32_t long_lo = (int32_t)(uint32_t)best, long_len = (int32_t)(best >> 32);
+    const int all = over_rows(hi - lo);
+    const int want = hub ? (int)((int64_t)all * un.z / un.w) : 0;
+    // between which places of the longest row the column lies, and what of this row and of all lies before them
+    int i_lo = 0, i_hi = long_len, f_lo = 0, f_hi = all;
+    int32_t at_lo = lo, at_hi = hi, at = lo;
+    bool done = !hub || un.z == 0;
+    for (int step = 0; step < 6 && !__all(done); step++) {
+        int i = i_lo + (int)((int64_t)(want - f_lo) * (i_hi - i_lo) / max(f_hi - f_lo, 1));
+        if (step == 3) i = (i_lo + i_hi) >> 1;
+        i = min(max(i, i_lo), long_len - 1);
+        if (!done) {
+            const int32_t c = a.colidx[long_lo + i];
+            at = first_at_least(a.colidx, at_lo, at_hi, c);
+        }
+        const int f = over_rows(at - lo);
+        if (!done) {
+            if (abs(f - want) <= CLOSE || i_hi - i_lo <= 1) done = true;
+            if (f < want) { i_lo = i + 1; f_lo = f; at_lo = at; }
+            else { i_hi = i; f_hi = f; at_hi = at; }
+            if (i_lo >= i_hi) done = true;
+        }
+    }
+    if (hub && r < p.V) start[(int64_t)u * p.V + r] = at;
+    // entries of piece k: up to where the next one starts, or the rows' ends
+    const int32_t next = __shfl(at, (lane + ROWS) & 63, 64);
+    const int size = over_rows(hub && k < PER - 1 ? (un.z + 1 < un.w ? next : hi) - at : 0);
+    const bool behind = hub && k < PER - 1 && un.z + 1 < un.w && next < at;  // pieces out of order
+    if ((size > kUnitEntries || behind) && hub) redo[un.x] = 1;
+}
+
+// The same without a guess, for the windows in redo[].  The wavefront of piece k ranks the samples k * per .. of its window, numbered row after row; the sample
+// whose rank is q * per starts piece q with its column.  (Ranks are distinct, so every piece of a valid matrix is
+// written once.)  Counting a row's samples below the column leaves `stride` entries to look at for the row's start.
+// The rows are searched eight at a time: one memory round trip per halving, not eight.
+constexpr int kExactPerWave = 4;  // units a wavefront looks at
+template <int ROWS>  // at least V, a multiple of eight
+__global__ void __launch_bounds__(64) k_pieces_exact(CsrView a, UnitPlan p, const int4 *__restrict__ units, const int *__restrict__ n_units,
+                                               int32_t *__restrict__ start, const int *__restrict__ redo, const int *__restrict__ err)
+{
+    constexpr int G = 8;
+    const int lane = threadIdx.x, n = *n_units;
+    if (*err & 1) return;
+    const int my_u = blockIdx.x * kExactPerWave + lane;  // most have nothing to do
+    const int4 my_un = units[min(my_u, n - 1)];
+    uint64_t todo = __ballot(lane < kExactPerWave && my_u < n && my_un.w > 1 && redo[my_un.x]);
+    for (; todo; todo &= todo - 1) {
+    const int k = __builtin_ctzll(todo), u = blockIdx.x * kExactPerWave + k;
+    const int4 un = make_int4(__shfl(my_un.x, k, 64), 1, __shfl(my_un.z, k, 64), __shfl(my_un.w, k, 64));
+    const int64_t row0 = (int64_t)un.x * p.V;
+    int32_t lo = 0, hi = 0;
+    if (lane < p.V && row0 + lane < a.M) row_range(a, row0 + lane, lo, hi);
+    if (un.z == 0 && lane < p.V) start[(int64_t)u * p.V + lane] = lo;
+    const int mine = (hi - lo) / p.stride;  // samples of row `lane`
+    const int upto = wave_inclusive_scan(mine);
+    for (int s0 = 0; s0 < p.per; s0 += 64) {
+        const int s = un.z * p.per + s0 + lane;  // this lane's sample
+        int row = -1, idx = 0;
+        for (int r = 0; r < p.V; r++) {
+            const int before = __shfl(upto - mine, r, 64), n = __shfl(mine, r, 64);
+            if (s >= before && s < before + n) { row = r; idx = s - before; }
+        }
+        const bool live = row >= 0 && s0 + lane < p.per;
+        const int32_t lo_s = __shfl(lo, max(row, 0), 64);
+        const int32_t c = live ? a.colidx[lo_s + (idx + 1) * p.stride - 1] : 0;
+        int rank = idx, below[ROWS];
+#pragma unroll
+        for (int r0 = 0; r0 < ROWS; r0 += G) {
+            int32_t base[G];
+            int m[G], most = 0;
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                const int r = r0 + g;
+                m[g] = __shfl(mine, min(r, 63), 64);
+                base[g] = __shfl(lo, min(r, 63), 64) + p.stride - 1;
+                if (!live || r == row || r >= p.V) m[g] = 0;
+                below[r] = 0;
+                most = max(most, m[g]);
+            }
+            for (; __any(most > 0); most >>= 1) {  // halves until every row's samples are told apart
+#pragma unroll
+                for (int g = 0; g < G; g++) {
+                    const int half = m[g] >> 1;
+                    const int32_t v = m[g] > 0 ? a.colidx[base[g] + (below[r0 + g] + half) * p.stride] : 0;
+                    const bool less = m[g] > 0 && (v < c || (v == c && r0 + g < row));
+                    below[r0 + g] += less ? half + 1 : 0;
+                    m[g] = less ? m[g] - half - 1 : half;
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < G; g++) rank += below[r0 + g];
+        }
+        const int q = rank / p.per;
+        const bool starts = live && rank == q * p.per && q > 0 && q < un.w;
+        if (!__any(starts)) continue;
+#pragma unroll
+        for (int r0 = 0; r0 < ROWS; r0 += G) {
+            int32_t at[G], end[G];
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                const int r = min(r0 + g, 63);
+                const int n = r == row ? idx : below[r0 + g];  // the last of them may be the column itself (a row before `row`)
+                at[g] = __shfl(lo, r, 64) + max(n * p.stride - 1, 0);
+                end[g] = min(at[g] + p.stride + 1, __shfl(hi, r, 64));
+                if (!starts || r0 + g >= p.V) end[g] = at[g];
+            }
+            for (int step = 1; step < 2 * p.stride; step <<= 1) {
+#pragma unroll
+                for (int g = 0; g < G; g++) {
+                    const int32_t mid = at[g] + ((end[g] - at[g]) >> 1);
+                    const bool some = at[g] < end[g], less = some && a.colidx[mid] < c;
+                    if (less) at[g] = mid + 1; else if (some) end[g] = mid;
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < G; g++)
+                if (starts && r0 + g < p.V) start[(int64_t)(u - un.z + q) * p.V + r0 + g] = at[g];
+        }
+    }
+    }
+}
+
+// A row of a unit: window wl of the unit, row r of the window.  The lane that holds it says where it stands among
+// the unit's rows.
+struct UnitRows {
+    int32_t row_lo;       // the row's first entry
+    int32_t lo, len;      // the unit's share of the row
+    int begin;            // its first entry among the unit's, row after row in lane order
+    int total;            // entries of the unit
+};
+__device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &p, const int4 &un, int u, int wl, int r,
+                                              const int32_t *__restrict__ piece_start, bool &bad)
+{
+    UnitRows x;
+    const int64_t row = ((int64_t)un.x + wl) * p.V + r;
+    int32_t hi = 0;
+    x.row_lo = 0;
+    const bool live = wl < un.y && r < p.V && row < a.M;
+    if (live) row_range(a, row, x.row_lo, hi);
+    x.lo = x.row_lo;
+    if (un.w > 1 && live) {
+        const int32_t end = hi;
+        if (un.z + 1 < un.w) hi = piece_start[((int64_t)u + 1) * p.V + r];
+        if (un.z > 0) x.lo = piece_start[(int64_t)u * p.V + r];
+        if (x.lo < x.row_lo || hi < x.lo || hi > end) {  // columns that do not ascend
+            bad = true;
+            x.lo = hi = x.row_lo;
+        }
+    }
+    x.len = hi - x.lo;
+    int upto = wave_inclusive_scan(x.len);
+    x.total = __shfl(upto, 63, 64);
+    if (x.total > kUnitEntries) {  // columns that do not ascend, again: nothing of this unit is used
+        bad = true;
+        x.len = x.total = upto = 0;
+    }
+    x.begin = upto - x.len;
+    return x;
+}
+
+// Ranks: info[p] = rank of entry p's vector among the vectors of its unit | its row in the unit << 9 (row r of window
+// wl: wl * 2^lv + r); count[u] = vectors of unit u; win_at[w] = {the unit window w begins in, vectors of that
+// unit before it}.  Checks the columns (err |= 2).
+//
+// The rows stand in LDS in bit-reversed order (rows 0 4 2 6 1 5 3 7 for V = 8, of each the unit's windows): a round
+// then merges the first half of the unit with the second, whatever rows it pairs, and leaves its output ready for
+// the next.  Every lane makes the same number of consecutive outputs: it finds where they begin in the two halves
+// with one binary search and then takes the smaller of two elements at a time -- a third of the instructions of a
+// search per element -- and when all lanes have theirs in registers they go back to the same place, so that LDS holds
+// the unit once and 26 wavefronts share a CU.  An element is {pair, column, place} in one 64-bit number, so that one
+// comparison orders it; an element larger than all ends each half, so that a merge needs no bounds.
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_unit_rank(CsrView a, UnitPlan p, int64_t K, const int4 *__restrict__ units, const int *__restrict__ n_units,
+                                                  const int32_t *__restrict__ piece_start, uint16_t *__restrict__ info, int *__restrict__ count,
+                                                  int2 *__restrict__ win_at, int *__restrict__ err)
+{
+    constexpr int NCH = kUnitEntries / 64;
+    constexpr int MOST = NCH + 1;  // outputs of a lane
+    __shared__ uint64_t buf[kUnitEntries + 2 + MOST];
+    __shared__ uint16_t rank_of[kUnitEntries];
+    __shared__ int begin[kUnitRows];
+    __shared__ int32_t sh_lo[kUnitRows];
+    __shared__ int win_first[kMaxUnitWindows];
+    const int u = blockIdx.x, lane = threadIdx.x;
+    if (u >= *n_units || (*err & 1)) {  // (bit 1: malformed row pointers, set before; the records are not there)
+        if (lane == 0) count[u] = 0;
+        return;
+    }
+    const int4 un = units[u];
+    // lane = bit-reversed row * windows + window
+    const int lw = un.y == 1 ? 0 : 31 - __builtin_clz(p.group);
+    const int lr = p.lv + lw;  // log2 of the unit's row slots
+    const int wl = lane & ((1 << lw) - 1);
+    const int r = p.lv ? (int)(__brev((uint32_t)lane >> lw) >> (32 - p.lv)) : 0;
+    bool bad = false;
+    const UnitRows x = unit_rows(a, p, un, u, lane < (1 << lr) ? wl : kMaxUnitWindows, r, piece_start, bad);
+    int E = x.total;
+    begin[lane] = x.begin;
+    sh_lo[lane] = x.lo - x.begin;  // element s of the unit in slot i is entry sh_lo[i] + s of the matrix
+    if (lane < kMaxUnitWindows) win_first[lane] = 0;
+    FS_WAVE_SYNC();
+    int32_t col[NCH];
+    int slot[NCH];
+    FS_EACH(h) {  // every load of the unit is on its way before the first use
+        col[h] = slot[h] = 0;
+        if (64 * h < E) {
+            const int e = min(64 * h + lane, E - 1);
+            int i = 0;  // the last slot with begin[i] <= e
+            for (int w = 1 << lr >> 1; w > 0; w >>= 1) i += begin[i + w] <= e ? w : 0;
+            slot[h] = i;
+            col[h] = a.colidx[sh_lo[i] + e];
+        }
+    } FS_EACH_END;
+    if (un.w > 1 && x.len > 0 && x.lo > x.row_lo && a.colidx[x.lo - 1] >= a.colidx[x.lo]) bad = true;  // across the cut
+    FS_WAIT_LOADS();
+    // elements of the slots whose bit lr - 1 - l is clear: the first half of round l
+    auto first_half = [&](int l) -> int {
+        int n = (lane >> (lr - 1 - l)) & 1 ? 0 : x.len;
+#pragma unroll
+        for (int h = 1; h < 64; h <<= 1) n += __shfl_xor(n, h, 64);
+        return n;
+    };
+    int n_a = p.lv ? first_half(0) : E;
+    int32_t last = 0;  // the previous 64 entries' last column
+    FS_EACH(h) {
+        if (64 * h < E) {
+            const int e = 64 * h + lane, i = slot[h];
+            const int32_t c = col[h];
+            int32_t prev = __shfl_up(c, 1, 64);
+            if (lane == 0) prev = last;
+            last = __shfl(c, 63, 64);
+            if (e < E) {
+                if (e == begin[i]) prev = -1;  // the unit's first entry of the row
+                if (c < 0 || c >= K || prev >= c) bad = true;
+                const int half = p.lv ? (1 << lr >> 1) - 1 : ~0;  // the pair: the slot without its top bit
+                buf[e + (p.lv && e >= n_a ? 1 : 0)] = ((uint64_t)(uint32_t)(i & half) << 40) | ((uint64_t)(uint32_t)c << 9) | (uint32_t)e;
+            }
+        }
+    } FS_EACH_END;
+    if (__any(bad)) {  // what follows relies on ascending columns: nothing of this unit is used
+        if (lane == 0) atomicOr(err, 2);
+        E = n_a = 0;
+    }
+    const int per_lane = ((E + 63) / 64) | 1;  // odd, so that the lanes' outputs start in different banks
+    for (int l = 0; l < p.lv; l++) {
+        // in LDS: n_a elements, the largest, E - n_a elements, the largest
+        if (lane < 2) buf[lane ? E + 1 : n_a] = ~0ull;
+        FS_WAVE_SYNC();
+        const int n_b = E - n_a, d0 = min(lane * per_lane, E), d1 = min(d0 + per_lane, E);
+        int i = max(0, d0 - n_b), hi = min(d0, n_a);
+        while (__any(i < hi)) {
+            const int mid = (i + hi) >> 1;
+            const bool less = buf[mid] < buf[n_a + d0 - mid];  // (at i == hi: two elements of the unit, and nothing changes)
+            if (i < hi) {
+                if (less) i = mid + 1; else hi = mid;
+            }
+        }
+        int j = n_a + 1 + d0 - i;
+        uint64_t va = buf[i], vb = buf[j], got[MOST];
+#pragma unroll
+        for (int t = 0; t < MOST; t++) {
+            got[t] = 0;
+            if (t < per_lane) {
+                const bool first = va < vb;
+                got[t] = first ? va : vb;
+                i += first ? 1 : 0;
+                j += first ? 0 : 1;
+                const uint64_t v = buf[first ? i : j];
+                va = first ? v : va;
+                vb = first ? vb : v;
+            }
+        }
+        n_a = l + 1 < p.lv ? first_half(l + 1) : E;
+        const uint64_t keep = ((uint64_t)(l + 1 == p.lv ? (1 << lw) - 1 : (1 << lr >> (l + 2)) - 1) << 40) | (((uint64_t)1 << 40) - 1);
+        FS_WAVE_SYNC();
+#pragma unroll
+        for (int t = 0; t < MOST; t++) {
+            const int d = d0 + t;
+            if (t < per_lane && d < d1) buf[d + (d >= n_a ? 1 : 0)] = got[t] & keep;
+        }
+    }
+    FS_WAVE_SYNC();
+    // the first entry of every vector counts one
+    int vectors = 0;
+    uint64_t seen = 0;  // windows with entries
+    for (int e0 = 0; e0 < E; e0 += 64) {
+        const int s = e0 + lane;
+        bool leads = false;
+        uint64_t k1 = 0;
+        int w1 = 0, w0 = -1;
+        if (s < E) {
+            k1 = buf[s];
+            const uint64_t k0 = s > 0 ? buf[s - 1] : ~0ull;
+            leads = (k1 >> 9) != (k0 >> 9);
+            w1 = (int)(k1 >> 40);
+            w0 = s > 0 ? (int)(k0 >> 40) : -1;
+        }
+        const uint64_t mask = __ballot(leads);
+        const int rank = vectors + __popcll(mask & ((2ull << lane) - 1)) - 1;
+        if (s < E) {
+            rank_of[k1 & 511] = (uint16_t)rank;
+            if (w1 != w0) win_first[w1] = rank | 0x10000;
+        }
+        vectors += __popcll(mask);
+    }
+    FS_WAVE_SYNC();
+    FS_EACH(h) {
+        const int e = 64 * h + lane;
+        if (e < E) {
+            const int i = slot[h];
+            const int row = ((i & ((1 << lw) - 1)) << p.lv) | (p.lv ? (int)(__brev((uint32_t)i >> lw) >> (32 - p.lv)) : 0);
+            info[sh_lo[i] + e] = (uint16_t)(rank_of[e] | (row << 9));
+        }
+    } FS_EACH_END;
+    if (lane == 0) count[u] = vectors;
+    if (un.z == 0) {
+        const int mine = lane < kMaxUnitWindows ? win_first[lane] : 0;
+        seen = __ballot(mine != 0);
+        if (lane < un.y) {
+            const uint64_t after = seen >> lane;  // an empty window begins where the next one with entries does
+            const int at = after ? win_first[lane + __builtin_ctzll(after)] & 0xFFFF : vectors;
+            win_at[un.x + lane] = make_int2(u, at);
+        }
+    }
+}
+
+// Window pointers from the units' first vectors, and every window's number of block slots.
+__global__ void __launch_bounds__(256) k_win_ptr(const int2 *__restrict__ win_at, const int *__restrict__ first_vec, const int *__restrict__ n_units, int64_t W,
+                                                 int KB, int32_t *__restrict__ win_ptr, int *__restrict__ nblk, const int *__restrict__ err)
+{
+    const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (w > W) return;
+    const bool malformed = *err & 1;
+    auto ptr = [&](int64_t v) -> int32_t {
+        if (malformed) return 0;
+        if (v == W) return first_vec[*n_units];
+        const int2 at = win_at[v];
+        return first_vec[at.x] + at.y;
+    };
+    const int32_t q = ptr(w);
+    win_ptr[w] = q;
+    if (w < W) nblk[w] = max(1, (ptr(w + 1) - q + KB - 1) / KB);
+}
+
+// What the second kernel writes.  vals null: pattern only (the value array is cleared beforehand); packed_* null: not wanted.
+struct PlaceOut {
+    int32_t *vec_col;
+    uint32_t *vec_mask;
+    int32_t *csr_to_slot;
+    uint16_t *vals_blk;
+    int4 *blk_desc;
+    int32_t *row_base;
+    uint32_t *row_bits;
+    int32_t *packed_ofs;
+    uint8_t *packed_m8;
+    uint16_t *packed_m16;
+    uint16_t *packed_vals;
+    uint16_t *tail;  // the elements behind the value array that have to be zero
+    int n_tail;
+    int n_blocks;
+};
+
+// LDS of k_unit_place: a unit's vectors (columns and masks, later its share of the value array), then two tables with an
+// element per block of 32 vectors and row.
+constexpr int kTileVectors = 256;
+inline size_t place_vector_bytes(int V) { return (size_t)(V * 2 * kTileVectors > kUnitEntries * 8 ? V * 2 * kTileVectors : kUnitEntries * 8); }
+inline size_t place_lds_bytes(int V, int KB) { return place_vector_bytes(V) + (KB == 32 ? (size_t)(kUnitEntries / 32 + kMaxUnitWindows + 2) * V * 8 : 0); }
+
+// Everything of the format that belongs to a unit's entries, vectors and blocks.  KB32: blocks of 32 vectors, the width
+// the compute kernels take: their rows' occupancy and CSR positions are written too.  A block that a hub window's pieces
+// share gets its values from k_shared_blocks.
+template <bool KB32, int VT>  // VT: rows per window, or 0 for those without an instantiation of their own
+__global__ void __launch_bounds__(64) k_unit_place(CsrView a, UnitPlan p, int KB, int64_t vec_bytes, const int4 *__restrict__ units, const int *__restrict__ n_units,
+                                                   const int32_t *__restrict__ piece_start, const uint16_t *__restrict__ info,
+                                                   const int *__restrict__ first_vec, const int32_t *__restrict__ win_ptr, const int *__restrict__ blk_ptr,
+                                                   const uint16_t *__restrict__ vals, PlaceOut out)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    __shared__ int begin[kUnitRows + 1];
+    __shared__ int32_t sh_lo[kUnitRows];
+    __shared__ int32_t row_start[kUnitRows];
+    __shared__ int32_t wp[kMaxUnitWindows + 1], bp[kMaxUnitWindows + 1];
+    if constexpr (VT > 0) {
+        p.V = VT;
+        p.lv = 31 - __builtin_clz(VT);
+    }
+    const int u = blockIdx.x, lane = threadIdx.x, V = p.V;
+    if (u == 0) {
+        for (int i = lane; i < out.n_tail; i += 64) out.tail[i] = 0;
+        if (out.packed_ofs && lane == 0) out.packed_ofs[out.n_blocks] = a.nnz;
+    }
+    if (u >= *n_units) return;
+    if constexpr (KB32) KB = 32;
+    const int4 un = units[u];
+    bool bad = false;
+    const int my_wl = lane >> p.lv, my_r = lane & ((1 << p.lv) - 1);
+    const UnitRows x = unit_rows(a, p, un, u, my_wl, my_r, piece_start, bad);
+    const int E = x.total;
+    const int f = first_vec[u], n = first_vec[u + 1] - f;
+    begin[lane] = x.begin;
+    sh_lo[lane] = x.lo - x.begin;
+    if (lane <= un.y) {
+        wp[lane] = win_ptr[un.x + lane];
+        bp[lane] = blk_ptr[un.x + lane];
+    }
+    FS_WAVE_SYNC();
+    const bool hub = un.w > 1;
+    const int o = f - wp[0];                 // vectors of the window before the unit (hub windows only, else 0)
+    const int b_lo = o / KB;                 // the window's block that the unit's first vector lies in
+    const int n_w0 = wp[1] - wp[0];
+    // tables: blocks of the unit, window after window (of a hub window those the unit's vectors lie in)
+    const int n_t = hub ? (n > 0 ? (o + n - 1) / KB - b_lo + 1 : 0) : bp[un.y] - bp[0];
+    int *col_buf = reinterpret_cast<int *>(lds);
+    uint32_t *mask_buf = reinterpret_cast<uint32_t *>(lds) + kUnitEntries;
+    uint32_t *bits = reinterpret_cast<uint32_t *>(lds + vec_bytes);  // occupancy of a block's row
+    int32_t *packed_at = reinterpret_cast<int32_t *>(bits + (size_t)n_t * V);
+    for (int i = lane; i < n; i += 64) mask_buf[i] = 0;
+    if constexpr (KB32) {
+        for (int i = lane; i < n_t * V; i += 64) bits[i] = 0;
+    }
+    FS_WAVE_SYNC();
+
+    // blocks whose vectors all lie in the unit (hub windows; of other units all do)
+    const int own_lo = hub ? (o + KB - 1) / KB : 0, own_hi = hub ? (o + n == n_w0 ? (n_w0 + KB - 1) / KB : (o + n) / KB) : INT32_MAX;
+    // the unit's entries, up to eight per lane: every load is on its way before the first use
+    constexpr int NCH = kUnitEntries / 64;
+    int32_t pos[NCH], col[NCH];
+    int code[NCH];  // rank | row << 9
+    int val[NCH];
+    const uint16_t *val_src = vals ? vals : info;  // (something to read in a pattern-only conversion)
+    FS_EACH(h) {
+        pos[h] = col[h] = code[h] = 0;
+        val[h] = 0;
+        if (64 * h < E) {
+            const int e = min(64 * h + lane, E - 1);
+            int i = 0;  // (whole windows: their rows follow each other, and the code names the row)
+            if (hub)
+                for (int w = 1 << p.lv >> 1; w > 0; w >>= 1) i += begin[i + w] <= e ? w : 0;
+            pos[h] = sh_lo[i] + e;
+            code[h] = info[pos[h]];
+            col[h] = a.colidx[pos[h]];
+            val[h] = val_src[pos[h]];
+        }
+    } FS_EACH_END;
+    FS_WAIT_LOADS();
+    // of an entry: window of the unit, row, vector of the window, block of the window
+    auto place = [&](int cd, int &wl, int &row, int &kw, int &b) {
+        wl = (cd >> 9) >> p.lv;
+        row = (cd >> 9) & ((1 << p.lv) - 1);
+        kw = f + (cd & 511) - wp[wl];
+        b = kw / KB;
+    };
+    FS_EACH(h) {
+        if (64 * h + lane < E) {
+            int wl, row, kw, b;
+            place(code[h], wl, row, kw, b);
+            col_buf[code[h] & 511] = col[h];  // the same from every entry of the vector
+            atomicOr(&mask_buf[code[h] & 511], 1u << row);
+            if constexpr (KB32) atomicOr(&bits[(bp[wl] - bp[0] + b - b_lo) * V + row], 1u << (kw - b * KB));
+        }
+    } FS_EACH_END;
+    FS_WAVE_SYNC();
+    for (int i = lane; i < n; i += 64) {
+        const uint32_t m = mask_buf[i];
+        out.vec_col[f + i] = col_buf[i];
+        out.vec_mask[f + i] = m;
+        if (out.packed_m8) out.packed_m8[f + i] = (uint8_t)m;
+        if (out.packed_m16) out.packed_m16[f + i] = (uint16_t)m;
+    }
+    // Block tables, 64 (block, row) pairs at a time, in the order the format keeps them.
+    auto window_of_block = [&](int t) -> int {  // of the unit's block t
+        int w = 0;
+        if (un.y > 1)
+            for (int h = kMaxUnitWindows >> 1; h > 0; h >>= 1) w += w + h < un.y && bp[w + h] - bp[0] <= t ? h : 0;
+        return w;
+    };
+    if constexpr (KB32) {
+        row_start[lane] = x.lo;
+        // entries of the window that earlier pieces hold
+        int ahead = x.lo - x.row_lo;
+        for (int h = 1; h < (1 << p.lv); h <<= 1) ahead += __shfl_xor(ahead, h, 64);
+        int packed = __shfl(x.row_lo, 0, 64) + __shfl(ahead, 0, 64);  // in packed order entries go block by block, row by row
+        const int n_pairs = n_t * V;
+        FS_WAVE_SYNC();
+        for (int i0 = 0; i0 < n_pairs; i0 += 64) {
+            const int i = i0 + lane;
+            const uint32_t m = i < n_pairs ? bits[i] : 0u;
+            const int cnt = __popc(m);
+            const int upto = wave_inclusive_scan(cnt);
+            if (i < n_pairs) packed_at[i] = packed + upto - cnt;
+            packed += __shfl(upto, 63, 64);
+        }
+        FS_WAVE_SYNC();
+        for (int i0 = 0; i0 < n_pairs; i0 += 64) {
+            const int i = i0 + lane;
+            if (i < n_pairs) {
+                const int t = i / V, row = i - t * V;
+                const int wl = window_of_block(t), first_t = bp[wl] - bp[0];
+                int before = 0;  // the row's entries in the window's earlier blocks of the unit
+                for (int k = first_t; k < t; k++) before += __popc(bits[k * V + row]);
+                const int b = b_lo + t - first_t;
+                if (b * KB >= o) {  // the block starts here
+                    const int64_t at = (int64_t)(bp[wl] + b) * V + row;
+                    out.row_base[at] = row_start[(wl << p.lv) + row] + before;
+                    if (b < own_hi) out.row_bits[at] = bits[i];
+                }
+            }
+        }
+    }
+    for (int t = lane; t < n_t; t += 64) {
+        const int wl = window_of_block(t), b = b_lo + t - (bp[wl] - bp[0]);
+        if (b * KB >= o) {
+            const int n_w = wp[wl + 1] - wp[wl], kb = max(0, min(KB, n_w - b * KB));
+            out.blk_desc[bp[wl] + b] = make_int4(wp[wl] + b * KB, kb | ((b + 1) * KB >= n_w ? 256 : 0) | (b == 0 ? 512 : 0), un.x + wl, 0);
+            if (KB32 && out.packed_ofs) out.packed_ofs[bp[wl] + b] = packed_at[t * V];
+        }
+    }
+    FS_WAVE_SYNC();
+    // The unit's share of the value array, put together where the columns were, kTileVectors vectors at a time: zeros,
+    // then the entries, then the copy out; after it the packed values, in their order.
+    const int v_lo = hub ? min(own_lo * KB, n_w0) + wp[0] : f;
+    const int v_hi = hub ? max(min(own_hi * KB, n_w0) + wp[0], v_lo) : f + n;
+    const int A = V * v_lo, n_el = V * (v_hi - v_lo);
+    int slot[NCH];  // relative to A; negative: not the unit's own
+    int pk[NCH];    // place in packed order
+    const int pk_lo = KB32 && out.packed_vals && v_lo < v_hi ? packed_at[(own_lo - b_lo) * V] : 0;
+    int n_pk = 0;
+    FS_EACH(h) {
+        slot[h] = -1;
+        pk[h] = 0;
+        if (64 * h < E) {
+            bool own = false;
+            if (64 * h + lane < E) {
+                int wl, row, kw, b;
+                place(code[h], wl, row, kw, b);
+                const int c = kw - b * KB, kb = min(KB, wp[wl + 1] - wp[wl] - b * KB);
+                const int at = V * (wp[wl] + b * KB) + row * kb + c;
+                out.csr_to_slot[pos[h]] = at;
+                own = b >= own_lo && b < own_hi;
+                if (own) slot[h] = at - A;
+                if (KB32 && own && out.packed_vals) {
+                    const int i = (bp[wl] - bp[0] + b - b_lo) * V + row;
+                    pk[h] = packed_at[i] + __popc(bits[i] & ((1u << c) - 1)) - pk_lo;
+                }
+            }
+            n_pk += __popcll(__ballot(own));
+        }
+    } FS_EACH_END;
+    if (!vals) return;
+    uint16_t *tile = reinterpret_cast<uint16_t *>(lds);
+    for (int e0 = 0; e0 < n_el; e0 += kTileVectors * V) {
+        const int m = min(n_el - e0, kTileVectors * V);
+        for (int i = lane * 8; i < m; i += 512) *reinterpret_cast<fs_u4 *>(tile + i) = fs_u4{0u, 0u, 0u, 0u};
+        FS_WAVE_SYNC();
+        FS_EACH(h) {
+            if (64 * h < E && slot[h] >= e0 && slot[h] < e0 + m) tile[slot[h] - e0] = (uint16_t)val[h];
+        } FS_EACH_END;
+        FS_WAVE_SYNC();
+        uint16_t *dst = out.vals_blk + A + e0;
+        if (V % 8 == 0) {
+            for (int i = lane * 8; i < m; i += 512) *reinterpret_cast<fs_u4 *>(dst + i) = *reinterpret_cast<const fs_u4 *>(tile + i);
+        } else if (V % 4 == 0) {
+            for (int i = lane * 4; i < m; i += 256) *reinterpret_cast<uint2 *>(dst + i) = *reinterpret_cast<const uint2 *>(tile + i);
+        } else {
+            for (int i = lane; i < m; i += 64) dst[i] = tile[i];
+        }
+        FS_WAVE_SYNC();
+    }
+    if (KB32 && out.packed_vals) {
+        FS_EACH(h) {
+            if (64 * h < E && slot[h] >= 0) tile[pk[h]] = (uint16_t)val[h];
+        } FS_EACH_END;
+        FS_WAVE_SYNC();
+        for (int i = lane; i < n_pk; i += 64) out.packed_vals[pk_lo + i] = tile[i];
+    }
+}
+
+// A block that more than one piece of a hub window reaches into, one wavefront each: the wavefront of the first
+// piece that begins inside it.  Its vectors, and the CSR position of each row's first entry in it, are in place.
+constexpr int kSharedPerWave = 2;  // units a wavefront looks at
+template <bool KB32>
+__global__ void __launch_bounds__(64) k_shared_blocks(int V, int KB, const int4 *__restrict__ units, const int *__restrict__ n_units, const int *__restrict__ first_vec,
+                                                      const int32_t *__restrict__ win_ptr, const int *__restrict__ blk_ptr,
+                                                      const uint16_t *__restrict__ vals, PlaceOut out)
+{
+    const int lane = threadIdx.x, n = *n_units;
+    const int my_u = blockIdx.x * kSharedPerWave + lane;
+    int my_x = -1, my_s = 0, my_kb = 0;  // the block that lane's unit is the first to begin inside
+    if (lane < kSharedPerWave && my_u < n) {
+        const int4 un = units[my_u];
+        if (un.w > 1 && un.z > 0) {
+            const int f_w = win_ptr[un.x], n_w = win_ptr[un.x + 1] - f_w;
+            const int o = first_vec[my_u] - f_w, b = o / KB;
+            if (o > b * KB && o < n_w && first_vec[my_u - 1] - f_w <= b * KB) {
+                my_x = blk_ptr[un.x] + b;
+                my_s = f_w + b * KB;
+                my_kb = min(KB, n_w - b * KB);
+            }
+        }
+    }
+    for (uint64_t todo = __ballot(my_x >= 0); todo; todo &= todo - 1) {
+    const int k = __builtin_ctzll(todo);
+    const int xb = __shfl(my_x, k, 64), s = __shfl(my_s, k, 64), kb = __shfl(my_kb, k, 64);
+    const uint32_t m = lane < kb ? out.vec_mask[s + lane] : 0u;
+    int32_t base = lane < V ? out.row_base[(int64_t)xb * V + lane] : 0;
+    int32_t packed = out.packed_vals ? out.packed_ofs[xb] : 0;
+    const uint64_t below = (1ull << lane) - 1;
+    for (int r0 = 0; r0 < V; r0 += 8) {  // eight rows' loads together
+        uint16_t v[8];
+        uint64_t row[8];
+#pragma unroll
+        for (int g = 0; g < 8; g++) {
+            const int r = r0 + g;
+            const bool has = r < V && ((m >> r) & 1u);
+            row[g] = __ballot(has);
+            const int32_t q = __shfl(base, min(r, 63), 64) + __popcll(row[g] & below);
+            v[g] = has && vals ? vals[q] : (uint16_t)0;
+        }
+#pragma unroll
+        for (int g = 0; g < 8; g++) {
+            const int r = r0 + g;
+            if (r >= V) break;
+            if (KB32 && lane == 0) out.row_bits[(int64_t)xb * V + r] = (uint32_t)row[g];
+            if (vals && lane < kb) {
+                out.vals_blk[(int64_t)V * s + r * kb + lane] = v[g];
+                if (out.packed_vals && ((m >> r) & 1u)) out.packed_vals[packed + __popcll(row[g] & below)] = v[g];
+            }
+            packed += __popcll(row[g]);
+        }
+    }
+    }
+}
+
+}  // namespace

@@ -1,0 +1,93 @@
+"""The conversion where its units of work change: windows just below and above what one wavefront takes, hub windows cut
+by columns (rows alike, one long row, identical rows, a longest row that says nothing about the others), groups of tiny
+and empty windows, a single row per window, every array bit for bit against the reference converter."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import upload_csr
+from test_gpu_parity import assert_format_equal, assert_items_valid, assert_row_base_valid, fs  # noqa: F401
+from workloads import Csr, csr_from_coo, stream
+
+pytestmark = pytest.mark.gpu
+
+
+def from_rows(rows, K, dtype="f16"):
+    """CSR with the given columns per row."""
+    r = np.repeat(np.arange(len(rows)), [len(c) for c in rows])
+    c = np.concatenate(rows) if len(r) else np.zeros(0, dtype=np.int64)
+    return csr_from_coo(len(rows), K, r, c, "u11", dtype, stream(3, 94, len(rows)))
+
+
+def pattern(kind, V, rng):
+    K = 40000
+    pick = lambda n, lo=0, hi=K: np.sort(rng.choice(hi - lo, size=n, replace=False)) + lo  # noqa: E731
+    rows = []
+    if kind == "edges":  # windows of 511, 512, 513 and 514 entries, then one entry, then none
+        for total in (511, 512, 513, 514, 1):
+            for r in range(V):
+                rows.append(pick((total + V - 1 - r) // V))
+        rows += [pick(0)] * V
+    elif kind == "alike":
+        rows = [pick(900) for _ in range(2 * V)]
+    elif kind == "one long row":
+        rows = [pick(20000)] + [pick(3) for _ in range(V - 1)] + [pick(7) for _ in range(V)]
+    elif kind == "identical":  # every vector full
+        c = pick(1500)
+        rows = [c] * V + [pick(2)] * V
+    elif kind == "apart":  # the longest row's columns lie before all others'
+        rows = [np.arange(3000)] + [pick(2500, 10000) for _ in range(V - 1)]
+    elif kind == "dense start":  # all rows hold the first columns, then thin out
+        rows = [np.unique(np.concatenate([np.arange(700), pick(300 * (r % 3 + 1))])) for r in range(2 * V)]
+    else:  # tiny: windows of a handful of entries and empty ones, ragged end
+        rows = [pick(int(rng.integers(0, 3))) if rng.random() < 0.6 else pick(0) for _ in range(37 * V + max(V - 3, 0))]
+    return from_rows(rows, K)
+
+
+@pytest.mark.parametrize("V,KB", [(1, 32), (2, 32), (4, 32), (8, 32), (16, 32), (32, 32), (3, 8), (8, 5)])
+@pytest.mark.parametrize("kind", ["edges", "alike", "one long row", "identical", "apart", "dense start", "tiny"])
+def test_convert_units_bit_exact(fs, kind, V, KB):  # noqa: F811
+    A = pattern(kind, V, np.random.default_rng(V * 100 + KB))
+    rp, ci, va = upload_csr(A)
+    for vals in (va, None):
+        fmt = fs.fs_convert(rp, ci, vals, A.M, A.K, torch_dtype=va.dtype, V=V, KB=KB)
+        ref = assert_format_equal(fmt, A, V, KB, with_vals=vals is not None)
+        assert_items_valid(fmt)
+        assert_row_base_valid(fmt, A)
+        if KB == 32:  # the occupancy masks, seen from the rows
+            desc = fmt.blk_desc_t().cpu().numpy().astype(np.int64)
+            want = np.zeros((fmt.n_blocks, V), dtype=np.uint32)
+            for x, (s, kf, _, _) in enumerate(desc):
+                m = ref.vec_mask[s:s + (kf & 255)]
+                for r in range(V):
+                    want[x, r] = int(((m >> np.uint32(r)) & np.uint32(1)) @ (np.uint32(1) << np.arange(len(m), dtype=np.uint32))) if len(m) else 0
+            assert np.array_equal(fmt.blk_row_bits_t().cpu().numpy().view(np.uint32), want)
+
+
+def test_convert_columns_beyond_26_bits_and_bad_hub_rows(fs):  # noqa: F811
+    """Columns up to 2^31 - 2, and hub windows whose columns do not ascend: refused wherever the fault lies."""
+    rng = np.random.default_rng(5)
+    K = 2 ** 31 - 1
+    rows = [np.sort(rng.choice(2 ** 31 - 2, size=n, replace=False)) for n in (900, 3, 400, 0, 70, 1, 2, 600, 5)]
+    A = from_rows(rows, K)
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, A.M, A.K, V=8)
+    assert_format_equal(fmt, A, 8, 32)
+    for row, at in ((0, 1), (0, 450), (0, 899), (2, 200), (7, 599), (8, 4)):
+        bad = ci.clone()
+        p = int(A.rowptr[row]) + at
+        bad[p] = bad[p - 1]
+        with pytest.raises(fs.FsError) as e:
+            fs.fs_convert(rp, bad, va, A.M, A.K, V=8)
+        assert e.value.code == 2
+        bad = ci.clone()
+        bad[int(A.rowptr[row]) + at] = -5
+        with pytest.raises(fs.FsError) as e:
+            fs.fs_convert(rp, bad, va, A.M, A.K, V=8)
+        assert e.value.code == 2
+    for i, v in ((3, 10 ** 9), (5, -1), (A.M, A.nnz - 1), (0, 1)):
+        bad_rp = rp.clone()
+        bad_rp[i] = v
+        with pytest.raises(fs.FsError) as e:
+            fs.fs_convert(bad_rp, ci, va, A.M, A.K, V=8)
+        assert e.value.code == 2
