@@ -11,6 +11,8 @@ import ctypes
 import os
 from typing import Optional, Tuple
 
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # FLASHSPARSE_LIB points at an alternative build of the same library (e.g. one compiled with other -D flags)
 _LIB_PATH = os.environ.get("FLASHSPARSE_LIB") or os.path.join(_HERE, "libflashsparse_hip.so")
@@ -51,11 +53,11 @@ def library_path() -> str:
 
 
 def load_library():
-    """Load the HIP library; raises (never falls back) when it has not been built."""
+    """Load the HIP library (after torch, so that it binds to the HIP runtime torch has loaded); raises (never falls back)
+    when it has not been built."""
     global _lib
     if _lib is not None:
         return _lib
-    import torch  # noqa: F401  (first, so that this library binds to the HIP runtime torch has loaded)
     if not os.path.exists(_LIB_PATH):
         raise ImportError("%s is missing: build it with `python -m paper_2412_11007_amd.build`" % _LIB_PATH)
     lib = ctypes.CDLL(_LIB_PATH)
@@ -127,7 +129,6 @@ def fs_status_string(code: int) -> str:
 
 
 def _dtype_code(torch_dtype) -> int:
-    import torch
     if torch_dtype == torch.float16:
         return FS_F16
     if torch_dtype == torch.bfloat16:
@@ -135,10 +136,27 @@ def _dtype_code(torch_dtype) -> int:
     raise TypeError("element type must be torch.float16 or torch.bfloat16")
 
 
+# Small calls are bound by the host (a launch takes about 3 us, the kernel of a 4096-row SpMM 4.6 us), so the way to the
+# C call makes no object it can do without: a stream's handle straight from torch (0.1 us; through a
+# torch.cuda.Stream 2.8 us), no workspace query where no window is cut, outputs from new_empty.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
 def _stream_ptr(stream) -> int:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    """Handle of ``stream``, or of the current device's current stream."""
+    return _raw_stream(_current_device()) if stream is None else int(stream.cuda_stream)
+
+
+def _workspace(fmt, work, like, query, *args):
+    """The caller's workspace or, where there is none, one of the size ``query(fmt, *args)`` asks for, as (tensor that has
+    to outlive the call, pointer, bytes).  A workspace holds the parts of cut windows: without any there is none."""
+    if work is None:
+        need = query(fmt, *args) if fmt.c.n_split_items else 0
+        if not need:
+            return None, 0, 0
+        work = like.new_empty(need, dtype=torch.uint8)
+    return work, work.data_ptr(), work.numel() * work.element_size()
 
 
 def fs_format_bytes(M: int, nnz: int, V: int = 0, KB: int = 0, dtype: int = FS_F16) -> Tuple[int, int]:
@@ -166,61 +184,48 @@ class FsFormat:
 
     # views of the converted arrays (device tensors sharing the arena's memory)
     def win_ptr_t(self):
-        import torch
-        return self._view(self.c.win_ptr, 4 * (self.c.W + 1), torch.int32)
+            return self._view(self.c.win_ptr, 4 * (self.c.W + 1), torch.int32)
 
     def vec_col_t(self):
-        import torch
-        return self._view(self.c.vec_col, 4 * self.c.nvec, torch.int32)
+            return self._view(self.c.vec_col, 4 * self.c.nvec, torch.int32)
 
     def vec_mask_t(self):
-        import torch
-        return self._view(self.c.vec_mask, 4 * self.c.nvec, torch.int32)
+            return self._view(self.c.vec_mask, 4 * self.c.nvec, torch.int32)
 
     def csr_to_slot_t(self):
-        import torch
-        return self._view(self.c.csr_to_slot, 4 * self.c.nnz, torch.int32)
+            return self._view(self.c.csr_to_slot, 4 * self.c.nnz, torch.int32)
 
     def vals_blk_t(self):
         return self._view(self.c.vals_blk, 2 * self.c.V * self.c.nvec, self.torch_dtype)
 
     def blk_desc_t(self):
-        import torch
-        return self._view(self.c.blk_desc, 16 * self.c.n_blocks, torch.int32).view(-1, 4)
+            return self._view(self.c.blk_desc, 16 * self.c.n_blocks, torch.int32).view(-1, 4)
 
     def items_t(self):
-        import torch
-        return self._view(self.c.items, 16 * self.c.n_items, torch.int32).view(-1, 4)
+            return self._view(self.c.items, 16 * self.c.n_items, torch.int32).view(-1, 4)
 
     def item_order_t(self):
-        import torch
-        return self._view(self.c.item_order, 4 * self.c.n_items, torch.int32)
+            return self._view(self.c.item_order, 4 * self.c.n_items, torch.int32)
 
     def items_by_cost_t(self):
-        import torch
-        return self._view(self.c.items_by_cost, 16 * self.c.n_items, torch.int32).view(-1, 4)
+            return self._view(self.c.items_by_cost, 16 * self.c.n_items, torch.int32).view(-1, 4)
 
     def blk_row_base_t(self):
-        import torch
-        return self._view(self.c.blk_row_base, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
+            return self._view(self.c.blk_row_base, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
 
     def blk_row_bits_t(self):
-        import torch
-        return self._view(self.c.blk_row_bits, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
+            return self._view(self.c.blk_row_bits, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
 
     def split_windows_t(self):
-        import torch
-        return self._view(self.c.split_windows, 16 * self.c.n_split_windows, torch.int32).view(-1, 4)
+            return self._view(self.c.split_windows, 16 * self.c.n_split_windows, torch.int32).view(-1, 4)
 
     def slot_range_t(self):
-        import torch
-        return self._view(self.c.slot_range, 8 * self.c.n_split_items, torch.int32).view(-1, 2)
+            return self._view(self.c.slot_range, 8 * self.c.n_split_items, torch.int32).view(-1, 2)
 
 
 def fs_convert(rowptr, colidx, vals, M: int, K: int, torch_dtype=None, V: int = 0, KB: int = 0, chunk: int = 0,
                stream=None, arena=None, scratch=None) -> FsFormat:
     """CSR (int32 device tensors) -> window format.  ``vals`` may be None (pattern only)."""
-    import torch
     lib = load_library()
     nnz = int(colidx.numel())
     if vals is not None:
@@ -260,18 +265,17 @@ def fs_spmm(fmt: FsFormat, B, vals=None, out=None, work=None, stream=None, event
     ``events`` = (before, after) raw hipEvent_t handles switches to fs_spmm_timed,
     which records them around the main kernel.
     """
-    import torch
     K, N = B.shape
     assert B.is_cuda and B.dtype == fmt.torch_dtype and B.stride(1) == 1 and K == fmt.c.K
     if out is None:
-        out = torch.empty((fmt.c.M, N), dtype=B.dtype, device=B.device)
-    assert out.shape == (fmt.c.M, N) and out.stride(1) == 1 and out.dtype == B.dtype
-    need = fs_spmm_workspace_bytes(fmt, N)
-    if work is None and need:
-        work = torch.empty(need, dtype=torch.uint8, device=B.device)
-    args = (ctypes.byref(fmt.c), 0 if vals is None else vals.data_ptr(), B.data_ptr(), N,
-            B.stride(0), out.data_ptr(), out.stride(0),
-            0 if work is None else work.data_ptr(), 0 if work is None else work.numel(), _stream_ptr(stream))
+        out = B.new_empty(fmt.c.M, N)
+        ldo = N
+    else:
+        assert out.shape == (fmt.c.M, N) and out.stride(1) == 1 and out.dtype == B.dtype
+        ldo = out.stride(0)
+    work, work_ptr, work_bytes = _workspace(fmt, work, B, fs_spmm_workspace_bytes, N)
+    args = (ctypes.byref(fmt.c), 0 if vals is None else vals.data_ptr(), B.data_ptr(), N, B.stride(0), out.data_ptr(), ldo,
+            work_ptr, work_bytes, _stream_ptr(stream))
     if events is None:
         rc = load_library().fs_spmm(*args)
     else:
@@ -285,16 +289,13 @@ def bind_spmm(fmt: FsFormat, B, out, work=None, vals=None, stream=None):
     """fs_spmm with its arguments checked and marshalled once: returns a callable that only makes the C call
     (for loops that repeat one call and cannot afford the per-call checks of ``fs_spmm``).  The tensors must
     stay alive and unchanged in place; the stream is the one current now unless given."""
-    import torch
     K, N = B.shape
     assert B.is_cuda and B.dtype == fmt.torch_dtype and B.stride(1) == 1 and K == fmt.c.K
     assert out.shape == (fmt.c.M, N) and out.stride(1) == 1 and out.dtype == B.dtype
-    need = fs_spmm_workspace_bytes(fmt, N)
-    if work is None and need:
-        work = torch.empty(need, dtype=torch.uint8, device=B.device)
+    work, work_ptr, work_bytes = _workspace(fmt, work, B, fs_spmm_workspace_bytes, N)
     fn = load_library().fs_spmm
     args = (ctypes.byref(fmt.c), 0 if vals is None else vals.data_ptr(), B.data_ptr(), N, B.stride(0), out.data_ptr(),
-            out.stride(0), 0 if work is None else work.data_ptr(), 0 if work is None else work.numel(), _stream_ptr(stream))
+            out.stride(0), work_ptr, work_bytes, _stream_ptr(stream))
     keep = (fmt, B, out, work, vals)
 
     def call():
@@ -341,18 +342,17 @@ def fs_sddmm(fmt: FsFormat, X, Y, out=None, stream=None, out_csr=None, blocked=T
     """Scores (X @ Y^T) at the stored positions of A.  Returns them in the vals_blk layout (V*nvec elements);
     ``out_csr`` (nnz elements) additionally receives them in CSR order from the same kernel.  With
     ``blocked=False`` only ``out_csr`` is written (allocated if not given) and returned."""
-    import torch
     assert X.is_cuda and Y.is_cuda and X.dtype == fmt.torch_dtype and Y.dtype == fmt.torch_dtype
     assert X.shape[0] == fmt.c.M and Y.shape[0] == fmt.c.K and X.shape[1] == Y.shape[1]
     assert X.stride(1) == 1 and Y.stride(1) == 1
     if blocked:
         if out is None:
-            out = torch.empty(fmt.c.V * fmt.c.nvec, dtype=X.dtype, device=X.device)
+            out = X.new_empty(fmt.c.V * fmt.c.nvec)
         assert out.numel() == fmt.c.V * fmt.c.nvec and out.is_contiguous()
     else:
         out = None
         if out_csr is None:
-            out_csr = torch.empty(fmt.c.nnz, dtype=X.dtype, device=X.device)
+            out_csr = X.new_empty(fmt.c.nnz)
     if out_csr is not None:
         assert out_csr.numel() == fmt.c.nnz and out_csr.is_contiguous() and out_csr.dtype == X.dtype
     rc = load_library().fs_sddmm(ctypes.byref(fmt.c), X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0),
@@ -373,19 +373,14 @@ def fs_edge_softmax_workspace_bytes(fmt: FsFormat) -> int:
 
 def fs_edge_softmax(fmt: FsFormat, vals, out=None, scale: float = 1.0, work=None, stream=None):
     """Row softmax of scale * value over the stored entries, on vals_blk-layout arrays (out may be vals)."""
-    import torch
     assert vals.is_cuda and vals.dtype == fmt.torch_dtype and vals.is_contiguous()
     assert vals.numel() == fmt.c.V * fmt.c.nvec
     if out is None:
         out = torch.empty_like(vals)
     assert out.numel() == vals.numel() and out.dtype == vals.dtype and out.is_contiguous()
-    need = fs_edge_softmax_workspace_bytes(fmt)
-    if work is None and need > 0:
-        work = torch.empty(need, dtype=torch.uint8, device=vals.device)
-    rc = load_library().fs_edge_softmax(ctypes.byref(fmt.c), vals.data_ptr(), out.data_ptr(), float(scale),
-                                        work.data_ptr() if work is not None else None,
-                                        work.numel() * work.element_size() if work is not None else 0,
-                                        _stream_ptr(stream))
+    work, work_ptr, work_bytes = _workspace(fmt, work, vals, fs_edge_softmax_workspace_bytes)
+    rc = load_library().fs_edge_softmax(ctypes.byref(fmt.c), vals.data_ptr(), out.data_ptr(), float(scale), work_ptr,
+                                        work_bytes, _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_edge_softmax")
     return out
@@ -394,19 +389,14 @@ def fs_edge_softmax(fmt: FsFormat, vals, out=None, scale: float = 1.0, work=None
 def fs_edge_softmax_backward(fmt: FsFormat, probs, grad, out=None, scale: float = 1.0, work=None, stream=None):
     """Gradient of fs_edge_softmax: scale * p * (g - row sum of p * g), on vals_blk-layout arrays (out may be
     either input)."""
-    import torch
     for t in (probs, grad):
         assert t.is_cuda and t.dtype == fmt.torch_dtype and t.is_contiguous() and t.numel() == fmt.c.V * fmt.c.nvec
     if out is None:
         out = torch.empty_like(probs)
     assert out.numel() == probs.numel() and out.dtype == probs.dtype and out.is_contiguous()
-    need = fs_edge_softmax_workspace_bytes(fmt)
-    if work is None and need > 0:
-        work = torch.empty(need, dtype=torch.uint8, device=probs.device)
+    work, work_ptr, work_bytes = _workspace(fmt, work, probs, fs_edge_softmax_workspace_bytes)
     rc = load_library().fs_edge_softmax_backward(ctypes.byref(fmt.c), probs.data_ptr(), grad.data_ptr(), float(scale),
-                                                 out.data_ptr(), work.data_ptr() if work is not None else None,
-                                                 work.numel() * work.element_size() if work is not None else 0,
-                                                 _stream_ptr(stream))
+                                                 out.data_ptr(), work_ptr, work_bytes, _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_edge_softmax_backward")
     return out
@@ -414,7 +404,6 @@ def fs_edge_softmax_backward(fmt: FsFormat, probs, grad, out=None, scale: float 
 
 def fs_pack_values(fmt: FsFormat, vals=None, out=None, stream=None):
     """Bitmap-packed copy of a vals_blk-layout array (default: the format's own values) for fs_spmm_packed."""
-    import torch
     lib = load_library()
     n = ctypes.c_size_t(0)
     rc = lib.fs_pack_bytes(ctypes.byref(fmt.c), ctypes.byref(n))
@@ -433,21 +422,15 @@ def fs_pack_values(fmt: FsFormat, vals=None, out=None, stream=None):
 
 def fs_spmm_packed(fmt: FsFormat, packed, B, out=None, work=None, stream=None):
     """C = A @ B with A's values taken from a buffer made by fs_pack_values."""
-    import torch
     assert B.is_cuda and B.dtype == fmt.torch_dtype and B.dim() == 2 and B.stride(1) == 1 and B.shape[0] == fmt.c.K
     assert packed.is_cuda and packed.dtype == torch.uint8
     N = B.shape[1]
     if out is None:
-        out = torch.empty((fmt.c.M, N), dtype=B.dtype, device=B.device)
+        out = B.new_empty(fmt.c.M, N)
     assert out.shape == (fmt.c.M, N) and out.dtype == B.dtype and out.stride(1) == 1
-    need = fs_spmm_workspace_bytes(fmt, N)
-    if work is None and need > 0:
-        work = torch.empty(need, dtype=torch.uint8, device=B.device)
+    work, work_ptr, work_bytes = _workspace(fmt, work, B, fs_spmm_workspace_bytes, N)
     rc = load_library().fs_spmm_packed(ctypes.byref(fmt.c), packed.data_ptr(), B.data_ptr(), N, B.stride(0),
-                                       out.data_ptr(), out.stride(0),
-                                       work.data_ptr() if work is not None else None,
-                                       work.numel() * work.element_size() if work is not None else 0,
-                                       _stream_ptr(stream))
+                                       out.data_ptr(), out.stride(0), work_ptr, work_bytes, _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_spmm_packed")
     return out
@@ -473,22 +456,17 @@ def fs_attention(fmt: FsFormat, X, Y, H, scale: float = 1.0, out=None, work=None
 
 
 def _attention_like(name, fmt, X, Y, H, scale, out, work, stream):
-    import torch
     for t in (X, Y, H):
         assert t.is_cuda and t.dtype == fmt.torch_dtype and t.dim() == 2 and t.stride(1) == 1
     d, N = X.shape[1], H.shape[1]
     assert X.shape[0] == fmt.c.M and Y.shape == (fmt.c.K, d) and H.shape[0] == fmt.c.K
     if out is None:
-        out = torch.empty((fmt.c.M, N), dtype=H.dtype, device=H.device)
+        out = H.new_empty(fmt.c.M, N)
     assert out.shape == (fmt.c.M, N) and out.dtype == H.dtype and out.stride(1) == 1
-    need = fs_attention_workspace_bytes(fmt, N)
-    if work is None and need > 0:
-        work = torch.empty(need, dtype=torch.uint8, device=H.device)
+    work, work_ptr, work_bytes = _workspace(fmt, work, H, fs_attention_workspace_bytes, N)
     rc = getattr(load_library(), name)(ctypes.byref(fmt.c), X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), d,
                                      float(scale), H.data_ptr(), N, H.stride(0), out.data_ptr(), out.stride(0),
-                                     work.data_ptr() if work is not None else None,
-                                     work.numel() * work.element_size() if work is not None else 0,
-                                     _stream_ptr(stream))
+                                     work_ptr, work_bytes, _stream_ptr(stream))
     if rc:
         raise FsError(rc, name)
     return out
@@ -496,9 +474,8 @@ def _attention_like(name, fmt, X, Y, H, scale, out, work, stream):
 
 def fs_blk_to_csr(fmt: FsFormat, blk, out=None, stream=None):
     """Reorder a vals_blk-layout array into CSR order."""
-    import torch
     if out is None:
-        out = torch.empty(fmt.c.nnz, dtype=blk.dtype, device=blk.device)
+        out = blk.new_empty(fmt.c.nnz)
     rc = load_library().fs_blk_to_csr(ctypes.byref(fmt.c), blk.data_ptr(), out.data_ptr(), _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_blk_to_csr")
@@ -507,11 +484,10 @@ def fs_blk_to_csr(fmt: FsFormat, blk, out=None, stream=None):
 
 def fs_csr_to_blk(fmt: FsFormat, vals_csr, out=None, stream=None):
     """CSR-order values -> vals_blk layout (zeros elsewhere): new values for the same pattern."""
-    import torch
     assert vals_csr.is_cuda and vals_csr.dtype == fmt.torch_dtype and vals_csr.is_contiguous()
     assert vals_csr.numel() == fmt.c.nnz
     if out is None:
-        out = torch.empty(fmt.c.V * fmt.c.nvec, dtype=vals_csr.dtype, device=vals_csr.device)
+        out = vals_csr.new_empty(fmt.c.V * fmt.c.nvec)
     assert out.numel() == fmt.c.V * fmt.c.nvec and out.is_contiguous()
     rc = load_library().fs_csr_to_blk(ctypes.byref(fmt.c), vals_csr.data_ptr(), out.data_ptr(), _stream_ptr(stream))
     if rc:
@@ -522,7 +498,6 @@ def fs_csr_to_blk(fmt: FsFormat, vals_csr, out=None, stream=None):
 def fs_csr_transpose(rowptr, colidx, M: int, K: int, stream=None):
     """CSR of A^T on the GPU: returns (rowptr_t[K+1], colidx_t[nnz], perm[nnz]), perm[q] = position in
     A's CSR order of entry q of A^T's.  Convert the result with fs_convert for A^T * dC."""
-    import torch
     assert rowptr.is_cuda and colidx.is_cuda and rowptr.dtype == torch.int32 and colidx.dtype == torch.int32
     assert rowptr.is_contiguous() and colidx.is_contiguous() and rowptr.numel() == M + 1
     nnz = colidx.numel()
@@ -547,11 +522,10 @@ def fs_csr_transpose(rowptr, colidx, M: int, K: int, stream=None):
 
 def fs_gather16(src, idx, out=None, stream=None):
     """out[i] = src[idx[i]] on 16-bit elements (values of A carried into the CSR order of A^T)."""
-    import torch
     assert src.is_cuda and idx.is_cuda and idx.dtype == torch.int32 and src.element_size() == 2
     assert src.is_contiguous() and idx.is_contiguous()
     if out is None:
-        out = torch.empty(idx.numel(), dtype=src.dtype, device=src.device)
+        out = src.new_empty(idx.numel())
     assert out.numel() == idx.numel() and out.dtype == src.dtype and out.is_contiguous()
     rc = load_library().fs_gather16(src.data_ptr(), idx.data_ptr(), idx.numel(), out.data_ptr(), _stream_ptr(stream))
     if rc:
@@ -561,7 +535,6 @@ def fs_gather16(src, idx, out=None, stream=None):
 
 def fs_gather_probe(fmt: FsFormat, B, sink=None, stream=None):
     """Measurement aid: only the gather of fs_spmm (the rows of B named by the format's column indices)."""
-    import torch
     assert B.is_cuda and B.dim() == 2 and B.stride(1) == 1 and B.shape[0] == fmt.c.K and B.element_size() == 2
     if sink is None:
         sink = torch.empty(1024 * 256, dtype=torch.int32, device=B.device)
@@ -574,7 +547,6 @@ def fs_gather_probe(fmt: FsFormat, B, sink=None, stream=None):
 
 def fs_read_bytes(src, repeats: int = 1, sink=None, stream=None):
     """Measurement aid: read ``src`` ``repeats`` times in one kernel (L2 bandwidth when it fits the L2s)."""
-    import torch
     if sink is None:
         sink = torch.empty(2048 * 256, dtype=torch.int32, device=src.device)
     rc = load_library().fs_read_bytes(src.data_ptr(), src.numel() * src.element_size(), int(repeats), sink.data_ptr(),
