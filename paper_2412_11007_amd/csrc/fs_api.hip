@@ -205,7 +205,7 @@ extern "C" fs_status fs_sddmm(const fs_format *fmt, const void *d_X, int64_t ldx
     if (d % 8 || ldx % 8 || ldy % 8 || !aligned(d_X, 16) || !aligned(d_Y, 16) || !aligned(d_out_blk, 16) ||
         !aligned(d_out_csr, 2))
         return FS_ERR_INVALID_ARG;
-    if (d_out_csr && !fmt->blk_row_base) return FS_ERR_INVALID_ARG;
+    if (!fmt->blk_row_bits || (d_out_csr && !fmt->blk_row_base)) return FS_ERR_INVALID_ARG;
     if (d >= ((int64_t)1 << 24)) return FS_ERR_TOO_LARGE;
     return fs_sddmm_launch(fmt, d_X, ldx, d_Y, ldy, d, d_out_blk, d_out_csr, (hipStream_t)stream);
 }

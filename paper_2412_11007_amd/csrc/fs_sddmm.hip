@@ -29,10 +29,10 @@
 namespace {
 
 // The scores of one block, masked by the pattern, to memory.  Lane (j, g): acc[t][e] is the score of window row
-// j and vector 8g + 4t + e; msk is the occupancy mask of vector `lane` (zero past the width), rbase the CSR position
-// of row j's first entry in the block, blk the block's place in the value array (null: CSR order only).
+// j and vector 8g + 4t + e; bit c of bits says whether row j stores vector c, rbase is the CSR position of row j's first
+// entry in the block, blk the block's place in the value array (null: CSR order only).
 template <int DT, int V, bool CSR>
-__device__ __forceinline__ void fs_store_scores(const fs_f4 (&acc)[2], uint32_t msk, int kb, int rbase, int lane, uint16_t *tile,
+__device__ __forceinline__ void fs_store_scores(const fs_f4 (&acc)[2], uint32_t bits, int kb, int rbase, int lane, uint16_t *tile,
                                                 uint16_t *__restrict__ blk, uint16_t *__restrict__ out_csr)
 {
     const int j = lane & 15, g = lane >> 4;
@@ -41,14 +41,6 @@ __device__ __forceinline__ void fs_store_scores(const fs_f4 (&acc)[2], uint32_t 
     o.u.y = fs_pack2<DT>(acc[0][2], acc[0][3]);
     o.u.z = fs_pack2<DT>(acc[1][0], acc[1][1]);
     o.u.w = fs_pack2<DT>(acc[1][2], acc[1][3]);
-    // bit c of `bits`: vector c of the block stores window row j.  Wave-wide ballots over the
-    // per-vector occupancy masks, one per window row, instead of eight cross-lane reads.
-    uint32_t bits = 0;
-#pragma unroll
-    for (int r = 0; r < V; r++) {
-        const uint32_t has = (uint32_t)__ballot((msk >> r) & 1u);
-        bits = (j == r) ? has : bits;
-    }
     const uint32_t mine = bits >> (8 * g);  // bit x: vector 8g + x
     uint32_t keep[4];  // 0xFFFF per stored position, else 0: sign-extended single bits
 #pragma unroll
@@ -117,7 +109,7 @@ __device__ __forceinline__ bool fs_sddmm_unit(const int4 *__restrict__ items, in
 template <int DT, int V, int KS, int BB, bool CHUNKS, bool BIG, bool CSR>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
 k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n_blocks, int G, const int4 *__restrict__ blk_desc,
-        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ vec_mask, int nvec,
+        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ row_bits, int nvec,
         const uint16_t *__restrict__ X, int64_t ldx, const uint16_t *__restrict__ Y, int64_t ldy, int d,
         uint16_t *__restrict__ out, int64_t M, uint16_t *__restrict__ out_csr, const int32_t *__restrict__ row_base)
 {
@@ -164,11 +156,8 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
         const char *base = reinterpret_cast<const char *>(vec_col + min(b.s, nvec - 1));
         return *reinterpret_cast<const int32_t *>(base + min(v_byte, 4u * (uint32_t)(max(b.kb, 1) - 1)));
     };
-    auto load_mask = [&](const BlockDesc &b) -> uint32_t {
-        const char *base = reinterpret_cast<const char *>(vec_mask + min(b.s, nvec - 1));
-        const uint32_t m = *reinterpret_cast<const uint32_t *>(base + min(4u * (uint32_t)lane, 4u * (uint32_t)(max(b.kb, 1) - 1)));
-        return lane < b.kb ? m : 0u;
-    };
+    // occupancy of the lane's window row in block i of the unit (any row's for lanes past V, which store nothing)
+    auto load_bits = [&](int i) -> uint32_t { return row_bits[(int64_t)(first + min(i, nblk - 1)) * V + (j & (V - 1))]; };
     fs_u4 stage[NLD];
     uint32_t grow[NLD];  // byte offsets of the rows this lane gathers in a step (row numbers if BIG)
     auto rows_of = [&](const int (&cols)[BB]) {
@@ -202,26 +191,26 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
     const int n_steps = (nblk + BB - 1) / BB;
     BlockDesc cur[BB], nxt[BB];
     int col[BB];
-    uint32_t msk[BB], msk_n[BB];
+    uint32_t bits[BB], bits_n[BB];
     fs_frag xf[BB][KS];
     auto load_xs = [&](const BlockDesc (&blk)[BB], int f_base) {
 #pragma unroll
         for (int b = 0; b < BB; b++) load_x(blk[b].w, f_base, xf[b]);
     };
-    // the indices and masks of a later step, loaded ahead
+    // the indices and row occupancies of a later step, loaded ahead
     auto look_ahead = [&](int st) {
 #pragma unroll
         for (int b = 0; b < BB; b++) {
             nxt[b] = fs_item_block(my_desc, st * BB + b, nblk);
             col[b] = load_cols(nxt[b]);
-            msk_n[b] = load_mask(nxt[b]);
+            bits_n[b] = load_bits(st * BB + b);
         }
     };
 #pragma unroll
     for (int b = 0; b < BB; b++) {
         cur[b] = fs_item_block(my_desc, b, nblk);
         col[b] = load_cols(cur[b]);
-        msk[b] = load_mask(cur[b]);
+        bits[b] = load_bits(b);
     }
     rows_of(col);
     gather(0);
@@ -268,7 +257,7 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
             if (kb <= 0) continue;
             int rbase = 0;
             if constexpr (CSR) rbase = j < V ? row_base[(int64_t)(first + st * BB + u) * V + j] : 0;
-            fs_store_scores<DT, V, CSR>(acc[u], msk[u], kb, rbase, lane, tile, out ? out + (int64_t)V * cur[u].s : nullptr, out_csr);
+            fs_store_scores<DT, V, CSR>(acc[u], bits[u], kb, rbase, lane, tile, out ? out + (int64_t)V * cur[u].s : nullptr, out_csr);
         }
         if (more) {
 #pragma unroll
@@ -276,7 +265,7 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
                 // blocks of one window keep its rows of X (in operand layout, so a load of half a step's gather)
                 if (!CHUNKS && nxt[b].w != cur[b].w) load_x(nxt[b].w, 0, xf[b]);
                 cur[b] = nxt[b];
-                msk[b] = msk_n[b];
+                bits[b] = bits_n[b];
             }
             look_ahead(st + 2);
         }
@@ -288,7 +277,7 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
 template <int DT, int V, bool BIG, bool CSR>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CSR ? 5 : 6)))
 k_sddmm_short(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n_blocks, int G, const int4 *__restrict__ blk_desc,
-        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ vec_mask, int,
+        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ row_bits, int,
         const uint16_t *__restrict__ X, int64_t ldx, const uint16_t *__restrict__ Y, int64_t ldy, int d,
         uint16_t *__restrict__ out, int64_t M, uint16_t *__restrict__ out_csr, const int32_t *__restrict__ row_base)
 {
@@ -307,18 +296,18 @@ k_sddmm_short(const int4 *__restrict__ items, int n_items, int slice, int n_swz,
     const int4 my_desc = blk_desc[first + min(lane, nblk - 1)];
 
     for (int b0 = 0; b0 < nblk; b0 += BB) {
-        // round of up to BB blocks: first every block's indices, masks and X rows, then every Y row,
+        // round of up to BB blocks: first every block's indices, row occupancies and X rows, then every Y row,
         // so that a round costs two memory round trips however many blocks it holds
         BlockDesc dsc[BB];
         int col[BB];
-        uint32_t msk[BB];
+        uint32_t bits[BB];
         int rbase[BB];  // CSR position of window row j's first entry in the block (CSR-order output only)
         fs_frag xf[BB];
 #pragma unroll
         for (int u = 0; u < BB; u++) {
             dsc[u] = fs_item_block(my_desc, b0 + u, nblk);
             col[u] = (lane < dsc[u].kb) ? vec_col[dsc[u].s + lane] : -1;
-            msk[u] = (lane < dsc[u].kb) ? vec_mask[dsc[u].s + lane] : 0u;
+            bits[u] = row_bits[(int64_t)(first + min(b0 + u, nblk - 1)) * V + (j & (V - 1))];
             rbase[u] = 0;
             if constexpr (CSR) rbase[u] = (j < V && b0 + u < nblk) ? row_base[(int64_t)(first + b0 + u) * V + j] : 0;
             // X operand: lane (j, g) holds X[w*V + j][8g .. 8g+7]; rows past V or M are zero
@@ -350,7 +339,7 @@ k_sddmm_short(const int4 *__restrict__ items, int n_items, int slice, int n_swz,
             fs_f4 acc[2];
 #pragma unroll
             for (int t = 0; t < 2; t++) acc[t] = fs_mfma_16x16x32<DT>(yf[u][t], xf[u], fs_f4{0.f, 0.f, 0.f, 0.f});
-            fs_store_scores<DT, V, CSR>(acc, msk[u], kb, rbase[u], lane, lds, out ? out + (int64_t)V * dsc[u].s : nullptr, out_csr);
+            fs_store_scores<DT, V, CSR>(acc, bits[u], kb, rbase[u], lane, lds, out ? out + (int64_t)V * dsc[u].s : nullptr, out_csr);
         }
     }
 }
@@ -362,11 +351,13 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
     if (f->n_blocks == 0) return FS_OK;
     const int n_blocks = (int)f->n_blocks;
     // The launch order pays where hub windows hold a good part of the work and Y is more than one XCD's L2 holds
-    // (R-MAT, d = 32: 47 -> 44 us with 16 MB of Y, 12.7 -> 13.0 us with 4 MB); otherwise four block slots per
-    // wavefront (4 to 8 measured best from 30 thousand to 200 thousand blocks, 16 and more lose 5-15 %).
+    // (R-MAT, d = 32: 47 -> 44 us with 16 MB of Y, 12.7 -> 13.0 us with 4 MB); otherwise up to four block slots per
+    // wavefront (4 to 8 measured best from 11 thousand to 200 thousand blocks, 16 and more lose 5-15 %), fewer where that
+    // leaves less than eight wavefronts per CU: then a wavefront's own chain of steps is the whole time (R-MAT of 8 k
+    // rows, 3 k blocks, d = 248: 14.1 us with four slots, 8.5 us with one).
     const bool ordered = f->n_cut_items * 8 >= f->n_items && f->K * ldy * 2 > ((int64_t)4 << 20);
     const int4 *items = ordered ? (const int4 *)f->items_by_cost : nullptr;
-    int G = 4;
+    int G = std::min(std::max(n_blocks / 2048, 1), 4);
 #ifdef FS_TUNING_ENV  // tuning builds only (-DFS_TUNING_ENV): the shipped library reads no environment
     if (const char *e = getenv("FS_SDDMM_G")) G = std::min(std::max(atoi(e), 1), 64);
 #endif
@@ -376,7 +367,7 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
                      (f->M + 32) * ldx * 2 >= ((int64_t)1 << 32);
     const fs_launch_geometry geo = fs_launch_geometry_for(f, 1);
     const dim3 grid(ordered ? (unsigned)geo.nbx : (unsigned)(((int64_t)n_blocks + G - 1) / G)), block(64);
-#define FS_SDDMM_ARGS items, (int)f->n_items, geo.slice, geo.n_swz, n_blocks, G, (const int4 *)f->blk_desc, f->vec_col, f->vec_mask, (int)f->nvec, X, ldx, Y, ldy, (int)d, out, f->M, out_csr, f->blk_row_base
+#define FS_SDDMM_ARGS items, (int)f->n_items, geo.slice, geo.n_swz, n_blocks, G, (const int4 *)f->blk_desc, f->vec_col, f->blk_row_bits, (int)f->nvec, X, ldx, Y, ldy, (int)d, out, f->M, out_csr, f->blk_row_base
 #define FS_SDDMM_LAUNCH(...)  /* the kernel and its first template arguments */                         \
     {                                                                                                     \
         if (out_csr) {                                                                                    \
