@@ -1,9 +1,10 @@
-"""ctypes binding of the C ABI in ``include/flashsparse.h``.
+"""Binding of the C ABI in ``include/flashsparse.h``.
 
 Same names as the C entry points.  Argument marshalling only: every step of the
 computation runs in the HIP library; torch supplies device memory and the
-current stream.  There is no fallback: if the shared library is missing the
-first call raises.
+current stream.  Calls that allocate their own result go through ``_fs_torch``,
+a small native module; the others, and whatever it does not take, through ctypes.
+There is no fallback: if a shared library is missing the first call raises.
 """
 from __future__ import annotations
 
@@ -17,6 +18,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 # FLASHSPARSE_LIB points at an alternative build of the same library (e.g. one compiled with other -D flags)
 _LIB_PATH = os.environ.get("FLASHSPARSE_LIB") or os.path.join(_HERE, "libflashsparse_hip.so")
 _lib = None
+_native = None  # the _fs_torch module, once load_library has given it the library's entry points
 
 FS_F16, FS_BF16 = 0, 1
 
@@ -55,7 +57,7 @@ def library_path() -> str:
 def load_library():
     """Load the HIP library (after torch, so that it binds to the HIP runtime torch has loaded); raises (never falls back)
     when it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -116,8 +118,27 @@ def load_library():
     lib.fs_read_bytes.argtypes = [vp, sz, i32, vp, sz, vp]
     lib.fs_copy_bytes.restype = ctypes.c_int
     lib.fs_copy_bytes.argtypes = [vp, vp, sz, vp]
-    _lib = lib
+    from . import _fs_torch
+    _fs_torch.bind(*(ctypes.cast(f, vp).value for f in (
+        lib.fs_spmm_workspace_bytes, lib.fs_attention_workspace_bytes, lib.fs_edge_softmax_workspace_bytes, lib.fs_spmm,
+        lib.fs_sddmm, lib.fs_attention, lib.fs_sddmm_spmm, lib.fs_edge_softmax, lib.fs_edge_softmax_backward,
+        lib.fs_csr_to_blk, lib.fs_blk_to_csr, lib.fs_gather16)))
+    _lib, _native = lib, _fs_torch
     return lib
+
+
+def _calls():
+    """The native calls.  Each returns the result, the library's status (an int), or None where an argument is not what
+    the call expects: then the checks of the caller say what."""
+    if _native is None:
+        load_library()
+    return _native
+
+
+def _result(got, where: str):
+    if got.__class__ is int:
+        raise FsError(got, where)
+    return got
 
 
 def fs_version() -> int:
@@ -137,8 +158,8 @@ def _dtype_code(torch_dtype) -> int:
 
 
 # Small calls are bound by the host (a launch takes about 3 us, the kernel of a 4096-row SpMM 4.6 us), so the way to the
-# C call makes no object it can do without: a stream's handle straight from torch (0.1 us; through a
-# torch.cuda.Stream 2.8 us), no workspace query where no window is cut, outputs from new_empty.
+# C call makes no object it can do without: a stream's handle comes straight from torch (0.1 us; through a
+# torch.cuda.Stream 2.8 us).
 _raw_stream = torch._C._cuda_getCurrentRawStream
 _current_device = torch._C._cuda_getDevice
 
@@ -265,6 +286,10 @@ def fs_spmm(fmt: FsFormat, B, vals=None, out=None, work=None, stream=None, event
     ``events`` = (before, after) raw hipEvent_t handles switches to fs_spmm_timed,
     which records them around the main kernel.
     """
+    if out is None and work is None and events is None:
+        got = _calls().spmm(ctypes.addressof(fmt.c), B, vals, _stream_ptr(stream))
+        if got is not None:
+            return _result(got, "fs_spmm")
     K, N = B.shape
     assert B.is_cuda and B.dtype == fmt.torch_dtype and B.stride(1) == 1 and K == fmt.c.K
     if out is None:
@@ -342,6 +367,10 @@ def fs_sddmm(fmt: FsFormat, X, Y, out=None, stream=None, out_csr=None, blocked=T
     """Scores (X @ Y^T) at the stored positions of A.  Returns them in the vals_blk layout (V*nvec elements);
     ``out_csr`` (nnz elements) additionally receives them in CSR order from the same kernel.  With
     ``blocked=False`` only ``out_csr`` is written (allocated if not given) and returned."""
+    if out is None and out_csr is None:
+        got = _calls().sddmm(ctypes.addressof(fmt.c), X, Y, bool(blocked), _stream_ptr(stream))
+        if got is not None:
+            return _result(got, "fs_sddmm")
     assert X.is_cuda and Y.is_cuda and X.dtype == fmt.torch_dtype and Y.dtype == fmt.torch_dtype
     assert X.shape[0] == fmt.c.M and Y.shape[0] == fmt.c.K and X.shape[1] == Y.shape[1]
     assert X.stride(1) == 1 and Y.stride(1) == 1
@@ -373,6 +402,10 @@ def fs_edge_softmax_workspace_bytes(fmt: FsFormat) -> int:
 
 def fs_edge_softmax(fmt: FsFormat, vals, out=None, scale: float = 1.0, work=None, stream=None):
     """Row softmax of scale * value over the stored entries, on vals_blk-layout arrays (out may be vals)."""
+    if out is None and work is None:
+        got = _calls().softmax(ctypes.addressof(fmt.c), vals, scale, _stream_ptr(stream))
+        if got is not None:
+            return _result(got, "fs_edge_softmax")
     assert vals.is_cuda and vals.dtype == fmt.torch_dtype and vals.is_contiguous()
     assert vals.numel() == fmt.c.V * fmt.c.nvec
     if out is None:
@@ -389,6 +422,10 @@ def fs_edge_softmax(fmt: FsFormat, vals, out=None, scale: float = 1.0, work=None
 def fs_edge_softmax_backward(fmt: FsFormat, probs, grad, out=None, scale: float = 1.0, work=None, stream=None):
     """Gradient of fs_edge_softmax: scale * p * (g - row sum of p * g), on vals_blk-layout arrays (out may be
     either input)."""
+    if out is None and work is None:
+        got = _calls().softmax_backward(ctypes.addressof(fmt.c), probs, grad, scale, _stream_ptr(stream))
+        if got is not None:
+            return _result(got, "fs_edge_softmax_backward")
     for t in (probs, grad):
         assert t.is_cuda and t.dtype == fmt.torch_dtype and t.is_contiguous() and t.numel() == fmt.c.V * fmt.c.nvec
     if out is None:
@@ -456,6 +493,10 @@ def fs_attention(fmt: FsFormat, X, Y, H, scale: float = 1.0, out=None, work=None
 
 
 def _attention_like(name, fmt, X, Y, H, scale, out, work, stream):
+    if out is None and work is None:
+        got = _calls().attention(ctypes.addressof(fmt.c), X, Y, H, scale, name == "fs_attention", _stream_ptr(stream))
+        if got is not None:
+            return _result(got, name)
     for t in (X, Y, H):
         assert t.is_cuda and t.dtype == fmt.torch_dtype and t.dim() == 2 and t.stride(1) == 1
     d, N = X.shape[1], H.shape[1]
@@ -475,6 +516,9 @@ def _attention_like(name, fmt, X, Y, H, scale, out, work, stream):
 def fs_blk_to_csr(fmt: FsFormat, blk, out=None, stream=None):
     """Reorder a vals_blk-layout array into CSR order."""
     if out is None:
+        got = _calls().blk_to_csr(ctypes.addressof(fmt.c), blk, _stream_ptr(stream))
+        if got is not None:
+            return _result(got, "fs_blk_to_csr")
         out = blk.new_empty(fmt.c.nnz)
     rc = load_library().fs_blk_to_csr(ctypes.byref(fmt.c), blk.data_ptr(), out.data_ptr(), _stream_ptr(stream))
     if rc:
@@ -484,6 +528,10 @@ def fs_blk_to_csr(fmt: FsFormat, blk, out=None, stream=None):
 
 def fs_csr_to_blk(fmt: FsFormat, vals_csr, out=None, stream=None):
     """CSR-order values -> vals_blk layout (zeros elsewhere): new values for the same pattern."""
+    if out is None:
+        got = _calls().csr_to_blk(ctypes.addressof(fmt.c), vals_csr, _stream_ptr(stream))
+        if got is not None:
+            return _result(got, "fs_csr_to_blk")
     assert vals_csr.is_cuda and vals_csr.dtype == fmt.torch_dtype and vals_csr.is_contiguous()
     assert vals_csr.numel() == fmt.c.nnz
     if out is None:
@@ -522,6 +570,10 @@ def fs_csr_transpose(rowptr, colidx, M: int, K: int, stream=None):
 
 def fs_gather16(src, idx, out=None, stream=None):
     """out[i] = src[idx[i]] on 16-bit elements (values of A carried into the CSR order of A^T)."""
+    if out is None:
+        got = _calls().gather16(src, idx, _stream_ptr(stream))
+        if got is not None:
+            return _result(got, "fs_gather16")
     assert src.is_cuda and idx.is_cuda and idx.dtype == torch.int32 and src.element_size() == 2
     assert src.is_contiguous() and idx.is_contiguous()
     if out is None:

@@ -1,4 +1,4 @@
-"""Builds libflashsparse_hip.so for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Builds libflashsparse_hip.so for gfx950 with hipcc (cross-compiles without a GPU) and the Python binding's native calls."""
 from __future__ import annotations
 
 import os
@@ -9,6 +9,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 SOURCES = ["fs_convert.hip", "fs_spmm.hip", "fs_sddmm.hip", "fs_softmax.hip", "fs_attention.hip", "fs_transpose.hip", "fs_api.hip"]
 LIB = os.path.join(_HERE, "libflashsparse_hip.so")
+CALLS_SRC = os.path.join(_HERE, "csrc", "fs_torch.cpp")
+CALLS_LIB = os.path.join(_HERE, "_fs_torch.so")
 OBJ_DIR = os.path.join(_HERE, "_build")  # object files; ignored by git
 # k_sddmm uses its matrix-core results at once: let them land in ordinary vector registers instead of
 # accumulation registers that eight copy instructions per block would have to read back (the other kernels
@@ -44,6 +46,18 @@ def build_library(verbose: bool = False, defines=(), lib: str = LIB) -> str:
     return lib
 
 
+def build_calls() -> str:
+    """Compile the binding's native calls (host code only) against torch's headers; returns the module's path."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    includes = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+         + ["-I" + i for i in includes] + [CALLS_SRC, "-o", CALLS_LIB] + ["-L" + d for d in cpp_extension.library_paths()]
+         + ["-lc10", "-ltorch_cpu", "-ltorch_python"], False)
+    return CALLS_LIB
+
+
 EXAMPLE_SRC = os.path.join(ROOT, "tests", "c_abi_example.c")
 EXAMPLE_BIN = os.path.join(ROOT, "tests", "c_abi_example")
 
@@ -61,4 +75,5 @@ def build_c_example() -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_calls())
     print(build_c_example())

@@ -1,0 +1,70 @@
+"""Calls that allocate their own result run through the native module: same bits as the calls that are given it, same
+errors for what they do not take."""
+import pytest
+import torch
+
+from gpu_util import upload_csr
+from test_gpu_parity import fs  # noqa: F401
+from workloads import random_csr
+
+pytestmark = pytest.mark.gpu
+
+
+def same(a, b):
+    torch.cuda.synchronize()  # (the calls may have run on another stream than the comparison's)
+    assert a.shape == b.shape and a.dtype == b.dtype and torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,K,density,chunk,dtype", [(40, 56, 0.2, 0, "f16"), (64, 900, 0.5, 64, "bf16"), (8, 8, 0.05, 0, "f16")])
+def test_native_calls_match_calls_with_given_outputs(fs, M, K, density, chunk, dtype):  # noqa: F811
+    A = random_csr(M, K, density, dtype, seed=7)
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, M, K, chunk=chunk)
+    dt = va.dtype
+    assert chunk == 0 or fmt.n_split_items > 0  # a workspace is needed
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    X, Y, B = (torch.randn((r, c), generator=gen, device="cuda").to(dt) for r, c in ((M, 40), (K, 40), (K, 48)))
+    new = lambda *shape: torch.empty(shape, dtype=dt, device="cuda")  # noqa: E731
+    side = torch.cuda.Stream()
+    for stream in (None, side):
+        same(fs.fs_spmm(fmt, B, stream=stream), fs.fs_spmm(fmt, B, out=new(M, 48), stream=stream))
+        same(fs.fs_spmm(fmt, B[:, 8:24], stream=stream), fs.fs_spmm(fmt, B[:, 8:24], out=new(M, 16), stream=stream))
+        torch.cuda.synchronize()
+        S = fs.fs_sddmm(fmt, X, Y, stream=stream)
+        same(S, fs.fs_sddmm(fmt, X, Y, out=new(fmt.V * fmt.nvec), stream=stream))
+        csr = fs.fs_sddmm(fmt, X, Y, blocked=False, stream=stream)
+        same(csr, fs.fs_sddmm(fmt, X, Y, blocked=False, out_csr=new(fmt.nnz), stream=stream))
+        same(fs.fs_blk_to_csr(fmt, S, stream=stream), csr)
+        same(fs.fs_csr_to_blk(fmt, csr, stream=stream), S)
+        P = fs.fs_edge_softmax(fmt, S, scale=0.5, stream=stream)
+        same(P, fs.fs_edge_softmax(fmt, S, out=torch.empty_like(S), scale=0.5, stream=stream))
+        same(fs.fs_edge_softmax_backward(fmt, P, S, scale=0.5, stream=stream),
+             fs.fs_edge_softmax_backward(fmt, P, S, out=torch.empty_like(S), scale=0.5, stream=stream))
+        same(fs.fs_spmm(fmt, B, vals=P, stream=stream), fs.fs_spmm(fmt, B, vals=P, out=new(M, 48), stream=stream))
+        for call in (fs.fs_attention, fs.fs_sddmm_spmm):
+            same(call(fmt, X, Y, B, 0.25, stream=stream), call(fmt, X, Y, B, 0.25, out=new(M, 48), stream=stream))
+        idx = torch.arange(fmt.nnz - 1, -1, -1, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()  # idx was made on the current stream
+        same(fs.fs_gather16(va, idx, stream=stream), va.flip(0))
+
+
+def test_native_calls_refuse_what_the_others_refuse(fs):  # noqa: F811
+    A = random_csr(40, 56, 0.2, "f16", seed=7)
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, 40, 56)
+    t = lambda *shape, dtype=torch.float16, device="cuda": torch.zeros(shape, dtype=dtype, device=device)  # noqa: E731
+    for bad in (t(56, 16, device="cpu"), t(56, 16, dtype=torch.bfloat16), t(55, 16), t(16, 56).T):
+        with pytest.raises(AssertionError):
+            fs.fs_spmm(fmt, bad)
+        with pytest.raises(AssertionError):
+            fs.fs_sddmm(fmt, t(40, 16), bad)
+        with pytest.raises(AssertionError):
+            fs.fs_attention(fmt, t(40, 16), t(56, 16), bad)
+    for call in (lambda: fs.fs_spmm(fmt, t(56, 12)), lambda: fs.fs_sddmm(fmt, t(40, 12), t(56, 12)),
+                 lambda: fs.fs_attention(fmt, t(40, 16), t(56, 16), t(56, 12))):
+        with pytest.raises(fs.FsError) as e:
+            call()
+        assert e.value.code == 1
+    for call in (lambda: fs.fs_edge_softmax(fmt, t(3)), lambda: fs.fs_csr_to_blk(fmt, t(3)), lambda: fs.fs_gather16(t(3), t(3))):
+        with pytest.raises(AssertionError):
+            call()
