@@ -205,43 +205,43 @@ class FsFormat:
 
     # views of the converted arrays (device tensors sharing the arena's memory)
     def win_ptr_t(self):
-            return self._view(self.c.win_ptr, 4 * (self.c.W + 1), torch.int32)
+        return self._view(self.c.win_ptr, 4 * (self.c.W + 1), torch.int32)
 
     def vec_col_t(self):
-            return self._view(self.c.vec_col, 4 * self.c.nvec, torch.int32)
+        return self._view(self.c.vec_col, 4 * self.c.nvec, torch.int32)
 
     def vec_mask_t(self):
-            return self._view(self.c.vec_mask, 4 * self.c.nvec, torch.int32)
+        return self._view(self.c.vec_mask, 4 * self.c.nvec, torch.int32)
 
     def csr_to_slot_t(self):
-            return self._view(self.c.csr_to_slot, 4 * self.c.nnz, torch.int32)
+        return self._view(self.c.csr_to_slot, 4 * self.c.nnz, torch.int32)
 
     def vals_blk_t(self):
         return self._view(self.c.vals_blk, 2 * self.c.V * self.c.nvec, self.torch_dtype)
 
     def blk_desc_t(self):
-            return self._view(self.c.blk_desc, 16 * self.c.n_blocks, torch.int32).view(-1, 4)
+        return self._view(self.c.blk_desc, 16 * self.c.n_blocks, torch.int32).view(-1, 4)
 
     def items_t(self):
-            return self._view(self.c.items, 16 * self.c.n_items, torch.int32).view(-1, 4)
+        return self._view(self.c.items, 16 * self.c.n_items, torch.int32).view(-1, 4)
 
     def item_order_t(self):
-            return self._view(self.c.item_order, 4 * self.c.n_items, torch.int32)
+        return self._view(self.c.item_order, 4 * self.c.n_items, torch.int32)
 
     def items_by_cost_t(self):
-            return self._view(self.c.items_by_cost, 16 * self.c.n_items, torch.int32).view(-1, 4)
+        return self._view(self.c.items_by_cost, 16 * self.c.n_items, torch.int32).view(-1, 4)
 
     def blk_row_base_t(self):
-            return self._view(self.c.blk_row_base, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
+        return self._view(self.c.blk_row_base, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
 
     def blk_row_bits_t(self):
-            return self._view(self.c.blk_row_bits, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
+        return self._view(self.c.blk_row_bits, 4 * self.c.V * self.c.n_blocks, torch.int32).view(-1, self.c.V)
 
     def split_windows_t(self):
-            return self._view(self.c.split_windows, 16 * self.c.n_split_windows, torch.int32).view(-1, 4)
+        return self._view(self.c.split_windows, 16 * self.c.n_split_windows, torch.int32).view(-1, 4)
 
     def slot_range_t(self):
-            return self._view(self.c.slot_range, 8 * self.c.n_split_items, torch.int32).view(-1, 2)
+        return self._view(self.c.slot_range, 8 * self.c.n_split_items, torch.int32).view(-1, 2)
 
 
 def fs_convert(rowptr, colidx, vals, M: int, K: int, torch_dtype=None, V: int = 0, KB: int = 0, chunk: int = 0,
