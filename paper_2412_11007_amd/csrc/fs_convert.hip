@@ -668,22 +668,14 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         } else {
             // cand, upos and cut_pos are free again: keys alternate between cand and upos, the payload between cut_pos and item_order
             const int tile = n_items <= 65536 ? kSortTileSmall : kSortTile;
-            const int64_t ntile = ((int64_t)n_items + tile - 1) / tile;
             int *hist = scr + sp.hist;
             int32_t *kbuf[2] = {upos, cand};              // pass p reads kbuf[(p + 1) & 1], writes kbuf[p & 1]
             int32_t *vbuf[2] = {item_order, cut_pos};     // pass p writes vbuf[p & 1]; the last pass (2) writes item_order
             for (int p = 0; p < 3; p++) {
                 const int32_t *src_k = kbuf[(p + 1) & 1];
-                k_digit_hist<<<(unsigned)ntile, 64, 0, s>>>(src_k, n_items, 8 * p, ntile, hist, tile);
-                FS_LAUNCH_CHECK();
-                if ((st = scan_exclusive(hist, (int64_t)kDigits * ntile, tmp, s)) != FS_OK) return st;
-                if (p == 0)
-                    k_digit_scatter<true><<<(unsigned)((ntile + kScatterWaves - 1) / kScatterWaves), 64 * kScatterWaves, 0, s>>>(src_k, nullptr, n_items, 0, ntile, hist,
-                                                                        kbuf[0], vbuf[0], tile);
-                else
-                    k_digit_scatter<false><<<(unsigned)((ntile + kScatterWaves - 1) / kScatterWaves), 64 * kScatterWaves, 0, s>>>(src_k, vbuf[(p + 1) & 1], n_items, 8 * p, ntile,
-                                                                         hist, kbuf[p & 1], vbuf[p & 1], tile);
-                FS_LAUNCH_CHECK();
+                if ((st = sort_pass<kDigitBits>(src_k, p == 0 ? nullptr : vbuf[(p + 1) & 1], n_items, kDigitBits * p, tile, hist, tmp, kbuf[p & 1],
+                                                vbuf[p & 1], s)) != FS_OK)
+                    return st;
             }
             k_item_permute<<<grid_for(n_items, 256), 256, 0, s>>>(items, item_order, n_items, items_by_cost);
             FS_LAUNCH_CHECK();

@@ -1,11 +1,11 @@
-// One pass of a stable least-significant-digit radix sort on 8-bit digits of int32 keys, one wavefront per
+// One pass of a stable least-significant-digit radix sort on 8- or 9-bit digits of int32 keys, one wavefront per
 // tile of 2048 entries, shared by the translation units that sort (the CSR transposition sorts entries by
 // column; the conversion orders the work list).  Every translation unit gets its own copy.
 //   hist     per tile, the number of entries per digit value
 //   scan     (the caller's, fs_scan.h) exclusive prefix sum over (digit value, tile), digit-major: where
 //            each tile's entries with a given digit start in the output
 //   scatter  each wavefront walks its tile in order, 64 entries at a time; a lane's rank among the lanes
-//            of the same digit comes from eight wave-wide ballots, so equal digits keep their input order;
+//            of the same digit comes from one wave-wide ballot per digit bit, so equal digits keep their input order;
 //            four wavefronts (four consecutive tiles) share a workgroup and write their output together
 // No atomics touch global memory and the result does not depend on scheduling.
 #pragma once
@@ -20,23 +20,28 @@ namespace {
 constexpr int kSortTile = 2048;       // entries per wavefront for large sorts
 constexpr int kSortTileSmall = 256;   // ... and for sorts of a few thousand entries, where a wavefront's 32 sequential
                                       // rounds per 2048-entry tile would be the whole run time
-constexpr int kDigitBits = 8;
-constexpr int kDigits = 1 << kDigitBits;
+// Digits of 8 bits, or of 9 where those make a pass fewer.  A wide pass costs more (twice the counts, one more ballot per
+// round, 28 instead of 22 KB of LDS per workgroup), but two of them less than three narrow ones: transposition of 5.3 M
+// entries with 18-bit columns 368 -> 350 us.
+constexpr int kDigitBits = 8, kWideDigitBits = 9;
+constexpr int kDigits = 1 << kDigitBits, kWideDigits = 1 << kWideDigitBits;
 
+template <int BITS>
 __global__ void __launch_bounds__(64) k_digit_hist(const int32_t *__restrict__ keys, int64_t n, int shift, int64_t ntile,
-                                                   int *__restrict__ hist, int tile = kSortTile)
+                                                   int *__restrict__ hist, int tile)
 {
-    __shared__ int h[kDigits];
+    constexpr int n_digits = 1 << BITS;
+    __shared__ int h[n_digits];
     const int lane = threadIdx.x;
 #pragma unroll
-    for (int i = 0; i < kDigits / 64; i++) h[lane + 64 * i] = 0;
+    for (int i = 0; i < n_digits / 64; i++) h[lane + 64 * i] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * tile;
     const int64_t end = std::min<int64_t>(base + tile, n);
-    for (int64_t i = base + lane; i < end; i += 64) atomicAdd(&h[((uint32_t)keys[i] >> shift) & (kDigits - 1)], 1);
+    for (int64_t i = base + lane; i < end; i += 64) atomicAdd(&h[((uint32_t)keys[i] >> shift) & (n_digits - 1)], 1);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kDigits / 64; i++) {
+    for (int i = 0; i < n_digits / 64; i++) {
         const int d = lane + 64 * i;
         hist[(int64_t)d * ntile + blockIdx.x] = h[d];
     }
@@ -53,27 +58,38 @@ __global__ void __launch_bounds__(64) k_digit_hist(const int32_t *__restrict__ k
 constexpr int kScatterWaves = 4;
 constexpr int kMaxRounds = kSortTile / 64;
 
-template <bool FIRST>
+template <int BITS, bool FIRST>
 __global__ void __launch_bounds__(64 * kScatterWaves)
 k_digit_scatter(const int32_t *__restrict__ keys, const int32_t *__restrict__ vals, int64_t n, int shift, int64_t ntile,
                 const int *__restrict__ start, int32_t *__restrict__ out_keys, int32_t *__restrict__ out_vals,
-                int tile = kSortTile)
+                int tile)
 {
-    static_assert(64 * kScatterWaves == kDigits && kDigits == kScanThreads, "one thread per digit value builds the tables");
-    __shared__ int cur[kScatterWaves][kDigits];  // where a tile's next entry with digit d goes in the output
-    __shared__ int gbase[kDigits];               // where the group's entries with digit d start in the output ...
-    __shared__ int lstart[kDigits];              // ... and among the group's own output slots
+    constexpr int n_digits = 1 << BITS, kPer = n_digits / kScanThreads;  // kPer consecutive digit values per thread in the tables
+    static_assert(64 * kScatterWaves == kScanThreads && kPer * kScanThreads == n_digits, "every digit value has a thread");
+    __shared__ int cur[kScatterWaves][n_digits];  // where a tile's next entry with digit d goes in the output
+    __shared__ int gbase[n_digits];               // where the group's entries with digit d start in the output ...
+    __shared__ int lstart[n_digits];              // ... and among the group's own output slots
     __shared__ uint16_t source[kScatterWaves * kSortTile];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t t0 = (int64_t)blockIdx.x * kScatterWaves, t1 = std::min<int64_t>(t0 + kScatterWaves, ntile);
     {
-        const int d = threadIdx.x;
-        const int g0 = start[(int64_t)d * ntile + t0], g1 = start[(int64_t)d * ntile + t1];
-        int tot;
-        lstart[d] = block_exclusive_scan(g1 - g0, &tot);
-        gbase[d] = g0;
+        int count[kPer], sum = 0, tot;
 #pragma unroll
-        for (int k = 0; k < kScatterWaves; k++) cur[k][d] = t0 + k < ntile ? start[(int64_t)d * ntile + t0 + k] : 0;
+        for (int i = 0; i < kPer; i++) {
+            const int d = threadIdx.x * kPer + i;
+            const int g0 = start[(int64_t)d * ntile + t0];
+            count[i] = start[(int64_t)d * ntile + t1] - g0;
+            sum += count[i];
+            gbase[d] = g0;
+#pragma unroll
+            for (int k = 0; k < kScatterWaves; k++) cur[k][d] = t0 + k < ntile ? start[(int64_t)d * ntile + t0 + k] : 0;
+        }
+        int ofs = block_exclusive_scan(sum, &tot);
+#pragma unroll
+        for (int i = 0; i < kPer; i++) {
+            lstart[threadIdx.x * kPer + i] = ofs;
+            ofs += count[i];
+        }
     }
     __syncthreads();
     const int64_t first = t0 * tile;  // the group's first entry
@@ -90,10 +106,10 @@ k_digit_scatter(const int32_t *__restrict__ keys, const int32_t *__restrict__ va
         if (r * 64 >= tile || base + r * 64 >= end) break;  // the same for all lanes
         const int64_t i = base + r * 64 + lane;
         const bool valid = i < end;
-        const int digit = ((uint32_t)key[r] >> shift) & (kDigits - 1);
+        const int digit = ((uint32_t)key[r] >> shift) & (n_digits - 1);
         uint64_t same = __ballot(valid);
 #pragma unroll
-        for (int b = 0; b < kDigitBits; b++) {
+        for (int b = 0; b < BITS; b++) {
             const bool bit = (digit >> b) & 1;
             const uint64_t set = __ballot(valid && bit);
             same &= bit ? set : ~set;
@@ -115,11 +131,29 @@ k_digit_scatter(const int32_t *__restrict__ keys, const int32_t *__restrict__ va
         const int64_t i = first + source[s];
         const int32_t k = keys[i];
         const int32_t v = FIRST ? (int32_t)i : vals[i];
-        const int digit = ((uint32_t)k >> shift) & (kDigits - 1);
+        const int digit = ((uint32_t)k >> shift) & (n_digits - 1);
         const int pos = gbase[digit] + (s - lstart[digit]);
         out_keys[pos] = k;
         out_vals[pos] = v;
     }
+}
+
+// One pass: keys (and payload; null: an entry's position) to out_keys and out_vals.  hist: 2^BITS * ntile + 1 ints,
+// tmp: what a scan of them takes.
+template <int BITS>
+fs_status sort_pass(const int32_t *keys, const int32_t *vals, int64_t n, int shift, int tile, int *hist, int *tmp, int32_t *out_keys,
+                    int32_t *out_vals, hipStream_t st)
+{
+    const int64_t ntile = (n + tile - 1) / tile;
+    const dim3 grid((unsigned)((ntile + kScatterWaves - 1) / kScatterWaves)), block(64 * kScatterWaves);
+    k_digit_hist<BITS><<<(unsigned)ntile, 64, 0, st>>>(keys, n, shift, ntile, hist, tile);
+    FS_LAUNCH_CHECK();
+    const fs_status s = scan_exclusive(hist, ntile << BITS, tmp, st);
+    if (s != FS_OK) return s;
+    if (!vals) k_digit_scatter<BITS, true><<<grid, block, 0, st>>>(keys, nullptr, n, shift, ntile, hist, out_keys, out_vals, tile);
+    else k_digit_scatter<BITS, false><<<grid, block, 0, st>>>(keys, vals, n, shift, ntile, hist, out_keys, out_vals, tile);
+    FS_LAUNCH_CHECK();
+    return FS_OK;
 }
 
 }  // namespace

@@ -6,14 +6,8 @@
 // per-entry values (edge weights, attention coefficients) from A's order into A^T's.
 //
 // The stored entries of A, taken in CSR order, are sorted by (row, column).  A STABLE sort of them by
-// column alone therefore leaves them sorted by (column, row): the CSR order of A^T.  The sort is a
-// least-significant-digit radix sort on 8-bit digits of the column index, one wavefront per tile:
-//   hist     per tile, the number of entries per digit value
-//   scan     exclusive prefix sum over (digit value, tile), digit-major: where each tile's entries
-//            with a given digit start in the output
-//   scatter  each wavefront walks its tile in order, 64 entries at a time; a lane's rank among the
-//            lanes of the same digit comes from eight wave-wide ballots, so equal digits keep their
-//            input order
+// column alone therefore leaves them sorted by (column, row): the CSR order of A^T.  The sort is the
+// least-significant-digit radix sort of fs_sort.h on the column index.
 // No atomics touch global memory and the result does not depend on scheduling.
 #include <algorithm>
 
@@ -69,7 +63,7 @@ __global__ void k_gather16(const uint16_t *__restrict__ src, const int32_t *__re
 
 inline unsigned grid_of(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
-// Scratch layout (ints): [keys 0: nnz][keys 1: nnz][payload: nnz][digit counts: 256 * tiles + 1][scan tmp]
+// Scratch layout (ints): [keys 0: nnz][keys 1: nnz][payload: nnz][digit counts: 512 * tiles + 1][scan tmp]
 struct TransposePlan {
     int64_t ntile;
     size_t key0, key1, val1, hist, tmp, total_ints;
@@ -83,8 +77,8 @@ TransposePlan plan_transpose(int64_t nnz)
     p.key0 = o; o += e;
     p.key1 = o; o += e;
     p.val1 = o; o += e;
-    p.hist = o; o += fs_align_up((size_t)kDigits * p.ntile + 1, 64);
-    p.tmp = o; o += scan_tmp_ints((int64_t)kDigits * p.ntile);
+    p.hist = o; o += fs_align_up((size_t)kWideDigits * p.ntile + 1, 64);
+    p.tmp = o; o += scan_tmp_ints((int64_t)kWideDigits * p.ntile);
     p.total_ints = o;
     return p;
 }
@@ -128,29 +122,25 @@ extern "C" fs_status fs_csr_transpose(int64_t M, int64_t K, int64_t nnz, const i
 
     int bits = 0;
     while (bits < 31 && ((K - 1) >> bits) != 0) bits++;
-    const int P = std::max(1, (bits + kDigitBits - 1) / kDigitBits);
+    // digits of 9 bits where those save a pass (columns of 17 and 18 bits: two passes instead of three)
+    const int P8 = std::max(1, (bits + kDigitBits - 1) / kDigitBits), P9 = std::max(1, (bits + kWideDigitBits - 1) / kWideDigitBits);
+    const bool wide = P9 < P8;
+    const int P = wide ? P9 : P8;
     const int32_t *src_key = d_colidx;
     const int32_t *src_val = nullptr;
     for (int p = 0; p < P; p++) {
-        const int shift = p * kDigitBits;
         int32_t *dst_key = key[p & 1];
         int32_t *dst_val = ((P - 1 - p) & 1) ? S + pl.val1 : d_perm;  // the last pass writes d_perm
-        k_digit_hist<<<(unsigned)pl.ntile, 64, 0, st>>>(src_key, nnz, shift, pl.ntile, hist);
-        FS_LAUNCH_CHECK();
-        fs_status s = scan_exclusive(hist, (int64_t)kDigits * pl.ntile, tmp, st);
+        const fs_status s = wide ? sort_pass<kWideDigitBits>(src_key, src_val, nnz, kWideDigitBits * p, kSortTile, hist, tmp, dst_key, dst_val, st)
+                                 : sort_pass<kDigitBits>(src_key, src_val, nnz, kDigitBits * p, kSortTile, hist, tmp, dst_key, dst_val, st);
         if (s != FS_OK) return s;
-        if (p == 0)
-            k_digit_scatter<true><<<(unsigned)((pl.ntile + kScatterWaves - 1) / kScatterWaves), 64 * kScatterWaves, 0, st>>>(src_key, nullptr, nnz, shift, pl.ntile, hist, dst_key, dst_val);
-        else
-            k_digit_scatter<false><<<(unsigned)((pl.ntile + kScatterWaves - 1) / kScatterWaves), 64 * kScatterWaves, 0, st>>>(src_key, src_val, nnz, shift, pl.ntile, hist, dst_key, dst_val);
-        FS_LAUNCH_CHECK();
         src_key = dst_key;
         src_val = dst_val;
     }
     k_rowptr_of_sorted<<<grid_of(K + 1, 256), 256, 0, st>>>(src_key, (int32_t)nnz, K, d_rowptr_t);
     FS_LAUNCH_CHECK();
     int32_t *row_of = key[P & 1];  // the key buffer the last pass did not write
-    int32_t *group_rows = hist;  // the digit counts are no longer needed; 256 * tiles + 1 >= nnz / 256 + 2 ints
+    int32_t *group_rows = hist;  // the digit counts are no longer needed; 512 * tiles + 1 >= nnz / 256 + 2 ints
     const int64_t n_groups = (nnz + kEntriesPerGroup - 1) / kEntriesPerGroup;
     k_group_rows<<<grid_of(n_groups + 1, 256), 256, 0, st>>>(d_rowptr, M, nnz, n_groups, group_rows);
     FS_LAUNCH_CHECK();

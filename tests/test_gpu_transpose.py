@@ -46,6 +46,16 @@ def test_transpose_small(fs, M, K, density, seed):
     check_transpose(fs, A)
 
 
+@pytest.mark.parametrize("K", [65536, 65537, 1 << 18, (1 << 18) + 1])
+def test_transpose_digit_widths(fs, K):
+    """Where the sort goes from 8-bit digits to 9-bit ones and back, with the first and the last column stored, over
+    several tiles."""
+    rng = np.random.default_rng(K)
+    M = 700
+    key = np.unique(np.concatenate([rng.integers(0, M * K, 9000), np.arange(0, M, 3) * K, np.arange(1, M, 3) * K + K - 1]))
+    check_transpose(fs, csr_from_coo(M, K, key // K, key % K, "u01", "f16", rng))
+
+
 def test_transpose_hub_columns(fs):
     """A few columns referenced by most rows: equal keys span many tiles, where stability matters."""
     rng = np.random.default_rng(21)
