@@ -22,28 +22,39 @@ constexpr int kSortTileSmall = 256;   // ... and for sorts of a few thousand ent
                                       // rounds per 2048-entry tile would be the whole run time
 // Digits of 8 bits, or of 9 where those make a pass fewer.  A wide pass costs more (twice the counts, one more ballot per
 // round, 28 instead of 22 KB of LDS per workgroup), but two of them less than three narrow ones: transposition of 5.3 M
-// entries with 18-bit columns 368 -> 350 us.
+// entries with 18-bit columns 368 -> 350 us, 322 with the counting below.
 constexpr int kDigitBits = 8, kWideDigitBits = 9;
 constexpr int kDigits = 1 << kDigitBits, kWideDigits = 1 << kWideDigitBits;
 
+constexpr int kScatterWaves = 4;
+constexpr int kMaxRounds = kSortTile / 64;
+
+// Four wavefronts count four consecutive tiles: their counts of one digit value are neighbours in hist, so they leave in
+// 16-byte pieces, and a wavefront has eight loads in flight (5.3 M entries, 9 bits: 21.2 -> 10.4 us with a
+// wavefront per workgroup, one load at a time and 4-byte stores before).
 template <int BITS>
-__global__ void __launch_bounds__(64) k_digit_hist(const int32_t *__restrict__ keys, int64_t n, int shift, int64_t ntile,
-                                                   int *__restrict__ hist, int tile)
+__global__ void __launch_bounds__(64 * kScatterWaves) k_digit_hist(const int32_t *__restrict__ keys, int64_t n, int shift, int64_t ntile,
+                                                                   int *__restrict__ hist, int tile)
 {
-    constexpr int n_digits = 1 << BITS;
-    __shared__ int h[n_digits];
-    const int lane = threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < n_digits / 64; i++) h[lane + 64 * i] = 0;
+    constexpr int n_digits = 1 << BITS, kAhead = 8;
+    __shared__ int h[kScatterWaves][n_digits];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < kScatterWaves * n_digits; i += 64 * kScatterWaves) (&h[0][0])[i] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * tile;
-    const int64_t end = std::min<int64_t>(base + tile, n);
-    for (int64_t i = base + lane; i < end; i += 64) atomicAdd(&h[((uint32_t)keys[i] >> shift) & (n_digits - 1)], 1);
-    __syncthreads();
+    const int64_t t0 = (int64_t)blockIdx.x * kScatterWaves;
+    const int64_t base = (t0 + w) * tile, end = std::min<int64_t>(base + tile, n);
+    for (int64_t i0 = base + lane; i0 < end; i0 += 64 * kAhead) {
+        int32_t key[kAhead];
 #pragma unroll
-    for (int i = 0; i < n_digits / 64; i++) {
-        const int d = lane + 64 * i;
-        hist[(int64_t)d * ntile + blockIdx.x] = h[d];
+        for (int r = 0; r < kAhead; r++) key[r] = keys[std::min<int64_t>(i0 + 64 * r, n - 1)];
+#pragma unroll
+        for (int r = 0; r < kAhead; r++)
+            if (i0 + 64 * r < end) atomicAdd(&h[w][((uint32_t)key[r] >> shift) & (n_digits - 1)], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kScatterWaves * n_digits; i += 64 * kScatterWaves) {
+        const int d = i / kScatterWaves, k = i % kScatterWaves;
+        if (t0 + k < ntile) hist[(int64_t)d * ntile + t0 + k] = h[k][d];
     }
 }
 
@@ -55,9 +66,6 @@ __global__ void __launch_bounds__(64) k_digit_hist(const int32_t *__restrict__ k
 // fetches their entries again (they are still in cache), so that neighbouring lanes write neighbouring
 // addresses: runs of ~128 bytes instead of scattered 4-byte pieces of ~32-byte runs.
 // FIRST: the payload of entry i is i itself (its position in the source CSR order).
-constexpr int kScatterWaves = 4;
-constexpr int kMaxRounds = kSortTile / 64;
-
 template <int BITS, bool FIRST>
 __global__ void __launch_bounds__(64 * kScatterWaves)
 k_digit_scatter(const int32_t *__restrict__ keys, const int32_t *__restrict__ vals, int64_t n, int shift, int64_t ntile,
@@ -146,7 +154,7 @@ fs_status sort_pass(const int32_t *keys, const int32_t *vals, int64_t n, int shi
 {
     const int64_t ntile = (n + tile - 1) / tile;
     const dim3 grid((unsigned)((ntile + kScatterWaves - 1) / kScatterWaves)), block(64 * kScatterWaves);
-    k_digit_hist<BITS><<<(unsigned)ntile, 64, 0, st>>>(keys, n, shift, ntile, hist, tile);
+    k_digit_hist<BITS><<<grid, block, 0, st>>>(keys, n, shift, ntile, hist, tile);
     FS_LAUNCH_CHECK();
     const fs_status s = scan_exclusive(hist, ntile << BITS, tmp, st);
     if (s != FS_OK) return s;
