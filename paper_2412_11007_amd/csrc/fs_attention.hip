@@ -119,7 +119,7 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
     auto load_x = [&](const BlockDesc &b) {
         const int64_t xrow = (int64_t)b.w * V + j;
         const bool ok = j < V && xrow < M;
-        const uint32_t xoff = __umul24((uint32_t)(ok ? xrow : 0), ldx2);
+        const uint32_t xoff = fs_mul24((uint32_t)(ok ? xrow : 0), ldx2);
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
             xf[ks].u = *reinterpret_cast<const fs_u4 *>(Xb + xoff + f_off[ks]);
@@ -132,7 +132,7 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
 #define FS_YROWS(cols)                                                                           \
     {                                                                                            \
         _Pragma("unroll") for (int t = 0; t < 2; t++)                                            \
-            yoff[t] = __umul24((uint32_t)__shfl(cols, holder(8 * (j >> 2) + 4 * t + (j & 3)), 64), ldy2); \
+            yoff[t] = fs_mul24((uint32_t)__shfl(cols, holder(8 * (j >> 2) + 4 * t + (j & 3)), 64), ldy2); \
     }
 #define FS_YGATHER()                                                                             \
     _Pragma("unroll") for (int t = 0; t < 2; t++)                                                \
@@ -144,7 +144,7 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
     {                                                                                            \
         fs_for_each_index([&](auto l_) {                                                         \
             constexpr int l = decltype(l_)::value;                                               \
-            grow[l] = __umul24((uint32_t)fs_row_bcast<l>(cols), ldh2) + g_colb;                  \
+            grow[l] = fs_mul24((uint32_t)fs_row_bcast<l>(cols), ldh2) + g_colb;                  \
         }, std::make_integer_sequence<int, NLD>{});                                              \
     }
     fs_u4 stage[NLD];

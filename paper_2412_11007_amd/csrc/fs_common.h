@@ -46,6 +46,10 @@ union fs_frag {
     fs_s4 s[2];
 };
 
+// Row number times row pitch, both below 2^24, the product below 2^32.  HIP's __umul24 returns an int: widened to 64 bits
+// as it is, an offset from 2 GiB on would turn negative.
+__device__ __forceinline__ uint32_t fs_mul24(uint32_t a, uint32_t b) { return (uint32_t)__umul24(a, b); }
+
 // fp32 -> 16-bit storage, round to nearest even.
 __device__ __forceinline__ uint16_t fs_f32_to_f16_bits(float x)
 {

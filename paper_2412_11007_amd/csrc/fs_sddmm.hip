@@ -166,7 +166,7 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
             int idx;
             if constexpr (LPR == 16) idx = fs_row_bcast<l>(cols[b]);
             else idx = __shfl(cols[b], vector_of(l * RPI + g_row), 64);
-            grow[k] = BIG ? (uint32_t)idx : __umul24((uint32_t)idx, ldy2);
+            grow[k] = BIG ? (uint32_t)idx : fs_mul24((uint32_t)idx, ldy2);
         }, std::make_integer_sequence<int, NLD>{});
     };
     auto gather = [&](int f_base) {
@@ -179,7 +179,7 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
     auto load_x = [&](int w, int f_base, fs_frag (&x)[KS]) {
         const int64_t row = (int64_t)w * V + j;
         const bool ok = j < V && row < M;
-        const uint64_t off = BIG ? (uint64_t)row * ldx2 : (uint64_t)__umul24((uint32_t)row, ldx2);
+        const uint64_t off = BIG ? (uint64_t)row * ldx2 : (uint64_t)fs_mul24((uint32_t)row, ldx2);
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
             const int f = f_base + 32 * ks + 8 * g;
@@ -313,7 +313,7 @@ k_sddmm_short(const int4 *__restrict__ items, int n_items, int slice, int n_swz,
             // X operand: lane (j, g) holds X[w*V + j][8g .. 8g+7]; rows past V or M are zero
             const int64_t xrow = (int64_t)dsc[u].w * V + j;
             const bool x_ok = dsc[u].kb > 0 && j < V && xrow < M;
-            const uint64_t xoff = BIG ? (uint64_t)xrow * ldx2 : (uint64_t)__umul24((uint32_t)xrow, ldx2);
+            const uint64_t xoff = BIG ? (uint64_t)xrow * ldx2 : (uint64_t)fs_mul24((uint32_t)xrow, ldx2);
             xf[u].u = fs_u4{0u, 0u, 0u, 0u};
             if (x_ok && 8 * g < d) xf[u].u = *reinterpret_cast<const fs_u4 *>(Xb + xoff + 16 * g);
         }
@@ -327,7 +327,7 @@ k_sddmm_short(const int4 *__restrict__ items, int n_items, int slice, int n_swz,
             for (int t = 0; t < 2; t++) {
                 int yrow = __shfl(col[u], 8 * (j >> 2) + 4 * t + (j & 3), 64);
                 yrow = yrow < 0 ? first : yrow;
-                const uint64_t yoff = BIG ? (uint64_t)yrow * ldy2 : (uint64_t)__umul24((uint32_t)yrow, ldy2);
+                const uint64_t yoff = BIG ? (uint64_t)yrow * ldy2 : (uint64_t)fs_mul24((uint32_t)yrow, ldy2);
                 yf[u][t].u = *reinterpret_cast<const fs_u4 *>(Yb + yoff + (8 * g < d ? 16 * g : 0));
                 if (8 * g >= d) yf[u][t].u = fs_u4{0u, 0u, 0u, 0u};
             }

@@ -196,12 +196,12 @@ k_spmm(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk
             fs_for_each_index([&](auto l_) {                                                     \
                 constexpr int l = decltype(l_)::value;                                           \
                 const int idx_ = fs_row_bcast<l>(cols);                                          \
-                grow[l] = BIG ? (uint32_t)idx_ : __umul24((uint32_t)idx_, ldb2) + g_colb;        \
+                grow[l] = BIG ? (uint32_t)idx_ : fs_mul24((uint32_t)idx_, ldb2) + g_colb;        \
             }, std::make_integer_sequence<int, NLD>{});                                          \
         } else {                                                                                 \
             _Pragma("unroll") for (int l = 0; l < NLD; l++) {                                    \
                 const int idx_ = __shfl(cols, l * RPI + g_row, 64);                              \
-                grow[l] = BIG ? (uint32_t)idx_ : __umul24((uint32_t)idx_, ldb2) + g_colb;        \
+                grow[l] = BIG ? (uint32_t)idx_ : fs_mul24((uint32_t)idx_, ldb2) + g_colb;        \
             }                                                                                    \
         }                                                                                        \
     }
