@@ -504,9 +504,9 @@ __global__ void __launch_bounds__(256) k_win_ptr(const int2 *__restrict__ win_at
 {
     const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (w > W) return;
-    const bool malformed = *err & 1;
+    const bool nothing = W == 0 || (*err & 1);  // no rows, or malformed row pointers: nothing was counted
     auto ptr = [&](int64_t v) -> int32_t {
-        if (malformed) return 0;
+        if (nothing) return 0;
         if (v == W) return first_vec[*n_units];
         const int2 at = win_at[v];
         return first_vec[at.x] + at.y;

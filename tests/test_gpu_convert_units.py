@@ -91,3 +91,14 @@ def test_convert_columns_beyond_26_bits_and_bad_hub_rows(fs):  # noqa: F811
         with pytest.raises(fs.FsError) as e:
             fs.fs_convert(bad_rp, ci, va, A.M, A.K, V=8)
         assert e.value.code == 2
+
+
+@pytest.mark.parametrize("V", [0, 1, 4, 16])
+def test_convert_no_rows_in_a_used_scratch_buffer(fs, V):  # noqa: F811
+    """M = 0: the one window pointer is 0 whatever the scratch buffer held before."""
+    import torch
+    rp, none = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.empty(0, dtype=torch.int32, device="cuda")
+    _, need = fs.fs_format_bytes(0, 0, V)
+    scratch = torch.full((need,), 0x7F, dtype=torch.uint8, device="cuda")
+    fmt = fs.fs_convert(rp, none, None, 0, 9, torch_dtype=torch.float16, V=V, scratch=scratch)
+    assert fmt.win_ptr_t().tolist() == [0] and fmt.nvec == 0 and fmt.n_blocks == 0 and fmt.c.n_items == 0
