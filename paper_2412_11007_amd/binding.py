@@ -180,6 +180,20 @@ def _workspace(fmt, work, like, query, *args):
     return work, work.data_ptr(), work.numel() * work.element_size()
 
 
+def _check_blocked(fmt, t):
+    """``t`` has a 16-bit element for every position of the vals_blk layout: the kernels read them all unasked."""
+    assert t.is_cuda and t.element_size() == 2 and t.is_contiguous() and t.numel() >= fmt.c.V * fmt.c.nvec
+
+
+def _values_ptr(fmt, vals) -> int:
+    """Pointer of a value array for fs_spmm, 0 for the format's own."""
+    if vals is None:
+        return 0
+    _check_blocked(fmt, vals)
+    assert vals.dtype == fmt.torch_dtype or not vals.is_floating_point()  # (raw bits may come as integers)
+    return vals.data_ptr()
+
+
 def fs_format_bytes(M: int, nnz: int, V: int = 0, KB: int = 0, dtype: int = FS_F16) -> Tuple[int, int]:
     a, s = ctypes.c_size_t(0), ctypes.c_size_t(0)
     rc = load_library().fs_format_bytes(M, nnz, V, KB, dtype, ctypes.byref(a), ctypes.byref(s))
@@ -299,7 +313,7 @@ def fs_spmm(fmt: FsFormat, B, vals=None, out=None, work=None, stream=None, event
         assert out.shape == (fmt.c.M, N) and out.stride(1) == 1 and out.dtype == B.dtype
         ldo = out.stride(0)
     work, work_ptr, work_bytes = _workspace(fmt, work, B, fs_spmm_workspace_bytes, N)
-    args = (ctypes.byref(fmt.c), 0 if vals is None else vals.data_ptr(), B.data_ptr(), N, B.stride(0), out.data_ptr(), ldo,
+    args = (ctypes.byref(fmt.c), _values_ptr(fmt, vals), B.data_ptr(), N, B.stride(0), out.data_ptr(), ldo,
             work_ptr, work_bytes, _stream_ptr(stream))
     if events is None:
         rc = load_library().fs_spmm(*args)
@@ -319,7 +333,7 @@ def bind_spmm(fmt: FsFormat, B, out, work=None, vals=None, stream=None):
     assert out.shape == (fmt.c.M, N) and out.stride(1) == 1 and out.dtype == B.dtype
     work, work_ptr, work_bytes = _workspace(fmt, work, B, fs_spmm_workspace_bytes, N)
     fn = load_library().fs_spmm
-    args = (ctypes.byref(fmt.c), 0 if vals is None else vals.data_ptr(), B.data_ptr(), N, B.stride(0), out.data_ptr(),
+    args = (ctypes.byref(fmt.c), _values_ptr(fmt, vals), B.data_ptr(), N, B.stride(0), out.data_ptr(),
             out.stride(0), work_ptr, work_bytes, _stream_ptr(stream))
     keep = (fmt, B, out, work, vals)
 
@@ -356,7 +370,7 @@ def fs_spmm_static(fmt: FsFormat, B, out, vals=None, stream=None):
     K, N = B.shape
     assert B.is_cuda and B.dtype == fmt.torch_dtype and B.stride(1) == 1 and K == fmt.c.K
     assert out.shape == (fmt.c.M, N) and out.stride(1) == 1 and out.dtype == B.dtype
-    rc = load_library().fs_spmm_static(ctypes.byref(fmt.c), 0 if vals is None else vals.data_ptr(), B.data_ptr(), N,
+    rc = load_library().fs_spmm_static(ctypes.byref(fmt.c), _values_ptr(fmt, vals), B.data_ptr(), N,
                                        B.stride(0), out.data_ptr(), out.stride(0), _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_spmm_static")
@@ -519,7 +533,10 @@ def fs_blk_to_csr(fmt: FsFormat, blk, out=None, stream=None):
         got = _calls().blk_to_csr(ctypes.addressof(fmt.c), blk, _stream_ptr(stream))
         if got is not None:
             return _result(got, "fs_blk_to_csr")
+    _check_blocked(fmt, blk)
+    if out is None:
         out = blk.new_empty(fmt.c.nnz)
+    assert out.is_cuda and out.element_size() == 2 and out.is_contiguous() and out.numel() >= fmt.c.nnz
     rc = load_library().fs_blk_to_csr(ctypes.byref(fmt.c), blk.data_ptr(), out.data_ptr(), _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_blk_to_csr")
@@ -536,7 +553,7 @@ def fs_csr_to_blk(fmt: FsFormat, vals_csr, out=None, stream=None):
     assert vals_csr.numel() == fmt.c.nnz
     if out is None:
         out = vals_csr.new_empty(fmt.c.V * fmt.c.nvec)
-    assert out.numel() == fmt.c.V * fmt.c.nvec and out.is_contiguous()
+    assert out.is_cuda and out.element_size() == 2 and out.numel() == fmt.c.V * fmt.c.nvec and out.is_contiguous()
     rc = load_library().fs_csr_to_blk(ctypes.byref(fmt.c), vals_csr.data_ptr(), out.data_ptr(), _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_csr_to_blk")

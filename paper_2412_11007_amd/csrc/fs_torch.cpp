@@ -105,7 +105,7 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
     }
 
 FS_ENTRY(spmm, 4)  // format, B, values or None, stream
-    if (!matrix(a[1], f, f->K) || !(a[2] == Py_None || THPVariable_Check(a[2]))) Py_RETURN_NONE;
+    if (!matrix(a[1], f, f->K) || !(a[2] == Py_None || flat(a[2], f, f->V * f->nvec))) Py_RETURN_NONE;
     const at::Tensor &B = THPVariable_Unpack(a[1]);
     const int64_t N = B.size(1);
     const void *vals = a[2] == Py_None ? nullptr : THPVariable_Unpack(a[2]).data_ptr();

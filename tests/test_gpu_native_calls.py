@@ -68,3 +68,33 @@ def test_native_calls_refuse_what_the_others_refuse(fs):  # noqa: F811
     for call in (lambda: fs.fs_edge_softmax(fmt, t(3)), lambda: fs.fs_csr_to_blk(fmt, t(3)), lambda: fs.fs_gather16(t(3), t(3))):
         with pytest.raises(AssertionError):
             call()
+
+
+def test_value_arrays_are_checked_before_they_are_read(fs):  # noqa: F811
+    """fs_blk_to_csr and the ``vals`` of the SpMM calls: too short, on the host, strided, of another type -- refused by
+    the call with or without its result given; longer arrays and raw bits stay accepted."""
+    A = random_csr(40, 56, 0.2, "f16", seed=7)
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, 40, 56)
+    n, own = fmt.V * fmt.nvec, fmt.vals_blk_t()
+    t = lambda n, dtype=torch.float16, device="cuda": torch.zeros(n, dtype=dtype, device=device)  # noqa: E731
+    B, C = torch.ones((56, 16), dtype=torch.float16, device="cuda"), t((40, 16))
+    calls = {"fs_blk_to_csr": lambda v: fs.fs_blk_to_csr(fmt, v), "out": lambda v: fs.fs_blk_to_csr(fmt, v, out=t(fmt.nnz)),
+             "fs_spmm": lambda v: fs.fs_spmm(fmt, B, vals=v), "fs_spmm out": lambda v: fs.fs_spmm(fmt, B, vals=v, out=C),
+             "bind_spmm": lambda v: fs.bind_spmm(fmt, B, C, vals=v)(), "fs_spmm_static": lambda v: fs.fs_spmm_static(fmt, B, C, vals=v)}
+    for name, call in calls.items():
+        for bad in (t(n - 1), t(n, device="cpu"), t(2 * n)[::2], t(n, torch.float32)):
+            with pytest.raises(AssertionError):
+                call(bad)
+        if "csr" not in name and name != "out":
+            with pytest.raises(AssertionError):
+                call(t(n, torch.bfloat16))
+        want = call(own).clone()
+        for good in (torch.cat([own, t(8)]), own.view(torch.int16)):
+            same(call(good).view(torch.float16), want)
+    for bad in (t(fmt.nnz - 1), t(fmt.nnz, device="cpu"), t(2 * fmt.nnz)[::2], t(fmt.nnz, torch.float32)):
+        with pytest.raises(AssertionError):
+            fs.fs_blk_to_csr(fmt, own, out=bad)
+    for bad in (t(n, device="cpu"), t(n, torch.float32)):
+        with pytest.raises(AssertionError):
+            fs.fs_csr_to_blk(fmt, va, out=bad)
