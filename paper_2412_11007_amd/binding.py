@@ -169,14 +169,24 @@ def _stream_ptr(stream) -> int:
     return _raw_stream(_current_device()) if stream is None else int(stream.cuda_stream)
 
 
-def _workspace(fmt, work, like, query, *args):
+def _temporary(nbytes, device, stream):
+    """A buffer that is given back when the call returns, from the memory of the stream the kernels run on: only work on
+    that stream may have it next."""
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    on = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, device)
+    with torch.cuda.stream(on):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def _workspace(fmt, work, like, stream, query, *args):
     """The caller's workspace or, where there is none, one of the size ``query(fmt, *args)`` asks for, as (tensor that has
     to outlive the call, pointer, bytes).  A workspace holds the parts of cut windows: without any there is none."""
     if work is None:
         need = query(fmt, *args) if fmt.c.n_split_items else 0
         if not need:
             return None, 0, 0
-        work = like.new_empty(need, dtype=torch.uint8)
+        work = _temporary(need, like.device, stream)
     return work, work.data_ptr(), work.numel() * work.element_size()
 
 
@@ -276,7 +286,7 @@ def fs_convert(rowptr, colidx, vals, M: int, K: int, torch_dtype=None, V: int = 
     if arena is None:
         arena = torch.empty(a_bytes, dtype=torch.uint8, device=dev)
     if scratch is None:
-        scratch = torch.empty(s_bytes, dtype=torch.uint8, device=dev)
+        scratch = _temporary(s_bytes, dev, stream)
     st = _FsFormatStruct()
     rc = lib.fs_convert(M, K, nnz, rowptr.data_ptr(), colidx.data_ptr(), 0 if vals is None else vals.data_ptr(),
                         code, V, KB, chunk, arena.data_ptr(), arena.numel(), scratch.data_ptr(), scratch.numel(),
@@ -301,7 +311,7 @@ def fs_spmm(fmt: FsFormat, B, vals=None, out=None, work=None, stream=None, event
     which records them around the main kernel.
     """
     if out is None and work is None and events is None:
-        got = _calls().spmm(ctypes.addressof(fmt.c), B, vals, _stream_ptr(stream))
+        got = _calls().spmm(ctypes.addressof(fmt.c), B, vals, stream, _stream_ptr(stream))
         if got is not None:
             return _result(got, "fs_spmm")
     K, N = B.shape
@@ -312,7 +322,7 @@ def fs_spmm(fmt: FsFormat, B, vals=None, out=None, work=None, stream=None, event
     else:
         assert out.shape == (fmt.c.M, N) and out.stride(1) == 1 and out.dtype == B.dtype
         ldo = out.stride(0)
-    work, work_ptr, work_bytes = _workspace(fmt, work, B, fs_spmm_workspace_bytes, N)
+    work, work_ptr, work_bytes = _workspace(fmt, work, B, stream, fs_spmm_workspace_bytes, N)
     args = (ctypes.byref(fmt.c), _values_ptr(fmt, vals), B.data_ptr(), N, B.stride(0), out.data_ptr(), ldo,
             work_ptr, work_bytes, _stream_ptr(stream))
     if events is None:
@@ -331,7 +341,7 @@ def bind_spmm(fmt: FsFormat, B, out, work=None, vals=None, stream=None):
     K, N = B.shape
     assert B.is_cuda and B.dtype == fmt.torch_dtype and B.stride(1) == 1 and K == fmt.c.K
     assert out.shape == (fmt.c.M, N) and out.stride(1) == 1 and out.dtype == B.dtype
-    work, work_ptr, work_bytes = _workspace(fmt, work, B, fs_spmm_workspace_bytes, N)
+    work, work_ptr, work_bytes = _workspace(fmt, work, B, stream, fs_spmm_workspace_bytes, N)
     fn = load_library().fs_spmm
     args = (ctypes.byref(fmt.c), _values_ptr(fmt, vals), B.data_ptr(), N, B.stride(0), out.data_ptr(),
             out.stride(0), work_ptr, work_bytes, _stream_ptr(stream))
@@ -417,7 +427,7 @@ def fs_edge_softmax_workspace_bytes(fmt: FsFormat) -> int:
 def fs_edge_softmax(fmt: FsFormat, vals, out=None, scale: float = 1.0, work=None, stream=None):
     """Row softmax of scale * value over the stored entries, on vals_blk-layout arrays (out may be vals)."""
     if out is None and work is None:
-        got = _calls().softmax(ctypes.addressof(fmt.c), vals, scale, _stream_ptr(stream))
+        got = _calls().softmax(ctypes.addressof(fmt.c), vals, scale, stream, _stream_ptr(stream))
         if got is not None:
             return _result(got, "fs_edge_softmax")
     assert vals.is_cuda and vals.dtype == fmt.torch_dtype and vals.is_contiguous()
@@ -425,7 +435,7 @@ def fs_edge_softmax(fmt: FsFormat, vals, out=None, scale: float = 1.0, work=None
     if out is None:
         out = torch.empty_like(vals)
     assert out.numel() == vals.numel() and out.dtype == vals.dtype and out.is_contiguous()
-    work, work_ptr, work_bytes = _workspace(fmt, work, vals, fs_edge_softmax_workspace_bytes)
+    work, work_ptr, work_bytes = _workspace(fmt, work, vals, stream, fs_edge_softmax_workspace_bytes)
     rc = load_library().fs_edge_softmax(ctypes.byref(fmt.c), vals.data_ptr(), out.data_ptr(), float(scale), work_ptr,
                                         work_bytes, _stream_ptr(stream))
     if rc:
@@ -437,7 +447,7 @@ def fs_edge_softmax_backward(fmt: FsFormat, probs, grad, out=None, scale: float 
     """Gradient of fs_edge_softmax: scale * p * (g - row sum of p * g), on vals_blk-layout arrays (out may be
     either input)."""
     if out is None and work is None:
-        got = _calls().softmax_backward(ctypes.addressof(fmt.c), probs, grad, scale, _stream_ptr(stream))
+        got = _calls().softmax_backward(ctypes.addressof(fmt.c), probs, grad, scale, stream, _stream_ptr(stream))
         if got is not None:
             return _result(got, "fs_edge_softmax_backward")
     for t in (probs, grad):
@@ -445,7 +455,7 @@ def fs_edge_softmax_backward(fmt: FsFormat, probs, grad, out=None, scale: float 
     if out is None:
         out = torch.empty_like(probs)
     assert out.numel() == probs.numel() and out.dtype == probs.dtype and out.is_contiguous()
-    work, work_ptr, work_bytes = _workspace(fmt, work, probs, fs_edge_softmax_workspace_bytes)
+    work, work_ptr, work_bytes = _workspace(fmt, work, probs, stream, fs_edge_softmax_workspace_bytes)
     rc = load_library().fs_edge_softmax_backward(ctypes.byref(fmt.c), probs.data_ptr(), grad.data_ptr(), float(scale),
                                                  out.data_ptr(), work_ptr, work_bytes, _stream_ptr(stream))
     if rc:
@@ -479,7 +489,7 @@ def fs_spmm_packed(fmt: FsFormat, packed, B, out=None, work=None, stream=None):
     if out is None:
         out = B.new_empty(fmt.c.M, N)
     assert out.shape == (fmt.c.M, N) and out.dtype == B.dtype and out.stride(1) == 1
-    work, work_ptr, work_bytes = _workspace(fmt, work, B, fs_spmm_workspace_bytes, N)
+    work, work_ptr, work_bytes = _workspace(fmt, work, B, stream, fs_spmm_workspace_bytes, N)
     rc = load_library().fs_spmm_packed(ctypes.byref(fmt.c), packed.data_ptr(), B.data_ptr(), N, B.stride(0),
                                        out.data_ptr(), out.stride(0), work_ptr, work_bytes, _stream_ptr(stream))
     if rc:
@@ -508,7 +518,8 @@ def fs_attention(fmt: FsFormat, X, Y, H, scale: float = 1.0, out=None, work=None
 
 def _attention_like(name, fmt, X, Y, H, scale, out, work, stream):
     if out is None and work is None:
-        got = _calls().attention(ctypes.addressof(fmt.c), X, Y, H, scale, name == "fs_attention", _stream_ptr(stream))
+        got = _calls().attention(ctypes.addressof(fmt.c), X, Y, H, scale, name == "fs_attention", stream,
+                                 _stream_ptr(stream))
         if got is not None:
             return _result(got, name)
     for t in (X, Y, H):
@@ -518,7 +529,7 @@ def _attention_like(name, fmt, X, Y, H, scale, out, work, stream):
     if out is None:
         out = H.new_empty(fmt.c.M, N)
     assert out.shape == (fmt.c.M, N) and out.dtype == H.dtype and out.stride(1) == 1
-    work, work_ptr, work_bytes = _workspace(fmt, work, H, fs_attention_workspace_bytes, N)
+    work, work_ptr, work_bytes = _workspace(fmt, work, H, stream, fs_attention_workspace_bytes, N)
     rc = getattr(load_library(), name)(ctypes.byref(fmt.c), X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), d,
                                      float(scale), H.data_ptr(), N, H.stride(0), out.data_ptr(), out.stride(0),
                                      work_ptr, work_bytes, _stream_ptr(stream))
@@ -575,13 +586,12 @@ def fs_csr_transpose(rowptr, colidx, M: int, K: int, stream=None):
     rowptr_t = torch.empty(K + 1, dtype=torch.int32, device=dev)
     colidx_t = torch.empty(nnz, dtype=torch.int32, device=dev)
     perm = torch.empty(nnz, dtype=torch.int32, device=dev)
-    scratch = torch.empty(need.value, dtype=torch.uint8, device=dev)
+    scratch = _temporary(need.value, dev, stream)
     rc = lib.fs_csr_transpose(M, K, nnz, rowptr.data_ptr(), colidx.data_ptr(), rowptr_t.data_ptr(),
                               colidx_t.data_ptr(), perm.data_ptr(), scratch.data_ptr(), need.value,
                               _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_csr_transpose")
-    scratch.record_stream(torch.cuda.current_stream() if stream is None else stream)
     return rowptr_t, colidx_t, perm
 
 

@@ -3,14 +3,17 @@
 // A small product is bound by its host path: the kernel of a 4096-row SpMM takes 4.6 us, its launch 3 us, and marshalling
 // one call in Python 3 us (attention, with more operands, a second launch and a workspace: 7 us).  Here the checks, the
 // allocation of the result and of the workspace and the call are compiled; what is left for Python is to pass the
-// tensors.  Every function takes (address of the fs_format, tensors, ..., stream handle) and returns the result tensor,
+// tensors.  Every function takes (address of the fs_format, tensors, ..., stream handle; before it, where a workspace may be
+// needed, the stream object or None for the current stream) and returns the result tensor,
 // the library's status as an int where the call failed, or None where an argument is not what the call expects, which
 // the binding's checks in Python then name.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/StreamGuard.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/Stream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "flashsparse.h"
@@ -59,18 +62,27 @@ PyObject *finish(const at::Tensor &out, fs_status st)
     return st == FS_OK ? THPVariable_Wrap(out) : PyLong_FromLong((long)st);
 }
 
-// A workspace holds the parts of cut windows: without any there is none.
+bool stream_or_none(PyObject *o) { return o == Py_None || THPStream_Check(o); }
+
+// A workspace holds the parts of cut windows: without any there is none.  It comes from the memory of the stream `on` that
+// the kernels run on (None: the current one): it is given back when the call returns, and only work on that stream may
+// have it next.
 struct Work {
     at::Tensor t;
     void *p = nullptr;
     size_t bytes = 0;
     fs_status st = FS_OK;
     template <typename Query>
-    Work(const fs_format *f, const at::Tensor &like, Query query)
+    Work(const fs_format *f, const at::Tensor &like, PyObject *on, Query query)
     {
         if (f->n_split_items == 0) return;
         st = query(&bytes);
         if (st != FS_OK || bytes == 0) return;
+        c10::OptionalStreamGuard guard;
+        if (on != Py_None) {
+            const THPStream *s = (const THPStream *)on;
+            guard.reset_stream(c10::Stream::unpack3(s->stream_id, (c10::DeviceIndex)s->device_index, (c10::DeviceType)s->device_type));
+        }
         t = at::empty({(int64_t)bytes}, like.options().dtype(at::kByte));
         p = t.data_ptr();
     }
@@ -104,13 +116,13 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
         END_HANDLE_TH_ERRORS \
     }
 
-FS_ENTRY(spmm, 4)  // format, B, values or None, stream
-    if (!matrix(a[1], f, f->K) || !(a[2] == Py_None || flat(a[2], f, f->V * f->nvec))) Py_RETURN_NONE;
+FS_ENTRY(spmm, 5)  // format, B, values or None, stream object, stream
+    if (!matrix(a[1], f, f->K) || !(a[2] == Py_None || flat(a[2], f, f->V * f->nvec)) || !stream_or_none(a[3])) Py_RETURN_NONE;
     const at::Tensor &B = THPVariable_Unpack(a[1]);
     const int64_t N = B.size(1);
     const void *vals = a[2] == Py_None ? nullptr : THPVariable_Unpack(a[2]).data_ptr();
     at::Tensor out = at::empty({f->M, N}, B.options());
-    Work w(f, B, [&](size_t *b) { return g.spmm_work(f, N, b); });
+    Work w(f, B, a[3], [&](size_t *b) { return g.spmm_work(f, N, b); });
     if (w.st != FS_OK) return finish(out, w.st);
     FS_CALL(st, g.spmm(f, vals, B.data_ptr(), N, B.stride(0), out.data_ptr(), N, w.p, w.bytes, stream))
     return finish(out, st);
@@ -128,40 +140,40 @@ FS_ENTRY(sddmm, 5)  // format, X, Y, true: vals_blk layout, false: CSR order, st
     return finish(out, st);
 FS_ENTRY_END
 
-FS_ENTRY(attention, 7)  // format, X, Y, H, scale, true: with the softmax, stream
-    if (!matrix(a[1], f, f->M) || !matrix(a[2], f, f->K) || !matrix(a[3], f, f->K)) Py_RETURN_NONE;
+FS_ENTRY(attention, 8)  // format, X, Y, H, scale, true: with the softmax, stream object, stream
+    if (!matrix(a[1], f, f->M) || !matrix(a[2], f, f->K) || !matrix(a[3], f, f->K) || !stream_or_none(a[6])) Py_RETURN_NONE;
     const at::Tensor &X = THPVariable_Unpack(a[1]), &Y = THPVariable_Unpack(a[2]), &H = THPVariable_Unpack(a[3]);
     const int64_t d = X.size(1), N = H.size(1);
     if (Y.size(1) != d) Py_RETURN_NONE;
     const float scale = (float)PyFloat_AsDouble(a[4]);
     if (PyErr_Occurred()) return nullptr;
     at::Tensor out = at::empty({f->M, N}, H.options());
-    Work w(f, H, [&](size_t *b) { return g.attention_work(f, N, b); });
+    Work w(f, H, a[6], [&](size_t *b) { return g.attention_work(f, N, b); });
     if (w.st != FS_OK) return finish(out, w.st);
     FS_CALL(st, (a[5] == Py_True ? g.attention : g.sddmm_spmm)(f, X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), d, scale,
                                                                H.data_ptr(), N, H.stride(0), out.data_ptr(), N, w.p, w.bytes, stream))
     return finish(out, st);
 FS_ENTRY_END
 
-FS_ENTRY(softmax, 4)  // format, values, scale, stream
-    if (!flat(a[1], f, f->V * f->nvec)) Py_RETURN_NONE;
+FS_ENTRY(softmax, 5)  // format, values, scale, stream object, stream
+    if (!flat(a[1], f, f->V * f->nvec) || !stream_or_none(a[3])) Py_RETURN_NONE;
     const at::Tensor &v = THPVariable_Unpack(a[1]);
     const float scale = (float)PyFloat_AsDouble(a[2]);
     if (PyErr_Occurred()) return nullptr;
     at::Tensor out = at::empty(v.sizes(), v.options());
-    Work w(f, v, [&](size_t *b) { return g.softmax_work(f, b); });
+    Work w(f, v, a[3], [&](size_t *b) { return g.softmax_work(f, b); });
     if (w.st != FS_OK) return finish(out, w.st);
     FS_CALL(st, g.softmax(f, v.data_ptr(), out.data_ptr(), scale, w.p, w.bytes, stream))
     return finish(out, st);
 FS_ENTRY_END
 
-FS_ENTRY(softmax_backward, 5)  // format, probabilities, their gradient, scale, stream
-    if (!flat(a[1], f, f->V * f->nvec) || !flat(a[2], f, f->V * f->nvec)) Py_RETURN_NONE;
+FS_ENTRY(softmax_backward, 6)  // format, probabilities, their gradient, scale, stream object, stream
+    if (!flat(a[1], f, f->V * f->nvec) || !flat(a[2], f, f->V * f->nvec) || !stream_or_none(a[4])) Py_RETURN_NONE;
     const at::Tensor &p = THPVariable_Unpack(a[1]), &gr = THPVariable_Unpack(a[2]);
     const float scale = (float)PyFloat_AsDouble(a[3]);
     if (PyErr_Occurred()) return nullptr;
     at::Tensor out = at::empty(p.sizes(), p.options());
-    Work w(f, p, [&](size_t *b) { return g.softmax_work(f, b); });
+    Work w(f, p, a[4], [&](size_t *b) { return g.softmax_work(f, b); });
     if (w.st != FS_OK) return finish(out, w.st);
     FS_CALL(st, g.softmax_backward(f, p.data_ptr(), gr.data_ptr(), scale, out.data_ptr(), w.p, w.bytes, stream))
     return finish(out, st);

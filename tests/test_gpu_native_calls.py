@@ -98,3 +98,44 @@ def test_value_arrays_are_checked_before_they_are_read(fs):  # noqa: F811
     for bad in (t(n, device="cpu"), t(n, torch.float32)):
         with pytest.raises(AssertionError):
             fs.fs_csr_to_blk(fmt, va, out=bad)
+
+
+@pytest.mark.parametrize("call", ["spmm", "spmm out", "bind_spmm", "spmm_packed", "attention", "attention out", "sddmm_spmm", "softmax",
+                                  "softmax out", "softmax_backward", "softmax_backward out", "transpose", "convert"])
+@pytest.mark.parametrize("external", [False, True])
+def test_temporary_memory_belongs_to_the_stream_of_the_kernels(fs, call, external):  # noqa: F811
+    """What a call allocates and gives back comes from the memory of ``stream``, not from the current stream's, whose next
+    allocation could have it while the kernels are still running."""
+    A = random_csr(64, 900, 0.5, "f16", seed=7)
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, 64, 900, chunk=64)
+    assert fmt.n_split_items > 0  # a workspace is needed
+    X, Y, B = (torch.ones((r, c), dtype=torch.float16, device="cuda") for r, c in ((64, 40), (900, 40), (900, 48)))
+    out, P, packed = X.new_empty(64, 48), fmt.vals_blk_t().clone(), fs.fs_pack_values(fmt)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+
+    class Handle:  # what other frameworks' streams look like
+        cuda_stream = side.cuda_stream
+    stream = Handle() if external else side
+    calls = {
+        "spmm": lambda s: fs.fs_spmm(fmt, B, stream=s), "spmm out": lambda s: fs.fs_spmm(fmt, B, out=out, stream=s),
+        "bind_spmm": lambda s: fs.bind_spmm(fmt, B, out, stream=s)(), "spmm_packed": lambda s: fs.fs_spmm_packed(fmt, packed, B, stream=s),
+        "attention": lambda s: fs.fs_attention(fmt, X, Y, B, stream=s), "attention out": lambda s: fs.fs_attention(fmt, X, Y, B, out=out, stream=s),
+        "sddmm_spmm": lambda s: fs.fs_sddmm_spmm(fmt, X, Y, B, stream=s), "softmax": lambda s: fs.fs_edge_softmax(fmt, P, stream=s),
+        "softmax out": lambda s: fs.fs_edge_softmax(fmt, P, out=torch.empty_like(P), stream=s),
+        "softmax_backward": lambda s: fs.fs_edge_softmax_backward(fmt, P, P, stream=s),
+        "softmax_backward out": lambda s: fs.fs_edge_softmax_backward(fmt, P, P, out=torch.empty_like(P), stream=s),
+        "transpose": lambda s: fs.fs_csr_transpose(rp, ci, 64, 900, stream=s)[2].view(torch.int16),
+        "convert": lambda s: fs.fs_convert(rp, ci, va, 64, 900, chunk=64, stream=s).vals_blk_t(),
+    }
+    want = calls[call](None).clone()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()  # nothing is left of what earlier tests allocated on this stream
+
+    def held():
+        return sum(g["total_size"] for g in torch.cuda.memory_snapshot() if g["stream"] == side.cuda_stream)
+    assert held() == 0
+    got = calls[call](stream)
+    assert held() > 0
+    same(got, want)
