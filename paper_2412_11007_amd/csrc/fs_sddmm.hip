@@ -355,12 +355,20 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
 {
     if (f->n_blocks == 0) return FS_OK;
     const int n_blocks = (int)f->n_blocks;
-    // The launch order pays where hub windows hold a good part of the work and Y is more than one XCD's L2 holds
-    // (R-MAT, d = 32: 47 -> 44 us with 16 MB of Y, 12.7 -> 13.0 us with 4 MB); otherwise up to four block slots per
-    // wavefront (4 to 8 measured best from 11 thousand to 200 thousand blocks, 16 and more lose 5-15 %), fewer where that
-    // leaves less than eight wavefronts per CU: then a wavefront's own chain of steps is the whole time (R-MAT of 8 k
-    // rows, 3 k blocks, d = 248: 14.1 us with four slots, 8.5 us with one).
-    const bool ordered = f->n_cut_items * 8 >= f->n_items && f->K * ldy * 2 > ((int64_t)4 << 20);
+    // The launch order pays where parts of hub windows are a good share of the items, what is read of Y is more than
+    // one XCD's L2 holds, and there are wavefronts enough, because each then takes a whole item.  In order, us against
+    // slot by slot, d = 128: R-MAT of 262 k rows, 17.5 k items, 75 and 108; of 65 k rows, 5.2 k items, 20 and 22; of
+    // 32 k rows, 2.7 k items, 17 and 12; of 8 k rows, 0.6 k items, 9 and 5.  Items that are nearly all parts of hubs are
+    // alike and get by with fewer (64 rows of 20 k entries among 4 k short ones, 1.8 k items: 12 and 18; 100 rows of
+    // 5 k, 1.2 k items: 12 and 13, at d = 64 9 and 7).  For d <= 32 the rows are short and the L2s set the time:
+    // only where hubs hold most of the work (500 rows of 4 k entries among 30 k short ones: 22 and 25; R-MAT of 131 k
+    // rows: 21 and 20).
+    const int64_t n_cut = f->n_cut_items, n_items = f->n_items;
+    const bool many = n_items >= 4096 && n_cut * (d <= 32 ? 2 : 8) >= n_items;
+    const bool ordered = f->K * d * 2 > ((int64_t)4 << 20) && (many || (d > 32 && n_items >= 1536 && n_cut * 4 >= n_items * 3));
+    // Otherwise up to four block slots per wavefront (4 to 8 measured best from 11 thousand to 200 thousand blocks, 16 and
+    // more lose 5-15 %), fewer where that leaves less than eight wavefronts per CU: then a wavefront's own chain of steps
+    // is the whole time (R-MAT of 8 k rows, 3 k blocks, d = 248: 14.1 us with four slots, 8.5 us with one).
     const int4 *items = ordered ? (const int4 *)f->items_by_cost : nullptr;
     int G = std::min(std::max(n_blocks / 2048, 1), 4);
 #ifdef FS_TUNING_ENV  // tuning builds only (-DFS_TUNING_ENV): the shipped library reads no environment

@@ -1,13 +1,12 @@
 """SDDMM at the feature counts where its kernel changes or ends a chunk raggedly, bit for bit on exact inputs
-(every product and partial sum is a multiple of 1/2 far below 2^24), in both orders in which blocks are taken: Y
-within one XCD's L2, and rows so far apart that it is not (hub windows then go in launch order)."""
+(every product and partial sum is a multiple of 1/2 far below 2^24), and in both orders in which blocks are taken."""
 import numpy as np
 import pytest
 
 import oracle
 from gpu_util import from_dev_bits, to_dev, upload_csr
 from test_gpu_exact import fs, halves, hub_matrix, int_dense, same_bits  # noqa: F401
-from workloads import Dense, stream
+from workloads import Dense, csr_from_coo, stream
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +35,33 @@ def test_sddmm_widths_bit_exact(fs, d, V):  # noqa: F811
         got[fmt.csr_to_slot_t().cpu().numpy()] = 0
         assert not got.any(), "positions outside the pattern must be +0.0"
         same_bits(from_dev_bits(fs.fs_sddmm(fmt, Xd, Yv, blocked=False)), want, "fs_sddmm, CSR order, V=%d d=%d" % (V, d))
+
+
+@pytest.mark.parametrize("d", [32, 40, 64, 128, 264])
+@pytest.mark.parametrize("V,dtype", [(8, "f16"), (16, "bf16")])
+@pytest.mark.parametrize("kind", ["hubs", "some hubs", "few items"])
+def test_sddmm_block_order(fs, kind, V, dtype, d):  # noqa: F811
+    """Enough items and enough of Y for launch order (all items parts of hub windows; one in five, which d <= 32 leaves
+    in slot order), and the same hubs with too few items for it."""
+    import torch
+    K = 70000  # more than 4 MB of Y from d = 32 on
+    hubs, n, short = {"hubs": (2 * V, 60000, 0), "some hubs": (V, 60000, 60000), "few items": (V, 3000, 3)}[kind]
+    rng = stream(V + d, 95, 1)
+    cols = [rng.choice(K, size=n, replace=False) for _ in range(hubs)]
+    rows = [np.full(n, i) for i in range(hubs)]
+    rows.append(hubs + np.arange(short))
+    cols.append(rng.integers(0, K, size=short))
+    A = csr_from_coo(hubs + short, K, np.concatenate(rows), np.concatenate(cols), "u11", dtype, rng)
+    lim = 1 if dtype == "bf16" else 2
+    X = Dense(halves(stream(V + d, 95, 2), (A.M, d), -lim, lim, dtype), dtype)
+    Y = int_dense(K, d, dtype, seed=V + d, tid=4, lim=lim)
+    ref, _ = oracle.sddmm(A.M, A.K, A.rowptr, A.colidx, X.bits, Y.bits, dtype, want_scale=False)
+    want = oracle.round_f64_to_bits(ref, dtype)
+    rp, ci, _ = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, None, A.M, A.K, torch_dtype=torch.float16 if dtype == "f16" else torch.bfloat16, V=V, chunk=32)
+    cut, items = fmt.n_cut_items, fmt.n_items
+    assert {"hubs": items >= 4096 and cut * 4 >= items * 3, "some hubs": items >= 4096 and items <= 8 * cut and cut * 2 < items,
+            "few items": items < 1536}[kind], (cut, items)
+    Xd, Yd = to_dev(X.bits, dtype), to_dev(Y.bits, dtype)
+    same_bits(from_dev_bits(fs.fs_blk_to_csr(fmt, fs.fs_sddmm(fmt, Xd, Yd))), want, "fs_sddmm")
+    same_bits(from_dev_bits(fs.fs_sddmm(fmt, Xd, Yd, blocked=False)), want, "fs_sddmm, CSR order")
