@@ -533,12 +533,11 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     CsrView a{d_rowptr, d_colidx, M, (int32_t)nnz};
 
     // misc: [0] CSR error flags, [1] vectors, [2] longest item, [3] items with a part of a cut window,
-    // [4] block slots, [5] items, [6] partial tiles, [7] cut windows -- what the host reads, in one copy;
-    // [8] units
+    // [4] block slots, [5] items, [6] partial tiles, [7] cut windows, [8] units -- what the host reads, in one copy
     FS_HIP(hipMemsetAsync(misc, 0, 64 * sizeof(int), s));
     const UnitPlan up = unit_plan(M, nnz, V);
     const int64_t n_groups = (W + up.group - 1) / up.group;
-    const unsigned unit_grid = (unsigned)units_bound(W, nnz);
+    const int64_t max_units = units_bound(up, W, nnz);
     const int *n_units = misc + 8;
     k_units<false><<<grid_for(std::max<int64_t>(n_groups, 1), 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
     FS_LAUNCH_CHECK();
@@ -547,16 +546,22 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         k_units<true><<<grid_for(n_groups, 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
         FS_LAUNCH_CHECK();
         if (nnz > kUnitEntries) {
-            if (V <= 8) k_pieces<8><<<(unit_grid + 6) / 7, 64, 0, s>>>(a, up, units, n_units, pieces, redo, misc);
-            else k_pieces<32><<<unit_grid, 64, 0, s>>>(a, up, units, n_units, pieces, redo, misc);
-            FS_LAUNCH_CHECK();
-            if (V <= 8) k_pieces_exact<8><<<(unit_grid + kExactPerWave - 1) / kExactPerWave, 64, 0, s>>>(a, up, units, n_units, pieces, redo, misc);
-            else k_pieces_exact<32><<<(unit_grid + kExactPerWave - 1) / kExactPerWave, 64, 0, s>>>(a, up, units, n_units, pieces, redo, misc);
-            FS_LAUNCH_CHECK();
+            st = launch_units(V <= 8 ? (max_units + 6) / 7 : max_units, [&](int first, unsigned grid) {
+                if (V <= 8) k_pieces<8><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
+                else k_pieces<32><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
+            });
+            if (st != FS_OK) return st;
+            st = launch_units((max_units + kExactPerWave - 1) / kExactPerWave, [&](int first, unsigned grid) {
+                if (V <= 8) k_pieces_exact<8><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
+                else k_pieces_exact<32><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
+            });
+            if (st != FS_OK) return st;
         }
-        k_unit_rank<<<unit_grid, 64, 0, s>>>(a, up, K, units, n_units, pieces, info, first_vec, win_at, misc);
-        FS_LAUNCH_CHECK();
-        if ((st = scan_exclusive(first_vec, unit_grid, tmp, s, misc + 1)) != FS_OK) return st;
+        st = launch_units(max_units, [&](int first, unsigned grid) {
+            k_unit_rank<<<grid, 64, 0, s>>>(first, a, up, K, units, n_units, pieces, info, first_vec, win_at, misc);
+        });
+        if (st != FS_OK) return st;
+        if ((st = scan_exclusive(first_vec, max_units, tmp, s, misc + 1)) != FS_OK) return st;
     }
     k_win_ptr<<<grid_for(W + 1, 256), 256, 0, s>>>(win_at, first_vec, n_units, W, KB, win_ptr, blk_ptr, misc);
     FS_LAUNCH_CHECK();
@@ -580,12 +585,13 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         if ((st = scan_exclusive(slot_ptr, n_cand_max, tmp, s, misc + 6, cut_pos, misc + 7)) != FS_OK) return st;
     }
 
-    int h_misc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int h_misc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     FS_HIP(hipMemcpyAsync(h_misc, misc, sizeof(h_misc), hipMemcpyDeviceToHost, s));
     FS_HIP(hipStreamSynchronize(s));
     if (h_misc[0]) return FS_ERR_INVALID_CSR;
     const int64_t nvec = h_misc[1];
     const int NB = h_misc[4];  // block slots in total
+    const int units_made = h_misc[8];
     if (library_picks_rows && V == 8 && wants_packed_values(M, nnz, 4, KB) && prefers_four_rows(nnz, nvec))
         return fs_convert(M, K, nnz, d_rowptr, d_colidx, d_vals, dtype, 4, KB, chunk, d_arena, arena_bytes, d_scratch,
                           scratch_bytes, stream, out);
@@ -636,24 +642,26 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         const size_t lds = place_lds_bytes(V, KB);
         const int64_t vb = (int64_t)place_vector_bytes(V);
         const uint16_t *va = (const uint16_t *)d_vals;
-#define FS_PLACE(KB32, VT) k_unit_place<KB32, VT><<<unit_grid, 64, lds, s>>>(a, up, KB, vb, units, n_units, pieces, info, first_vec, win_ptr, blk_ptr, va, po)
-        if (KB == 32) {
-            if (V == 4) FS_PLACE(true, 4);
+        st = launch_units(units_made, [&](int first, unsigned grid) {
+#define FS_PLACE(KB32, VT) k_unit_place<KB32, VT><<<grid, 64, lds, s>>>(first, a, up, KB, vb, units, pieces, info, first_vec, win_ptr, blk_ptr, va, po)
+            if (KB != 32) FS_PLACE(false, 0);
+            else if (V == 4) FS_PLACE(true, 4);
             else if (V == 8) FS_PLACE(true, 8);
             else if (V == 16) FS_PLACE(true, 16);
             else FS_PLACE(true, 0);
-            FS_LAUNCH_CHECK();
-        } else {
-            FS_PLACE(false, 0);
-            FS_LAUNCH_CHECK();
+#undef FS_PLACE
+        });
+        if (st != FS_OK) return st;
+        if (KB != 32) {
             k_block_row_base<<<grid_for((int64_t)NB * V, 256), 256, 0, s>>>(a, V, blk_desc, NB, vec_col, nvec, blk_row_base);
             FS_LAUNCH_CHECK();
         }
-#undef FS_PLACE
         if (nnz > kUnitEntries) {
-            if (KB == 32) k_shared_blocks<true><<<(unit_grid + kSharedPerWave - 1) / kSharedPerWave, 64, 0, s>>>(V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
-            else k_shared_blocks<false><<<(unit_grid + kSharedPerWave - 1) / kSharedPerWave, 64, 0, s>>>(V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
-            FS_LAUNCH_CHECK();
+            st = launch_units((units_made + kSharedPerWave - 1) / kSharedPerWave, [&](int first, unsigned grid) {
+                if (KB == 32) k_shared_blocks<true><<<grid, 64, 0, s>>>(first, V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
+                else k_shared_blocks<false><<<grid, 64, 0, s>>>(first, V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
+            });
+            if (st != FS_OK) return st;
         }
     }
 

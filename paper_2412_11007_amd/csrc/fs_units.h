@@ -12,6 +12,8 @@
 // 427 us (0.9 GB, most of it written, 170 us; the LDS tile and scattered two-byte accesses are the rest).
 #pragma once
 
+#include <algorithm>
+
 #include "fs_common.h"
 #include "fs_scan.h"
 #include "fs_tile.h"  // FS_WAVE_SYNC: a barrier would also wait for every store under way
@@ -71,8 +73,27 @@ inline UnitPlan unit_plan(int64_t M, int64_t nnz, int V)
     p.per = (kUnitEntries / p.stride - 2 * V) * 5 / 6;
     return p;
 }
-// at most this many units: per * stride >= 208 for every V
+// At most this many units, for every V (per * stride >= 208): what the scratch buffer has room for.
 inline int64_t units_bound(int64_t W, int64_t nnz) { return W + nnz / 208 + 2; }
+// ... and for a plan: a unit per group; of the at most nnz / (kUnitEntries + 1) groups that do not fit one, a unit per window;
+// of a hub window one more per (per * stride) entries.  (Launched for the bound above, a matrix with fewer entries than
+// rows ran mostly empty workgroups: 16 M rows, 1 M entries, four-row windows 3.49 -> 1.09 ms.)
+inline int64_t units_bound(const UnitPlan &p, int64_t W, int64_t nnz)
+{
+    const int64_t groups = (W + p.group - 1) / p.group;
+    return std::min(groups + (p.group - 1) * (nnz / (kUnitEntries + 1)), W) + nnz / (p.per * p.stride) + 2;
+}
+// Wavefronts per launch: a launch has fewer than 2^32 threads, so a larger number takes several.
+constexpr int64_t kUnitLaunch = (int64_t)1 << 24;
+template <typename Launch>
+fs_status launch_units(int64_t n, Launch launch)
+{
+    for (int64_t first = 0; first < n; first += kUnitLaunch) {
+        launch((int)first, (unsigned)std::min(n - first, kUnitLaunch));
+        FS_LAUNCH_CHECK();
+    }
+    return FS_OK;
+}
 
 // Pieces of window w (1: it fits a unit).
 __device__ __forceinline__ int window_pieces(const CsrView &a, const UnitPlan &p, int64_t w, int64_t &entries)
@@ -148,14 +169,14 @@ __device__ __forceinline__ int32_t first_at_least(const int32_t *__restrict__ co
 // one of whose pieces came out too large for a unit is noted in redo[] for k_pieces_exact.  64 / ROWS pieces per
 // wavefront, one row per lane; the last one of a wavefront is only there for the size of the one before.
 template <int ROWS>  // a power of two, at least V
-__global__ void __launch_bounds__(64) k_pieces(CsrView a, UnitPlan p, const int4 *__restrict__ units, const int *__restrict__ n_units,
+__global__ void __launch_bounds__(64) k_pieces(int block0, CsrView a, UnitPlan p, const int4 *__restrict__ units, const int *__restrict__ n_units,
                                                int32_t *__restrict__ start, int *__restrict__ redo, const int *__restrict__ err)
 {
     constexpr int PER = 64 / ROWS;
     constexpr int CLOSE = kUnitEntries / 12;  // near enough: pieces are planned at most five sixths full
     const int lane = threadIdx.x, k = lane / ROWS, r = lane % ROWS;
-    const int u = blockIdx.x * (PER - 1) + k, n = *n_units;
-    if (blockIdx.x * (PER - 1) >= n || (*err & 1)) return;
+    const int u0 = (block0 + blockIdx.x) * (PER - 1), u = u0 + k, n = *n_units;
+    if (u0 >= n || (*err & 1)) return;
     const int4 un = units[min(u, n - 1)];
     const bool hub = u < n && un.w > 1;
     if (!__any(hub)) return;
@@ -210,17 +231,17 @@ __global__ void __launch_bounds__(64) k_pieces(CsrView a, UnitPlan p, const int4
 // The rows are searched eight at a time: one memory round trip per halving, not eight.
 constexpr int kExactPerWave = 4;  // units a wavefront looks at
 template <int ROWS>  // at least V, a multiple of eight
-__global__ void __launch_bounds__(64) k_pieces_exact(CsrView a, UnitPlan p, const int4 *__restrict__ units, const int *__restrict__ n_units,
+__global__ void __launch_bounds__(64) k_pieces_exact(int block0, CsrView a, UnitPlan p, const int4 *__restrict__ units, const int *__restrict__ n_units,
                                                int32_t *__restrict__ start, const int *__restrict__ redo, const int *__restrict__ err)
 {
     constexpr int G = 8;
     const int lane = threadIdx.x, n = *n_units;
     if (*err & 1) return;
-    const int my_u = blockIdx.x * kExactPerWave + lane;  // most have nothing to do
+    const int u0 = (block0 + blockIdx.x) * kExactPerWave, my_u = u0 + lane;  // most have nothing to do
     const int4 my_un = units[min(my_u, n - 1)];
     uint64_t todo = __ballot(lane < kExactPerWave && my_u < n && my_un.w > 1 && redo[my_un.x]);
     for (; todo; todo &= todo - 1) {
-    const int k = __builtin_ctzll(todo), u = blockIdx.x * kExactPerWave + k;
+    const int k = __builtin_ctzll(todo), u = u0 + k;
     const int4 un = make_int4(__shfl(my_un.x, k, 64), 1, __shfl(my_un.z, k, 64), __shfl(my_un.w, k, 64));
     const int64_t row0 = (int64_t)un.x * p.V;
     int32_t lo = 0, hi = 0;
@@ -344,7 +365,7 @@ __device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &
 // search per element -- and when all lanes have theirs in registers they go back to the same place, so that LDS holds
 // the unit once and 26 wavefronts share a CU.  An element is {pair, column, place} in one 64-bit number, so that one
 // comparison orders it; an element larger than all ends each half, so that a merge needs no bounds.
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_unit_rank(CsrView a, UnitPlan p, int64_t K, const int4 *__restrict__ units, const int *__restrict__ n_units,
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_unit_rank(int block0, CsrView a, UnitPlan p, int64_t K, const int4 *__restrict__ units, const int *__restrict__ n_units,
                                                   const int32_t *__restrict__ piece_start, uint16_t *__restrict__ info, int *__restrict__ count,
                                                   int2 *__restrict__ win_at, int *__restrict__ err)
 {
@@ -355,7 +376,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_
     __shared__ int begin[kUnitRows];
     __shared__ int32_t sh_lo[kUnitRows];
     __shared__ int win_first[kMaxUnitWindows];
-    const int u = blockIdx.x, lane = threadIdx.x;
+    const int u = block0 + blockIdx.x, lane = threadIdx.x;
     if (u >= *n_units || (*err & 1)) {  // (bit 1: malformed row pointers, set before; the records are not there)
         if (lane == 0) count[u] = 0;
         return;
@@ -544,7 +565,7 @@ inline size_t place_lds_bytes(int V, int KB) { return place_vector_bytes(V) + (K
 // the compute kernels take: their rows' occupancy and CSR positions are written too.  A block that a hub window's pieces
 // share gets its values from k_shared_blocks.
 template <bool KB32, int VT>  // VT: rows per window, or 0 for those without an instantiation of their own
-__global__ void __launch_bounds__(64) k_unit_place(CsrView a, UnitPlan p, int KB, int64_t vec_bytes, const int4 *__restrict__ units, const int *__restrict__ n_units,
+__global__ void __launch_bounds__(64) k_unit_place(int block0, CsrView a, UnitPlan p, int KB, int64_t vec_bytes, const int4 *__restrict__ units,
                                                    const int32_t *__restrict__ piece_start, const uint16_t *__restrict__ info,
                                                    const int *__restrict__ first_vec, const int32_t *__restrict__ win_ptr, const int *__restrict__ blk_ptr,
                                                    const uint16_t *__restrict__ vals, PlaceOut out)
@@ -558,12 +579,11 @@ __global__ void __launch_bounds__(64) k_unit_place(CsrView a, UnitPlan p, int KB
         p.V = VT;
         p.lv = 31 - __builtin_clz(VT);
     }
-    const int u = blockIdx.x, lane = threadIdx.x, V = p.V;
+    const int u = block0 + blockIdx.x, lane = threadIdx.x, V = p.V;
     if (u == 0) {
         for (int i = lane; i < out.n_tail; i += 64) out.tail[i] = 0;
         if (out.packed_ofs && lane == 0) out.packed_ofs[out.n_blocks] = a.nnz;
     }
-    if (u >= *n_units) return;
     if constexpr (KB32) KB = 32;
     const int4 un = units[u];
     bool bad = false;
@@ -753,12 +773,12 @@ __global__ void __launch_bounds__(64) k_unit_place(CsrView a, UnitPlan p, int KB
 // piece that begins inside it.  Its vectors, and the CSR position of each row's first entry in it, are in place.
 constexpr int kSharedPerWave = 2;  // units a wavefront looks at
 template <bool KB32>
-__global__ void __launch_bounds__(64) k_shared_blocks(int V, int KB, const int4 *__restrict__ units, const int *__restrict__ n_units, const int *__restrict__ first_vec,
+__global__ void __launch_bounds__(64) k_shared_blocks(int block0, int V, int KB, const int4 *__restrict__ units, const int *__restrict__ n_units, const int *__restrict__ first_vec,
                                                       const int32_t *__restrict__ win_ptr, const int *__restrict__ blk_ptr,
                                                       const uint16_t *__restrict__ vals, PlaceOut out)
 {
     const int lane = threadIdx.x, n = *n_units;
-    const int my_u = blockIdx.x * kSharedPerWave + lane;
+    const int my_u = (block0 + blockIdx.x) * kSharedPerWave + lane;
     int my_x = -1, my_s = 0, my_kb = 0;  // the block that lane's unit is the first to begin inside
     if (lane < kSharedPerWave && my_u < n) {
         const int4 un = units[my_u];

@@ -102,3 +102,25 @@ def test_convert_no_rows_in_a_used_scratch_buffer(fs, V):  # noqa: F811
     scratch = torch.full((need,), 0x7F, dtype=torch.uint8, device="cuda")
     fmt = fs.fs_convert(rp, none, None, 0, 9, torch_dtype=torch.float16, V=V, scratch=scratch)
     assert fmt.win_ptr_t().tolist() == [0] and fmt.nvec == 0 and fmt.n_blocks == 0 and fmt.c.n_items == 0
+
+
+def test_convert_more_units_than_one_launch_takes(fs):  # noqa: F811
+    """2^28 mostly empty rows in windows of one: more than 2^24 units.  A window is a row, so win_ptr is the row pointer,
+    every entry a vector of its own, in CSR order."""
+    import torch
+    M, K = (1 << 28) + 1000, 50000
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    rows = torch.randint(0, M, (3000,), generator=gen, device="cuda")
+    rows = torch.cat([rows, torch.tensor([0, 5, M - 1], device="cuda"), torch.full((1500,), M // 2, device="cuda")])  # one row is cut by columns
+    key = torch.unique(rows * K + torch.randint(0, K, rows.shape, generator=gen, device="cuda"))
+    ci = (key % K).to(torch.int32)
+    counts = torch.zeros(M + 1, dtype=torch.int32, device="cuda")
+    counts.index_add_(0, key // K + 1, torch.ones_like(ci))
+    rp = torch.cumsum(counts, 0, dtype=torch.int32)
+    del counts
+    fmt = fs.fs_convert(rp, ci, torch.ones_like(ci, dtype=torch.float16), M, K, V=1)
+    assert fmt.nvec == ci.numel() and torch.equal(fmt.win_ptr_t(), rp) and torch.equal(fmt.vec_col_t(), ci)
+    assert torch.equal(fmt.csr_to_slot_t(), torch.arange(ci.numel(), dtype=torch.int32, device="cuda"))
+    assert (fmt.vec_mask_t() == 1).all() and (fmt.vals_blk_t() == 1).all()
+    del fmt, rp
+    torch.cuda.empty_cache()
