@@ -539,20 +539,22 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     const int64_t n_groups = (W + up.group - 1) / up.group;
     const int64_t max_units = units_bound(up, W, nnz);
     const int *n_units = misc + 8;
-    k_units<false><<<grid_for(std::max<int64_t>(n_groups, 1), 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
+    k_units_count<<<grid_for(std::max<int64_t>(n_groups, 1), 64), kCountThreads, 0, s>>>(a, up, W, group_pos, misc);
     FS_LAUNCH_CHECK();
     if (W > 0) {
         if ((st = scan_exclusive(group_pos, n_groups, tmp, s, misc + 8)) != FS_OK) return st;
-        k_units<true><<<grid_for(n_groups, 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
+        k_units_fill<<<grid_for(n_groups, 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
         FS_LAUNCH_CHECK();
         if (nnz > kUnitEntries) {
-            st = launch_units(V <= 8 ? (max_units + 6) / 7 : max_units, [&](int first, unsigned grid) {
+            st = launch_units(V <= 8 ? (max_units + 6) / 7 : V <= 16 ? (max_units + 2) / 3 : max_units, [&](int first, unsigned grid) {
                 if (V <= 8) k_pieces<8><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
+                else if (V <= 16) k_pieces<16><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
                 else k_pieces<32><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
             });
             if (st != FS_OK) return st;
             st = launch_units((max_units + kExactPerWave - 1) / kExactPerWave, [&](int first, unsigned grid) {
                 if (V <= 8) k_pieces_exact<8><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
+                else if (V <= 16) k_pieces_exact<16><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
                 else k_pieces_exact<32><<<grid, 64, 0, s>>>(first, a, up, units, n_units, pieces, redo, misc);
             });
             if (st != FS_OK) return st;

@@ -95,8 +95,12 @@ fs_status launch_units(int64_t n, Launch launch)
     return FS_OK;
 }
 
-// Pieces of window w (1: it fits a unit).
-__device__ __forceinline__ int window_pieces(const CsrView &a, const UnitPlan &p, int64_t w, int64_t &entries)
+// Pieces of a window of e entries and so many samples (1: it fits a unit).
+__device__ __forceinline__ int pieces_of(const UnitPlan &p, int64_t e, int64_t samples)
+{
+    return e <= kUnitEntries ? 1 : (int)max((samples + p.per - 1) / p.per, (int64_t)1);
+}
+__device__ __forceinline__ int window_pieces(const CsrView &a, const UnitPlan &p, int64_t w)
 {
     int64_t e = 0, samples = 0;
     for (int r = 0; r < p.V && w * p.V + r < a.M; r++) {
@@ -105,50 +109,85 @@ __device__ __forceinline__ int window_pieces(const CsrView &a, const UnitPlan &p
         e += hi - lo;
         samples += (hi - lo) / p.stride;
     }
-    entries = e;
-    return e <= kUnitEntries ? 1 : (int)max((samples + p.per - 1) / p.per, (int64_t)1);
+    return pieces_of(p, e, samples);
 }
 
-// One thread per group: how many units it becomes (FILL = false, which also checks the row pointers), or their records
-// {first window, windows, piece, pieces of the window} from position pos[group] on.
-template <bool FILL>
-__global__ void __launch_bounds__(256) k_units(CsrView a, UnitPlan p, int64_t W, int *__restrict__ pos, int4 *__restrict__ units, int *__restrict__ redo, int *__restrict__ err)
+// One thread per group: how many units it becomes, and a check of its row pointers.  Those of the workgroup's 64 groups
+// pass through LDS, so that they are read side by side (16 M rows: 155 us read by each thread for itself, now 36).
+constexpr int kCountThreads = 256;  // that read; the first 64 of them count
+__global__ void __launch_bounds__(kCountThreads) k_units_count(CsrView a, UnitPlan p, int64_t W, int *__restrict__ pos, int *__restrict__ err)
 {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int kMost = 64 * kUnitRows + 1;
+    __shared__ int32_t rp[kMost + kMost / 32 + 1];
+    auto at = [](int i) -> int { return i + (i >> 5); };  // groups are a power of two apart: spread them over the banks
+    const int64_t g0 = (int64_t)blockIdx.x * 64, g = g0 + threadIdx.x;
+    const int rows = p.group * p.V;  // of a group
+    const int64_t row0 = g0 * rows, left = a.M - row0;
+    const int here = (int)min((int64_t)64 * rows, left);
+    for (int i0 = threadIdx.x; i0 <= here; i0 += 4 * kCountThreads) {
+        int32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) v[k] = a.rowptr[row0 + min(i0 + k * kCountThreads, here)];
+#pragma unroll
+        for (int k = 0; k < 4; k++) rp[at(min(i0 + k * kCountThreads, here))] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
     const int64_t w0 = g * p.group, w1 = min(w0 + p.group, W);
-    if (!FILL && W == 0 && g == 0 && a.rowptr[0] != 0) atomicOr(err, 1);
-    if (w0 >= W || (FILL && (*err & 1))) return;
-    if constexpr (!FILL) {
-        bool bad = false;
-        int32_t last = a.rowptr[w0 * p.V];
-        if (w0 == 0 && last != 0) bad = true;
-        for (int64_t i = w0 * p.V; i < min(w1 * p.V, a.M); i++) {
-            const int32_t next = a.rowptr[i + 1];
-            if (last < 0 || next < last) bad = true;
+    if (W == 0 && g == 0 && rp[0] != 0) atomicOr(err, 1);
+    if (w0 >= W) return;
+    int i = threadIdx.x * rows;
+    int32_t last = rp[at(i)];
+    bool bad = last < 0 || (w0 == 0 && last != 0);
+    int64_t total = 0, n = 0;
+    for (int64_t w = w0; w < w1; w++) {
+        int64_t e = 0, samples = 0;
+        for (int r = 0; r < p.V && i < here; r++) {
+            const int32_t next = rp[at(++i)];
+            if (next < last) bad = true;
+            const int32_t lo = min(max(last, 0), a.nnz), len = min(max(next, lo), a.nnz) - lo;  // as row_range has them
+            e += len;
+            samples += len / p.stride;
             last = next;
         }
-        if (last > a.nnz || (w1 == W && last != a.nnz)) bad = true;
-        if (bad) atomicOr(err, 1);
-    }
-    int64_t total = 0, n = 0, e;
-    for (int64_t w = w0; w < w1; w++) {
-        n += window_pieces(a, p, w, e);
         total += e;
+        n += pieces_of(p, e, samples);
     }
-    if (total <= kUnitEntries) {
-        if constexpr (FILL) units[pos[g]] = make_int4((int)w0, (int)(w1 - w0), 0, 1);
-        else pos[g] = 1;
-        return;
+    if (last > a.nnz || (w1 == W && last != a.nnz)) bad = true;
+    if (bad) atomicOr(err, 1);
+    pos[g] = total <= kUnitEntries ? 1 : (int)n;
+}
+
+// One thread per group again: the records {first window, windows, piece, pieces of the window} of its units, from position
+// pos[group] on (pos = exclusive scan of the counts).  The many records of a hub window are written by the whole
+// wavefront (a row of 5 M entries, 16 k records: 346 us by one thread, now 10).
+__global__ void __launch_bounds__(256) k_units_fill(CsrView a, UnitPlan p, int64_t W, const int *__restrict__ pos, int4 *__restrict__ units, int *__restrict__ redo, const int *__restrict__ err)
+{
+    if (*err & 1) return;
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t w0 = g * p.group, w1 = min(w0 + p.group, W);
+    const int lane = threadIdx.x & 63;
+    int u = 0, n = 0;
+    if (w0 < W) {
+        u = pos[g];
+        n = pos[g + 1] - u;
     }
-    if constexpr (!FILL) {
-        pos[g] = (int)n;
-    } else {
-        int u = pos[g];
-        for (int64_t w = w0; w < w1; w++) {
-            const int np = window_pieces(a, p, w, e);
+    if (n == 1) units[u] = make_int4((int)w0, (int)(w1 - w0), 0, 1);  // it fits (or is one window that does)
+    for (int i = 0; i < p.group && __any(n > 1); i++) {
+        const int64_t w = w0 + i;
+        int np = 0;
+        if (n > 1 && w < w1) {
+            np = window_pieces(a, p, w);
             redo[w] = 0;
-            for (int k = 0; k < np; k++) units[u++] = make_int4((int)w, 1, k, np);
         }
+        constexpr int kFew = 16;
+        if (np <= kFew)
+            for (int k = 0; k < np; k++) units[u + k] = make_int4((int)w, 1, k, np);
+        for (uint64_t todo = __ballot(np > kFew); todo; todo &= todo - 1) {
+            const int l = __builtin_ctzll(todo), first = __shfl(u, l, 64), many = __shfl(np, l, 64), of = __shfl((int)w, l, 64);
+            for (int k = lane; k < many; k += 64) units[first + k] = make_int4(of, 1, k, many);
+        }
+        u += np;
     }
 }
 
