@@ -22,6 +22,7 @@
 // costs 2-5 % there and is left out.
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "fs_common.h"
 #include "fs_tile.h"
@@ -80,6 +81,10 @@ __device__ __forceinline__ void fs_store_scores(const fs_f4 (&acc)[2], uint32_t 
     }
 }
 
+// Bytes between rows; BIG takes any pitch, up to rows of 4 GiB and more.
+template <bool BIG>
+using fs_pitch = std::conditional_t<BIG, uint64_t, uint32_t>;
+
 // Which block slots a wavefront takes; false: none.  With `items`, those of a work item, in the launch order of
 // SpMM: parts of hub windows by column, placed per XCD, so that they share rows of Y in L2 (R-MAT of 262 k rows,
 // d = 128: 132 -> 105 us).  Without, G consecutive slots straight from the block table, whatever windows they
@@ -129,7 +134,7 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
     const int j = lane & 15, g = lane >> 4;
     const unsigned char *Xb = reinterpret_cast<const unsigned char *>(X);
     const unsigned char *Yb = reinterpret_cast<const unsigned char *>(Y);
-    const uint32_t ldx2 = (uint32_t)ldx * 2, ldy2 = (uint32_t)ldy * 2;  // bytes between rows
+    const fs_pitch<BIG> ldx2 = (fs_pitch<BIG>)ldx * 2, ldy2 = (fs_pitch<BIG>)ldy * 2;  // bytes between rows
 
     // descriptors of the unit's blocks (at most 64), one per lane
     const int4 my_desc = blk_desc[first + min(lane, nblk - 1)];
@@ -295,7 +300,7 @@ k_sddmm_short(const int4 *__restrict__ items, int n_items, int slice, int n_swz,
     const int j = lane & 15, g = lane >> 4;
     const unsigned char *Xb = reinterpret_cast<const unsigned char *>(X);
     const unsigned char *Yb = reinterpret_cast<const unsigned char *>(Y);
-    const uint32_t ldx2 = (uint32_t)ldx * 2, ldy2 = (uint32_t)ldy * 2;  // bytes between rows
+    const fs_pitch<BIG> ldx2 = (fs_pitch<BIG>)ldx * 2, ldy2 = (fs_pitch<BIG>)ldy * 2;  // bytes between rows
 
     // descriptors of the unit's blocks (at most 64), one per lane
     const int4 my_desc = blk_desc[first + min(lane, nblk - 1)];
@@ -371,6 +376,7 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
     // is the whole time (R-MAT of 8 k rows, 3 k blocks, d = 248: 14.1 us with four slots, 8.5 us with one).
     const int4 *items = ordered ? (const int4 *)f->items_by_cost : nullptr;
     int G = std::min(std::max(n_blocks / 2048, 1), 4);
+    if (n_blocks >= 1 << 27) G = 16;  // (a launch has fewer than 2^32 threads)
 #ifdef FS_TUNING_ENV  // tuning builds only (-DFS_TUNING_ENV): the shipped library reads no environment
     if (const char *e = getenv("FS_SDDMM_G")) G = std::min(std::max(atoi(e), 1), 64);
 #endif

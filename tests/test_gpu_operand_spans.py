@@ -1,5 +1,6 @@
 """Dense operands whose rows lie far apart, where the byte offset of a row changes its kind: from 2 GiB on it no longer fits
-a signed 32-bit number.  Exact inputs (every product and partial sum is a multiple of 1/2 far below 2^24), bit for bit."""
+a signed 32-bit number, from 4 GiB on no 32-bit number at all (the kernels then take 64-bit addresses), and a pitch of 4 GiB
+does not fit one either.  Exact inputs (every product and partial sum is a multiple of 1/2 far below 2^24), bit for bit."""
 import numpy as np
 import pytest
 
@@ -22,7 +23,7 @@ def far_rows(t, pitch):
 
 @pytest.mark.parametrize("d", [32, 64, 128, 264])
 @pytest.mark.parametrize("which", ["X", "Y"])
-@pytest.mark.parametrize("pitch", [16384])  # elements: 2.3 GB
+@pytest.mark.parametrize("pitch", [16384, 32768])  # elements: 2.3 GB and 4.6 GB
 def test_sddmm_far_rows(fs, pitch, which, d):  # noqa: F811
     import torch
     M, K = (FAR, 300) if which == "X" else (300, FAR)
@@ -43,6 +44,27 @@ def test_sddmm_far_rows(fs, pitch, which, d):  # noqa: F811
     same_bits(from_dev_bits(fs.fs_blk_to_csr(fmt, fs.fs_sddmm(fmt, Xd, Yd))), want, "fs_sddmm")
     same_bits(from_dev_bits(fs.fs_sddmm(fmt, Xd, Yd, blocked=False)), want, "fs_sddmm, CSR order")
     del Xd, Yd
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("d", [32, 64, 128, 264])
+@pytest.mark.parametrize("which", ["X", "Y"])
+def test_sddmm_rows_of_4_gib(fs, which, d):  # noqa: F811
+    import torch
+    M, K = (3, 40) if which == "X" else (40, 3)
+    A = random_csr(M, K, 0.5, "f16", seed=80)
+    rp, ci, _ = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, None, M, K, torch_dtype=torch.float16)
+    X, Y = (torch.randint(-2, 3, (n, d), device="cuda").half() for n in (M, K))
+    want = fs.fs_sddmm(fmt, X, Y)
+    pitch = (1 << 31) + 8
+    base = torch.empty(2 * pitch + d, dtype=torch.float16, device="cuda")
+    far = torch.as_strided(base, (3, d), (pitch, 1))
+    far.copy_(X if which == "X" else Y)
+    base[d:2 * d] = float("nan")  # where a pitch cut to 32 bits would look
+    got = fs.fs_sddmm(fmt, far, Y) if which == "X" else fs.fs_sddmm(fmt, X, far)
+    same_bits(from_dev_bits(got), from_dev_bits(want), "fs_sddmm")
+    del base, far
     torch.cuda.empty_cache()
 
 
