@@ -128,7 +128,11 @@ typedef struct fs_format {
     size_t arena_used;            /* bytes of the arena actually occupied */
 } fs_format;
 
-/* Library version: major*10000 + minor*100 + patch. */
+/*
+ * Library version: major*10000 + minor*100 + patch.  The layout of fs_format belongs to the version: fs_convert writes the
+ * struct whole, so a program must only use a library whose fs_version() is the FS_VERSION it was compiled with.
+ */
+#define FS_VERSION 400
 int fs_version(void);
 
 /* Static string for a status code (never NULL). */

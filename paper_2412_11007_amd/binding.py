@@ -21,6 +21,7 @@ _lib = None
 _native = None  # the _fs_torch module, once load_library has given it the library's entry points
 
 FS_F16, FS_BF16 = 0, 1
+_VERSION = 400  # of the header that _FsFormatStruct mirrors
 
 
 class FsError(RuntimeError):
@@ -68,6 +69,8 @@ def load_library():
     szp = ctypes.POINTER(ctypes.c_size_t)
     lib.fs_version.restype = ctypes.c_int
     lib.fs_version.argtypes = []
+    if lib.fs_version() != _VERSION:  # another layout of fs_format, which fs_convert would write past the end of this one
+        raise ImportError("%s has version %d, expected %d: build it again" % (_LIB_PATH, lib.fs_version(), _VERSION))
     lib.fs_status_string.restype = ctypes.c_char_p
     lib.fs_status_string.argtypes = [ctypes.c_int]
     lib.fs_format_bytes.restype = ctypes.c_int

@@ -791,7 +791,7 @@ extern "C" fs_status fs_pack_values(const fs_format *fmt, const void *d_vals_blk
     return FS_OK;
 }
 
-extern "C" int fs_version(void) { return 300; }  // 0.3.0: fused attention, CSR of the transposed matrix
+extern "C" int fs_version(void) { return FS_VERSION; }
 
 extern "C" const char *fs_status_string(fs_status s)
 {

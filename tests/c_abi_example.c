@@ -183,6 +183,7 @@ int main(void)
             }
         }
     }
+    if (fs_version() != FS_VERSION) { printf("library version %d, header version %d\n", fs_version(), FS_VERSION); return 1; }
     printf("flashsparse %d: M=%d K=%d nnz=%d nvec=%lld items=%lld cut windows=%lld: %s\n", fs_version(), M, K, nnz,
            (long long)fmt.nvec, (long long)fmt.n_items, (long long)fmt.n_split_windows, bad ? "MISMATCH" : "OK");
     return bad ? 1 : 0;

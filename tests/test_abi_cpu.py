@@ -60,6 +60,20 @@ def test_status_strings_and_version(fs):
     assert fs.fs_status_string(99) == "unknown status"
 
 
+def test_version_of_header_library_and_binding(fs, tmp_path):
+    """The layout of fs_format belongs to the version: a change of one asks for a change of the other, here."""
+    from paper_2412_11007_amd import binding
+    assert int(re.search(r"#define FS_VERSION (\d+)", open(HEADER).read()).group(1)) == fs.fs_version() == binding._VERSION == 400
+    assert ctypes.sizeof(binding._FsFormatStruct) == 216
+    # a library of another version is refused before it can write a format
+    src, other = tmp_path / "other.c", tmp_path / "libother.so"
+    src.write_text("int fs_version(void) { return 300; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", str(src), "-o", str(other)], check=True)
+    res = subprocess.run([sys.executable, "-c", "import paper_2412_11007_amd as fs; fs.load_library()"], cwd=ROOT, text=True,
+                         capture_output=True, env=dict(os.environ, FLASHSPARSE_LIB=str(other)))
+    assert res.returncode != 0 and "ImportError" in res.stderr and "version 300" in res.stderr
+
+
 def test_format_bytes_bounds(fs):
     a, s = fs.fs_format_bytes(65536, 1000000, 8, 32, 0)
     # values (2*V bytes) + three int32 arrays per stored entry, at least
