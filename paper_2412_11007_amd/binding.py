@@ -163,13 +163,15 @@ def _dtype_code(torch_dtype) -> int:
 # Small calls are bound by the host (a launch takes about 3 us, the kernel of a 4096-row SpMM 4.6 us), so the way to the
 # C call makes no object it can do without: a stream's handle comes straight from torch (0.1 us; through a
 # torch.cuda.Stream 2.8 us).
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # a torch without a GPU backend has neither: the
+_current_device = getattr(torch._C, "_cuda_getDevice", None)        # package imports, and the first call raises
 
 
 def _stream_ptr(stream) -> int:
     """Handle of ``stream``, or of the current device's current stream."""
-    return _raw_stream(_current_device()) if stream is None else int(stream.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    return _raw_stream(_current_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
 
 
 def _temporary(nbytes, device, stream):

@@ -74,6 +74,13 @@ def test_version_of_header_library_and_binding(fs, tmp_path):
     assert res.returncode != 0 and "ImportError" in res.stderr and "version 300" in res.stderr
 
 
+def test_imports_with_a_torch_that_has_no_gpu_backend():
+    prog = ("import torch\nfor n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'): delattr(torch._C, n)\n"
+            "import paper_2412_11007_amd as fs\nprint(fs.fs_format_bytes(10, 10)[0] > 0)")
+    res = subprocess.run([sys.executable, "-c", prog], cwd=ROOT, text=True, capture_output=True)
+    assert res.returncode == 0 and res.stdout.split() == ["True"], res.stderr
+
+
 def test_format_bytes_bounds(fs):
     a, s = fs.fs_format_bytes(65536, 1000000, 8, 32, 0)
     # values (2*V bytes) + three int32 arrays per stored entry, at least
