@@ -103,7 +103,7 @@ def test_transpose_scratch_size(fs):
     lib = fs.load_library()
     need = ctypes.c_size_t(0)
     assert lib.fs_csr_transpose_bytes(1000, 2000, 1000000, ctypes.byref(need)) == 0
-    # two key buffers and one payload buffer of nnz int32, plus 256 counters per 2048 entries
+    # two key buffers and one payload buffer of nnz int32, plus 512 counters per 2048 entries
     assert 12 * 1000000 <= need.value <= 14 * 1000000
     assert lib.fs_csr_transpose_bytes(0, 0, 0, ctypes.byref(need)) == 0 and need.value > 0
     assert lib.fs_csr_transpose_bytes(1, 1, -1, ctypes.byref(need)) == 1

@@ -56,6 +56,18 @@ def test_transpose_digit_widths(fs, K):
     check_transpose(fs, csr_from_coo(M, K, key // K, key % K, "u01", "f16", rng))
 
 
+@pytest.mark.parametrize("K", [1 << 24, (1 << 24) + 1, 1 << 27, (1 << 27) + 1])
+def test_transpose_three_wide_passes(fs, K):
+    """25 to 27 column bits: three passes on 9-bit digits, and the 8-bit ones on either side (three and four)."""
+    import torch
+    rng = np.random.default_rng(K)
+    M = 300
+    key = np.unique(np.concatenate([rng.integers(0, M * K, 9000), np.arange(0, M, 3) * K, np.arange(1, M, 3) * K + K - 1,
+                                    np.arange(M) * K + (K >> 9)]))  # (a column most rows share: equal keys over several tiles)
+    check_transpose(fs, csr_from_coo(M, K, key // K, key % K, "u01", "f16", rng))
+    torch.cuda.empty_cache()
+
+
 def test_transpose_hub_columns(fs):
     """A few columns referenced by most rows: equal keys span many tiles, where stability matters."""
     rng = np.random.default_rng(21)
