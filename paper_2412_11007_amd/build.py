@@ -51,9 +51,10 @@ def build_calls() -> str:
     import sysconfig
     import torch
     from torch.utils import cpp_extension
-    includes = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
-    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
-         + ["-I" + i for i in includes] + [CALLS_SRC, "-o", CALLS_LIB] + ["-L" + d for d in cpp_extension.library_paths()]
+    foreign = [a for i in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]] for a in ("-isystem", i)]
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-Werror",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + os.path.join(ROOT, "include")]
+         + foreign + [CALLS_SRC, "-o", CALLS_LIB] + ["-L" + d for d in cpp_extension.library_paths()]
          + ["-lc10", "-ltorch_cpu", "-ltorch_python"], False)
     return CALLS_LIB
 
