@@ -2,8 +2,9 @@
 //
 // The paper states only that the translation runs as GPU kernels (Section 3.1)
 // and what it must produce (Section 3.5); the algorithm below is this
-// library's own.  It needs no sort and no atomics, so the output is
-// deterministic and bit-identical to a sequential construction:
+// library's own.  The format's arrays need no sort and no atomics on memory (LDS ones
+// only where the order of additions cannot show), so they are deterministic and
+// bit-identical to a sequential construction; the work list is sorted, stably:
 //
 //   1. units  at most 512 stored entries each, one wavefront's work: a few windows, one window, or a range of
 //             columns of a hub window (fs_units.h).
@@ -17,8 +18,8 @@
 //             vectors, shorter ones are packed whole into items of about four blocks (boundary candidates, scan,
 //             compact), and the items are put in launch order.
 //
-// A small matrix is bound by the number of launches, about 5 us each, and by the one time the host waits for the
-// sizes (R-MAT of 65 k rows, 0.9 M entries: 35 launches, 292 us; now 19 and 222 us).
+// A small matrix is bound by the number of launches, about 5 us each, and by the two times the host waits,
+// for the sizes and at the end (R-MAT of 65 k rows, 0.9 M entries: 35 launches, 292 us; now 19 and 222 us).
 #include <algorithm>
 #include <cstdlib>
 
@@ -434,7 +435,7 @@ ScratchPlan plan_scratch(int64_t nnz, int64_t W, int V, int KB)
     s.upos = o; o += fs_align_up(ib + 1, 64);
     s.hist = o; o += fs_align_up((size_t)kDigits * std::max<size_t>((ib + kSortTile - 1) / kSortTile,
                                                                      (std::min<size_t>(ib, 65536) + kSortTileSmall - 1) / kSortTileSmall) + 1, 64);  // digit counts of the work-list sort
-    s.total_ints = std::max(o, (size_t)nnz);  // (callers have counted on four bytes per entry)
+    s.total_ints = std::max(o, (size_t)nnz);  // (never less than the four bytes per entry of earlier layouts)
     return s;
 }
 

@@ -17,7 +17,7 @@
 // vector-memory unit then takes a cycle per lane: 64-70 cycles per wave-wide load, 9 TB/s over the chip, however
 // often the rows hit a cache.  With neighbouring lanes on one row a load takes 18-24 cycles.  So for d > 32
 // the rows are gathered row by row like those of SpMM and turned into operand layout in LDS (R-MAT of 65 k rows,
-// d = 128: 38 -> 23.5 us; lognormal graph of 262 k rows, d = 256: 560 -> 421 us, 6.4 TB/s of rows that miss the
+// d = 128: 38 -> 20 us; lognormal graph of 262 k rows, d = 256: 560 -> 421 us, 6.4 TB/s of rows that miss the
 // L2s).  For d <= 32 a row is half a cache line at most, the loads are few and the L2s set the time; the detour
 // costs 2-5 % there and is left out.
 #include <algorithm>
@@ -87,7 +87,7 @@ using fs_pitch = std::conditional_t<BIG, uint64_t, uint32_t>;
 
 // Which block slots a wavefront takes; false: none.  With `items`, those of a work item, in the launch order of
 // SpMM: parts of hub windows by column, placed per XCD, so that they share rows of Y in L2 (R-MAT of 262 k rows,
-// d = 128: 132 -> 105 us).  Without, G consecutive slots straight from the block table, whatever windows they
+// d = 128: 108 -> 75 us).  Without, G consecutive slots straight from the block table, whatever windows they
 // belong to -- a block of scores depends on nothing but its own descriptor, and the item record would be one
 // more dependent load.  One wavefront per workgroup: wavefronts share nothing, and a workgroup keeps its slots
 // until its slowest wavefront is done.
@@ -287,7 +287,7 @@ k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n
 template <int DT, int V, bool BIG, bool CSR>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CSR ? 5 : 6)))
 k_sddmm_short(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n_blocks, int G, const int4 *__restrict__ blk_desc,
-        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ row_bits, int,
+        const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ row_bits, int /* as k_sddmm, which the launch shares its arguments with */,
         const uint16_t *__restrict__ X, int64_t ldx, const uint16_t *__restrict__ Y, int64_t ldy, int d,
         uint16_t *__restrict__ out, int64_t M, uint16_t *__restrict__ out_csr, const int32_t *__restrict__ row_base)
 {

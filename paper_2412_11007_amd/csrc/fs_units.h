@@ -280,78 +280,78 @@ __global__ void __launch_bounds__(64) k_pieces_exact(int block0, CsrView a, Unit
     const int4 my_un = units[min(my_u, n - 1)];
     uint64_t todo = __ballot(lane < kExactPerWave && my_u < n && my_un.w > 1 && redo[my_un.x]);
     for (; todo; todo &= todo - 1) {
-    const int k = __builtin_ctzll(todo), u = u0 + k;
-    const int4 un = make_int4(__shfl(my_un.x, k, 64), 1, __shfl(my_un.z, k, 64), __shfl(my_un.w, k, 64));
-    const int64_t row0 = (int64_t)un.x * p.V;
-    int32_t lo = 0, hi = 0;
-    if (lane < p.V && row0 + lane < a.M) row_range(a, row0 + lane, lo, hi);
-    if (un.z == 0 && lane < p.V) start[(int64_t)u * p.V + lane] = lo;
-    const int mine = (hi - lo) / p.stride;  // samples of row `lane`
-    const int upto = wave_inclusive_scan(mine);
-    for (int s0 = 0; s0 < p.per; s0 += 64) {
-        const int s = un.z * p.per + s0 + lane;  // this lane's sample
-        int row = -1, idx = 0;
-        for (int r = 0; r < p.V; r++) {
-            const int before = __shfl(upto - mine, r, 64), n = __shfl(mine, r, 64);
-            if (s >= before && s < before + n) { row = r; idx = s - before; }
-        }
-        const bool live = row >= 0 && s0 + lane < p.per;
-        const int32_t lo_s = __shfl(lo, max(row, 0), 64);
-        const int32_t c = live ? a.colidx[lo_s + (idx + 1) * p.stride - 1] : 0;
-        int rank = idx, below[ROWS];
-#pragma unroll
-        for (int r0 = 0; r0 < ROWS; r0 += G) {
-            int32_t base[G];
-            int m[G], most = 0;
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-                const int r = r0 + g;
-                m[g] = __shfl(mine, min(r, 63), 64);
-                base[g] = __shfl(lo, min(r, 63), 64) + p.stride - 1;
-                if (!live || r == row || r >= p.V) m[g] = 0;
-                below[r] = 0;
-                most = max(most, m[g]);
+        const int k = __builtin_ctzll(todo), u = u0 + k;
+        const int4 un = make_int4(__shfl(my_un.x, k, 64), 1, __shfl(my_un.z, k, 64), __shfl(my_un.w, k, 64));
+        const int64_t row0 = (int64_t)un.x * p.V;
+        int32_t lo = 0, hi = 0;
+        if (lane < p.V && row0 + lane < a.M) row_range(a, row0 + lane, lo, hi);
+        if (un.z == 0 && lane < p.V) start[(int64_t)u * p.V + lane] = lo;
+        const int mine = (hi - lo) / p.stride;  // samples of row `lane`
+        const int upto = wave_inclusive_scan(mine);
+        for (int s0 = 0; s0 < p.per; s0 += 64) {
+            const int s = un.z * p.per + s0 + lane;  // this lane's sample
+            int row = -1, idx = 0;
+            for (int r = 0; r < p.V; r++) {
+                const int before = __shfl(upto - mine, r, 64), n = __shfl(mine, r, 64);
+                if (s >= before && s < before + n) { row = r; idx = s - before; }
             }
-            for (; __any(most > 0); most >>= 1) {  // halves until every row's samples are told apart
-#pragma unroll
+            const bool live = row >= 0 && s0 + lane < p.per;
+            const int32_t lo_s = __shfl(lo, max(row, 0), 64);
+            const int32_t c = live ? a.colidx[lo_s + (idx + 1) * p.stride - 1] : 0;
+            int rank = idx, below[ROWS];
+    #pragma unroll
+            for (int r0 = 0; r0 < ROWS; r0 += G) {
+                int32_t base[G];
+                int m[G], most = 0;
+    #pragma unroll
                 for (int g = 0; g < G; g++) {
-                    const int half = m[g] >> 1;
-                    const int32_t v = m[g] > 0 ? a.colidx[base[g] + (below[r0 + g] + half) * p.stride] : 0;
-                    const bool less = m[g] > 0 && (v < c || (v == c && r0 + g < row));
-                    below[r0 + g] += less ? half + 1 : 0;
-                    m[g] = less ? m[g] - half - 1 : half;
+                    const int r = r0 + g;
+                    m[g] = __shfl(mine, min(r, 63), 64);
+                    base[g] = __shfl(lo, min(r, 63), 64) + p.stride - 1;
+                    if (!live || r == row || r >= p.V) m[g] = 0;
+                    below[r] = 0;
+                    most = max(most, m[g]);
                 }
+                for (; __any(most > 0); most >>= 1) {  // halves until every row's samples are told apart
+    #pragma unroll
+                    for (int g = 0; g < G; g++) {
+                        const int half = m[g] >> 1;
+                        const int32_t v = m[g] > 0 ? a.colidx[base[g] + (below[r0 + g] + half) * p.stride] : 0;
+                        const bool less = m[g] > 0 && (v < c || (v == c && r0 + g < row));
+                        below[r0 + g] += less ? half + 1 : 0;
+                        m[g] = less ? m[g] - half - 1 : half;
+                    }
+                }
+    #pragma unroll
+                for (int g = 0; g < G; g++) rank += below[r0 + g];
             }
-#pragma unroll
-            for (int g = 0; g < G; g++) rank += below[r0 + g];
-        }
-        const int q = rank / p.per;
-        const bool starts = live && rank == q * p.per && q > 0 && q < un.w;
-        if (!__any(starts)) continue;
-#pragma unroll
-        for (int r0 = 0; r0 < ROWS; r0 += G) {
-            int32_t at[G], end[G];
-#pragma unroll
-            for (int g = 0; g < G; g++) {
-                const int r = min(r0 + g, 63);
-                const int n = r == row ? idx : below[r0 + g];  // the last of them may be the column itself (a row before `row`)
-                at[g] = __shfl(lo, r, 64) + max(n * p.stride - 1, 0);
-                end[g] = min(at[g] + p.stride + 1, __shfl(hi, r, 64));
-                if (!starts || r0 + g >= p.V) end[g] = at[g];
-            }
-            for (int step = 1; step < 2 * p.stride; step <<= 1) {
-#pragma unroll
+            const int q = rank / p.per;
+            const bool starts = live && rank == q * p.per && q > 0 && q < un.w;
+            if (!__any(starts)) continue;
+    #pragma unroll
+            for (int r0 = 0; r0 < ROWS; r0 += G) {
+                int32_t at[G], end[G];
+    #pragma unroll
                 for (int g = 0; g < G; g++) {
-                    const int32_t mid = at[g] + ((end[g] - at[g]) >> 1);
-                    const bool some = at[g] < end[g], less = some && a.colidx[mid] < c;
-                    if (less) at[g] = mid + 1; else if (some) end[g] = mid;
+                    const int r = min(r0 + g, 63);
+                    const int n = r == row ? idx : below[r0 + g];  // the last of them may be the column itself (a row before `row`)
+                    at[g] = __shfl(lo, r, 64) + max(n * p.stride - 1, 0);
+                    end[g] = min(at[g] + p.stride + 1, __shfl(hi, r, 64));
+                    if (!starts || r0 + g >= p.V) end[g] = at[g];
                 }
+                for (int step = 1; step < 2 * p.stride; step <<= 1) {
+    #pragma unroll
+                    for (int g = 0; g < G; g++) {
+                        const int32_t mid = at[g] + ((end[g] - at[g]) >> 1);
+                        const bool some = at[g] < end[g], less = some && a.colidx[mid] < c;
+                        if (less) at[g] = mid + 1; else if (some) end[g] = mid;
+                    }
+                }
+    #pragma unroll
+                for (int g = 0; g < G; g++)
+                    if (starts && r0 + g < p.V) start[(int64_t)(u - un.z + q) * p.V + r0 + g] = at[g];
             }
-#pragma unroll
-            for (int g = 0; g < G; g++)
-                if (starts && r0 + g < p.V) start[(int64_t)(u - un.z + q) * p.V + r0 + g] = at[g];
         }
-    }
     }
 }
 
@@ -402,7 +402,7 @@ __device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &
 // the next.  Every lane makes the same number of consecutive outputs: it finds where they begin in the two halves
 // with one binary search and then takes the smaller of two elements at a time -- a third of the instructions of a
 // search per element -- and when all lanes have theirs in registers they go back to the same place, so that LDS holds
-// the unit once and 26 wavefronts share a CU.  An element is {pair, column, place} in one 64-bit number, so that one
+// the unit once and 28 wavefronts share a CU.  An element is {pair, column, place} in one 64-bit number, so that one
 // comparison orders it; an element larger than all ends each half, so that a merge needs no bounds.
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_unit_rank(int block0, CsrView a, UnitPlan p, int64_t K, const int4 *__restrict__ units, const int *__restrict__ n_units,
                                                   const int32_t *__restrict__ piece_start, uint16_t *__restrict__ info, int *__restrict__ count,
@@ -832,35 +832,35 @@ __global__ void __launch_bounds__(64) k_shared_blocks(int block0, int V, int KB,
         }
     }
     for (uint64_t todo = __ballot(my_x >= 0); todo; todo &= todo - 1) {
-    const int k = __builtin_ctzll(todo);
-    const int xb = __shfl(my_x, k, 64), s = __shfl(my_s, k, 64), kb = __shfl(my_kb, k, 64);
-    const uint32_t m = lane < kb ? out.vec_mask[s + lane] : 0u;
-    int32_t base = lane < V ? out.row_base[(int64_t)xb * V + lane] : 0;
-    int32_t packed = out.packed_vals ? out.packed_ofs[xb] : 0;
-    const uint64_t below = (1ull << lane) - 1;
-    for (int r0 = 0; r0 < V; r0 += 8) {  // eight rows' loads together
-        uint16_t v[8];
-        uint64_t row[8];
-#pragma unroll
-        for (int g = 0; g < 8; g++) {
-            const int r = r0 + g;
-            const bool has = r < V && ((m >> r) & 1u);
-            row[g] = __ballot(has);
-            const int32_t q = __shfl(base, min(r, 63), 64) + __popcll(row[g] & below);
-            v[g] = has && vals ? vals[q] : (uint16_t)0;
-        }
-#pragma unroll
-        for (int g = 0; g < 8; g++) {
-            const int r = r0 + g;
-            if (r >= V) break;
-            if (KB32 && lane == 0) out.row_bits[(int64_t)xb * V + r] = (uint32_t)row[g];
-            if (vals && lane < kb) {
-                out.vals_blk[(int64_t)V * s + r * kb + lane] = v[g];
-                if (out.packed_vals && ((m >> r) & 1u)) out.packed_vals[packed + __popcll(row[g] & below)] = v[g];
+        const int k = __builtin_ctzll(todo);
+        const int xb = __shfl(my_x, k, 64), s = __shfl(my_s, k, 64), kb = __shfl(my_kb, k, 64);
+        const uint32_t m = lane < kb ? out.vec_mask[s + lane] : 0u;
+        int32_t base = lane < V ? out.row_base[(int64_t)xb * V + lane] : 0;
+        int32_t packed = out.packed_vals ? out.packed_ofs[xb] : 0;
+        const uint64_t below = (1ull << lane) - 1;
+        for (int r0 = 0; r0 < V; r0 += 8) {  // eight rows' loads together
+            uint16_t v[8];
+            uint64_t row[8];
+    #pragma unroll
+            for (int g = 0; g < 8; g++) {
+                const int r = r0 + g;
+                const bool has = r < V && ((m >> r) & 1u);
+                row[g] = __ballot(has);
+                const int32_t q = __shfl(base, min(r, 63), 64) + __popcll(row[g] & below);
+                v[g] = has && vals ? vals[q] : (uint16_t)0;
             }
-            packed += __popcll(row[g]);
+    #pragma unroll
+            for (int g = 0; g < 8; g++) {
+                const int r = r0 + g;
+                if (r >= V) break;
+                if (KB32 && lane == 0) out.row_bits[(int64_t)xb * V + r] = (uint32_t)row[g];
+                if (vals && lane < kb) {
+                    out.vals_blk[(int64_t)V * s + r * kb + lane] = v[g];
+                    if (out.packed_vals && ((m >> r) & 1u)) out.packed_vals[packed + __popcll(row[g] & below)] = v[g];
+                }
+                packed += __popcll(row[g]);
+            }
         }
-    }
     }
 }
 
