@@ -19,7 +19,7 @@
 //             compact), and the items are put in launch order.
 //
 // A small matrix is bound by the number of launches, about 5 us each, and by the two times the host waits,
-// for the sizes and at the end (R-MAT of 65 k rows, 0.9 M entries: 35 launches, 292 us; now 19 and 222 us).
+// for the sizes and at the end (R-MAT of 65 k rows, 0.9 M entries: 35 launches, 292 us; now 19 and 214 us).
 #include <algorithm>
 #include <cstdlib>
 
