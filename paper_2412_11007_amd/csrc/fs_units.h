@@ -404,7 +404,7 @@ __device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &
 // search per element -- and when all lanes have theirs in registers they go back to the same place, so that LDS holds
 // the unit once and 28 wavefronts share a CU.  An element is {pair, column, place} in one 64-bit number, so that one
 // comparison orders it; an element larger than all ends each half, so that a merge needs no bounds.
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_unit_rank(int block0, CsrView a, UnitPlan p, int64_t K, const int4 *__restrict__ units, const int *__restrict__ n_units,
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) k_unit_rank(int block0, CsrView a, UnitPlan p, int64_t K, const int4 *__restrict__ units, const int *__restrict__ n_units,
                                                   const int32_t *__restrict__ piece_start, uint16_t *__restrict__ info, int *__restrict__ count,
                                                   int2 *__restrict__ win_at, int *__restrict__ err)
 {
@@ -476,7 +476,20 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) k_
         E = n_a = 0;
     }
     const int per_lane = ((E + 63) / 64) | 1;  // odd, so that the lanes' outputs start in different banks
-    for (int l = 0; l < p.lv; l++) {
+    // Up to an entry per lane: its place is the number of smaller ones, and no rounds are needed (16 M rows, 1 M entries,
+    // four entries per unit: 280 -> 164 us).
+    const bool few = E <= 64;
+    if (few && p.lv) {
+        const uint64_t key = ((uint64_t)(uint32_t)(slot[0] & ((1 << lw) - 1)) << 40) | ((uint64_t)(uint32_t)col[0] << 9) | (uint32_t)lane;
+        int at = 0;
+        for (int j = 0; j < E; j++) {
+            const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)key, j), hi = __builtin_amdgcn_readlane((uint32_t)(key >> 32), j);
+            at += (((uint64_t)hi << 32) | lo) < key ? 1 : 0;
+        }
+        FS_WAVE_SYNC();
+        if (lane < E) buf[at] = key;
+    }
+    for (int l = few ? p.lv : 0; l < p.lv; l++) {
         // in LDS: n_a elements, the largest, E - n_a elements, the largest
         if (lane < 2) buf[lane ? E + 1 : n_a] = ~0ull;
         FS_WAVE_SYNC();

@@ -39,13 +39,20 @@ def pattern(kind, V, rng):
         rows = [np.arange(3000)] + [pick(2500, 10000) for _ in range(V - 1)]
     elif kind == "dense start":  # all rows hold the first columns, then thin out
         rows = [np.unique(np.concatenate([np.arange(700), pick(300 * (r % 3 + 1))])) for r in range(2 * V)]
+    elif kind == "few":  # units of 0 to 70 entries: up to 64 an entry has a lane of its own; many share a column
+        group = 1
+        while group < 16 and (2 * group) * V <= 64:
+            group *= 2
+        for n in (0, 1, 2, 3, 31, 62, 63, 64, 65, 66, 70, 64, 5):
+            at = np.sort(rng.integers(0, group * V, n))
+            rows += [pick(int((at == r).sum()), 0, 90 if n % 2 else K) for r in range(group * V)]
     else:  # tiny: windows of a handful of entries and empty ones, ragged end
         rows = [pick(int(rng.integers(0, 3))) if rng.random() < 0.6 else pick(0) for _ in range(37 * V + max(V - 3, 0))]
     return from_rows(rows, K)
 
 
 @pytest.mark.parametrize("V,KB", [(1, 32), (2, 32), (4, 32), (8, 32), (16, 32), (32, 32), (3, 8), (8, 5)])
-@pytest.mark.parametrize("kind", ["edges", "alike", "one long row", "identical", "apart", "dense start", "tiny"])
+@pytest.mark.parametrize("kind", ["edges", "alike", "one long row", "identical", "apart", "dense start", "few", "tiny"])
 def test_convert_units_bit_exact(fs, kind, V, KB):  # noqa: F811
     A = pattern(kind, V, np.random.default_rng(V * 100 + KB))
     rp, ci, va = upload_csr(A)
