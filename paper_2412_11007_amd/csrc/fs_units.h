@@ -7,9 +7,9 @@
 // probe is a cache line (31.4 M entries in eight-row windows: 1.7 ms in two such kernels).  In LDS the V sorted rows of
 // a window are merged pairwise in log2(V) rounds, the neighbours of an entry in the merged
 // order tell which entries share a vector, and a prefix sum over the first ones of each vector is the rank.
-// Those entries (R-MAT of 1 M rows): the whole conversion 2.70 -> 1.20 ms, of which ranking takes 330 us (about thirty
+// Those entries (R-MAT of 1 M rows): the whole conversion 2.70 -> 1.17 ms, of which ranking takes 300 us (about thirty
 // instructions per entry and round: searching the merge paths bounds it, not memory: 260 MB are 50 us) and placing
-// 415 us (0.9 GB, most of it written, 170 us; the LDS tile and scattered two-byte accesses are the rest).
+// 418 us (0.9 GB, most of it written, 170 us; the LDS tile and scattered two-byte accesses are the rest).
 #pragma once
 
 #include <algorithm>
