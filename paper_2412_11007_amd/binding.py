@@ -174,14 +174,11 @@ def _stream_ptr(stream) -> int:
     return _raw_stream(_current_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
 
 
-def _temporary(nbytes, device, stream):
+def _temporary(nbytes, like, stream):
     """A buffer that is given back when the call returns, from the memory of the stream the kernels run on: only work on
     that stream may have it next."""
-    if stream is None:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
-    on = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, device)
-    with torch.cuda.stream(on):
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    got = _calls().temporary(nbytes, like, stream)
+    return got if got is not None else _calls().temporary(nbytes, like, torch.cuda.ExternalStream(stream.cuda_stream, like.device))
 
 
 def _workspace(fmt, work, like, stream, query, *args):
@@ -191,20 +188,16 @@ def _workspace(fmt, work, like, stream, query, *args):
         need = query(fmt, *args) if fmt.c.n_split_items else 0
         if not need:
             return None, 0, 0
-        work = _temporary(need, like.device, stream)
+        work = _temporary(need, like, stream)
     return work, work.data_ptr(), work.numel() * work.element_size()
 
 
-def _check_blocked(fmt, t):
-    """``t`` has a 16-bit element for every position of the vals_blk layout: the kernels read them all unasked."""
-    assert t.is_cuda and t.element_size() == 2 and t.is_contiguous() and t.numel() >= fmt.c.V * fmt.c.nvec
-
-
 def _values_ptr(fmt, vals) -> int:
-    """Pointer of a value array for fs_spmm, 0 for the format's own."""
+    """Pointer of a value array for fs_spmm (a 16-bit element for every position of the vals_blk layout: the kernels read them
+    all unasked), 0 for the format's own."""
     if vals is None:
         return 0
-    _check_blocked(fmt, vals)
+    assert _calls().holds16(vals, fmt.c.V * fmt.c.nvec)
     assert vals.dtype == fmt.torch_dtype or not vals.is_floating_point()  # (raw bits may come as integers)
     return vals.data_ptr()
 
@@ -291,7 +284,7 @@ def fs_convert(rowptr, colidx, vals, M: int, K: int, torch_dtype=None, V: int = 
     if arena is None:
         arena = torch.empty(a_bytes, dtype=torch.uint8, device=dev)
     if scratch is None:
-        scratch = _temporary(s_bytes, dev, stream)
+        scratch = _temporary(s_bytes, rowptr, stream)
     st = _FsFormatStruct()
     rc = lib.fs_convert(M, K, nnz, rowptr.data_ptr(), colidx.data_ptr(), 0 if vals is None else vals.data_ptr(),
                         code, V, KB, chunk, arena.data_ptr(), arena.numel(), scratch.data_ptr(), scratch.numel(),
@@ -549,10 +542,10 @@ def fs_blk_to_csr(fmt: FsFormat, blk, out=None, stream=None):
         got = _calls().blk_to_csr(ctypes.addressof(fmt.c), blk, _stream_ptr(stream))
         if got is not None:
             return _result(got, "fs_blk_to_csr")
-    _check_blocked(fmt, blk)
+    assert _calls().holds16(blk, fmt.c.V * fmt.c.nvec)
     if out is None:
         out = blk.new_empty(fmt.c.nnz)
-    assert out.is_cuda and out.element_size() == 2 and out.is_contiguous() and out.numel() >= fmt.c.nnz
+    assert _calls().holds16(out, fmt.c.nnz)
     rc = load_library().fs_blk_to_csr(ctypes.byref(fmt.c), blk.data_ptr(), out.data_ptr(), _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_blk_to_csr")
@@ -569,7 +562,7 @@ def fs_csr_to_blk(fmt: FsFormat, vals_csr, out=None, stream=None):
     assert vals_csr.numel() == fmt.c.nnz
     if out is None:
         out = vals_csr.new_empty(fmt.c.V * fmt.c.nvec)
-    assert out.is_cuda and out.element_size() == 2 and out.numel() == fmt.c.V * fmt.c.nvec and out.is_contiguous()
+    assert out.numel() == fmt.c.V * fmt.c.nvec and _calls().holds16(out, fmt.c.V * fmt.c.nvec)
     rc = load_library().fs_csr_to_blk(ctypes.byref(fmt.c), vals_csr.data_ptr(), out.data_ptr(), _stream_ptr(stream))
     if rc:
         raise FsError(rc, "fs_csr_to_blk")
@@ -591,7 +584,7 @@ def fs_csr_transpose(rowptr, colidx, M: int, K: int, stream=None):
     rowptr_t = torch.empty(K + 1, dtype=torch.int32, device=dev)
     colidx_t = torch.empty(nnz, dtype=torch.int32, device=dev)
     perm = torch.empty(nnz, dtype=torch.int32, device=dev)
-    scratch = _temporary(need.value, dev, stream)
+    scratch = _temporary(need.value, rowptr, stream)
     rc = lib.fs_csr_transpose(M, K, nnz, rowptr.data_ptr(), colidx.data_ptr(), rowptr_t.data_ptr(),
                               colidx_t.data_ptr(), perm.data_ptr(), scratch.data_ptr(), need.value,
                               _stream_ptr(stream))

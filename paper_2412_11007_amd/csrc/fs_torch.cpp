@@ -64,9 +64,19 @@ PyObject *finish(const at::Tensor &out, fs_status st)
 
 bool stream_or_none(PyObject *o) { return o == Py_None || THPStream_Check(o); }
 
-// A workspace holds the parts of cut windows: without any there is none.  It comes from the memory of the stream `on` that
-// the kernels run on (None: the current one): it is given back when the call returns, and only work on that stream may
-// have it next.
+// A buffer that is given back when the call returns, from the memory of the stream `on` that the kernels run on (None: the
+// current one): only work on that stream may have it next.
+at::Tensor temporary_on(const at::Tensor &like, int64_t bytes, PyObject *on)
+{
+    c10::OptionalStreamGuard guard;
+    if (on != Py_None) {
+        const THPStream *s = (const THPStream *)on;
+        guard.reset_stream(c10::Stream::unpack3(s->stream_id, (c10::DeviceIndex)s->device_index, (c10::DeviceType)s->device_type));
+    }
+    return at::empty({bytes}, like.options().dtype(at::kByte));
+}
+
+// A workspace holds the parts of cut windows: without any there is none.
 struct Work {
     at::Tensor t;
     void *p = nullptr;
@@ -78,12 +88,7 @@ struct Work {
         if (f->n_split_items == 0) return;
         st = query(&bytes);
         if (st != FS_OK || bytes == 0) return;
-        c10::OptionalStreamGuard guard;
-        if (on != Py_None) {
-            const THPStream *s = (const THPStream *)on;
-            guard.reset_stream(c10::Stream::unpack3(s->stream_id, (c10::DeviceIndex)s->device_index, (c10::DeviceType)s->device_type));
-        }
-        t = at::empty({(int64_t)bytes}, like.options().dtype(at::kByte));
+        t = temporary_on(like, (int64_t)bytes, on);
         p = t.data_ptr();
     }
 };
@@ -213,9 +218,34 @@ PyObject *gather16(PyObject *, PyObject *const *a, Py_ssize_t n)  // source, ind
     END_HANDLE_TH_ERRORS
 }
 
+// What the calls made through ctypes need of the above.
+PyObject *temporary(PyObject *, PyObject *const *a, Py_ssize_t n)  // bytes, a tensor on the device, stream object or None
+{
+    HANDLE_TH_ERRORS
+    if (n != 3) { PyErr_SetString(PyExc_TypeError, "wrong number of arguments"); return nullptr; }
+    const int64_t bytes = PyLong_AsLongLong(a[0]);
+    if (PyErr_Occurred()) return nullptr;
+    if (!THPVariable_Check(a[1]) || !stream_or_none(a[2])) Py_RETURN_NONE;
+    return THPVariable_Wrap(temporary_on(THPVariable_Unpack(a[1]), bytes, a[2]));
+    END_HANDLE_TH_ERRORS
+}
+
+PyObject *holds16(PyObject *, PyObject *const *a, Py_ssize_t n)  // a tensor; does it hold so many 16-bit elements, side by side on a GPU?
+{
+    HANDLE_TH_ERRORS
+    if (n != 2) { PyErr_SetString(PyExc_TypeError, "wrong number of arguments"); return nullptr; }
+    const int64_t numel = PyLong_AsLongLong(a[1]);
+    if (PyErr_Occurred()) return nullptr;
+    if (!THPVariable_Check(a[0])) Py_RETURN_FALSE;
+    const at::Tensor &t = THPVariable_Unpack(a[0]);
+    return PyBool_FromLong(t.is_cuda() && t.element_size() == 2 && t.is_contiguous() && t.numel() >= numel);
+    END_HANDLE_TH_ERRORS
+}
+
 #define FS_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FS_METHOD(bind), FS_METHOD(spmm), FS_METHOD(sddmm), FS_METHOD(attention), FS_METHOD(softmax),
                          FS_METHOD(softmax_backward), FS_METHOD(csr_to_blk), FS_METHOD(blk_to_csr), FS_METHOD(gather16),
+                         FS_METHOD(temporary), FS_METHOD(holds16),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fs_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
