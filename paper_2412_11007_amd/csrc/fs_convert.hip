@@ -198,6 +198,7 @@ __global__ void k_item_permute(const int4 *__restrict__ items, const int32_t *__
 // The same for a short list, in one launch: a single workgroup sorts the keys in LDS, three stable passes of eight bits.
 // Every wavefront keeps a run of consecutive keys in registers and ranks them 64 at a time, by
 // ballots, against counts of its own per digit.
+constexpr int kKeyDigitBits = 8, kKeyDigits = 1 << kKeyDigitBits;
 constexpr int kSortSmallMax = 8192, kSortSmallThreads = 1024;
 __global__ void __launch_bounds__(kSortSmallThreads) k_item_sort_small(const int32_t *__restrict__ keys, int n, const int4 *__restrict__ items,
                                                                        int32_t *__restrict__ order, int4 *__restrict__ by_cost)
@@ -205,8 +206,8 @@ __global__ void __launch_bounds__(kSortSmallThreads) k_item_sort_small(const int
     constexpr int NW = kSortSmallThreads / 64, ROUNDS = kSortSmallMax / kSortSmallThreads;
     __shared__ int32_t key_buf[kSortSmallMax];
     __shared__ uint16_t idx_buf[kSortSmallMax];
-    __shared__ int cur[NW][kDigits];
-    __shared__ int digit_sum[kDigits / 64];
+    __shared__ int cur[NW][kKeyDigits];
+    __shared__ int digit_sum[kKeyDigits / 64];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int per = (n + kSortSmallThreads - 1) / kSortSmallThreads * 64;  // keys per wavefront
     const int lo = min(w * per, n), hi = min(lo + per, n);
@@ -219,18 +220,18 @@ __global__ void __launch_bounds__(kSortSmallThreads) k_item_sort_small(const int
         idx[r] = i;
         pos[r] = 0;
     }
-    for (int shift = 0; shift < 24; shift += kDigitBits) {
-        for (int i = t; i < NW * kDigits; i += kSortSmallThreads) (&cur[0][0])[i] = 0;
+    for (int shift = 0; shift < 24; shift += kKeyDigitBits) {
+        for (int i = t; i < NW * kKeyDigits; i += kSortSmallThreads) (&cur[0][0])[i] = 0;
         __syncthreads();
         // place of every key among the wavefront's keys with its digit
 #pragma unroll
         for (int r = 0; r < ROUNDS; r++) {
             const bool valid = lo + 64 * r + lane < hi;
             if (lo + 64 * r >= hi) break;  // the same for all lanes
-            const int digit = ((uint32_t)key[r] >> shift) & (kDigits - 1);
+            const int digit = ((uint32_t)key[r] >> shift) & (kKeyDigits - 1);
             uint64_t same = __ballot(valid);
 #pragma unroll
-            for (int b = 0; b < kDigitBits; b++) {
+            for (int b = 0; b < kKeyDigitBits; b++) {
                 const bool bit = (digit >> b) & 1;
                 const uint64_t set = __ballot(valid && bit);
                 same &= bit ? set : ~set;
@@ -245,7 +246,7 @@ __global__ void __launch_bounds__(kSortSmallThreads) k_item_sort_small(const int
         __syncthreads();
         // where each wavefront's keys with a digit go: all smaller digits, then this digit of the wavefronts before
         int before[NW], inc = 0, mine = 0;
-        if (t < kDigits) {
+        if (t < kKeyDigits) {
 #pragma unroll
             for (int k = 0; k < NW; k++) before[k] = cur[k][t];
 #pragma unroll
@@ -258,7 +259,7 @@ __global__ void __launch_bounds__(kSortSmallThreads) k_item_sort_small(const int
             if (lane == 63) digit_sum[w] = inc;
         }
         __syncthreads();
-        if (t < kDigits) {
+        if (t < kKeyDigits) {
             int at = inc - mine;
             for (int k = 0; k < w; k++) at += digit_sum[k];
 #pragma unroll
@@ -268,7 +269,7 @@ __global__ void __launch_bounds__(kSortSmallThreads) k_item_sort_small(const int
 #pragma unroll
         for (int r = 0; r < ROUNDS; r++) {
             if (lo + 64 * r + lane < hi) {
-                const int at = cur[w][((uint32_t)key[r] >> shift) & (kDigits - 1)] + pos[r];
+                const int at = cur[w][((uint32_t)key[r] >> shift) & (kKeyDigits - 1)] + pos[r];
                 key_buf[at] = key[r];
                 idx_buf[at] = (uint16_t)idx[r];
             }
@@ -433,8 +434,7 @@ ScratchPlan plan_scratch(int64_t nnz, int64_t W, int V, int KB)
     s.slotp = o; o += fs_align_up(ib + 1, 64);
     s.cand = o; o += fs_align_up(ib + 1, 64);
     s.upos = o; o += fs_align_up(ib + 1, 64);
-    s.hist = o; o += fs_align_up((size_t)kDigits * std::max<size_t>((ib + kSortTile - 1) / kSortTile,
-                                                                     (std::min<size_t>(ib, 65536) + kSortTileSmall - 1) / kSortTileSmall) + 1, 64);  // digit counts of the work-list sort
+    s.hist = o; o += fs_align_up((size_t)kKeyDigits * sort_groups_bound((int64_t)ib) + 1, 64);  // digit counts of the work-list sort
     s.total_ints = std::max(o, (size_t)nnz);  // (never less than the four bytes per entry of earlier layouts)
     return s;
 }
@@ -678,14 +678,12 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
             FS_LAUNCH_CHECK();
         } else {
             // cand, upos and cut_pos are free again: keys alternate between cand and upos, the payload between cut_pos and item_order
-            const int tile = n_items <= 65536 ? kSortTileSmall : kSortTile;
             int *hist = scr + sp.hist;
             int32_t *kbuf[2] = {upos, cand};              // pass p reads kbuf[(p + 1) & 1], writes kbuf[p & 1]
             int32_t *vbuf[2] = {item_order, cut_pos};     // pass p writes vbuf[p & 1]; the last pass (2) writes item_order
             for (int p = 0; p < 3; p++) {
-                const int32_t *src_k = kbuf[(p + 1) & 1];
-                if ((st = sort_pass<kDigitBits>(src_k, p == 0 ? nullptr : vbuf[(p + 1) & 1], n_items, kDigitBits * p, tile, hist, tmp, kbuf[p & 1],
-                                                vbuf[p & 1], s)) != FS_OK)
+                if ((st = sort_pass<kKeyDigitBits>((const uint32_t *)kbuf[(p + 1) & 1], p == 0 ? nullptr : vbuf[(p + 1) & 1], n_items, kKeyDigitBits * p,
+                                                   kKeyDigitBits, hist, tmp, (uint32_t *)kbuf[p & 1], vbuf[p & 1], s)) != FS_OK)
                     return st;
             }
             k_item_permute<<<grid_for(n_items, 256), 256, 0, s>>>(items, item_order, n_items, items_by_cost);

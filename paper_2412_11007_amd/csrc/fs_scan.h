@@ -22,17 +22,18 @@ __device__ __forceinline__ int wave_inclusive_scan(int x)
     return x;
 }
 
-// Exclusive scan of one int per thread across a 256-thread block; *total gets the block sum.
+// Exclusive scan of one int per thread across a block of THREADS threads; *total gets the block sum.
+template <int THREADS = kScanThreads>
 __device__ __forceinline__ int block_exclusive_scan(int x, int *total)
 {
-    __shared__ int wave_sum[kScanThreads / 64];
+    __shared__ int wave_sum[THREADS / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int inc = wave_inclusive_scan(x);
     if (lane == 63) wave_sum[wave] = inc;
     __syncthreads();
     int ofs = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < kScanThreads / 64; w++) {
+    for (int w = 0; w < THREADS / 64; w++) {
         int s = wave_sum[w];
         if (w < wave) ofs += s;
         tot += s;
@@ -80,10 +81,28 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const int *__restr
     if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-// In place: data[i] <- sum of data[0..i); the last block also writes data[n] <- grand total.
-__global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ data, int64_t n, const int *__restrict__ bofs,
+// In place: data[i] <- sum of data[0..i); the last block also writes data[n] <- grand total.  before: what lies before each
+// block, or (SUMS) the blocks' sums, of which a block then adds up those before its own: up to kScanDirect of them,
+// two loads a thread and cheaper than the launch that would scan them.
+constexpr int64_t kScanDirect = 2048;
+template <bool SUMS>
+__global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ data, int64_t n, const int *__restrict__ before,
                                                              int *__restrict__ total_out)
 {
+    int ahead = 0;
+    if constexpr (SUMS) {
+        int s[kScanDirect / kScanThreads], mine = 0;
+#pragma unroll
+        for (int k = 0; k < kScanDirect / kScanThreads; k++) {
+            const int b = k * kScanThreads + threadIdx.x;
+            s[k] = b < blockIdx.x ? before[b] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kScanDirect / kScanThreads; k++) mine += s[k];
+        block_exclusive_scan(mine, &ahead);
+    } else if (before) {
+        ahead = before[blockIdx.x];
+    }
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPerThread;
     int v[kScanPerThread], o[kScanPerThread];
     scan_load8(data, base, n, v);
@@ -91,7 +110,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ d
 #pragma unroll
     for (int i = 0; i < kScanPerThread; i++) s += v[i];
     int tot;
-    int ofs = block_exclusive_scan(s, &tot) + (bofs ? bofs[blockIdx.x] : 0);
+    int ofs = block_exclusive_scan(s, &tot) + ahead;
 #pragma unroll
     for (int i = 0; i < kScanPerThread; i++) {
         o[i] = ofs;
@@ -183,15 +202,19 @@ fs_status scan_exclusive(int *data, int64_t n, int *tmp, hipStream_t st, int *to
         if (s != FS_OK) return s;
     }
     if (nb == 1) {
-        k_scan_apply<<<1, kScanThreads, 0, st>>>(data, n < 0 ? 0 : n, nullptr, total_out);
+        k_scan_apply<false><<<1, kScanThreads, 0, st>>>(data, n < 0 ? 0 : n, nullptr, total_out);
         FS_LAUNCH_CHECK();
         return FS_OK;
     }
     k_scan_reduce<<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp);
     FS_LAUNCH_CHECK();
-    fs_status s = scan_exclusive(tmp, nb, tmp + fs_align_up((size_t)nb + 1, 64), st);
-    if (s != FS_OK) return s;
-    k_scan_apply<<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp, total_out);
+    if (nb <= kScanDirect) {
+        k_scan_apply<true><<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp, total_out);
+    } else {
+        fs_status s = scan_exclusive(tmp, nb, tmp + fs_align_up((size_t)nb + 1, 64), st);
+        if (s != FS_OK) return s;
+        k_scan_apply<false><<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp, total_out);
+    }
     FS_LAUNCH_CHECK();
     return FS_OK;
 }

@@ -7,9 +7,13 @@
 //
 // The stored entries of A, taken in CSR order, are sorted by (row, column).  A STABLE sort of them by
 // column alone therefore leaves them sorted by (column, row): the CSR order of A^T.  The sort is the
-// least-significant-digit radix sort of fs_sort.h on the column index.
+// least-significant-digit radix sort of fs_sort.h on the column index.  Up to 2^20 columns it takes two passes, and a word
+// has room for a column's upper digit and the row, which then travel together: the last pass leaves the column indices of
+// A^T, with no gather through the permutation, and the counts of both passes tell where A^T's rows start (5.3 M entries,
+// 18 bits: 320 -> 151 us with the values, of which a gather of rows was 70 and the table it read 16).
 // No atomics touch global memory and the result does not depend on scheduling.
 #include <algorithm>
+#include <type_traits>
 
 #include "fs_common.h"
 #include "fs_rows.h"
@@ -29,6 +33,39 @@ __global__ void k_rowptr_of_sorted(const int32_t *__restrict__ sorted_cols, int3
         if (sorted_cols[mid] < k) lo = mid + 1; else hi = mid;
     }
     rowptr_t[k] = lo;
+}
+
+// The same from the counts of two passes on low_bits and high_bits column bits (low_bits = 0: of one).  The last pass'
+// input is sorted by the low digit, and the low digit `low` starts at first_of[low] of it; so the entries before column
+// (high, low) are those the last pass puts before its group's with the digit `high`, and those of that group up to there.  One workgroup
+// per low digit, neighbours on one XCD (they write neighbouring pointers).
+constexpr int kCountsThreads = 512;
+__global__ void __launch_bounds__(kCountsThreads) k_rowptr_of_counts(const uint32_t *__restrict__ words, const int *__restrict__ first_of, const int *__restrict__ start, int ngroup,
+                                                          int group, int low_bits, int high_bits, int32_t n, int64_t K, int32_t *__restrict__ rowptr_t)
+{
+    __shared__ int h[1 << kMaxDigitBits];
+    const int lows = 1 << low_bits, per = (lows + 7) / 8;
+    const int low = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || low >= lows) return;
+    for (int i = threadIdx.x; i < 1 << high_bits; i += kCountsThreads) h[i] = 0;
+    __syncthreads();
+    const int64_t upto = first_of ? first_of[low] : 0;
+    const int g = (int)std::min<int64_t>(upto / group, ngroup - 1);
+    constexpr int kAhead = 8;
+    for (int64_t i0 = (int64_t)g * group + threadIdx.x; i0 < upto; i0 += kCountsThreads * kAhead) {
+        uint32_t word[kAhead];
+#pragma unroll
+        for (int r = 0; r < kAhead; r++) word[r] = words[std::min(i0 + r * kCountsThreads, upto - 1)];
+#pragma unroll
+        for (int r = 0; r < kAhead; r++)
+            if (i0 + r * kCountsThreads < upto) atomicAdd(&h[word[r] & ((1u << high_bits) - 1)], 1);
+    }
+    __syncthreads();
+    for (int high = threadIdx.x; high < 1 << high_bits; high += kCountsThreads) {
+        const int64_t k = (int64_t)high << low_bits | low;
+        if (k < K) rowptr_t[k] = start[(int64_t)high * ngroup + g] + h[high];
+    }
+    if (low == 0 && threadIdx.x == 0) rowptr_t[K] = n;
 }
 
 // row_of[p] = the row of A that stores entry p: the last r with rowptr[r] <= p.
@@ -63,22 +100,39 @@ __global__ void k_gather16(const uint16_t *__restrict__ src, const int32_t *__re
 
 inline unsigned grid_of(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
-// Scratch layout (ints): [keys 0: nnz][keys 1: nnz][payload: nnz][digit counts: 512 * tiles + 1][scan tmp]
+// The passes, and the scratch layout (ints): [keys 0: nnz][keys 1: nnz][payload: nnz][digit counts][scan tmp][first digit's starts]
 struct TransposePlan {
-    int64_t ntile;
-    size_t key0, key1, val1, hist, tmp, total_ints;
+    int passes, bits[4];  // digits, low to high
+    bool rows;            // rows travel with the keys
+    int row_shift;        // of the row in the first pass' output
+    size_t key0, key1, val1, hist, tmp, first_of, total_ints;
 };
-TransposePlan plan_transpose(int64_t nnz)
+int bits_of(int64_t n)  // of 0 .. n - 1
+{
+    int b = 0;
+    while (b < 31 && ((n - 1) >> b) != 0) b++;
+    return b;
+}
+TransposePlan plan_transpose(int64_t M, int64_t K, int64_t nnz)
 {
     TransposePlan p;
-    p.ntile = (nnz + kSortTile - 1) / kSortTile;
-    const size_t e = fs_align_up((size_t)nnz, 64);
+    // as few passes as digits of ten bits take, evenly wide: 5.3 M entries, 18-bit columns, two passes of nine bits
+    const int bits = bits_of(std::max<int64_t>(K, 1));
+    p.passes = std::max(1, (bits + kMaxDigitBits - 1) / kMaxDigitBits);
+    for (int i = 0, left = bits; i < p.passes; i++) {
+        p.bits[i] = (left + p.passes - i - 1) / (p.passes - i);
+        left -= p.bits[i];
+    }
+    p.row_shift = bits - p.bits[0];
+    p.rows = p.passes <= 2 && p.row_shift + bits_of(std::max<int64_t>(M, 1)) <= 32;
+    const size_t e = fs_align_up((size_t)nnz, 64), counts = (size_t)sort_groups(std::max<int64_t>(nnz, 1)) << std::max(8, p.bits[0]);
     size_t o = 0;
     p.key0 = o; o += e;
-    p.key1 = o; o += e;
+    p.key1 = o; o += p.rows ? 0 : e;
     p.val1 = o; o += e;
-    p.hist = o; o += fs_align_up((size_t)kWideDigits * p.ntile + 1, 64);
-    p.tmp = o; o += scan_tmp_ints((int64_t)kWideDigits * p.ntile);
+    p.hist = o; o += fs_align_up(counts + 1, 64);
+    p.tmp = o; o += scan_tmp_ints((int64_t)counts);
+    p.first_of = o; o += 1 << kMaxDigitBits;
     p.total_ints = o;
     return p;
 }
@@ -96,7 +150,7 @@ extern "C" fs_status fs_csr_transpose_bytes(int64_t M, int64_t K, int64_t nnz, s
 {
     if (!scratch_bytes || !sizes_ok(M, K, nnz)) return FS_ERR_INVALID_ARG;
     if (!sizes_fit(M, K, nnz)) return FS_ERR_TOO_LARGE;
-    *scratch_bytes = plan_transpose(nnz).total_ints * sizeof(int) + 256;
+    *scratch_bytes = plan_transpose(M, K, nnz).total_ints * sizeof(int) + 256;
     return FS_OK;
 }
 
@@ -114,33 +168,44 @@ extern "C" fs_status fs_csr_transpose(int64_t M, int64_t K, int64_t nnz, const i
         return FS_OK;
     }
     if ((uintptr_t)d_scratch & 255) return FS_ERR_INVALID_ARG;
-    const TransposePlan pl = plan_transpose(nnz);
+    const TransposePlan pl = plan_transpose(M, K, nnz);
     if (scratch_bytes < pl.total_ints * sizeof(int)) return FS_ERR_BUFFER_TOO_SMALL;
     int *S = (int *)d_scratch;
-    int32_t *key[2] = {S + pl.key0, S + pl.key1};
-    int *hist = S + pl.hist, *tmp = S + pl.tmp;
+    uint32_t *key[2] = {(uint32_t *)(S + pl.key0), (uint32_t *)(S + pl.key1)};
+    int *hist = S + pl.hist, *tmp = S + pl.tmp, *first_of = S + pl.first_of;
 
-    int bits = 0;
-    while (bits < 31 && ((K - 1) >> bits) != 0) bits++;
-    // digits of 9 bits where those save a pass (columns of 17 and 18 bits: two passes instead of three)
-    const int P8 = std::max(1, (bits + kDigitBits - 1) / kDigitBits), P9 = std::max(1, (bits + kWideDigitBits - 1) / kWideDigitBits);
-    const bool wide = P9 < P8;
-    const int P = wide ? P9 : P8;
-    const int32_t *src_key = d_colidx;
+    const uint32_t *src_key = (const uint32_t *)d_colidx;
     const int32_t *src_val = nullptr;
-    for (int p = 0; p < P; p++) {
-        int32_t *dst_key = key[p & 1];
+    const int P = pl.passes;
+    for (int p = 0, shift = 0; p < P; shift += pl.bits[p++]) {
+        const bool last = p == P - 1;
+        uint32_t *dst_key = pl.rows && last ? (uint32_t *)d_colidx_t : key[p & 1];
         int32_t *dst_val = ((P - 1 - p) & 1) ? S + pl.val1 : d_perm;  // the last pass writes d_perm
-        const fs_status s = wide ? sort_pass<kWideDigitBits>(src_key, src_val, nnz, kWideDigitBits * p, kSortTile, hist, tmp, dst_key, dst_val, st)
-                                 : sort_pass<kDigitBits>(src_key, src_val, nnz, kDigitBits * p, kSortTile, hist, tmp, dst_key, dst_val, st);
+        const SortRows rows{d_rowptr, M, pl.row_shift};
+        int *starts = pl.rows && !last ? first_of : nullptr;
+        auto pass = [&](auto bits_) -> fs_status {
+            constexpr int BITS = decltype(bits_)::value;
+            return pl.rows ? sort_pass<BITS, true>(src_key, src_val, nnz, 0, pl.bits[p], hist, tmp, dst_key, dst_val, st, rows, starts)
+                           : sort_pass<BITS>(src_key, src_val, nnz, shift, pl.bits[p], hist, tmp, dst_key, dst_val, st);
+        };
+        const fs_status s = pl.bits[p] <= 8 ? pass(std::integral_constant<int, 8>{})
+                            : pl.bits[p] == 9 ? pass(std::integral_constant<int, 9>{}) : pass(std::integral_constant<int, 10>{});
         if (s != FS_OK) return s;
+        if (last && pl.rows) {
+            const int low_bits = P == 2 ? pl.bits[0] : 0;
+            k_rowptr_of_counts<<<(unsigned)((1 << low_bits) + 7) / 8 * 8, kCountsThreads, 0, st>>>(src_key, P == 2 ? first_of : nullptr, hist, (int)sort_groups(nnz),
+                                                                              kSortWaves * sort_tile(nnz), low_bits, pl.bits[p], (int32_t)nnz, K, d_rowptr_t);
+            FS_LAUNCH_CHECK();
+            return FS_OK;
+        }
         src_key = dst_key;
         src_val = dst_val;
     }
-    k_rowptr_of_sorted<<<grid_of(K + 1, 256), 256, 0, st>>>(src_key, (int32_t)nnz, K, d_rowptr_t);
+    // keys too wide to carry the rows along
+    k_rowptr_of_sorted<<<grid_of(K + 1, 256), 256, 0, st>>>((const int32_t *)src_key, (int32_t)nnz, K, d_rowptr_t);
     FS_LAUNCH_CHECK();
-    int32_t *row_of = key[P & 1];  // the key buffer the last pass did not write
-    int32_t *group_rows = hist;  // the digit counts are no longer needed; 512 * tiles + 1 >= nnz / 256 + 2 ints
+    int32_t *row_of = (int32_t *)key[P & 1];  // the key buffer the last pass did not write
+    int32_t *group_rows = hist;  // the digit counts are no longer needed; 256 a group + 1 >= nnz / 256 + 2 ints
     const int64_t n_groups = (nnz + kEntriesPerGroup - 1) / kEntriesPerGroup;
     k_group_rows<<<grid_of(n_groups + 1, 256), 256, 0, st>>>(d_rowptr, M, nnz, n_groups, group_rows);
     FS_LAUNCH_CHECK();

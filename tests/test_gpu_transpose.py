@@ -68,6 +68,25 @@ def test_transpose_three_wide_passes(fs, K):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("M,K,n", [
+    (700, 1024, 9000), (700, 1025, 9000),                        # one pass, two
+    (300, 1 << 20, 9000), (300, (1 << 20) + 1, 9000),            # rows travel with the keys, or are gathered (three passes)
+    ((1 << 22) - 1, 1 << 20, 6000), (1 << 22, 1 << 20, 6000),    # 10 bits of the column and 22 of the row fill a word ...
+    ((1 << 22) + 1, 1 << 20, 6000), ((1 << 22) + 1, 1 << 19, 6000),  # ... one row more does not fit, one column bit less does
+    (40, 70000, 1023), (40, 70000, 1024), (40, 70000, 1025), (3, 4000, 2049),  # a group's last entry, and the next group's first
+])
+def test_transpose_rows_travel(fs, M, K, n):
+    """The limits of the packed sort: digits of a pass, the word that holds column digit and row, and the groups."""
+    import torch
+    rng = np.random.default_rng(M + K + n)
+    key = np.concatenate([np.arange(0, M, max(M // 64, 1))[:64].astype(np.int64) * K, [M * K - 1, (M - 1) * K]])
+    more = rng.permutation(np.setdiff1d(np.unique(rng.integers(0, M * K, 3 * n)), key))
+    key = np.unique(np.concatenate([np.unique(key), more[:n - np.unique(key).shape[0]]]))
+    assert key.shape[0] == n
+    check_transpose(fs, csr_from_coo(M, K, key // K, key % K, "u01", "f16", rng))
+    torch.cuda.empty_cache()
+
+
 def test_transpose_hub_columns(fs):
     """A few columns referenced by most rows: equal keys span many tiles, where stability matters."""
     rng = np.random.default_rng(21)
