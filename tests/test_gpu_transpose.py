@@ -157,6 +157,26 @@ def test_gradient_wrt_dense_operand_full_size(fs):
     check_close(dB[rows], ref, S, "f16", "dB full size, sampled rows")
 
 
+@pytest.mark.parametrize("n,source", [
+    (5 << 19, 5 << 19), ((5 << 19) + 1, (5 << 19) + 1),        # plain, and the first banded size: a last workgroup of one element
+    (2621440 + 4097, 64), (2621440 + 4095, 40 << 20),           # everything in one band; most of it past the last one's start
+    (8 << 20, 8 << 20), ((8 << 20) + 63, (8 << 20) + 63),       # bands of 1 MB and of 2
+    ((1 << 25) + 1, 5 << 19),                                   # plain again
+])
+def test_gather16_bands(fs, n, source):
+    """fs_gather16 copies bits, whatever the order and the range of the indices."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    src = torch.randint(-32768, 32768, (source,), generator=gen, device="cuda", dtype=torch.int32).to(torch.int16)
+    idx = (torch.randperm(n, generator=gen, device="cuda") if source == n else torch.randint(0, source, (n,), generator=gen, device="cuda")).to(torch.int32)
+    idx[0], idx[n - 1] = source - 1, 0
+    got = fs.fs_gather16(src.view(torch.float16), idx)
+    assert torch.equal(got.view(torch.int16), src[idx.long()])
+    # a view that starts at an odd element: no alignment beyond the element's
+    got = fs.fs_gather16(src[1:].view(torch.float16), idx[1:] - (idx[1:] > 0).int())
+    assert torch.equal(got.view(torch.int16), src[1:][(idx[1:] - (idx[1:] > 0).int()).long()])
+
+
 def test_transpose_argument_errors(fs):
     import torch
     lib = fs.load_library()
