@@ -79,7 +79,7 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
     // per-lane constants of the gather of H and of the transposed read
     const int g_row = lane / LPR;
     const int g_col = n0 + (lane % LPR) * 8;
-    const uint32_t g_colb = (g_col < N ? g_col : 0) * 2;  // lanes past N read (never store) column 0
+    const uint32_t g_colb = (g_col < N ? g_col : N - 8) * 2;  // lanes past N repeat the last piece (no line of its own) and never store
     const unsigned char *Hb = reinterpret_cast<const unsigned char *>(H);
     const unsigned char *Xb = reinterpret_cast<const unsigned char *>(X);
     const unsigned char *Yb = reinterpret_cast<const unsigned char *>(Y);

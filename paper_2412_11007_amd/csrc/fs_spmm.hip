@@ -2,7 +2,7 @@
 //
 // One wavefront owns one work item = a run of consecutive 32-vector blocks
 // (whole small windows packed together, or a piece of a long window), and all
-// N output columns of a 128-column pass.  Per block of 32 vectors it
+// output columns of a pass (up to 128, or 256).  Per block of 32 vectors it
 //   * reads the 32 column indices (one per lane),
 //   * gathers the 32 rows of B they name, every lane loading 16 contiguous
 //     bytes so that a row is read as one contiguous run by adjacent lanes
@@ -65,7 +65,7 @@ __device__ __forceinline__ fs_u4 fs_expand8(fs_u4 raw, uint32_t m8)
 // after block and row-major inside a block, blk_ofs[b] is the first value of block slot b, and the
 // sparse operand is rebuilt from the per-vector occupancy masks (no zero is read from memory).
 template <int DT, int V, int NT, int WPB, bool BIG, bool PK = false>
-__global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(PK ? 3 : 4)))
+__global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(NT > 8 ? 2 : PK ? 3 : 4)))
 k_spmm(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk_desc, int nvec,
        const int32_t *__restrict__ vec_col, const uint16_t *__restrict__ vals,
        const uint16_t *__restrict__ B, int64_t ldb, int N,
@@ -115,7 +115,7 @@ k_spmm(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk
     // per-lane constants of the gather and of the transposed read
     const int g_row = lane / LPR;                         // row within one wave-wide load
     const int g_col = n0 + (lane % LPR) * 8;              // first column of this lane's 16 bytes
-    const uint32_t g_colb = (g_col < N ? g_col : 0) * 2;  // its byte offset; lanes past N read (never store) column 0
+    const uint32_t g_colb = (g_col < N ? g_col : N - 8) * 2;  // its byte offset; lanes past N repeat the last piece (no line of its own) and never store
     const unsigned char *Bb = reinterpret_cast<const unsigned char *>(B);
     const uint32_t ldb2 = (uint32_t)ldb * 2;              // bytes between rows of B
     const bool full_pass = n0 + NC <= N;                  // no column of this pass lies past N
@@ -412,8 +412,14 @@ k_spmm_reduce(const int4 *__restrict__ split_windows, const float *__restrict__ 
 
 // Columns per pass for N > 64: 128.  (With the work list in its own order, 64-column passes -- more, lighter
 // wavefronts per CU -- measured 11 % faster on large matrices; with parts of hub windows launched by column
-// the order reverses, cfg 4 at eight rows: 733 us against 779 us.)  A tuning build (-DFS_TUNING_ENV) lets
-// FS_SPMM_PASS=64|128 override the choice; the shipped library reads no environment.
+// the order reverses, cfg 4 at eight rows: 733 us against 779 us.)
+// Where N > 128 is no multiple of 64, rows of B do not begin at lines of 128 bytes, and every pass fetches the lines it
+// shares with its neighbour: then one pass takes 256 columns.  With two passes / one, us: uniform 100 k x 50 k, 11 a row,
+// N = 136 64 / 51, 200 86 / 70, 224 80 / 74; lognormal graph of 262 k rows, N = 136 366 / 269, 200 457 / 366; stencil 700^2, N = 200
+// 178 / 117.  Aligned rows gain nothing (N = 192 54 / 57, 256 71 / 78; lognormal N = 256 375 / 379), and with few items the
+// chain of one wavefront, longer per block, is the time (615 items, N = 200: 11.7 / 14.1; from 2485 on 24.7 / 21.4).
+// A tuning build (-DFS_TUNING_ENV) lets FS_SPMM_PASS=64|128|256 override the choice; the shipped library reads no environment.
+constexpr int kWidePassItems = 1024;
 int fs_spmm_pass_override()
 {
 #ifdef FS_TUNING_ENV
@@ -432,9 +438,9 @@ fs_status launch(const fs_format *f, const uint16_t *vals, const uint16_t *B, in
     if (f->n_items == 0) return FS_OK;
     const int4 *items = (const int4 *)f->items_by_cost;
     const int n_items = (int)f->n_items;
-    int nc = N <= 32 ? 32 : N <= 64 ? 64 : 128;  // columns per pass
-    if (blk_ofs && nc == 32) nc = 64;  // the packed-value kernels exist for 64- and 128-column passes
-    if (N > 64 && (fs_spmm_pass_override() == 64 || fs_spmm_pass_override() == 128)) nc = fs_spmm_pass_override();
+    int nc = N <= 32 ? 32 : N <= 64 ? 64 : N > 128 && N % 64 && n_items >= kWidePassItems ? 256 : 128;  // columns per pass
+    if (blk_ofs && nc == 32) nc = 64;  // the packed-value kernels exist for 64 columns and up
+    if (N > 64 && (fs_spmm_pass_override() == 64 || fs_spmm_pass_override() == 128 || fs_spmm_pass_override() == 256)) nc = fs_spmm_pass_override();
     // Wavefronts (= work items) per workgroup.  A workgroup keeps its slots until its slowest wavefront is
     // done, so small launches, whose tail is a large part of the run, do best with one item per workgroup
     // (cfg 2: 25.1 -> 23.7 us); 64-column passes measured best with two, wide passes on large matrices with four.
@@ -460,11 +466,15 @@ fs_status launch(const fs_format *f, const uint16_t *vals, const uint16_t *B, in
     if (blk_ofs) {
         if (big) return FS_ERR_UNSUPPORTED;
         if (nc == 64) k_spmm<DT, V, 4, 2, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
+        else if (nc == 256 && wpb == 1) k_spmm<DT, V, 16, 1, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
+        else if (nc == 256) k_spmm<DT, V, 16, 4, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
         else if (wpb == 1) k_spmm<DT, V, 8, 1, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
         else k_spmm<DT, V, 8, 4, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
     }
     else if (nc == 32) { FS_SPMM_GO(2, 4); }
     else if (nc == 64) { FS_SPMM_GO(4, 2); }
+    else if (nc == 256 && wpb == 1) { FS_SPMM_GO(16, 1); }
+    else if (nc == 256) { FS_SPMM_GO(16, 4); }
     else if (wpb == 1) { FS_SPMM_GO(8, 1); }
     else { FS_SPMM_GO(8, 4); }
 #undef FS_SPMM_GO

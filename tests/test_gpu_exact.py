@@ -158,3 +158,33 @@ def test_sddmm_spmm_fused_bit_exact(fs, d, N, V, dtype):
     fmt = fs.fs_convert(rp, ci, va, A.M, A.K, V=V, chunk=64)
     got = fs.fs_sddmm_spmm(fmt, to_dev(X.bits, dtype), to_dev(Y.bits, dtype), to_dev(H.bits, dtype))
     same_bits(from_dev_bits(got), want, "fs_sddmm_spmm V=%d d=%d N=%d" % (V, d, N))
+
+
+@pytest.mark.parametrize("N", [136, 192, 200, 248, 264, 520])
+@pytest.mark.parametrize("V", [4, 8, 16])
+@pytest.mark.parametrize("rows", [1500, 20000])
+def test_spmm_pass_widths_agree(fs, rows, V, N):
+    """However many columns a pass takes, a column's sum is the same: bit for bit the products of narrow column slices, on
+    few items (passes of 128 columns) and on enough for passes of 256, with cut windows and a ragged last window; plain and
+    packed values, and row numbers that need 64-bit offsets."""
+    import torch
+    M, K = rows + 5, 9000
+    gen = torch.Generator(device="cuda").manual_seed(N * V)
+    r = torch.arange(M, device="cuda").repeat_interleave(14)
+    c = torch.randint(0, K, (r.numel(),), generator=gen, device="cuda")
+    hub = torch.arange(3000, device="cuda") * 3
+    key = torch.unique(torch.cat([r * K + c, 17 * K + hub, (M - 1) * K + hub]))
+    rp = torch.searchsorted(key, torch.arange(M + 1, device="cuda") * K).int()
+    va = torch.randn(key.numel(), generator=gen, device="cuda").half()
+    fmt = fs.fs_convert(rp, (key % K).int(), va, M, K, V=V)
+    assert (fmt.n_items >= 1024) == (rows == 20000) and fmt.c.n_split_windows > 0
+    B = torch.randn((K, N), generator=gen, device="cuda").half()
+    want = torch.cat([fs.fs_spmm(fmt, B[:, n:n + 64].contiguous()) for n in range(0, N, 64)], 1).view(torch.int16)
+    assert torch.equal(fs.fs_spmm(fmt, B).view(torch.int16), want)
+    assert torch.equal(fs.fs_spmm_packed(fmt, fs.fs_pack_values(fmt), B).view(torch.int16), want)
+    if V == 8 and N == 200:
+        base = torch.zeros((K, 1 << 18), dtype=torch.half, device="cuda")  # rows 512 KB apart: 4.7 GB
+        base[:, :N] = B
+        assert torch.equal(fs.fs_spmm(fmt, base[:, :N]).view(torch.int16), want)
+        del base
+        torch.cuda.empty_cache()
