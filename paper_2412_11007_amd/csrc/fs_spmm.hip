@@ -39,28 +39,6 @@
 
 namespace {
 
-// 16 bytes at a 2-byte-aligned address, read with one load instruction
-typedef fs_u4 fs_u4_unaligned __attribute__((aligned(2)));
-
-// Packed values -> sparse operand.  `raw` holds the lane's stored values back to back (halfword 0 first),
-// bit x of m8 says whether vector x of the lane's eight is stored: stored positions take the next
-// halfword, the others +0.0.
-__device__ __forceinline__ fs_u4 fs_expand8(fs_u4 raw, uint32_t m8)
-{
-    uint64_t lo = raw.x | ((uint64_t)raw.y << 32), hi = raw.z | ((uint64_t)raw.w << 32);
-    uint32_t out[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int x = 0; x < 8; x++) {
-        const bool bit = (m8 >> x) & 1u;
-        const uint32_t h = (uint32_t)lo & 0xFFFFu;
-        out[x >> 1] |= bit ? (h << (16 * (x & 1))) : 0u;
-        const uint64_t lo_next = (lo >> 16) | (hi << 48);
-        lo = bit ? lo_next : lo;
-        hi = bit ? (hi >> 16) : hi;
-    }
-    return fs_u4{out[0], out[1], out[2], out[3]};
-}
-
 // BIG: B spans 4 GiB or more, 64-bit gather offsets.  PK: `vals` holds only the stored values, block
 // after block and row-major inside a block, blk_ofs[b] is the first value of block slot b, and the
 // sparse operand is rebuilt from the per-vector occupancy masks (no zero is read from memory).

@@ -1,7 +1,7 @@
 // Device pieces shared by the kernels that walk work items block by block and gather rows of a dense
 // operand through LDS onto the matrix cores (SpMM, the fused attention kernel): the layout of the staged
 // tile, block descriptors, the index hand-out, the launch-order turn of a wavefront and the flush of an
-// accumulator tile.  Every translation unit gets its own copy.
+// accumulator tile; and what all kernels that take values apart or together use.  Every translation unit gets its own copy.
 #pragma once
 
 #include <algorithm>
@@ -29,6 +29,49 @@ __device__ __forceinline__ constexpr int lds_row(int r)
         __builtin_amdgcn_wave_barrier();                            \
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");      \
     } while (0)
+
+// 16 bytes at a 2-byte-aligned address, read with one load instruction
+typedef fs_u4 fs_u4_unaligned __attribute__((aligned(2)));
+
+// A lane's stored values -> eight positions of its row.  `raw` holds the lane's stored values back to back (halfword 0 first),
+// bit x of m8 says whether vector x of the lane's eight is stored: stored positions take the next
+// halfword, the others +0.0.
+__device__ __forceinline__ fs_u4 fs_expand8(fs_u4 raw, uint32_t m8)
+{
+    uint64_t lo = raw.x | ((uint64_t)raw.y << 32), hi = raw.z | ((uint64_t)raw.w << 32);
+    uint32_t out[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int x = 0; x < 8; x++) {
+        const bool bit = (m8 >> x) & 1u;
+        const uint32_t h = (uint32_t)lo & 0xFFFFu;
+        out[x >> 1] |= bit ? (h << (16 * (x & 1))) : 0u;
+        const uint64_t lo_next = (lo >> 16) | (hi << 48);
+        lo = bit ? lo_next : lo;
+        hi = bit ? (hi >> 16) : hi;
+    }
+    return fs_u4{out[0], out[1], out[2], out[3]};
+}
+
+// The same with a table in LDS: entry m of sel[16] holds the byte selectors that spread a lane's first stored values over four
+// positions with occupancy m, so that four v_perm_b32 make the eight (about 20 instructions, not 80).
+__device__ __forceinline__ void fs_expand_table(uint2 *sel, int lane)
+{
+    if (lane < 16) {
+        uint32_t h[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) h[e] = (lane >> e) & 1 ? __popc(lane & ((1 << e) - 1)) * 0x0202u + 0x0100u : 0x0C0Cu;  // 0x0C: a zero byte
+        sel[lane] = make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
+    }
+}
+__device__ __forceinline__ fs_u4 fs_expand8(fs_u4 raw, uint32_t m8, const uint2 *sel)
+{
+    const uint2 s0 = sel[m8 & 15], s1 = sel[m8 >> 4 & 15];
+    const int n = __popc(m8 & 15);  // the second four start with value n
+    const uint32_t a = n >= 4 ? raw.z : n >= 2 ? raw.y : raw.x, b = n >= 4 ? raw.w : n >= 2 ? raw.z : raw.y, c = n >= 2 ? raw.w : raw.z;
+    const uint32_t lo = __builtin_amdgcn_alignbit(b, a, 16 * (n & 1)), hi = __builtin_amdgcn_alignbit(c, b, 16 * (n & 1));
+    return fs_u4{__builtin_amdgcn_perm(raw.y, raw.x, s0.x), __builtin_amdgcn_perm(raw.y, raw.x, s0.y),
+                 __builtin_amdgcn_perm(hi, lo, s1.x), __builtin_amdgcn_perm(hi, lo, s1.y)};
+}
 
 // One 32-vector block of an item (all fields are wave-uniform).
 struct BlockDesc {

@@ -519,6 +519,24 @@ def test_new_values_for_the_same_pattern(fs, V):
     check_close(C, want, S, "bf16", "spmm on re-laid values")
 
 
+@pytest.mark.parametrize("V", [1, 4, 5, 8, 16, 32])
+@pytest.mark.parametrize("M,K,density", [(1, 1, 1.0), (3, 5, 0.4), (16, 32, 1.0), (33, 31, 0.7), (65, 33, 0.9), (700, 900, 0.003), (40, 5000, 0.05), (9, 64, 0.0)])
+def test_new_values_block_edges(fs, M, K, density, V):
+    """The re-layout by blocks: fewer values than one load takes, full and narrow blocks, windows and rows without
+    entries, wavefronts whose last block does not exist -- and not an element past the array's end."""
+    import torch
+    A = random_csr(M, K, density, "f16", seed=M + V, empty_rows=0.3 if M > 600 else 0.0)
+    fmt = convert(fs, A, V, 32)
+    vals = (np.arange(A.nnz) % 65535 + 1).astype(np.uint16)  # every position has a value of its own
+    n = fmt.V * fmt.nvec
+    out = torch.full((n + 64,), 7, dtype=torch.int16, device="cuda")
+    if n:
+        fs.fs_csr_to_blk(fmt, to_dev(vals, "f16"), out=out[:n].view(torch.float16))
+    ref = oracle.convert_ref(A.M, A.K, A.rowptr, A.colidx, vals, V, 32)
+    assert np.array_equal(out[:n].cpu().numpy().view(np.uint16), ref.vals_blk)
+    assert (out[n:] == 7).all()
+
+
 def test_gather_probe_runs_and_checks_arguments(fs):
     """The measurement aid reads what fs_spmm reads: it must accept the same operands, write its sink and
     refuse a sink that is too small."""
