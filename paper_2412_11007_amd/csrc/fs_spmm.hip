@@ -64,6 +64,8 @@ k_spmm(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk
 
     __shared__ __attribute__((aligned(16))) unsigned char lds_all[WPB][(LDS_BYTES + 15) / 16 * 16];
 
+    __shared__ uint2 sels[PK ? WPB : 1][16];
+
     // column pass and group of WPB items of this workgroup
     const int pass = blockIdx.x / nbx;
     const int bx = blockIdx.x - pass * nbx;
@@ -72,6 +74,8 @@ k_spmm(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk
     const int turn = __builtin_amdgcn_readfirstlane(u + wave);  // wave-uniform
     if (turn >= n_items) return;  // no block-wide barrier is used below
     unsigned char *lds = lds_all[wave];
+    const uint2 *sel = sels[PK ? wave : 0];
+    if constexpr (PK) fs_expand_table(sels[wave], lane);
 
     const int4 it = items[turn];  // the work list in launch order, costliest items first  // {first block slot, blocks, first partial slot, first vector}
     const int nblk = it.y;
@@ -230,7 +234,7 @@ k_spmm(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk
         const int kb = d0.kb;
         // sparse operand: rows j < V of the block, vectors 8g .. 8g+7; vectors past kb are zero
         fs_frag sp;
-        sp.u = PK ? fs_expand8(raw0, m8_0) : raw0;
+        sp.u = PK ? fs_expand8(raw0, m8_0, sel) : raw0;
         if (!PK && kb > 0 && kb < 32) {
             *reinterpret_cast<fs_u4 *>(lds + 16 * lane) = raw0;  // V*kb*2 <= 1 KB of contiguous values
             FS_WAVE_SYNC();

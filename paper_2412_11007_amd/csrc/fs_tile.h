@@ -33,27 +33,10 @@ __device__ __forceinline__ constexpr int lds_row(int r)
 // 16 bytes at a 2-byte-aligned address, read with one load instruction
 typedef fs_u4 fs_u4_unaligned __attribute__((aligned(2)));
 
-// A lane's stored values -> eight positions of its row.  `raw` holds the lane's stored values back to back (halfword 0 first),
-// bit x of m8 says whether vector x of the lane's eight is stored: stored positions take the next
-// halfword, the others +0.0.
-__device__ __forceinline__ fs_u4 fs_expand8(fs_u4 raw, uint32_t m8)
-{
-    uint64_t lo = raw.x | ((uint64_t)raw.y << 32), hi = raw.z | ((uint64_t)raw.w << 32);
-    uint32_t out[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int x = 0; x < 8; x++) {
-        const bool bit = (m8 >> x) & 1u;
-        const uint32_t h = (uint32_t)lo & 0xFFFFu;
-        out[x >> 1] |= bit ? (h << (16 * (x & 1))) : 0u;
-        const uint64_t lo_next = (lo >> 16) | (hi << 48);
-        lo = bit ? lo_next : lo;
-        hi = bit ? (hi >> 16) : hi;
-    }
-    return fs_u4{out[0], out[1], out[2], out[3]};
-}
-
-// The same with a table in LDS: entry m of sel[16] holds the byte selectors that spread a lane's first stored values over four
-// positions with occupancy m, so that four v_perm_b32 make the eight (about 20 instructions, not 80).
+// A lane's stored values -> eight positions of its row.  `raw` holds the values back to back (halfword 0 first), bit x of m8
+// says whether position x is stored: stored positions take the next halfword, the others +0.0.  Entry m of sel[16], a table in
+// LDS, holds the byte selectors that spread values over four positions with occupancy m, so that four v_perm_b32 make the
+// eight (about 20 instructions, where shifting and selecting value by value took 80).
 __device__ __forceinline__ void fs_expand_table(uint2 *sel, int lane)
 {
     if (lane < 16) {
