@@ -5,8 +5,7 @@
 // writes the scores, reads and rewrites them, and reads them again; here a wavefront keeps them in
 // registers.  Per 32-vector block of its work item it
 //   * computes the V x 32 tile of scores on the matrix cores exactly as the SDDMM kernel does (gathered
-//     Y rows as the left operand, the window's X rows as the right one, 16 contiguous bytes per lane
-//     straight in operand layout), which leaves lane (j, g) with the scores of window row j and vectors
+//     Y rows as the left operand, for d > 32 by way of LDS, the window's X rows as the right one), which leaves lane (j, g) with the scores of window row j and vectors
 //     8g .. 8g+7 -- the lane's piece of the SpMM sparse operand;
 //   * masks them by the pattern, updates the running row maximum m and row sum l, turns them into
 //     p = 2^(t - m) (t = score * scale * log2 e) rounded to the element type, and scales the fp32
@@ -19,9 +18,14 @@
 //
 // One pass covers up to 256 output columns, so that the scores are computed once for N <= 256.
 //
+// What bounds it: on large graphs the fabric (lognormal graph of 262 k rows, d = 64, N = 256: 7.6 TB/s of missed rows); on those
+// the L2s hold, and on small ones, the instructions of a block.  Those went down by tiles as narrow as N, by reading a row's
+// occupancy instead of balloting it from the vectors' masks, by keeping a window's rows of X, and by gathering Y row by
+// row: R-MAT of 65 k rows, N = 64, d = 32 / 64 / 128: 33 / 40 / 58 us -> 25 / 28 / 34; of 8 k rows 15 -> 12.5.
+//
 // The same kernel with the softmax compiled out (SM = false) is SDDMM followed by SpMM: the weights are
 // the scaled scores, rounded to the element type as the SDDMM kernel stores them, and nothing is divided.
-#include <cstdlib>
+#include <type_traits>
 #include <utility>
 
 #include "fs_common.h"
@@ -36,9 +40,9 @@ __device__ __forceinline__ float fs_exp2(float x) { return __builtin_amdgcn_exp2
 // SM = false leaves the softmax out: the weights are the scaled scores themselves, rounded to the element
 // type exactly as the SDDMM kernel stores them (sl2 is then the plain scale).
 template <int DT, int V, int NT, int KS, int WPB, bool SM>
-__global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(NT > 8 ? 2 : 3)))
+__global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(NT > 8 || (NT == 8 && KS == 4) ? 2 : 3)))
 k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk_desc, int nvec,
-            const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ vec_mask,
+            const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ row_bits,
             const uint16_t *__restrict__ X, int64_t ldx, const uint16_t *__restrict__ Y, int64_t ldy, int d, float sl2,
             const uint16_t *__restrict__ H, int64_t ldh, int N,
             uint16_t *__restrict__ C, int64_t ldc, float *__restrict__ part, float *__restrict__ stats, int64_t M, int nbx,
@@ -49,7 +53,16 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
     constexpr int RPI = 64 / LPR; // rows per wave-wide load
     constexpr int NLD = 32 / RPI; // wave-wide loads per 32-vector block
     constexpr int RS = NC * 2;    // LDS row stride in bytes
-    constexpr int LDS_BYTES = lds_row<RS>(31) + RS;
+    constexpr bool DPPR = LPR >= 16;  // indices are handed out by DPP moves (see below)
+    // Rows of Y longer than 64 bytes are gathered row by row and turned into operand layout in LDS, as in the SDDMM kernel
+    // (loaded straight in operand layout a wave-wide load takes the vector-memory unit 64-70 cycles instead of 18-24);
+    // the tile is the one that the rows of H pass through afterwards.
+    constexpr bool YL = KS >= 2;
+    constexpr int YLPR = 4 * KS;        // lanes that share one gathered row of Y
+    constexpr int YRPI = 64 / YLPR;     // rows per wave-wide load
+    constexpr int NY = 2 * KS;          // 16-byte registers of Y per lane and block, in either form
+    constexpr int RSY = KS * 64 + 16;   // LDS row stride: an odd number of 16-byte pieces
+    constexpr int H_BYTES = lds_row<RS>(31) + RS, LDS_BYTES = YL && 32 * RSY > H_BYTES ? 32 * RSY : H_BYTES;
 
     __shared__ __attribute__((aligned(16))) unsigned char lds_all[WPB][(LDS_BYTES + 15) / 16 * 16];
 
@@ -99,19 +112,21 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
         f_off[ks] = f_ok[ks] ? 2 * (32 * ks + 8 * g) : 0;
     }
 
-    // Column indices of a block.  A gathered row of H is shared by 16 or 32 lanes, so every group of 16
+    // Column indices of a block.  Where a gathered row of H is shared by 16 or 32 lanes, every group of 16
     // lanes wants the same index for a given wave-wide load: lane i of a group holds the index for load i
-    // (vector i * RPI + the group's row) and a DPP broadcast hands it out.  Vectors past the block's width
-    // repeat its last one (their occupancy mask is zero, so whatever they gather is ignored).
+    // (vector i * RPI + the group's row) and a DPP broadcast hands it out.  Shorter rows keep them one per vector.
+    // Vectors past the block's width repeat its last one (no row stores them, so whatever they gather is ignored).
     auto load_cols = [&](const BlockDesc &b) -> int {
-        const int v = (lane & 15) * RPI + lane / LPR;
+        const int v = DPPR ? (lane & 15) * RPI + lane / LPR : lane;
         return vec_col[max(min(b.s + min(v, b.kb - 1), nvec - 1), 0)];
     };
     // the lane that holds vector u's index in that arrangement
-    auto holder = [&](int u) -> int { return (u % RPI) * LPR + u / RPI; };
-    auto load_mask = [&](const BlockDesc &b) -> uint32_t {
-        const uint32_t m = vec_mask[max(min(b.s + min(lane, b.kb - 1), nvec - 1), 0)];
-        return lane < b.kb ? m : 0u;
+    auto holder = [&](int u) -> int { return DPPR ? (u % RPI) * LPR + u / RPI : u; };
+    // occupancy of window row j in block i of the item: bit c, the row stores the block's vector c (any row's for lanes
+    // past V, whose products nobody reads).  (V ballots over the vectors' masks took 32 instructions a block.)
+    auto load_bits = [&](int i) -> uint32_t {
+        const uint32_t m = row_bits[(int64_t)(it.x + min(i, nblk - 1)) * V + (j & (V - 1))];
+        return i < nblk ? m : 0u;
     };
     // X operand of a block: lane (j, g) holds X[w*V + j][32ks + 8g .. +7]; rows past V or M and features
     // past d are zero.  The load itself is unconditional (row 0 stands in).
@@ -126,25 +141,45 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
             if (!ok || !f_ok[ks]) xf[ks].u = fs_u4{0u, 0u, 0u, 0u};
         }
     };
-    // Y operand: matrix row j of tile t is vector 8*(j/4) + 4t + (j%4) of the block
-    uint32_t yoff[2];
-    fs_frag yf[2][KS];
+    // Rows of Y.  Matrix row i of tile t is vector 8*(i/4) + 4t + (i%4) of the block.  In operand layout register t*KS + ks holds
+    // step ks of row j of tile t; row by row, register k holds the lane's piece of row p = k*YRPI + lane/YLPR, which is
+    // matrix row p%16 of tile p/16.  (Pieces past d repeat the row's last one and meet a zero X operand.)
+    auto vector_of = [](int p) -> int { return 8 * ((p & 15) >> 2) + 4 * (p >> 4) + (p & 3); };
+    uint32_t yoff[YL ? NY : 2];
+    fs_u4 yg[NY];
+    const uint32_t y_colb = YL ? 2 * (uint32_t)min((lane % YLPR) * 8, d - 8) : 0;
+    unsigned char *y_wr = lds + (lane / YLPR) * RSY + (lane % YLPR) * 16;  // + k*YRPI*RSY per register
+    const unsigned char *y_rd = lds + j * RSY + g * 16;                     // + 16*t*RSY + 64*ks per read
 #define FS_YROWS(cols)                                                                           \
     {                                                                                            \
-        _Pragma("unroll") for (int t = 0; t < 2; t++)                                            \
-            yoff[t] = fs_mul24((uint32_t)__shfl(cols, holder(8 * (j >> 2) + 4 * t + (j & 3)), 64), ldy2); \
+        fs_for_each_index([&](auto k_) {                                                         \
+            constexpr int k = decltype(k_)::value;                                               \
+            int idx_;                                                                            \
+            if constexpr (!YL) idx_ = __shfl(cols, holder(8 * (j >> 2) + 4 * k + (j & 3)), 64);  \
+            else if constexpr (LPR == 16 && KS == 4) idx_ = fs_row_bcast<2 * (k & 3) + (k >> 2)>(cols); \
+            else idx_ = __shfl(cols, holder(vector_of(k * YRPI + lane / YLPR)), 64);             \
+            yoff[k] = fs_mul24((uint32_t)idx_, ldy2) + y_colb;                                   \
+        }, std::make_integer_sequence<int, YL ? NY : 2>{});                                      \
     }
 #define FS_YGATHER()                                                                             \
-    _Pragma("unroll") for (int t = 0; t < 2; t++)                                                \
-        _Pragma("unroll") for (int ks = 0; ks < KS; ks++)                                        \
-            yf[t][ks].u = *reinterpret_cast<const fs_u4 *>(Yb + yoff[t] + f_off[ks]);
+    if constexpr (YL) {                                                                          \
+        _Pragma("unroll") for (int k = 0; k < NY; k++)                                           \
+            yg[k] = *reinterpret_cast<const fs_u4 *>(Yb + yoff[YL ? k : 0]);                     \
+    } else {                                                                                     \
+        _Pragma("unroll") for (int t = 0; t < 2; t++)                                            \
+            _Pragma("unroll") for (int ks = 0; ks < KS; ks++)                                    \
+                yg[t * KS + ks] = *reinterpret_cast<const fs_u4 *>(Yb + yoff[t] + f_off[ks]);    \
+    }
     // rows of H this lane gathers for a block, as 32-bit byte offsets
     uint32_t grow[NLD];
 #define FS_ROWS(cols)                                                                            \
     {                                                                                            \
         fs_for_each_index([&](auto l_) {                                                         \
             constexpr int l = decltype(l_)::value;                                               \
-            grow[l] = fs_mul24((uint32_t)fs_row_bcast<l>(cols), ldh2) + g_colb;                  \
+            int idx_;                                                                            \
+            if constexpr (DPPR) idx_ = fs_row_bcast<l>(cols);                                    \
+            else idx_ = __shfl(cols, l * RPI + g_row, 64);                                       \
+            grow[l] = fs_mul24((uint32_t)idx_, ldh2) + g_colb;                                   \
         }, std::make_integer_sequence<int, NLD>{});                                              \
     }
     fs_u4 stage[NLD];
@@ -158,7 +193,7 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
     const int col0 = load_cols(d0);
     const int col1 = load_cols(d1);
     int col2 = load_cols(d2);
-    uint32_t msk0 = load_mask(d0);
+    uint32_t bits0 = load_bits(0);
     bool from_first = d0.first;
     load_x(d0);
     FS_YROWS(col0)
@@ -184,30 +219,34 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
         constexpr bool SMALL_FIRST = NT <= 8;
         const BlockDesc d3 = block(step + 3);
         int col3 = 0;
-        uint32_t msk1 = 0;
+        uint32_t bits1 = 0;
         if constexpr (SMALL_FIRST) {
             col3 = load_cols(d3);
-            msk1 = load_mask(d1);
+            bits1 = load_bits(step + 1);
         }
         // ---- scores of this block -> probabilities relative to the running maximum
         fs_frag sp;
         float corr;
+        if constexpr (YL) {
+#pragma unroll
+            for (int k = 0; k < NY; k++) *reinterpret_cast<fs_u4 *>(y_wr + k * YRPI * RSY) = yg[k];
+            if (MORE) FS_YGATHER()
+            FS_WAVE_SYNC();
+        }
         {
             fs_f4 sc[2];
 #pragma unroll
             for (int t = 0; t < 2; t++) {
                 sc[t] = fs_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int ks = 0; ks < KS; ks++) sc[t] = fs_mfma_16x16x32<DT>(yf[t][ks], xf[ks], sc[t]);
+                for (int ks = 0; ks < KS; ks++) {
+                    fs_frag y;
+                    y.u = YL ? *reinterpret_cast<const fs_u4 *>(y_rd + 16 * t * RSY + 64 * ks) : yg[t * KS + ks];
+                    sc[t] = fs_mfma_16x16x32<DT>(y, xf[ks], sc[t]);
+                }
             }
-            // bit c of `bits`: vector c of the block stores window row j (from the per-vector occupancy masks)
-            uint32_t bits = 0;
-#pragma unroll
-            for (int r = 0; r < V; r++) {
-                const uint32_t has = (uint32_t)__ballot((msk0 >> r) & 1u);
-                bits = (j == r) ? has : bits;
-            }
-            const uint32_t mine = bits >> (8 * g);  // bit 4t + e: vector 8g + 4t + e
+            if constexpr (YL) FS_WAVE_SYNC();
+            const uint32_t mine = bits0 >> (8 * g);  // bit 4t + e: vector 8g + 4t + e
             float p[8];
             if constexpr (SM) {
                 float tv[8];
@@ -241,9 +280,11 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
             sp.u.w = fs_pack2<DT>(p[6], p[7]);
         }
         // ---- the next block's Y rows and X rows
-        if (MORE) FS_YGATHER()
-        load_x(d1);
-        if constexpr (!SMALL_FIRST) msk1 = load_mask(d1);
+        if constexpr (!YL) {
+            if (MORE) FS_YGATHER()
+        }
+        if (d1.w != d0.w) load_x(d1);  // blocks of one window keep its rows of X (in operand layout: 64-70 cycles a load)
+        if constexpr (!SMALL_FIRST) bits1 = load_bits(step + 1);
 
         if (kb > 0) {
             // the gathered rows of H go to LDS (this is where the wave waits for the gather)
@@ -300,7 +341,7 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
         if (d0.last) from_first = true;
         d0 = d1; d1 = d2; d2 = d3;
         col2 = col3;
-        msk0 = msk1;
+        bits0 = bits1;
     };
     if constexpr (NT <= 8) {
         for (; step + 1 < nblk; step++) block_step(std::true_type{});
@@ -402,7 +443,7 @@ fs_status launch_wpb(const fs_format *f, const uint16_t *X, int64_t ldx, const u
     const int64_t nblocks = (int64_t)nbx * passes;
     if (nblocks >= ((int64_t)1 << 31)) return FS_ERR_TOO_LARGE;
     dim3 grid((unsigned)nblocks, 1, 1), block(64 * WPB, 1, 1);
-#define FS_ATTN_ARGS (const int4 *)f->items_by_cost, n_items, (const int4 *)f->blk_desc, (int)f->nvec, f->vec_col, f->vec_mask, \
+#define FS_ATTN_ARGS (const int4 *)f->items_by_cost, n_items, (const int4 *)f->blk_desc, (int)f->nvec, f->vec_col, f->blk_row_bits, \
                      X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, f->M, nbx, geo.slice, geo.n_swz
     if (d <= 32) k_attention<DT, V, NT, 1, WPB, SM><<<grid, block, 0, st>>>(FS_ATTN_ARGS);
     else if (d <= 64) k_attention<DT, V, NT, 2, WPB, SM><<<grid, block, 0, st>>>(FS_ATTN_ARGS);
@@ -435,12 +476,17 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
     if (f->n_items == 0) return FS_OK;
     float *part = work;
     float *stats = work + (size_t)f->n_split_items * (size_t)V * (size_t)N;
-    if (softmax) {
-        if (N <= 128) return launch_nt<DT, V, 8, true>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
-        return launch_nt<DT, V, 16, true>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
-    }
-    if (N <= 128) return launch_nt<DT, V, 8, false>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
-    return launch_nt<DT, V, 16, false>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
+    const auto go = [&](auto sm) -> fs_status {
+        constexpr bool SM = decltype(sm)::value;
+        // Columns per pass: as few as hold N, up to 256, so that the scores are computed once.  A tile of 128 columns for
+        // N = 32 costs registers, LDS and instructions: R-MAT of 65 k rows, d = 64: 128 columns 33.6 us, 64 columns 27.9, 32
+        // columns 24.8; lognormal graph of 262 k rows, fabric-bound: no difference.
+        if (N <= 32) return launch_wpb<DT, V, 2, SM, 1>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
+        if (N <= 64) return launch_wpb<DT, V, 4, SM, 1>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
+        if (N <= 128) return launch_nt<DT, V, 8, SM>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
+        return launch_nt<DT, V, 16, SM>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
+    };
+    return softmax ? go(std::true_type{}) : go(std::false_type{});
 }
 
 }  // namespace

@@ -233,3 +233,32 @@ def test_attention_on_a_matrix_without_entries(fs):
     C = torch.full((20, 40), 5.0, dtype=torch.float16, device="cuda")
     fs.fs_spmm_packed(fmt, fs.fs_pack_values(fmt), H, out=C)
     assert (C == 0).all()
+
+
+@pytest.mark.parametrize("V", [4, 8, 16])
+@pytest.mark.parametrize("d", [8, 32, 40, 64, 72, 96, 128])
+def test_attention_pass_widths_and_feature_steps(fs, V, d):
+    """Every width of a pass (32, 64, 128 and 256 columns) and every form of the score contraction (one step in operand
+    layout; two or four by way of LDS, whole and with features missing): against the fp64 definition on one width, and the
+    other widths' columns bit for bit those, because a column's sum does not depend on how many columns a pass takes.
+    Hub windows cut across items and windows of several blocks, where a window's rows of X are kept."""
+    import torch
+    rng = np.random.default_rng(100 * V + d)
+    M, K = 150, 2500
+    deg = np.where(np.isin(np.arange(M), (5, 77)), 1500, rng.integers(0, 40, M))
+    rows = np.repeat(np.arange(M), deg)
+    cols = np.concatenate([rng.choice(K, size=n, replace=False) for n in deg])
+    A = csr_from_coo(M, K, rows, cols, "n01", "f16", rng)
+    X = dense(M, d, "n01", "f16", stream(9, 60, d))
+    Y = dense(K, d, "n01", "f16", stream(9, 61, d))
+    H = dense(K, 264, "n01", "f16", stream(9, 62, V))
+    fmt = convert(fs, A, V, 64)
+    err, got = run_and_check(fs, A, fmt, X, Y, H, d ** -0.5)
+    assert err <= bar("f16")
+    Xd, Yd, Hd = (to_dev(t.bits, "f16") for t in (X, Y, H))
+    full = fs.fs_attention(fmt, Xd, Yd, Hd, scale=d ** -0.5).view(torch.int16)
+    fused = fs.fs_sddmm_spmm(fmt, Xd, Yd, Hd).view(torch.int16)
+    for N in (8, 24, 32, 40, 64, 72, 128, 136, 256):
+        part = Hd[:, :N].contiguous()
+        assert torch.equal(fs.fs_attention(fmt, Xd, Yd, part, scale=d ** -0.5).view(torch.int16), full[:, :N]), N
+        assert torch.equal(fs.fs_sddmm_spmm(fmt, Xd, Yd, part).view(torch.int16), fused[:, :N]), N
