@@ -161,7 +161,10 @@ __global__ void __launch_bounds__(256) k_item_fill(const int4 *__restrict__ rec,
                                                    int4 *__restrict__ split_windows, int2 *__restrict__ slot_range)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_items) return;
+    if (i >= n_items) {
+        if (i < (n_items + 63) / 64 * 64) key[i] = INT32_MAX;  // (k_item_rank reads 64 keys at a time)
+        return;
+    }
     const int4 r = rec[i];
     const int slot = slot_ptr[i];
     items[i] = make_int4(r.x, r.y, r.y ? slot : 0, r.w);
@@ -195,102 +198,58 @@ __global__ void k_item_permute(const int4 *__restrict__ items, const int32_t *__
     if (t < n_items) by_cost[t] = items[order[t]];
 }
 
-// The same for a short list, in one launch: a single workgroup sorts the keys in LDS, three stable passes of eight bits.
-// Every wavefront keeps a run of consecutive keys in registers and ranks them 64 at a time, by
-// ballots, against counts of its own per digit.
-constexpr int kKeyDigitBits = 8, kKeyDigits = 1 << kKeyDigitBits;
-constexpr int kSortSmallMax = 8192, kSortSmallThreads = 1024;
-__global__ void __launch_bounds__(kSortSmallThreads) k_item_sort_small(const int32_t *__restrict__ keys, int n, const int4 *__restrict__ items,
-                                                                       int32_t *__restrict__ order, int4 *__restrict__ by_cost)
+__device__ __forceinline__ void count_if_less(int &n, int32_t key, int32_t x)  // n += key < x
 {
-    constexpr int NW = kSortSmallThreads / 64, ROUNDS = kSortSmallMax / kSortSmallThreads;
-    __shared__ int32_t key_buf[kSortSmallMax];
-    __shared__ uint16_t idx_buf[kSortSmallMax];
-    __shared__ int cur[NW][kKeyDigits];
-    __shared__ int digit_sum[kKeyDigits / 64];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int per = (n + kSortSmallThreads - 1) / kSortSmallThreads * 64;  // keys per wavefront
-    const int lo = min(w * per, n), hi = min(lo + per, n);
-    const uint64_t below = ((uint64_t)1 << lane) - 1;
-    int key[ROUNDS], idx[ROUNDS], pos[ROUNDS];  // of this lane's keys, 64 apart
+    asm("v_cmp_lt_i32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc" : "+v"(n) : "v"(key), "v"(x) : "vcc");
+}
+// The same for a short list, in one launch: an item's place is the number of keys before its own.  A workgroup takes 32
+// items; each half of its sixteen wavefronts compares them with its share of the keys, 64 at a time by way of LDS, two
+// instructions a comparison.  keys: padded to a multiple of 64 with keys larger than all.  5226 items: 22 us by one
+// workgroup that sorted them in three digit passes, now 8; from about 24 k items on the radix passes are the shorter way.
+constexpr int kRankItemsMax = 16384, kRankWaves = 16, kRankItems = 32;
+constexpr int kKeyDigitBits = 8, kKeyDigits = 1 << kKeyDigitBits;  // of the radix passes
+__global__ void __launch_bounds__(64 * kRankWaves) k_item_rank(const int32_t *__restrict__ keys, int n, const int4 *__restrict__ items,
+                                                               int32_t *__restrict__ order, int4 *__restrict__ by_cost)
+{
+    __shared__ __attribute__((aligned(16))) int32_t share[kRankWaves][2][64 + 4];  // the halves' keys, in different banks
+    __shared__ int part[2 * kRankWaves][kRankItems];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, half = lane >> 5;
+    const int i = blockIdx.x * kRankItems + (lane & 31), i0 = i & ~63;  // i0: the group of keys its own is in
+    const int32_t mine = keys[i];
+    const int groups = (n + 63) / 64;
+    int before = 0;
+    for (int g0 = 2 * w; g0 < groups; g0 += 2 * kRankWaves) {
+        share[w][0][lane] = keys[g0 * 64 + lane];
+        share[w][1][lane] = g0 + 1 < groups ? keys[g0 * 64 + 64 + lane] : INT32_MAX;
+        FS_WAVE_SYNC();
+        const int j0 = (g0 + half) * 64;
+        const int32_t bound = j0 < i0 ? mine + 1 : mine;  // of earlier items, equal keys come first
+        const int4 *k4 = reinterpret_cast<const int4 *>(share[w][half]);
+        if (j0 != i0) {
 #pragma unroll
-    for (int r = 0; r < ROUNDS; r++) {
-        const int i = lo + 64 * r + lane;
-        key[r] = i < hi ? keys[i] : 0;
-        idx[r] = i;
-        pos[r] = 0;
+            for (int q = 0; q < 16; q++) {
+                const int4 k = k4[q];
+                count_if_less(before, k.x, bound);
+                count_if_less(before, k.y, bound);
+                count_if_less(before, k.z, bound);
+                count_if_less(before, k.w, bound);
+            }
+        } else {
+            for (int j = 0; j < 64; j++) {
+                const int32_t k = share[w][half][j];
+                before += k < mine || (k == mine && j0 + j < i) ? 1 : 0;
+            }
+        }
+        FS_WAVE_SYNC();
     }
-    for (int shift = 0; shift < 24; shift += kKeyDigitBits) {
-        for (int i = t; i < NW * kKeyDigits; i += kSortSmallThreads) (&cur[0][0])[i] = 0;
-        __syncthreads();
-        // place of every key among the wavefront's keys with its digit
+    part[2 * w + half][lane & 31] = before;
+    __syncthreads();
+    if (threadIdx.x >= kRankItems || i >= n) return;
+    int at = 0;
 #pragma unroll
-        for (int r = 0; r < ROUNDS; r++) {
-            const bool valid = lo + 64 * r + lane < hi;
-            if (lo + 64 * r >= hi) break;  // the same for all lanes
-            const int digit = ((uint32_t)key[r] >> shift) & (kKeyDigits - 1);
-            uint64_t same = __ballot(valid);
-#pragma unroll
-            for (int b = 0; b < kKeyDigitBits; b++) {
-                const bool bit = (digit >> b) & 1;
-                const uint64_t set = __ballot(valid && bit);
-                same &= bit ? set : ~set;
-            }
-            const int rank = __popcll(same & below), cnt = __popcll(same);
-            const int at = cur[w][digit];
-            pos[r] = at + rank;
-            FS_WAVE_SYNC();  // the wavefront's reads stay before its update
-            if (valid && rank == cnt - 1) cur[w][digit] = at + cnt;
-            FS_WAVE_SYNC();
-        }
-        __syncthreads();
-        // where each wavefront's keys with a digit go: all smaller digits, then this digit of the wavefronts before
-        int before[NW], inc = 0, mine = 0;
-        if (t < kKeyDigits) {
-#pragma unroll
-            for (int k = 0; k < NW; k++) before[k] = cur[k][t];
-#pragma unroll
-            for (int k = 0; k < NW; k++) {
-                const int c = before[k];
-                before[k] = mine;
-                mine += c;
-            }
-            inc = wave_inclusive_scan(mine);
-            if (lane == 63) digit_sum[w] = inc;
-        }
-        __syncthreads();
-        if (t < kKeyDigits) {
-            int at = inc - mine;
-            for (int k = 0; k < w; k++) at += digit_sum[k];
-#pragma unroll
-            for (int k = 0; k < NW; k++) cur[k][t] = at + before[k];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ROUNDS; r++) {
-            if (lo + 64 * r + lane < hi) {
-                const int at = cur[w][((uint32_t)key[r] >> shift) & (kKeyDigits - 1)] + pos[r];
-                key_buf[at] = key[r];
-                idx_buf[at] = (uint16_t)idx[r];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ROUNDS; r++) {
-            if (lo + 64 * r + lane < hi) {
-                key[r] = key_buf[lo + 64 * r + lane];
-                idx[r] = idx_buf[lo + 64 * r + lane];
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < ROUNDS; r++) {
-        const int i = lo + 64 * r + lane;
-        if (i < hi) {
-            order[i] = idx[r];
-            by_cost[i] = items[idx[r]];
-        }
-    }
+    for (int k = 0; k < 2 * kRankWaves; k++) at += part[k][lane];
+    order[at] = i;
+    by_cost[at] = items[i];
 }
 
 // CSR position of the first stored entry of window row r that lies in block slot x or later:
@@ -740,8 +699,8 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         }
         if (nnz > kUnitEntries) {
             st = launch_units((units_made + kSharedPerWave - 1) / kSharedPerWave, [&](int first, unsigned grid) {
-                if (KB == 32) k_shared_blocks<true><<<grid, 64, 0, s>>>(first, V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
-                else k_shared_blocks<false><<<grid, 64, 0, s>>>(first, V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
+                if (KB == 32) k_shared_blocks<<<grid, 64, 0, s>>>(first, V, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
+                else k_shared_blocks_any<<<grid, 64, 0, s>>>(first, V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
             });
             if (st != FS_OK) return st;
         }
@@ -751,9 +710,9 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         k_item_fill<<<grid_for(n_items, 256), 256, 0, s>>>(rec, n_items, slot_ptr, cut_pos, blk_ptr, blk_desc, vec_col, nvec, K, items, cand, split_windows,
                                                            slot_range);
         FS_LAUNCH_CHECK();
-        // launch order: stable radix passes over the keys
-        if (n_items <= kSortSmallMax) {
-            k_item_sort_small<<<1, kSortSmallThreads, 0, s>>>(cand, n_items, items, item_order, items_by_cost);
+        // launch order: a stable sort by the keys
+        if (n_items <= kRankItemsMax) {
+            k_item_rank<<<grid_for(n_items, kRankItems), 64 * kRankWaves, 0, s>>>(cand, n_items, items, item_order, items_by_cost);
             FS_LAUNCH_CHECK();
         } else {
             // cand, upos and cut_pos are free again: keys alternate between cand and upos, the payload between cut_pos and item_order
