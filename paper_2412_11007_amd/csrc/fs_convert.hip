@@ -574,7 +574,7 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     // misc: [0] CSR error flags, [1] vectors, [2] longest item, [3] items with a part of a cut window,
     // [4] block slots, [5] items, [6] partial tiles, [7] cut windows, [8] units -- what the host reads, in one copy
     FS_HIP(hipMemsetAsync(misc, 0, 64 * sizeof(int), s));
-    const UnitPlan up = unit_plan(M, nnz, V);
+    const UnitPlan up = unit_plan(nnz, V);
     const int64_t n_groups = (W + up.group - 1) / up.group;
     const int64_t max_units = units_bound(up, W, nnz);
     const int *n_units = misc + 8;
@@ -582,7 +582,7 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     FS_LAUNCH_CHECK();
     if (W > 0) {
         if ((st = scan_exclusive(group_pos, n_groups, tmp, s, misc + 8)) != FS_OK) return st;
-        k_units_fill<<<grid_for(n_groups, 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
+        k_units_fill<<<grid_for(n_groups * up.group, 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
         FS_LAUNCH_CHECK();
         if (nnz > kUnitEntries) {
             st = launch_units(V <= 8 ? (max_units + 6) / 7 : V <= 16 ? (max_units + 2) / 3 : max_units, [&](int first, unsigned grid) {

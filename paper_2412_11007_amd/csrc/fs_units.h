@@ -7,9 +7,9 @@
 // probe is a cache line (31.4 M entries in eight-row windows: 1.7 ms in two such kernels).  In LDS the V sorted rows of
 // a window are merged pairwise in log2(V) rounds, the neighbours of an entry in the merged
 // order tell which entries share a vector, and a prefix sum over the first ones of each vector is the rank.
-// Those entries (R-MAT of 1 M rows): the whole conversion 2.70 -> 1.17 ms, of which ranking takes 300 us (about thirty
+// Those entries (R-MAT of 1 M rows): the whole conversion 2.70 -> 0.92 ms, of which ranking takes 239 us (about thirty
 // instructions per entry and round: searching the merge paths bounds it, not memory: 260 MB are 50 us) and placing
-// 418 us (0.9 GB, most of it written, 170 us; the LDS tile and scattered two-byte accesses are the rest).
+// 320 us (0.9 GB, most of it written, 170 us; the LDS tile and scattered two-byte accesses are the rest).
 #pragma once
 
 #include <algorithm>
@@ -48,8 +48,10 @@ __device__ __forceinline__ void row_range(const CsrView &a, int64_t i, int32_t &
     hi = min(max(a.rowptr[i + 1], lo), a.nnz);
 }
 
-// How windows become units.  Windows are taken in groups of `group`; a group that fits a unit is one.  The windows of
-// a group that does not fit are units of their own, and a window with more than kUnitEntries entries is cut by columns:
+// How windows become units.  Windows are taken in groups of `group`, as many as have at most kUnitRows rows; a group that fits a
+// unit is one, else its halves are looked at, and so on: a unit is the largest aligned run of 2^k windows that fits.  (With one
+// size of run for the whole matrix, the short windows beside the hubs of a power-law graph were units of their own: R-MAT
+// of 1 M rows, 32 a row, 202 k units of 156 entries, now 100 k of 314: ranking 297 -> 239 us, placing 419 -> 320.)  A window with more than kUnitEntries entries is cut by columns:
 // every `stride`-th entry of a row is a sample, a sample's rank counts the samples of all rows with a smaller
 // (column, row), and the columns of the samples with ranks `per`, 2 per, ... start new pieces.  A piece then
 // spans at most per + V - 1 samples, a row with q of them at most (q + 1) * stride - 1 entries of it: in all fewer than
@@ -57,25 +59,23 @@ __device__ __forceinline__ void row_range(const CsrView &a, int64_t i, int32_t &
 // fit as well, see k_pieces.)
 struct UnitPlan {
     int V, lv;     // rows per window, and log2 of the next power of two
-    int group;     // windows per group
+    int group;     // windows per group, a power of two
     int stride, per;
 };
-inline UnitPlan unit_plan(int64_t M, int64_t nnz, int V)
+inline UnitPlan unit_plan(int64_t nnz, int V)
 {
     UnitPlan p;
     p.V = V;
     p.lv = 0;
     while ((1 << p.lv) < V) p.lv++;
-    const double mean = M > 0 ? (double)nnz * V / (double)M : 0.;  // entries per window
-    p.group = 1;
-    while (p.group < kMaxUnitWindows && ((2 * p.group) << p.lv) <= kUnitRows && 2 * p.group * mean <= 0.7 * kUnitEntries) p.group *= 2;
-    p.stride = V <= 16 ? 8 : 4;
+    p.group = std::min(kMaxUnitWindows, kUnitRows >> p.lv);
+    p.stride = 4;
     p.per = (kUnitEntries / p.stride - 2 * V) * 5 / 6;
     return p;
 }
-// At most this many units, for every V (per * stride >= 208): what the scratch buffer has room for.
+// At most this many units, for every V (per * stride >= 212): what the scratch buffer has room for.
 inline int64_t units_bound(int64_t W, int64_t nnz) { return W + nnz / 208 + 2; }
-// ... and for a plan: a unit per group; of the at most nnz / (kUnitEntries + 1) groups that do not fit one, a unit per window;
+// ... and for a plan: a unit per group; of the at most nnz / (kUnitEntries + 1) groups that do not fit one, at most a unit per window;
 // of a hub window one more per (per * stride) entries.  (Launched for the bound above, a matrix with fewer entries than
 // rows ran mostly empty workgroups: 16 M rows, 1 M entries, four-row windows 3.49 -> 1.09 ms.)
 inline int64_t units_bound(const UnitPlan &p, int64_t W, int64_t nnz)
@@ -95,35 +95,40 @@ fs_status launch_units(int64_t n, Launch launch)
     return FS_OK;
 }
 
-// Pieces of a window of e entries and so many samples (1: it fits a unit).
-__device__ __forceinline__ int pieces_of(const UnitPlan &p, int64_t e, int64_t samples)
+// Units that begin with a window, one window per lane (groups are aligned runs of lanes).  run: windows of the unit, 0 if none
+// begins here; n: 1, or the pieces of a hub window.
+struct WindowUnits {
+    int run, n;
+};
+// first, end: the window's entries (of windows past the last: none, at the matrix' end); samples(): of a hub window, what its rows hold
+template <typename Samples>
+__device__ __forceinline__ WindowUnits window_units(const UnitPlan &p, int k, int32_t first, int32_t end, bool exists, Samples samples)
 {
-    return e <= kUnitEntries ? 1 : (int)max((samples + p.per - 1) / p.per, (int64_t)1);
-}
-__device__ __forceinline__ int window_pieces(const CsrView &a, const UnitPlan &p, int64_t w)
-{
-    int64_t e = 0, samples = 0;
-    for (int r = 0; r < p.V && w * p.V + r < a.M; r++) {
-        int32_t lo, hi;
-        row_range(a, w * p.V + r, lo, hi);
-        e += hi - lo;
-        samples += (hi - lo) / p.stride;
+    WindowUnits x{0, 0};
+    const int lane = threadIdx.x & 63;
+    bool hub = true;
+    for (int run = p.group; run >= 1; run >>= 1) {  // the largest aligned run around the window that fits
+        const int from = lane & -run;
+        const int e = __shfl(end, from + run - 1, 64) - __shfl(first, from, 64);
+        if (hub && e <= kUnitEntries) {
+            hub = false;
+            if (exists && (k & (run - 1)) == 0) x = WindowUnits{run, 1};
+        }
     }
-    return pieces_of(p, e, samples);
+    if (exists && hub) x = WindowUnits{1, (int)max((samples() + p.per - 1) / p.per, (int64_t)1)};
+    return x;
 }
 
-// One thread per group: how many units it becomes, and a check of its row pointers.  Those of the workgroup's 64 groups
-// pass through LDS, so that they are read side by side (16 M rows: 155 us read by each thread for itself, now 36).
-constexpr int kCountThreads = 256;  // that read; the first 64 of them count
+// How many units every group becomes, and a check of the row pointers.  Those of the workgroup's 64 groups pass through LDS,
+// so that they are read side by side (16 M rows: 155 us read by each thread for itself, now 36).
+constexpr int kCountThreads = 256;
 __global__ void __launch_bounds__(kCountThreads) k_units_count(CsrView a, UnitPlan p, int64_t W, int *__restrict__ pos, int *__restrict__ err)
 {
     constexpr int kMost = 64 * kUnitRows + 1;
     __shared__ int32_t rp[kMost + kMost / 32 + 1];
-    auto at = [](int i) -> int { return i + (i >> 5); };  // groups are a power of two apart: spread them over the banks
-    const int64_t g0 = (int64_t)blockIdx.x * 64, g = g0 + threadIdx.x;
-    const int rows = p.group * p.V;  // of a group
-    const int64_t row0 = g0 * rows, left = a.M - row0;
-    const int here = (int)min((int64_t)64 * rows, left);
+    auto at = [](int i) -> int { return i + (i >> 5); };  // windows are often a power of two apart: spread them over the banks
+    const int64_t w0 = (int64_t)blockIdx.x * 64 * p.group, row0 = w0 * p.V;
+    const int here = (int)min((int64_t)64 * p.group * p.V, a.M - row0);
     for (int i0 = threadIdx.x; i0 <= here; i0 += 4 * kCountThreads) {
         int32_t v[4];
 #pragma unroll
@@ -132,62 +137,52 @@ __global__ void __launch_bounds__(kCountThreads) k_units_count(CsrView a, UnitPl
         for (int k = 0; k < 4; k++) rp[at(min(i0 + k * kCountThreads, here))] = v[k];
     }
     __syncthreads();
-    if (threadIdx.x >= 64) return;
-    const int64_t w0 = g * p.group, w1 = min(w0 + p.group, W);
-    if (W == 0 && g == 0 && rp[0] != 0) atomicOr(err, 1);
-    if (w0 >= W) return;
-    int i = threadIdx.x * rows;
-    int32_t last = rp[at(i)];
-    bool bad = last < 0 || (w0 == 0 && last != 0);
-    int64_t total = 0, n = 0;
-    for (int64_t w = w0; w < w1; w++) {
-        int64_t e = 0, samples = 0;
-        for (int r = 0; r < p.V && i < here; r++) {
-            const int32_t next = rp[at(++i)];
-            if (next < last) bad = true;
-            const int32_t lo = min(max(last, 0), a.nnz), len = min(max(next, lo), a.nnz) - lo;  // as row_range has them
-            e += len;
-            samples += len / p.stride;
-            last = next;
-        }
-        total += e;
-        n += pieces_of(p, e, samples);
+    bool bad = w0 == 0 && threadIdx.x == 0 && rp[0] != 0;
+    if (threadIdx.x == 0 && row0 + here == a.M && rp[at(here)] != a.nnz) bad = true;
+    for (int i = threadIdx.x; i < 64 * p.group; i += kCountThreads) {  // (the same for the lanes of a wavefront)
+        const int lo = min(i * p.V, here), hi = min(lo + p.V, here);
+        for (int r = lo; r < hi; r++) bad |= rp[at(r + 1)] < rp[at(r)];
+        const WindowUnits x = window_units(p, i & (p.group - 1), rp[at(lo)], rp[at(hi)], w0 + i < W, [&]() -> int64_t {
+            int64_t n = 0;
+            for (int r = lo; r < hi; r++) n += max(rp[at(r + 1)] - rp[at(r)], 0) / p.stride;
+            return n;
+        });
+        int n = x.n;
+        for (int h = 1; h < p.group; h <<= 1) n += __shfl_xor(n, h, 64);
+        if (w0 + i < W && (i & (p.group - 1)) == 0) pos[(w0 + i) / p.group] = n;  // (of malformed row pointers any number: nothing is made of it)
     }
-    if (last > a.nnz || (w1 == W && last != a.nnz)) bad = true;
     if (bad) atomicOr(err, 1);
-    pos[g] = total <= kUnitEntries ? 1 : (int)n;
 }
 
-// One thread per group again: the records {first window, windows, piece, pieces of the window} of its units, from position
-// pos[group] on (pos = exclusive scan of the counts).  The many records of a hub window are written by the whole
+// One window per thread again: the records {first window, windows, piece, pieces of the window} of the units that begin with it, from
+// position pos[group] on (pos = exclusive scan of the counts).  The many records of a hub window are written by the whole
 // wavefront (a row of 5 M entries, 16 k records: 346 us by one thread, now 10).
 __global__ void __launch_bounds__(256) k_units_fill(CsrView a, UnitPlan p, int64_t W, const int *__restrict__ pos, int4 *__restrict__ units, int *__restrict__ redo, const int *__restrict__ err)
 {
     if (*err & 1) return;
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t w0 = g * p.group, w1 = min(w0 + p.group, W);
-    const int lane = threadIdx.x & 63;
-    int u = 0, n = 0;
-    if (w0 < W) {
-        u = pos[g];
-        n = pos[g + 1] - u;
+    const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63, k = lane & (p.group - 1);
+    const int64_t lo = min(w * p.V, a.M), hi = min(lo + p.V, a.M);
+    const int base = w - k < W ? pos[(w - k) / p.group] : 0;
+    const WindowUnits x = window_units(p, k, a.rowptr[lo], a.rowptr[hi], w < W, [&]() -> int64_t {
+        int64_t n = 0;
+        for (int64_t r = lo; r < hi; r++) n += (a.rowptr[r + 1] - a.rowptr[r]) / p.stride;
+        return n;
+    });
+    int upto = x.n;
+    for (int h = 1; h < p.group; h <<= 1) {
+        const int before = __shfl_up(upto, h, 64);
+        if (k >= h) upto += before;
     }
-    if (n == 1) units[u] = make_int4((int)w0, (int)(w1 - w0), 0, 1);  // it fits (or is one window that does)
-    for (int i = 0; i < p.group && __any(n > 1); i++) {
-        const int64_t w = w0 + i;
-        int np = 0;
-        if (n > 1 && w < w1) {
-            np = window_pieces(a, p, w);
-            redo[w] = 0;
-        }
-        constexpr int kFew = 16;
-        if (np <= kFew)
-            for (int k = 0; k < np; k++) units[u + k] = make_int4((int)w, 1, k, np);
-        for (uint64_t todo = __ballot(np > kFew); todo; todo &= todo - 1) {
-            const int l = __builtin_ctzll(todo), first = __shfl(u, l, 64), many = __shfl(np, l, 64), of = __shfl((int)w, l, 64);
-            for (int k = lane; k < many; k += 64) units[first + k] = make_int4(of, 1, k, many);
-        }
-        u += np;
+    const int u = base + upto - x.n;
+    if (x.n == 1) units[u] = make_int4((int)w, (int)min((int64_t)x.run, W - w), 0, 1);
+    if (x.n > 1) redo[w] = 0;
+    constexpr int kFew = 16;
+    if (x.n > 1 && x.n <= kFew)
+        for (int q = 0; q < x.n; q++) units[u + q] = make_int4((int)w, 1, q, x.n);
+    for (uint64_t todo = __ballot(x.n > kFew); todo; todo &= todo - 1) {
+        const int l = __builtin_ctzll(todo), first = __shfl(u, l, 64), many = __shfl(x.n, l, 64), of = __shfl((int)w, l, 64);
+        for (int q = lane; q < many; q += 64) units[first + q] = make_int4(of, 1, q, many);
     }
 }
 
@@ -422,7 +417,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) k_
     }
     const int4 un = units[u];
     // lane = bit-reversed row * windows + window
-    const int lw = un.y == 1 ? 0 : 31 - __builtin_clz(p.group);
+    const int lw = un.y == 1 ? 0 : 32 - __builtin_clz(un.y - 1);
     const int lr = p.lv + lw;  // log2 of the unit's row slots
     const int wl = lane & ((1 << lw) - 1);
     const int r = p.lv ? (int)(__brev((uint32_t)lane >> lw) >> (32 - p.lv)) : 0;

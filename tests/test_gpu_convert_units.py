@@ -39,6 +39,14 @@ def pattern(kind, V, rng):
         rows = [np.arange(3000)] + [pick(2500, 10000) for _ in range(V - 1)]
     elif kind == "dense start":  # all rows hold the first columns, then thin out
         rows = [np.unique(np.concatenate([np.arange(700), pick(300 * (r % 3 + 1))])) for r in range(2 * V)]
+    elif kind == "runs":  # runs of 1, 2, 4 ... windows that just fit a unit or just do not, hubs between them, a last group cut short
+        group = 64 // (1 << (V - 1).bit_length()) if V > 1 else 16
+        sizes = [0] * group + [512 // group] * group + [512 // group + 1] * group      # a whole group fits, exactly and not
+        sizes += [256, 256] * (group // 2) + [257, 256] * (group // 2)                 # pairs
+        sizes += ([1, 511, 512, 0, 600, 3, 509, 700, 2, 513, 1, 1, 400, 112, 113, 2000] * 2)[:max(group, 3)]
+        sizes += [5] * (group // 2 + 1)
+        for n in sizes:
+            rows += [pick((n + V - 1 - r) // V) for r in range(V)]
     elif kind == "few":  # units of 0 to 70 entries: up to 64 an entry has a lane of its own; many share a column
         group = 1
         while group < 16 and (2 * group) * V <= 64:
@@ -52,7 +60,7 @@ def pattern(kind, V, rng):
 
 
 @pytest.mark.parametrize("V,KB", [(1, 32), (2, 32), (4, 32), (8, 32), (16, 32), (32, 32), (3, 8), (8, 5)])
-@pytest.mark.parametrize("kind", ["edges", "alike", "one long row", "identical", "apart", "dense start", "few", "tiny"])
+@pytest.mark.parametrize("kind", ["edges", "alike", "one long row", "identical", "apart", "dense start", "runs", "few", "tiny"])
 def test_convert_units_bit_exact(fs, kind, V, KB):  # noqa: F811
     A = pattern(kind, V, np.random.default_rng(V * 100 + KB))
     rp, ci, va = upload_csr(A)
