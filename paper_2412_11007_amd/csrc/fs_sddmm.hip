@@ -108,11 +108,14 @@ __device__ __forceinline__ bool fs_sddmm_unit(const int4 *__restrict__ items, in
 }
 
 // d > 32.  KS = 32-feature steps of the contraction per chunk of 32 * KS features (one chunk for d <= 32 * KS, else d is
-// walked in several); BB = blocks per step, BB * KS = 4: a step gathers its rows in eight wave-wide loads.
+// walked in several); BB = blocks per step, BB * KS = 4: a step gathers its rows in eight wave-wide loads.  KS = 8 (BB = 1)
+// gathers whole rows of up to 512 bytes in sixteen: the two halves of a row are not fetched at different times, and blocks of
+// one window keep their rows of X, which chunks read anew (lognormal graph of 262 k rows, d = 256: 421 -> 382 us, 7.0 TB/s
+// of rows that miss the L2s; see the launch for where it is used).
 // CSR: also (or only) write the scores in CSR order; kept out of the plain instantiation, whose registers it
 // would cost.  BIG: X or Y spans 4 GiB or more.
 template <int DT, int V, int KS, int BB, bool CHUNKS, bool BIG, bool CSR>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(KS > 4 ? 2 : 4)))
 k_sddmm(const int4 *__restrict__ items, int n_items, int slice, int n_swz, int n_blocks, int G, const int4 *__restrict__ blk_desc,
         const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ row_bits, int nvec,
         const uint16_t *__restrict__ X, int64_t ldx, const uint16_t *__restrict__ Y, int64_t ldy, int d,
@@ -385,6 +388,12 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
                      ldy * 2 >= ((int64_t)1 << 24) || f->K * ldy * 2 >= ((int64_t)1 << 32) ||
                      (f->M + 32) * ldx * 2 >= ((int64_t)1 << 32);
     const fs_launch_geometry geo = fs_launch_geometry_for(f, 1);
+    // 128 < d <= 256: whole rows at a time where there are blocks for the fewer wavefronts that fit then, else in chunks of 128
+    // features.  Chunks / whole rows, us, d = 136, 168, 200, 256: lognormal graph of 262 k rows (196 k blocks) 332 / 284,
+    // 398 / 326, 466 / 376, 421 / 382; R-MAT of 262 k rows (in launch order) 138 / 149, 154 / 149, 189 / 156, 227 / 169; lognormal graph of
+    // 20 k rows (14 k blocks) 21 / 23, 26 / 25, 32 / 27, 33 / 29; stencil 500^2 49 / 49, 63 / 51, 79 / 57, 80 / 71; R-MAT of 8 k rows
+    // (3 k blocks) 7 / 9 at any width.  Up to d = 160 the second chunk is little work, and only rows that mostly miss the L2s gain.
+    const bool wide = n_blocks >= 8192 && (d > 160 || (!ordered && f->K * d * 2 > ((int64_t)8 << 20)));
     const dim3 grid(ordered ? (unsigned)geo.nbx : (unsigned)(((int64_t)n_blocks + G - 1) / G)), block(64);
 #define FS_SDDMM_ARGS items, (int)f->n_items, geo.slice, geo.n_swz, n_blocks, G, (const int4 *)f->blk_desc, f->vec_col, f->blk_row_bits, (int)f->nvec, X, ldx, Y, ldy, (int)d, out, f->M, out_csr, f->blk_row_base
 #define FS_SDDMM_LAUNCH(...)  /* the kernel and its first template arguments */                         \
@@ -400,6 +409,7 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
     if (d <= 32) FS_SDDMM_LAUNCH(k_sddmm_short<DT, V)
     else if (d <= 64) FS_SDDMM_LAUNCH(k_sddmm<DT, V, 2, 2, false)
     else if (d <= 128) FS_SDDMM_LAUNCH(k_sddmm<DT, V, 4, 1, false)
+    else if (d <= 256 && wide) FS_SDDMM_LAUNCH(k_sddmm<DT, V, 8, 1, false)
     else FS_SDDMM_LAUNCH(k_sddmm<DT, V, 4, 1, true)
 #undef FS_SDDMM_LAUNCH
 #undef FS_SDDMM_ARGS

@@ -65,3 +65,32 @@ def test_sddmm_block_order(fs, kind, V, dtype, d):  # noqa: F811
     Xd, Yd = to_dev(X.bits, dtype), to_dev(Y.bits, dtype)
     same_bits(from_dev_bits(fs.fs_blk_to_csr(fmt, fs.fs_sddmm(fmt, Xd, Yd))), want, "fs_sddmm")
     same_bits(from_dev_bits(fs.fs_sddmm(fmt, Xd, Yd, blocked=False)), want, "fs_sddmm, CSR order")
+
+
+@pytest.mark.parametrize("d", [136, 160, 168, 232, 256])
+@pytest.mark.parametrize("V", [4, 8, 16])
+@pytest.mark.parametrize("ordered", [False, True])
+def test_sddmm_whole_rows(fs, ordered, V, d):  # noqa: F811
+    """Enough blocks for rows of up to 512 bytes to be gathered whole: short windows, hubs of many blocks whose rows of X stay,
+    empty windows between them, a last window of fewer than V rows; in slot order and in launch order."""
+    import torch
+    dtype = "bf16" if (d // 8 + V // 4) % 2 else "f16"
+    rng = stream(V + d, 94, 1)
+    K, hubs, n, short = (60000, 5 * V, 60000, 0) if ordered else (30000, V, 700, 8300 * V)  # ordered: 9375 blocks
+    rows = [np.full(n, i) for i in range(hubs)] + [hubs + 3 * V + np.arange(short)]
+    cols = [rng.choice(K, size=n, replace=False) if not ordered else np.arange(n) for _ in range(hubs)] + [rng.integers(0, K, size=short)]
+    if not ordered:
+        rows.append(hubs + 3 * V + np.arange(short))
+        cols.append(rng.integers(0, K, size=short))
+    A = csr_from_coo(hubs + 3 * V + short + 3, K, np.concatenate(rows), np.concatenate(cols), "u11", dtype, rng)
+    lim = 1 if dtype == "bf16" else 2
+    X = Dense(halves(stream(V + d, 94, 2), (A.M, d), -lim, lim, dtype), dtype)
+    Y = int_dense(K, d, dtype, seed=V + d, tid=5, lim=lim)
+    ref, _ = oracle.sddmm(A.M, A.K, A.rowptr, A.colidx, X.bits, Y.bits, dtype, want_scale=False)
+    want = oracle.round_f64_to_bits(ref, dtype)
+    rp, ci, _ = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, None, A.M, A.K, torch_dtype=torch.float16 if dtype == "f16" else torch.bfloat16, V=V, chunk=64)
+    assert fmt.n_blocks >= 8192 and (fmt.n_items >= 4096 and fmt.n_cut_items * 8 >= fmt.n_items) == ordered, (fmt.n_blocks, fmt.n_items, fmt.n_cut_items)
+    Xd, Yd = to_dev(X.bits, dtype), to_dev(Y.bits, dtype)
+    same_bits(from_dev_bits(fs.fs_blk_to_csr(fmt, fs.fs_sddmm(fmt, Xd, Yd))), want, "fs_sddmm")
+    same_bits(from_dev_bits(fs.fs_sddmm(fmt, Xd, Yd, blocked=False)), want, "fs_sddmm, CSR order")
