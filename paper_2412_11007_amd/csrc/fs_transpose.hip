@@ -205,7 +205,7 @@ TransposePlan plan_transpose(int64_t M, int64_t K, int64_t nnz)
     const size_t e = fs_align_up((size_t)nnz, 64), counts = (size_t)sort_groups(std::max<int64_t>(nnz, 1)) << std::max(8, p.bits[0]);
     size_t o = 0;
     p.key0 = o; o += e;
-    p.key1 = o; o += p.rows ? 0 : e;
+    p.key1 = o; o += e;  // not used where rows travel: the size for nnz entries is at least 12 bytes each whatever M and K are
     p.val1 = o; o += e;
     p.hist = o; o += fs_align_up(counts + 1, 64);
     p.tmp = o; o += scan_tmp_ints((int64_t)counts);
