@@ -261,7 +261,7 @@ static fs_status attention_call(const fs_format *fmt, const void *d_X, int64_t l
     if (!(scale == scale) || scale - scale != 0.f) return FS_ERR_INVALID_ARG;  // NaN, infinity
     if (!kernels_support(fmt) || d > 128) return FS_ERR_UNSUPPORTED;
     if (N == 0 || fmt->M == 0) return FS_OK;
-    if (!d_X || !d_Y || !d_H || !d_out) return FS_ERR_INVALID_ARG;
+    if ((fmt->n_items > 0 && !fmt->blk_row_bits) || !d_X || !d_Y || !d_H || !d_out) return FS_ERR_INVALID_ARG;
     if (d % 8 || N % 8 || ldx % 8 || ldy % 8 || ldh % 8 || ldo % 8 || !aligned(d_X, 16) || !aligned(d_Y, 16) ||
         !aligned(d_H, 16) || !aligned(d_out, 16))
         return FS_ERR_INVALID_ARG;

@@ -764,7 +764,7 @@ extern "C" fs_status fs_csr_to_blk(const fs_format *fmt, const void *d_vals_csr,
     if (!d_out_blk || ((uintptr_t)d_out_blk & 15) || (fmt->nnz > 0 && !d_vals_csr)) return FS_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     uint16_t *out = (uint16_t *)d_out_blk;
-    if (fmt->KB == 32 && fmt->blk_row_bits && (fmt->V == 4 || fmt->V == 8 || fmt->V == 16)) {
+    if (fmt->KB == 32 && fmt->blk_desc && fmt->blk_row_bits && fmt->blk_row_base && (fmt->V == 4 || fmt->V == 8 || fmt->V == 16)) {
         const int nb = (int)fmt->n_blocks;
         const unsigned grid = grid_for(nb, 8 * 16 / fmt->V);  // four wavefronts of two rounds
 #define FS_TILES(V_) k_csr_to_tiles<V_><<<grid, 256, 0, s>>>((const int4 *)fmt->blk_desc, nb, fmt->blk_row_bits, fmt->blk_row_base, (const uint16_t *)d_vals_csr, (int)fmt->nnz, out)

@@ -130,6 +130,19 @@ def test_size_queries_reject_bad_arguments_without_a_gpu(fs):
     assert lib.fs_edge_softmax_workspace_bytes(ctypes.byref(f), ctypes.byref(n)) == 0 and n.value == 3 * 2 * 8 * 4
 
 
+def test_attention_refuses_a_format_without_row_occupancies(fs):
+    """The kernel reads blk_row_bits: without it the call is refused on the host, before any launch."""
+    from paper_2412_11007_amd.binding import _FsFormatStruct
+    lib = fs.load_library()
+    f = _FsFormatStruct()
+    f.M = f.K = 8
+    f.V, f.KB, f.chunk, f.nvec, f.n_items, f.n_blocks = 8, 32, 256, 1, 1, 1
+    for name in ("items", "items_by_cost", "win_ptr", "blk_desc", "vec_col", "vec_mask"):
+        setattr(f, name, 4096)  # never read
+    for call in (lib.fs_attention, lib.fs_sddmm_spmm):
+        assert call(ctypes.byref(f), 4096, 8, 4096, 8, 8, 1.0, 4096, 8, 8, 4096, 8, None, 0, None) == 1
+
+
 def test_product_package_does_not_touch_the_oracle():
     pkg = os.path.join(ROOT, "paper_2412_11007_amd")
     for dirpath, _, files in os.walk(pkg):
