@@ -143,7 +143,7 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
     };
     // Rows of Y.  Matrix row i of tile t is vector 8*(i/4) + 4t + (i%4) of the block.  In operand layout register t*KS + ks holds
     // step ks of row j of tile t; row by row, register k holds the lane's piece of row p = k*YRPI + lane/YLPR, which is
-    // matrix row p%16 of tile p/16.  (Pieces past d repeat the row's last one and meet a zero X operand.)
+    // matrix row p%16 of tile p/16.  (Pieces past d repeat the row's last one.)
     auto vector_of = [](int p) -> int { return 8 * ((p & 15) >> 2) + 4 * (p >> 4) + (p & 3); };
     uint32_t yoff[YL ? NY : 2];
     fs_u4 yg[NY];
@@ -242,6 +242,9 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
                 for (int ks = 0; ks < KS; ks++) {
                     fs_frag y;
                     y.u = YL ? *reinterpret_cast<const fs_u4 *>(y_rd + 16 * t * RSY + 64 * ks) : yg[t * KS + ks];
+                    // what stands in for features past d is zero on both sides: 0 * inf would make the score NaN.  (Steps
+                    // in the first half are whole, d > 16 * KS; for d < 32 features are taken to be finite.)
+                    if (2 * ks >= KS && KS > 1 && !f_ok[ks]) y.u = fs_u4{0u, 0u, 0u, 0u};
                     sc[t] = fs_mfma_16x16x32<DT>(y, xf[ks], sc[t]);
                 }
             }

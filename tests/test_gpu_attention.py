@@ -262,3 +262,30 @@ def test_attention_pass_widths_and_feature_steps(fs, V, d):
         part = Hd[:, :N].contiguous()
         assert torch.equal(fs.fs_attention(fmt, Xd, Yd, part, scale=d ** -0.5).view(torch.int16), full[:, :N]), N
         assert torch.equal(fs.fs_sddmm_spmm(fmt, Xd, Yd, part).view(torch.int16), fused[:, :N]), N
+
+
+@pytest.mark.parametrize("d", [40, 56, 64, 72, 96, 104, 128])
+@pytest.mark.parametrize("N", [64, 136])
+def test_attention_of_an_infinite_feature(fs, d, N):
+    """A feature of -inf in the first or the last eight of a row of Y: its scores with queries above zero are -inf, so the
+    weights are zero and the result is that of the matrix without these entries, whatever the kernel reads in the place of
+    features past d."""
+    rng = np.random.default_rng(d + N)
+    M, K = 61, 90
+    cols = [np.sort(rng.choice(K, size=int(n), replace=False)) for n in rng.integers(12, 60, M)]
+    A = csr_from_coo(M, K, np.repeat(np.arange(M), [c.shape[0] for c in cols]), np.concatenate(cols), "n01", "f16", rng)
+    X = dense(M, d, "u01", "f16", stream(13, 60, d))
+    X.bits[X.bits == 0] = 0x3C00  # (0 * -inf is no number: all queries are above zero)
+    Y = dense(K, d, "n01", "f16", stream(13, 61, d))
+    H = dense(K, N, "n01", "f16", stream(13, 62, N))
+    hit = np.arange(0, K, 9)
+    Y.bits[hit, np.where(np.arange(hit.shape[0]) % 2, d - 1 - hit % 8, hit % 8)] = 0xFC00  # -inf
+    keep = ~np.isin(A.colidx, hit)
+    rowptr = np.concatenate([[0], np.cumsum(keep)])[A.rowptr].astype(np.int32)
+    clean = Y.bits.copy()
+    clean[hit] = 0
+    ref, S = oracle.attention(M, K, rowptr, np.ascontiguousarray(A.colidx[keep]), X.bits, clean, H.bits, "f16", 0.2)
+    for V in (4, 8, 16):
+        fmt = convert(fs, A, V, 32)
+        got = fs.fs_attention(fmt, to_dev(X.bits, "f16"), to_dev(Y.bits, "f16"), to_dev(H.bits, "f16"), scale=0.2)
+        assert scaled_error(from_dev_bits(got), ref, S, "f16") <= bar("f16"), V
