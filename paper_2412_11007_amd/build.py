@@ -35,6 +35,7 @@ def build_library(verbose: bool = False, defines=(), lib: str = LIB) -> str:
     os.makedirs(obj_dir, exist_ok=True)
     flags = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
              "-I" + os.path.join(ROOT, "include"),
+             "-Werror=dangling-else",  # after an `if`, a macro that begins with another
              # keep the compiler from forming packed-fp32 instructions
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"] + ["-D" + d for d in defines]
     objs = [os.path.join(obj_dir, s.replace(".hip", ".o")) for s in SOURCES]

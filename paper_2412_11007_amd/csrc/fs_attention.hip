@@ -162,13 +162,15 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
         }, std::make_integer_sequence<int, YL ? NY : 2>{});                                      \
     }
 #define FS_YGATHER()                                                                             \
-    if constexpr (YL) {                                                                          \
-        _Pragma("unroll") for (int k = 0; k < NY; k++)                                           \
-            yg[k] = *reinterpret_cast<const fs_u4 *>(Yb + yoff[YL ? k : 0]);                     \
-    } else {                                                                                     \
-        _Pragma("unroll") for (int t = 0; t < 2; t++)                                            \
-            _Pragma("unroll") for (int ks = 0; ks < KS; ks++)                                    \
-                yg[t * KS + ks] = *reinterpret_cast<const fs_u4 *>(Yb + yoff[t] + f_off[ks]);    \
+    {                                                                                            \
+        if constexpr (YL) {                                                                      \
+            _Pragma("unroll") for (int k = 0; k < NY; k++)                                       \
+                yg[k] = *reinterpret_cast<const fs_u4 *>(Yb + yoff[YL ? k : 0]);                 \
+        } else {                                                                                 \
+            _Pragma("unroll") for (int t = 0; t < 2; t++)                                        \
+                _Pragma("unroll") for (int ks = 0; ks < KS; ks++)                                \
+                    yg[t * KS + ks] = *reinterpret_cast<const fs_u4 *>(Yb + yoff[t] + f_off[ks]); \
+        }                                                                                        \
     }
     // rows of H this lane gathers for a block, as 32-bit byte offsets
     uint32_t grow[NLD];
