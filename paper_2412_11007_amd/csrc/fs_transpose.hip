@@ -202,10 +202,12 @@ TransposePlan plan_transpose(int64_t M, int64_t K, int64_t nnz)
     }
     p.row_shift = bits - p.bits[0];
     p.rows = p.passes <= 2 && p.row_shift + bits_of(std::max<int64_t>(M, 1)) <= 32;
-    const size_t e = fs_align_up((size_t)nnz, 64), counts = (size_t)sort_groups(std::max<int64_t>(nnz, 1)) << std::max(8, p.bits[0]);
+    // The room is that of the widest digits and of the most groups that so many entries or fewer make: its size depends on
+    // nnz alone and never goes down as nnz goes up, so that a buffer for the largest of several matrices serves them all.
+    const size_t e = fs_align_up((size_t)nnz, 64), counts = (size_t)sort_groups_bound(std::max<int64_t>(nnz, 1)) << kMaxDigitBits;
     size_t o = 0;
     p.key0 = o; o += e;
-    p.key1 = o; o += e;  // not used where rows travel: the size for nnz entries is at least 12 bytes each whatever M and K are
+    p.key1 = o; o += e;  // (not used where rows travel)
     p.val1 = o; o += e;
     p.hist = o; o += fs_align_up(counts + 1, 64);
     p.tmp = o; o += scan_tmp_ints((int64_t)counts);

@@ -111,6 +111,25 @@ def test_transpose_scratch_size(fs):
     assert lib.fs_csr_transpose_bytes(1, 1, 1, None) == 1
 
 
+def test_transpose_scratch_of_a_larger_matrix_serves_a_smaller_one(fs):
+    """The size depends on the number of entries alone and never goes down as it goes up, over every step of the sort: the
+    length of a tile, the digits of a pass, the forms with and without rows in the keys."""
+    lib = fs.load_library()
+
+    def need(M, K, nnz):
+        n = ctypes.c_size_t(0)
+        assert lib.fs_csr_transpose_bytes(M, K, nnz, ctypes.byref(n)) == 0
+        return n.value
+    shapes = [(1000, 1), (1000, 256), (1000, 1024), (1000, 1025), (1000, 2048), (7, 1 << 20), (7, (1 << 20) + 1), (1 << 30, 1 << 20), (9, (1 << 31) - 5000)]
+    steps = [k << s for s in range(7, 28) for k in (1, 2, 3, 4, 5, 6, 7)]
+    sizes = sorted({max(n + o, 0) for n in steps for o in (-1, 0, 1)})
+    last = 0
+    for nnz in sizes:
+        got = {need(M, K, nnz) for M, K in shapes}
+        assert len(got) == 1 and min(got) >= last, (nnz, last, got)
+        last = max(got)
+
+
 def test_size_queries_reject_bad_arguments_without_a_gpu(fs):
     """The size queries are pure host code: they must answer (or refuse) with no device present."""
     from paper_2412_11007_amd.binding import _FsFormatStruct
