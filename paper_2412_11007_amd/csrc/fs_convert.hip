@@ -322,7 +322,6 @@ __global__ void __launch_bounds__(256) k_csr_to_tiles(const int4 *__restrict__ b
     const int lane = threadIdx.x & 63;
     uint2 *sel = sels[threadIdx.x >> 6];
     fs_expand_table(sel, lane);
-    FS_WAVE_SYNC();
     uint16_t *tile = tiles[threadIdx.x >> 6];
     const int g = lane & 3, j = (lane >> 2) % V, b = (lane >> 2) / V;
     const int x0 = (int)((blockIdx.x * 4 + (threadIdx.x >> 6)) * (PER * ROUNDS));

@@ -36,7 +36,8 @@ typedef fs_u4 fs_u4_unaligned __attribute__((aligned(2)));
 // A lane's stored values -> eight positions of its row.  `raw` holds the values back to back (halfword 0 first), bit x of m8
 // says whether position x is stored: stored positions take the next halfword, the others +0.0.  Entry m of sel[16], a table in
 // LDS, holds the byte selectors that spread values over four positions with occupancy m, so that four v_perm_b32 make the
-// eight (about 20 instructions, where shifting and selecting value by value took 80).
+// eight (about 20 instructions, where shifting and selecting value by value took 80).  The table is filled by sixteen lanes and
+// read by all, so the fence that orders the two is part of filling it.
 __device__ __forceinline__ void fs_expand_table(uint2 *sel, int lane)
 {
     if (lane < 16) {
@@ -45,6 +46,7 @@ __device__ __forceinline__ void fs_expand_table(uint2 *sel, int lane)
         for (int e = 0; e < 4; e++) h[e] = (lane >> e) & 1 ? __popc(lane & ((1 << e) - 1)) * 0x0202u + 0x0100u : 0x0C0Cu;  // 0x0C: a zero byte
         sel[lane] = make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
     }
+    FS_WAVE_SYNC();
 }
 __device__ __forceinline__ fs_u4 fs_expand8(fs_u4 raw, uint32_t m8, const uint2 *sel)
 {
