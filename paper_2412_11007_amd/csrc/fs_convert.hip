@@ -763,7 +763,13 @@ extern "C" fs_status fs_csr_to_blk(const fs_format *fmt, const void *d_vals_csr,
     if (!d_out_blk || ((uintptr_t)d_out_blk & 15) || (fmt->nnz > 0 && !d_vals_csr)) return FS_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     uint16_t *out = (uint16_t *)d_out_blk;
-    if (fmt->KB == 32 && fmt->blk_desc && fmt->blk_row_bits && fmt->blk_row_base && (fmt->V == 4 || fmt->V == 8 || fmt->V == 16)) {
+    // By blocks a row slot costs the same whether its row holds an entry or not, entry by entry only entries do.  Entry by entry /
+    // by blocks, us, four- / eight- / sixteen-row windows: 4 M rows, 1 M entries 7 / 42, 9.5 / 41, 14 / 40; 4 M rows, 4 M 20 / 45,
+    // 29 / 46, 49 / 47; 1 M rows, 1 M 7 / 13.5, 10 / 14, 15.4 / 15.1; 1 M rows, 2 M 12 / 14, 16 / 15, 25 / 16; 1 M rows, 3 M 16 / 15,
+    // 22 / 16, 35 / 26: the line is at about eleven entries a block.  Below 640 k row slots launches are the time, and
+    // three cost more than one (200 k rows with one entry each 7.3 / 4.8).
+    const bool few = fmt->V * fmt->n_blocks > 640 * 1024 && fmt->nnz < 11 * fmt->n_blocks && fmt->csr_to_slot;
+    if (!few && fmt->KB == 32 && fmt->blk_desc && fmt->blk_row_bits && fmt->blk_row_base && (fmt->V == 4 || fmt->V == 8 || fmt->V == 16)) {
         const int nb = (int)fmt->n_blocks;
         const unsigned grid = grid_for(nb, 8 * 16 / fmt->V);  // four wavefronts of two rounds
 #define FS_TILES(V_) k_csr_to_tiles<V_><<<grid, 256, 0, s>>>((const int4 *)fmt->blk_desc, nb, fmt->blk_row_bits, fmt->blk_row_base, (const uint16_t *)d_vals_csr, (int)fmt->nnz, out)
@@ -774,7 +780,7 @@ extern "C" fs_status fs_csr_to_blk(const fs_format *fmt, const void *d_vals_csr,
         FS_LAUNCH_CHECK();
         return FS_OK;
     }
-    // other block widths and window heights: clear the array, then place entry by entry
+    // few entries, other block widths and window heights: clear the array, then place entry by entry
     const int64_t n16 = n / 8;  // whole 16-byte pieces; fill kernels, not memset nodes, so the call can be captured
     if (n16 > 0) {
         k_zero16<<<(unsigned)std::min<int64_t>((n16 + 255) / 256, 65536), 256, 0, s>>>((fs_u4 *)out, n16);

@@ -537,6 +537,24 @@ def test_new_values_block_edges(fs, M, K, density, V):
     assert (out[n:] == 7).all()
 
 
+@pytest.mark.parametrize("V", [4, 8, 16])
+@pytest.mark.parametrize("blocks,less", [(0, 0), (1, 0), (1, 1)])
+def test_new_values_of_few_entries(fs, V, blocks, less):
+    """Either side of the rule that places few entries one by one: row slots (640 k), and eleven entries a block.  Bit for bit what
+    the conversion wrote, zeros included, whatever the array held before."""
+    import torch
+    W = 640 * 1024 // V + blocks
+    n, M, K = 11 * W - less, W * V, 100
+    rows = np.arange(n, dtype=np.int64) * M // n  # at most three in a row, one to eleven columns apart
+    A = csr_from_coo(M, K, rows, np.arange(n) % K, "n01", "f16", np.random.default_rng(V))
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, M, K, V=V)
+    assert fmt.n_blocks == W and fmt.nnz == n
+    out = torch.full((V * fmt.nvec,), 7.0, dtype=torch.float16, device="cuda")
+    fs.fs_csr_to_blk(fmt, va, out=out)
+    assert torch.equal(out.view(torch.int16), fmt.vals_blk_t().view(torch.int16))
+
+
 def test_gather_probe_runs_and_checks_arguments(fs):
     """The measurement aid reads what fs_spmm reads: it must accept the same operands, write its sink and
     refuse a sink that is too small."""
