@@ -98,27 +98,60 @@ __global__ void k_gather16(const uint16_t *__restrict__ src, const int32_t *__re
     if (i < n) dst[i] = src[idx[i]];
 }
 
-// The same for a source that an XCD's L2 does not hold, where nearly every element would be a missed line (5.3 M elements through
-// a random permutation: 61 us, 24 from a source of 2 MB).  A workgroup sorts its 4096 indices by band of the source (2^shift
-// elements, the last band open) in LDS and loads in that order, one load in flight per lane, so that all wavefronts
-// pass through the bands at about one pace and a band is in every L2 while it is read: 40 us.  (With all sixteen loads
-// issued at once the oldest wavefronts run ahead through all bands, and nothing is gained.)  From the first workgroup on that
-// has to wait for a place on the chip (8.4 M elements) the pace is lost, bit by bit.
+// The same where there are many indices.  If a source is more than an XCD's L2 holds, nearly every element is a missed line
+// (5.3 M elements through a random permutation: 61 us, 24 from a source of 2 MB).  A workgroup then sorts its 4096 indices by
+// band of the source (2^shift elements, the last band open) in LDS and loads in that order, one load in flight per lane, so
+// that all wavefronts pass through the bands at about one pace and a band is in every L2 while it is read: 40 us.  (With all
+// sixteen loads issued at once the oldest wavefronts run ahead through all bands, and nothing is gained.)  From the first workgroup
+// on that has to wait for a place on the chip (8.4 M elements) the pace is lost, bit by bit.
+// PEEK: every wavefront first looks at 64 of its indices; where they, and those of the workgroup's other wavefronts, lie close
+// together (a mesh' permutation, a short source, a copy), all are loaded as they come.  Permutation of a 1024^2 mesh, 5.2 M: one
+// element a thread 13.2 us, sorted 16.6, as they come 10.9; 3 M indices into 512 KB 13.5, 16.9 and 14.6.
 constexpr int kBands = 16, kBandEach = 16, kBandThreads = 256;
+constexpr uint32_t kNear = 5u << 18;  // elements: all indices into 2.5 MB are close together
+template <bool PEEK>
 __global__ void __launch_bounds__(kBandThreads) __attribute__((amdgpu_waves_per_eu(8))) k_gather16_banded(const uint16_t *__restrict__ src, const int32_t *__restrict__ idx, int64_t n, int shift,
                                                                   uint16_t *__restrict__ dst)
 {
     constexpr int kWaves = kBandThreads / 64, kAll = kBandThreads * kBandEach;
     __shared__ uint32_t stage[kAll];
     __shared__ uint16_t cur[kBands * kWaves];  // band-major
+    __shared__ uint2 seen[PEEK ? kWaves : 1];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t base = (int64_t)blockIdx.x * kAll;
     const int left = (int)std::min<int64_t>(n - base, kAll);
     idx += base;
     dst += base;
+    const auto index = [&](int e) -> uint32_t {
+        return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(idx) + 4u * (uint32_t)std::min((w * kBandEach + e) * 64 + lane, left - 1));
+    };
+    const auto element = [&](uint32_t i) -> uint16_t { return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(src) + i * 2u); };
+    if constexpr (PEEK) {
+        const uint32_t some = index(0), one = (uint32_t)__builtin_amdgcn_readfirstlane((int)some);
+        const bool wide = __any(std::max(some, one) - std::min(some, one) > kNear);
+        if (lane == 0) seen[w] = make_uint2(wide ? 0u : one, wide ? ~0u : one);
+        __syncthreads();
+        uint2 range = seen[0];
+#pragma unroll
+        for (int k = 1; k < kWaves; k++) range = make_uint2(std::min(range.x, seen[k].x), std::max(range.y, seen[k].y));
+        if (range.y - range.x <= kNear) {  // the same for the workgroup
+            uint32_t at[kBandEach];
+            uint16_t v[kBandEach];
+#pragma unroll
+            for (int e = 0; e < kBandEach; e++) at[e] = index(e);
+#pragma unroll
+            for (int e = 0; e < kBandEach; e++) v[e] = element(at[e]);
+            const uint32_t first = (uint32_t)(w * kBandEach * 64 + lane);
+            const int last = left - 1 - (int)first;
+#pragma unroll
+            for (int e = 0; e < kBandEach; e++)
+                if (e * 64 <= last) dst[first + e * 64] = v[e];
+            return;
+        }
+    }
     uint32_t at[kBandEach], slot[kBandEach];
 #pragma unroll
-    for (int e = 0; e < kBandEach; e++) at[e] = (uint32_t)idx[(uint32_t)std::min((w * kBandEach + e) * 64 + lane, left - 1)];
+    for (int e = 0; e < kBandEach; e++) at[e] = index(e);
     if (lane < kBands) cur[lane * kWaves + w] = 0;
     FS_WAVE_SYNC();
     const uint64_t below = ((uint64_t)1 << lane) - 1;
@@ -158,7 +191,7 @@ __global__ void __launch_bounds__(kBandThreads) __attribute__((amdgpu_waves_per_
     for (int k = 0; k < kBandEach; k++) at[k] = stage[k * kBandThreads + threadIdx.x];
 #pragma unroll
     for (int k = 0; k < kBandEach; k++) {
-        v[k] = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(src) + at[k] * 2u);
+        v[k] = element(at[k]);
         if (k + 1 < kBandEach) asm volatile("" : "+v"(at[k + 1]) : "v"((uint32_t)v[k]));  // the next address only once this element is here
     }
     __syncthreads();
@@ -300,14 +333,18 @@ extern "C" fs_status fs_gather16(const void *d_src, const int32_t *d_idx, int64_
     if (n < 0) return FS_ERR_INVALID_ARG;
     if (n == 0) return FS_OK;
     if (!d_src || !d_idx || !d_dst) return FS_ERR_INVALID_ARG;
-    // The source's size is not known; for a permutation it is n.  Plain / banded, us: 2 M elements 12.8 / 15, 3 M 23.7 / 19.8,
-    // 4.2 M 43 / 26.5, 8 M 108 / 77, 20 M 334 / 294, 60 M 1098 / 1084.
-    if (n > ((int64_t)5 << 19) && n <= ((int64_t)1 << 25)) {
-        const int shift = n <= (int64_t)kBands << 19 ? 19 : 20;  // bands of 1 or 2 MB
-        k_gather16_banded<<<grid_of(n, kBandThreads * kBandEach), kBandThreads, 0, (hipStream_t)stream>>>((const uint16_t *)d_src, d_idx, n, shift, (uint16_t *)d_dst);
-    } else {
-        k_gather16<<<grid_of(n, 256), 256, 0, (hipStream_t)stream>>>((const uint16_t *)d_src, d_idx, n, (uint16_t *)d_dst);
-    }
+    // One element a thread / sorted by band, a random permutation, us: 2 M elements 12.8 / 15, 3 M 23.7 / 19.8, 4.2 M 43 / 26.5,
+    // 8 M 108 / 77, 20 M 334 / 294, 30 M 524 / 485.  A graph's permutation, in which neighbours come by again soon, gains less: R-MAT
+    // of 512 k rows, 8 M 57 / 55; of 1 M rows, 31 M 298 / 360.
+    // A look at the indices first costs nothing where all workgroups start at once on an idle memory (5.3 M random 38.2 / 38.1), and a
+    // round trip through a busy one where they do not (10 M random 108 / 122); without it 8 M indices in order take 21 us for 18.
+    const unsigned grid = grid_of(n, kBandThreads * kBandEach);
+    const int shift = n <= (int64_t)kBands << 19 ? 19 : 20;  // bands of 1 or 2 MB
+    const uint16_t *src = (const uint16_t *)d_src;
+    uint16_t *dst = (uint16_t *)d_dst;
+    if (n > ((int64_t)5 << 19) && n <= ((int64_t)3 << 21)) k_gather16_banded<true><<<grid, kBandThreads, 0, (hipStream_t)stream>>>(src, d_idx, n, shift, dst);
+    else if (n > ((int64_t)5 << 19) && n <= ((int64_t)5 << 22)) k_gather16_banded<false><<<grid, kBandThreads, 0, (hipStream_t)stream>>>(src, d_idx, n, shift, dst);
+    else k_gather16<<<grid_of(n, 256), 256, 0, (hipStream_t)stream>>>(src, d_idx, n, dst);
     FS_LAUNCH_CHECK();
     return FS_OK;
 }

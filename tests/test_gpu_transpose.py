@@ -177,6 +177,25 @@ def test_gather16_bands(fs, n, source):
     assert torch.equal(got.view(torch.int16), src[1:][(idx[1:] - (idx[1:] > 0).int()).long()])
 
 
+@pytest.mark.parametrize("n", [(5 << 19) + 1, (5 << 19) + 4096, 3 << 21, (3 << 21) + 1, 5 << 22, (5 << 22) + 1])
+@pytest.mark.parametrize("order", ["in order", "backwards", "mesh", "half"])
+def test_gather16_close_indices(fs, n, order):
+    """Either side of the sizes that take each form, with indices that lie close together (loaded as they come), and half of the
+    workgroups', or of one workgroup's, spread over the source."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    src = torch.randint(-32768, 32768, (n,), generator=gen, device="cuda", dtype=torch.int32).to(torch.int16)
+    i = torch.arange(n, device="cuda", dtype=torch.int32)
+    if order == "backwards":
+        i = n - 1 - i
+    elif order == "mesh":
+        i = (i ^ 1234).clamp(max=n - 1)
+    elif order == "half":  # from the middle of a workgroup's 4096 on
+        i = torch.where(i < n // 2 + 2000, i, torch.randint(0, n, (n,), generator=gen, device="cuda", dtype=torch.int32))
+    got = fs.fs_gather16(src.view(torch.float16), i)
+    assert torch.equal(got.view(torch.int16), src[i.long()])
+
+
 def test_transpose_argument_errors(fs):
     import torch
     lib = fs.load_library()
