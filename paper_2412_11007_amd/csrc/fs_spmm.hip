@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(N
 k_spmm(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk_desc, int nvec,
        const int32_t *__restrict__ vec_col, const uint16_t *__restrict__ vals,
        const uint16_t *__restrict__ B, int64_t ldb, int N,
-       uint16_t *__restrict__ C, int64_t ldc, float *__restrict__ part, int64_t M, int nbx, int slice, int n_swz,
+       uint16_t *__restrict__ C, int64_t ldc, float *__restrict__ part, int64_t M, int nbx, int slice, int n_swz, int first_col,
        const int32_t *__restrict__ blk_ofs = nullptr, const void *__restrict__ masks = nullptr)
 {
     constexpr int NC = NT * 16;   // columns per pass
@@ -81,7 +81,7 @@ k_spmm(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk
     const int nblk = it.y;
     if (nblk == 0) return;
     int slot = it.z;
-    const int n0 = pass * NC;  // first column of this pass
+    const int n0 = first_col + pass * NC;  // first column of this pass
     const int j = lane & 15, g = lane >> 4;
 
     // descriptors of the item's blocks (at most 64), one per lane, and the column indices of its first
@@ -395,11 +395,14 @@ k_spmm_reduce(const int4 *__restrict__ split_windows, const float *__restrict__ 
 // Columns per pass for N > 64: 128.  (With the work list in its own order, 64-column passes -- more, lighter
 // wavefronts per CU -- measured 11 % faster on large matrices; with parts of hub windows launched by column
 // the order reverses, cfg 4 at eight rows: 733 us against 779 us.)
-// Where N > 128 is no multiple of 64, rows of B do not begin at lines of 128 bytes, and every pass fetches the lines it
-// shares with its neighbour: then one pass takes 256 columns.  With two passes / one, us: uniform 100 k x 50 k, 11 a row,
-// N = 136 64 / 51, 200 86 / 70, 224 80 / 74; lognormal graph of 262 k rows, N = 136 366 / 269, 200 457 / 366; stencil 700^2, N = 200
-// 178 / 117.  Aligned rows gain nothing (N = 192 54 / 57, 256 71 / 78; lognormal N = 256 375 / 379), and with few items the
-// chain of one wavefront, longer per block, is the time (615 items, N = 200: 11.7 / 14.1; from 2485 on 24.7 / 21.4).
+// Where N > 128 is no multiple of 64, columns past the first 128 neither begin nor end with a line of 128 bytes in most rows of B (or
+// the last pass takes half a line), and every pass fetches the lines it shares with its neighbour: then one pass takes 256
+// columns.  With two passes / one, us, rows of B back to back: uniform 100 k x 50 k, 11 a row, N = 136 69 / 50, 200 98 / 71; lognormal
+// graph of 262 k rows, N = 136 436 / 272, 200 537 / 367; stencil 700^2, N = 200 184 / 117; R-MAT of 65 k rows, N = 136 36 / 33.  It is the
+// width that counts, not the pitch: rows 512 bytes apart, N = 200, 89 / 76, 468 / 375, 181 / 137.  Whole lines gain nothing
+// (N = 192 54 / 57, 256 71 / 78; lognormal N = 256 375 / 379), and with few items the chain of one wavefront, longer per block, is the
+// time (615 items, N = 200: 11.7 / 14.1; from 2485 on 24.7 / 21.4).
+// Above 256 columns a rest of up to 128 has a launch of its own as wide as it is.
 // A tuning build (-DFS_TUNING_ENV) lets FS_SPMM_PASS=64|128|256 override the choice; the shipped library reads no environment.
 constexpr int kWidePassItems = 1024;
 int fs_spmm_pass_override()
@@ -420,48 +423,59 @@ fs_status launch(const fs_format *f, const uint16_t *vals, const uint16_t *B, in
     if (f->n_items == 0) return FS_OK;
     const int4 *items = (const int4 *)f->items_by_cost;
     const int n_items = (int)f->n_items;
-    int nc = N <= 32 ? 32 : N <= 64 ? 64 : N > 128 && N % 64 && n_items >= kWidePassItems ? 256 : 128;  // columns per pass
-    if (blk_ofs && nc == 32) nc = 64;  // the packed-value kernels exist for 64 columns and up
-    if (N > 64 && (fs_spmm_pass_override() == 64 || fs_spmm_pass_override() == 128 || fs_spmm_pass_override() == 256)) nc = fs_spmm_pass_override();
-    // Wavefronts (= work items) per workgroup.  A workgroup keeps its slots until its slowest wavefront is
-    // done, so small launches, whose tail is a large part of the run, do best with one item per workgroup
-    // (cfg 2: 25.1 -> 23.7 us); 64-column passes measured best with two, wide passes on large matrices with four.
-    const int wpb = nc == 32 ? 4 : nc == 64 ? 2 : (n_items < 16384 ? 1 : 4);
+    const bool wide = N > 128 && N % 64 && n_items >= kWidePassItems;
+    const auto width = [&](int64_t columns) -> int { return columns <= 32 && !blk_ofs ? 32 : columns <= 64 ? 64 : 128; };  // (packed values: 64 and up)
     int slice_len = 4096;  // launch positions per slice
 #ifdef FS_TUNING_ENV
     if (const char *e = getenv("FS_SPMM_SLICE")) slice_len = atoi(e);
 #endif
-    const fs_launch_geometry geo = fs_launch_geometry_for(f, wpb, slice_len);
-    const int nbx = geo.nbx, slice = geo.slice, n_swz = geo.n_swz;
-    const int passes = (int)((N + nc - 1) / nc);
-    const int64_t nblocks = (int64_t)nbx * passes;
-    if (nblocks >= ((int64_t)1 << 31)) return FS_ERR_TOO_LARGE;
-    dim3 grid((unsigned)nblocks, 1, 1), block(64 * wpb, 1, 1);
+    struct Columns {
+        int first, nc, wpb;  // first column, columns per pass, wavefronts (= work items) per workgroup
+        fs_launch_geometry geo;
+        unsigned grid;
+    } part_of[2];
+    int n_parts = 0;
+    const auto add = [&](int64_t first, int64_t end, int nc) -> bool {
+        // A workgroup keeps its slots until its slowest wavefront is done, so small launches, whose tail is a large part of the
+        // run, do best with one item per workgroup (cfg 2: 25.1 -> 23.7 us); 64-column passes measured best with two, wide passes
+        // on large matrices with four.
+        Columns &c = part_of[n_parts++];
+        c.first = (int)first;
+        c.nc = nc;
+        c.wpb = nc == 32 ? 4 : nc == 64 ? 2 : (n_items < 16384 ? 1 : 4);
+        c.geo = fs_launch_geometry_for(f, c.wpb, slice_len);
+        const int64_t nblocks = (int64_t)c.geo.nbx * ((end - first + nc - 1) / nc);
+        c.grid = (unsigned)nblocks;
+        return nblocks < ((int64_t)1 << 31);
+    };
+    const int64_t rest = wide && N > 256 && N % 256 <= 128 ? N % 256 : 0;
+    bool fits;
+    if (N > 64 && (fs_spmm_pass_override() == 64 || fs_spmm_pass_override() == 128 || fs_spmm_pass_override() == 256)) fits = add(0, N, fs_spmm_pass_override());
+    else fits = add(0, N - rest, wide ? 256 : width(N)) && (rest == 0 || add(N - rest, N, width(rest)));
+    if (!fits) return FS_ERR_TOO_LARGE;
     if (ev0) FS_HIP(hipEventRecord(ev0, st));
     // 32-bit gather offsets need B to span less than 4 GiB and row number and row pitch to fit 24 bits
     const bool big = f->K >= ((int64_t)1 << 24) || ldb * 2 >= ((int64_t)1 << 24) ||
                      f->K * ldb * 2 >= ((int64_t)1 << 32);
-#define FS_SPMM_ARGS items, n_items, (const int4 *)f->blk_desc, (int)f->nvec, f->vec_col, vals, B, ldb, (int)N, C, ldc, part, f->M, nbx, slice, n_swz
-#define FS_SPMM_GO(NT_, WPB_)                                                              \
-    if (big) k_spmm<DT, V, NT_, WPB_, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS);        \
-    else k_spmm<DT, V, NT_, WPB_, false><<<grid, block, 0, st>>>(FS_SPMM_ARGS)
-    if (blk_ofs) {
-        if (big) return FS_ERR_UNSUPPORTED;
-        if (nc == 64) k_spmm<DT, V, 4, 2, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
-        else if (nc == 256 && wpb == 1) k_spmm<DT, V, 16, 1, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
-        else if (nc == 256) k_spmm<DT, V, 16, 4, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
-        else if (wpb == 1) k_spmm<DT, V, 8, 1, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
-        else k_spmm<DT, V, 8, 4, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks);
-    }
-    else if (nc == 32) { FS_SPMM_GO(2, 4); }
-    else if (nc == 64) { FS_SPMM_GO(4, 2); }
-    else if (nc == 256 && wpb == 1) { FS_SPMM_GO(16, 1); }
-    else if (nc == 256) { FS_SPMM_GO(16, 4); }
-    else if (wpb == 1) { FS_SPMM_GO(8, 1); }
-    else { FS_SPMM_GO(8, 4); }
+    if (blk_ofs && big) return FS_ERR_UNSUPPORTED;
+    for (int i = 0; i < n_parts; i++) {
+        const Columns &c = part_of[i];
+        const dim3 grid(c.grid, 1, 1), block(64 * c.wpb, 1, 1);
+#define FS_SPMM_ARGS items, n_items, (const int4 *)f->blk_desc, (int)f->nvec, f->vec_col, vals, B, ldb, (int)N, C, ldc, part, f->M, c.geo.nbx, c.geo.slice, c.geo.n_swz, c.first
+#define FS_SPMM_GO(NT_, WPB_)                                                                                     \
+        if (blk_ofs) k_spmm<DT, V, NT_ < 4 ? 4 : NT_, NT_ < 4 ? 2 : WPB_, false, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS, blk_ofs, masks); \
+        else if (big) k_spmm<DT, V, NT_, WPB_, true><<<grid, block, 0, st>>>(FS_SPMM_ARGS);                        \
+        else k_spmm<DT, V, NT_, WPB_, false><<<grid, block, 0, st>>>(FS_SPMM_ARGS)
+        if (c.nc == 32) { FS_SPMM_GO(2, 4); }
+        else if (c.nc == 64) { FS_SPMM_GO(4, 2); }
+        else if (c.nc == 256 && c.wpb == 1) { FS_SPMM_GO(16, 1); }
+        else if (c.nc == 256) { FS_SPMM_GO(16, 4); }
+        else if (c.wpb == 1) { FS_SPMM_GO(8, 1); }
+        else { FS_SPMM_GO(8, 4); }
 #undef FS_SPMM_GO
 #undef FS_SPMM_ARGS
-    FS_LAUNCH_CHECK();
+        FS_LAUNCH_CHECK();
+    }
     if (ev1) FS_HIP(hipEventRecord(ev1, st));
     if (f->n_split_windows > 0) {
         const int64_t rblocks = f->n_split_windows * ((N + 31) / 32);  // one workgroup per window and 32 columns

@@ -188,3 +188,29 @@ def test_spmm_pass_widths_agree(fs, rows, V, N):
         assert torch.equal(fs.fs_spmm(fmt, base[:, :N]).view(torch.int16), want)
         del base
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("N", [264, 288, 296, 328, 376, 392, 648])
+@pytest.mark.parametrize("V", [4, 8, 16])
+def test_spmm_rest_of_a_wide_product(fs, V, N):
+    """Past the passes of 256 columns a rest of up to 128 has a launch as wide as it is (32, 64 or 128), a longer one a pass of 256:
+    bit for bit the products of narrow column slices, cut windows included, and nothing past the N columns is written."""
+    import torch
+    M, K = 20005, 9000
+    gen = torch.Generator(device="cuda").manual_seed(N * V + 1)
+    r = torch.arange(M, device="cuda").repeat_interleave(14)
+    c = torch.randint(0, K, (r.numel(),), generator=gen, device="cuda")
+    hub = torch.arange(3000, device="cuda") * 3
+    key = torch.unique(torch.cat([r * K + c, 17 * K + hub, (M - 1) * K + hub]))
+    rp = torch.searchsorted(key, torch.arange(M + 1, device="cuda") * K).int()
+    va = torch.randn(key.numel(), generator=gen, device="cuda").half()
+    fmt = fs.fs_convert(rp, (key % K).int(), va, M, K, V=V)
+    assert fmt.n_items >= 1024 and fmt.c.n_split_windows > 0
+    B = torch.randn((K, N + 16), generator=gen, device="cuda").half()
+    want = torch.cat([fs.fs_spmm(fmt, B[:, n:min(n + 64, N)].contiguous()) for n in range(0, N, 64)], 1).view(torch.int16)
+    out = torch.full((M, N + 8), 7.0, dtype=torch.half, device="cuda")
+    fs.fs_spmm(fmt, B[:, :N], out=out[:, :N])
+    assert torch.equal(out[:, :N].view(torch.int16), want) and (out[:, N:] == 7).all()
+    out.fill_(7.0)
+    fs.fs_spmm_packed(fmt, fs.fs_pack_values(fmt), B[:, :N], out=out[:, :N])
+    assert torch.equal(out[:, :N].view(torch.int16), want) and (out[:, N:] == 7).all()
