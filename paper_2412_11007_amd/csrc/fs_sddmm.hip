@@ -388,12 +388,26 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
                      ldy * 2 >= ((int64_t)1 << 24) || f->K * ldy * 2 >= ((int64_t)1 << 32) ||
                      (f->M + 32) * ldx * 2 >= ((int64_t)1 << 32);
     const fs_launch_geometry geo = fs_launch_geometry_for(f, 1);
-    // 128 < d <= 256: whole rows at a time where there are blocks for the fewer wavefronts that fit then, else in chunks of 128
-    // features.  Chunks / whole rows, us, d = 136, 168, 200, 256: lognormal graph of 262 k rows (196 k blocks) 332 / 284,
-    // 398 / 326, 466 / 376, 421 / 382; R-MAT of 262 k rows (in launch order) 138 / 149, 154 / 149, 189 / 156, 227 / 169; lognormal graph of
-    // 20 k rows (14 k blocks) 21 / 23, 26 / 25, 32 / 27, 33 / 29; stencil 500^2 49 / 49, 63 / 51, 79 / 57, 80 / 71; R-MAT of 8 k rows
-    // (3 k blocks) 7 / 9 at any width.  Up to d = 160 the second chunk is little work, and only rows that mostly miss the L2s gain.
-    const bool wide = n_blocks >= 8192 && (d > 160 || (!ordered && f->K * d * 2 > ((int64_t)8 << 20)));
+    // 128 < d <= 256: whole rows at a time, or chunks of 128 features.  Whole rows are fetched once, and keep a window's rows of X, by
+    // half the wavefronts; so they gain where rows of Y miss the L2s and windows are tall, and lose where rows hit.  Chunks / whole rows,
+    // us, d = 136, 168, 200, 256, blocks in brackets, "in order" in launch order:
+    //   eight rows: lognormal graph of 262 k rows (171 k) 381 / 288, 462 / 340, 540 / 390, 480 / 409; of 20 k rows (14 k) 20 / 23, 25 / 23,
+    //     32 / 26, 33 / 28; of 15 k rows (10 k) 16 / 18, 17 / 19, 19 / 21, 23 / 22; stencil 500^2 (31 k) 50 / 46, 64 / 49, 81 / 57, 80 / 72; 300^2
+    //     (11 k) 22 / 25, 25 / 27, 31 / 30, 31 / 34: from fifty blocks a CU on.  R-MAT of 32 k rows, hubs out of order (15 k) 20 / 23, 20 / 24,
+    //     22 / 24, 24 / 25: not.  In order, 512 k rows (276 k) 322 / 330, 361 / 322, 439 / 350, 494 / 406; 131 k (66 k) 68 / 76, 69 / 71,
+    //     83 / 74, 93 / 76: below d = 200 only where Y is much more than all L2s hold.
+    //   sixteen: lognormal 262 k 459 / 312, 565 / 366, 658 / 420, 573 / 441; uniform 60 k rows (11 k) 30 / 26, 36 / 29, 43 / 33, 40 / 35; R-MAT of 262 k
+    //     rows, in order 166 / 155, 209 / 134, 264 / 150, 287 / 174; of 32 k, hubs out of order (13 k) 19 / 21, 21 / 22, 24 / 23, 28 / 24; of 65 k (27 k)
+    //     37 / 36, 43 / 38, 53 / 40, 64 / 46.
+    //   four: lognormal 262 k (197 k) 334 / 281, 396 / 326, 466 / 378, 424 / 389, but uniform 60 k rows (15 k) 25 / 28, 29 / 30, 34 / 33, 32 / 34; stencil
+    //     500^2, blocks of 14 vectors 67 / 82, 69 / 83, 74 / 86, 84 / 89; R-MAT of 262 k rows, a tenth of the items hubs (165 k) 159 / 184,
+    //     170 / 190, 199 / 204, 289 / 264; of 1 M rows (1.1 M) 1193 / 1240, 1336 / 1257, 1594 / 1403, 1862 / 1688.
+    // Up to d = 160 the second chunk is little work, and only rows that mostly miss the L2s gain.
+    const int64_t y_bytes = f->K * d * 2;
+    const bool tall = V == 16 ? n_blocks >= 8192 && (ordered || d >= 200 || n_blocks >= 25600 || n_cut * 8 < n_items * 3)
+                      : V == 8 ? n_blocks >= 12800 && (ordered ? d >= 200 || y_bytes >= ((int64_t)64 << 20) : n_cut * 4 < n_items)
+                               : f->nvec >= 18 * f->n_blocks && n_blocks >= (n_cut * 16 < n_items ? 1 << 15 : d >= 240 ? 1 << 16 : 1 << 19);
+    const bool wide = tall && (d > 160 || (!ordered && y_bytes > ((int64_t)8 << 20)));
     const dim3 grid(ordered ? (unsigned)geo.nbx : (unsigned)(((int64_t)n_blocks + G - 1) / G)), block(64);
 #define FS_SDDMM_ARGS items, (int)f->n_items, geo.slice, geo.n_swz, n_blocks, G, (const int4 *)f->blk_desc, f->vec_col, f->blk_row_bits, (int)f->nvec, X, ldx, Y, ldy, (int)d, out, f->M, out_csr, f->blk_row_base
 #define FS_SDDMM_LAUNCH(...)  /* the kernel and its first template arguments */                         \

@@ -94,3 +94,33 @@ def test_sddmm_whole_rows(fs, ordered, V, d):  # noqa: F811
     Xd, Yd = to_dev(X.bits, dtype), to_dev(Y.bits, dtype)
     same_bits(from_dev_bits(fs.fs_blk_to_csr(fmt, fs.fs_sddmm(fmt, Xd, Yd))), want, "fs_sddmm")
     same_bits(from_dev_bits(fs.fs_sddmm(fmt, Xd, Yd, blocked=False)), want, "fs_sddmm, CSR order")
+
+
+@pytest.mark.parametrize("d", [136, 168, 200, 248])
+@pytest.mark.parametrize("V,kind", [(4, "short"), (8, "short"), (16, "short"), (4, "hubs"), (8, "hubs"), (16, "hubs")])
+def test_sddmm_whole_rows_by_height(fs, V, kind, d):  # noqa: F811
+    """Block counts from which rows are gathered whole at each window height: windows of three blocks (the last one narrow) in slot
+    order, and hub windows, one long row each, in launch order.  Exact in fp32, so bit for bit."""
+    import torch
+    dtype = "bf16" if (d // 8 + V // 4) % 2 else "f16"
+    rng = np.random.default_rng(V + d)
+    K = 30000
+    if kind == "short":
+        W = {4: 11000, 8: 4400, 16: 2800}[V]
+        rows = np.repeat(np.arange(W * V), 88 // V)
+        cols = rng.integers(0, K, size=rows.shape[0])
+    else:
+        W = {4: 120, 8: 24, 16: 16}[V]
+        rows, cols = np.repeat(np.arange(W) * V + 1, 18000), np.concatenate([rng.choice(K, size=18000, replace=False) for _ in range(W)])
+    A = csr_from_coo(W * V, K, rows, cols, "u11", dtype, rng)
+    lim = 1 if dtype == "bf16" else 2
+    X = Dense(halves(stream(V + d, 95, 2), (A.M, d), -lim, lim, dtype), dtype)
+    Y = int_dense(K, d, dtype, seed=V + d, tid=6, lim=lim)
+    ref, _ = oracle.sddmm(A.M, A.K, A.rowptr, A.colidx, X.bits, Y.bits, dtype, want_scale=False)
+    want = oracle.round_f64_to_bits(ref, dtype)
+    rp, ci, _ = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, None, A.M, A.K, torch_dtype=torch.float16 if dtype == "f16" else torch.bfloat16, V=V, chunk=64 if V > 4 else 256)
+    assert fmt.n_blocks >= {4: 1 << 15 if kind == "short" else 1 << 16, 8: 12800, 16: 8192}[V] and fmt.nvec >= 18 * fmt.n_blocks, (fmt.n_blocks, fmt.nvec)
+    Xd, Yd = to_dev(X.bits, dtype), to_dev(Y.bits, dtype)
+    same_bits(from_dev_bits(fs.fs_blk_to_csr(fmt, fs.fs_sddmm(fmt, Xd, Yd))), want, "fs_sddmm")
+    same_bits(from_dev_bits(fs.fs_sddmm(fmt, Xd, Yd, blocked=False)), want, "fs_sddmm, CSR order")
