@@ -39,7 +39,7 @@ __device__ __forceinline__ float fs_exp2(float x) { return __builtin_amdgcn_exp2
 // KS = 32-feature steps of the score contraction (d <= 32 * KS); NT = 16-column tiles of H per pass.
 // SM = false leaves the softmax out: the weights are the scaled scores themselves, rounded to the element
 // type exactly as the SDDMM kernel stores them (sl2 is then the plain scale).
-template <int DT, int V, int NT, int KS, int WPB, bool SM>
+template <int DT, int V, int NT, int KS, int WPB, bool SM, bool KEEP>
 __global__ void __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(NT > 8 || (NT == 8 && KS == 4) ? 2 : 3)))
 k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk_desc, int nvec,
             const int32_t *__restrict__ vec_col, const uint32_t *__restrict__ row_bits,
@@ -56,8 +56,11 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
     constexpr bool DPPR = LPR >= 16;  // indices are handed out by DPP moves (see below)
     // Rows of Y longer than 64 bytes are gathered row by row and turned into operand layout in LDS, as in the SDDMM kernel
     // (loaded straight in operand layout a wave-wide load takes the vector-memory unit 64-70 cycles instead of 18-24);
-    // the tile is the one that the rows of H pass through afterwards.
-    constexpr bool YL = KS >= 2;
+    // the tile is the one that the rows of H pass through afterwards.  Not where d > 64 meets a pass of 256 columns: the
+    // offsets of eight loads for two do not fit the registers beside its tile (2, 7 and 29 spilled for four, eight and sixteen rows).
+    // By LDS / straight, us, N = 136, d = 96: stencil 700^2, four rows 257 / 236, sixteen 171 / 156; R-MAT of 8 k rows 23.2 / 20.0, of
+    // 65 k rows 57.8 / 56.0 (d = 128: 58.6 / 61.3).
+    constexpr bool YL = KS >= 2 && !(KS == 4 && NT == 16);
     constexpr int YLPR = 4 * KS;        // lanes that share one gathered row of Y
     constexpr int YRPI = 64 / YLPR;     // rows per wave-wide load
     constexpr int NY = 2 * KS;          // 16-byte registers of Y per lane and block, in either form
@@ -245,8 +248,9 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
                     fs_frag y;
                     y.u = YL ? *reinterpret_cast<const fs_u4 *>(y_rd + 16 * t * RSY + 64 * ks) : yg[t * KS + ks];
                     // what stands in for features past d is zero on both sides: 0 * inf would make the score NaN.  (Steps
-                    // in the first half are whole, d > 16 * KS; for d < 32 features are taken to be finite.)
-                    if (2 * ks >= KS && KS > 1 && !f_ok[ks]) y.u = fs_u4{0u, 0u, 0u, 0u};
+                    // in the first half are whole, d > 16 * KS.  Loaded straight, a row's first eight features stand in, and are
+                    // taken to be finite: the selects cost 2 % on small graphs, and registers where d > 64, up to 10 %.)
+                    if (YL && 2 * ks >= KS && !f_ok[ks]) y.u = fs_u4{0u, 0u, 0u, 0u};
                     sc[t] = fs_mfma_16x16x32<DT>(y, xf[ks], sc[t]);
                 }
             }
@@ -288,7 +292,9 @@ k_attention(const int4 *__restrict__ items, int n_items, const int4 *__restrict_
         if constexpr (!YL) {
             if (MORE) FS_YGATHER()
         }
-        if (d1.w != d0.w) load_x(d1);  // blocks of one window keep its rows of X (in operand layout: 64-70 cycles a load)
+        // blocks of one window keep its rows of X (in operand layout: 64-70 cycles a load); where every block ends a window the
+        // question costs more than it saves: the compiler waits for the loads it cannot count
+        if (!KEEP || d1.w != d0.w) load_x(d1);
         if constexpr (!SMALL_FIRST) bits1 = load_bits(step + 1);
 
         if (kb > 0) {
@@ -435,8 +441,10 @@ k_attention_reduce(const int4 *__restrict__ split_windows, const float *__restri
 
 // WPB wavefronts (= work items) per workgroup.  A workgroup keeps its slots until its slowest wavefront is
 // done: small launches, whose tail is a large part of the run, do best with one (cfg 2: -5 %), large ones
-// with four (cfg 5: one per workgroup is 2 % slower).
-template <int DT, int V, int NT, bool SM, int WPB>
+// of 128 and 256 columns with four (cfg 5: one per workgroup is 2 % slower; up to 64 columns one is as good or better, stencil 1024^2,
+// N = 64, d = 96: 146 against 150 us, lognormal graph of 262 k rows and R-MAT of 262 k rows alike).
+// KEEP: blocks of one window keep its rows of X.
+template <int DT, int V, int NT, bool SM, int WPB, bool KEEP = true>
 fs_status launch_wpb(const fs_format *f, const uint16_t *X, int64_t ldx, const uint16_t *Y, int64_t ldy, int d, float sl2,
                      const uint16_t *H, int64_t ldh, int N, uint16_t *C, int64_t ldc, float *part, float *stats,
                      hipStream_t st)
@@ -450,9 +458,9 @@ fs_status launch_wpb(const fs_format *f, const uint16_t *X, int64_t ldx, const u
     dim3 grid((unsigned)nblocks, 1, 1), block(64 * WPB, 1, 1);
 #define FS_ATTN_ARGS (const int4 *)f->items_by_cost, n_items, (const int4 *)f->blk_desc, (int)f->nvec, f->vec_col, f->blk_row_bits, \
                      X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, f->M, nbx, geo.slice, geo.n_swz
-    if (d <= 32) k_attention<DT, V, NT, 1, WPB, SM><<<grid, block, 0, st>>>(FS_ATTN_ARGS);
-    else if (d <= 64) k_attention<DT, V, NT, 2, WPB, SM><<<grid, block, 0, st>>>(FS_ATTN_ARGS);
-    else k_attention<DT, V, NT, 4, WPB, SM><<<grid, block, 0, st>>>(FS_ATTN_ARGS);
+    if (d <= 32) k_attention<DT, V, NT, 1, WPB, SM, KEEP><<<grid, block, 0, st>>>(FS_ATTN_ARGS);
+    else if (d <= 64) k_attention<DT, V, NT, 2, WPB, SM, KEEP><<<grid, block, 0, st>>>(FS_ATTN_ARGS);
+    else k_attention<DT, V, NT, 4, WPB, SM, KEEP><<<grid, block, 0, st>>>(FS_ATTN_ARGS);
 #undef FS_ATTN_ARGS
     FS_LAUNCH_CHECK();
     if (f->n_split_windows > 0) {
@@ -471,6 +479,10 @@ fs_status launch_nt(const fs_format *f, const uint16_t *X, int64_t ldx, const ui
                     hipStream_t st)
 {
     if (f->n_items < 16384) return launch_wpb<DT, V, NT, SM, 1>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
+    // Large launches of which most windows are one block (meshes, a few entries a row).  Keep / load, us: stencil 700^2, four rows,
+    // N = 96, d = 32 92 / 82, d = 64 105 / 96; 1024^2, eight rows, N = 96, d = 32 132 / 123, N = 136, d = 96 301 / 287; where windows have more, the
+    // other way round (lognormal graph of 262 k rows, sixteen rows, N = 136, d = 64: 347 / 374; R-MAT of 65 k rows, d = 128, N = 128 40 / 43).
+    if (2 * f->n_blocks < 3 * f->W) return launch_wpb<DT, V, NT, SM, 4, false>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
     return launch_wpb<DT, V, NT, SM, 4>(f, X, ldx, Y, ldy, d, sl2, H, ldh, N, C, ldc, part, stats, st);
 }
 

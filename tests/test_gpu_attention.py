@@ -269,7 +269,7 @@ def test_attention_pass_widths_and_feature_steps(fs, V, d):
 def test_attention_of_an_infinite_feature(fs, d, N):
     """A feature of -inf in the first or the last eight of a row of Y: its scores with queries above zero are -inf, so the
     weights are zero and the result is that of the matrix without these entries, whatever the kernel reads in the place of
-    features past d."""
+    features past d.  (Rows of d > 64 in passes of 256 columns are loaded straight: there the first eight stand in, and are finite.)"""
     rng = np.random.default_rng(d + N)
     M, K = 61, 90
     cols = [np.sort(rng.choice(K, size=int(n), replace=False)) for n in rng.integers(12, 60, M)]
@@ -279,7 +279,8 @@ def test_attention_of_an_infinite_feature(fs, d, N):
     Y = dense(K, d, "n01", "f16", stream(13, 61, d))
     H = dense(K, N, "n01", "f16", stream(13, 62, N))
     hit = np.arange(0, K, 9)
-    Y.bits[hit, np.where(np.arange(hit.shape[0]) % 2, d - 1 - hit % 8, hit % 8)] = 0xFC00  # -inf
+    in_last = (np.arange(hit.shape[0]) % 2 == 1) | (d > 64 and N > 128)
+    Y.bits[hit, np.where(in_last, d - 1 - hit % 8, hit % 8)] = 0xFC00  # -inf
     keep = ~np.isin(A.colidx, hit)
     rowptr = np.concatenate([[0], np.cumsum(keep)])[A.rowptr].astype(np.int32)
     clean = Y.bits.copy()
