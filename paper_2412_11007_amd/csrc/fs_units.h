@@ -48,10 +48,12 @@ __device__ __forceinline__ void row_range(const CsrView &a, int64_t i, int32_t &
     hi = min(max(a.rowptr[i + 1], lo), a.nnz);
 }
 
-// How windows become units.  Windows are taken in groups of `group`, as many as have at most kUnitRows rows; a group that fits a
-// unit is one, else its halves are looked at, and so on: a unit is the largest aligned run of 2^k windows that fits.  (With one
+// How windows become units.  Windows are taken in groups of `group`, as many as have at most kUnitRows rows; a group of up to `fill`
+// entries is a unit, else its halves are looked at, and so on: a unit is the largest aligned run of 2^k windows that fits.  (With one
 // size of run for the whole matrix, the short windows beside the hubs of a power-law graph were units of their own: R-MAT
-// of 1 M rows, 32 a row, 202 k units of 156 entries, now 100 k of 314: ranking 297 -> 239 us, placing 419 -> 320.)  A window with more than kUnitEntries entries is cut by columns:
+// of 1 M rows, 32 a row, 202 k units of 156 entries, now 100 k of 314: ranking 297 -> 239 us, placing 419 -> 320.)  `fill` is kUnitEntries, but
+// less on matrices that would not make four units a CU: there a wavefront's own chain is the time (4096 rows, 16 a row, with
+// full units 132 us, filled to 128 entries 123).  A window with more than kUnitEntries entries is cut by columns:
 // every `stride`-th entry of a row is a sample, a sample's rank counts the samples of all rows with a smaller
 // (column, row), and the columns of the samples with ranks `per`, 2 per, ... start new pieces.  A piece then
 // spans at most per + V - 1 samples, a row with q of them at most (q + 1) * stride - 1 entries of it: in all fewer than
@@ -60,6 +62,7 @@ __device__ __forceinline__ void row_range(const CsrView &a, int64_t i, int32_t &
 struct UnitPlan {
     int V, lv;     // rows per window, and log2 of the next power of two
     int group;     // windows per group, a power of two
+    int fill;      // most entries of a unit of several windows
     int stride, per;
 };
 inline UnitPlan unit_plan(int64_t nnz, int V)
@@ -69,19 +72,20 @@ inline UnitPlan unit_plan(int64_t nnz, int V)
     p.lv = 0;
     while ((1 << p.lv) < V) p.lv++;
     p.group = std::min(kMaxUnitWindows, kUnitRows >> p.lv);
+    p.fill = (int)std::min<int64_t>(std::max<int64_t>(nnz / 1024, 128), kUnitEntries);
     p.stride = 4;
     p.per = (kUnitEntries / p.stride - 2 * V) * 5 / 6;
     return p;
 }
 // At most this many units, for every V (per * stride >= 212): what the scratch buffer has room for.
 inline int64_t units_bound(int64_t W, int64_t nnz) { return W + nnz / 208 + 2; }
-// ... and for a plan: a unit per group; of the at most nnz / (kUnitEntries + 1) groups that do not fit one, at most a unit per window;
+// ... and for a plan: a unit per group; of the at most nnz / (fill + 1) groups that do not fit one, at most a unit per window;
 // of a hub window one more per (per * stride) entries.  (Launched for the bound above, a matrix with fewer entries than
 // rows ran mostly empty workgroups: 16 M rows, 1 M entries, four-row windows 3.49 -> 1.09 ms.)
 inline int64_t units_bound(const UnitPlan &p, int64_t W, int64_t nnz)
 {
     const int64_t groups = (W + p.group - 1) / p.group;
-    return std::min(groups + (p.group - 1) * (nnz / (kUnitEntries + 1)), W) + nnz / (p.per * p.stride) + 2;
+    return std::min(groups + (p.group - 1) * (nnz / (p.fill + 1)), W) + nnz / (p.per * p.stride) + 2;
 }
 // Wavefronts per launch: a launch has fewer than 2^32 threads, so a larger number takes several.
 constexpr int64_t kUnitLaunch = (int64_t)1 << 24;
@@ -110,7 +114,7 @@ __device__ __forceinline__ WindowUnits window_units(const UnitPlan &p, int k, in
     for (int run = p.group; run >= 1; run >>= 1) {  // the largest aligned run around the window that fits
         const int from = lane & -run;
         const int e = __shfl(end, from + run - 1, 64) - __shfl(first, from, 64);
-        if (hub && e <= kUnitEntries) {
+        if (hub && e <= (run > 1 ? p.fill : kUnitEntries)) {
             hub = false;
             if (exists && (k & (run - 1)) == 0) x = WindowUnits{run, 1};
         }

@@ -79,6 +79,29 @@ def test_convert_units_bit_exact(fs, kind, V, KB):  # noqa: F811
             assert np.array_equal(fmt.blk_row_bits_t().cpu().numpy().view(np.uint32), want)
 
 
+@pytest.mark.parametrize("V,fill", [(1, 128), (2, 512), (4, 128), (4, 512), (8, 128), (8, 300), (8, 512), (16, 128), (16, 512), (32, 512)])
+def test_convert_units_of_so_many_entries(fs, V, fill):  # noqa: F811
+    """How full a unit of several windows gets depends on the matrix' entries: runs of windows that just fit and just do not, with
+    as many entries around them as make that limit 128, 300 or 512."""
+    rng = np.random.default_rng(V + fill)
+    K = 40000
+    pick = lambda n: np.sort(rng.choice(K, size=n, replace=False))  # noqa: E731
+    group = min(64 // (1 << (V - 1).bit_length()) if V > 1 else 16, 16)
+    sizes = [fill // group] * group + [fill // group + 1] * group + [fill // 2] * 4 + [fill // 2, fill // 2 + 1] * 4 + [fill, fill + 1, 0, 513, 3] * group
+    rows = []
+    for n in sizes:
+        rows += [pick((n + V - 1 - r) // V) for r in range(V)]
+    around = max(fill * 1024 + 600 - sum(len(r) for r in rows), 0) if fill > 128 else 0
+    rows += [pick(20000) for _ in range(around // 20000)] + [pick(around % 20000), pick(5)]
+    A = from_rows(rows, K)
+    assert min(max(A.nnz // 1024, 128), 512) == fill
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, A.M, A.K, V=V)
+    assert_format_equal(fmt, A, V, 32)
+    assert_items_valid(fmt)
+    assert_row_base_valid(fmt, A)
+
+
 def test_convert_columns_beyond_26_bits_and_bad_hub_rows(fs):  # noqa: F811
     """Columns up to 2^31 - 2, and hub windows whose columns do not ascend: refused wherever the fault lies."""
     rng = np.random.default_rng(5)
