@@ -29,7 +29,7 @@ fs_status fs_spmm_timed(const fs_format *fmt, const void *d_vals,
 /*
  * Measurement aid: the gather of fs_spmm and nothing else.  Loads, work item by work item in fs_spmm's launch
  * order and placement, the rows of B the column indices name -- with the load instructions and lane mapping of
- * the SpMM kernel's 128-column pass -- and discards them (one word per lane goes to d_sink so that the loads are kept).  Its
+ * the SpMM kernel's passes of 128 or, for the widths where it takes those, 256 columns -- and discards them (one word per lane goes to d_sink so that the loads are kept).  Its
  * duration is what this machine needs just to bring the method's operand rows to the registers for this
  * matrix: the floor under fs_spmm's time that no change to the rest of the kernel can go below.
  *   d_sink : 1 MiB (1024 * 256 * 4 bytes), 4-byte aligned.  N % 8 == 0, ldb % 8 == 0, d_B 16-byte aligned.

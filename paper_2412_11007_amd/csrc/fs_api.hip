@@ -77,34 +77,36 @@ __global__ void __launch_bounds__(256) k_read16(const fs_u4 *__restrict__ src, u
 // Measurement aid: nothing but the gather of fs_spmm, in fs_spmm's own launch order.  One wavefront per work
 // item, four per workgroup, placed like the SpMM kernel's; per block it reads the column indices and loads
 // the rows of B they name exactly as that kernel does -- 16 bytes per lane, 16 lanes per 128-column piece of a
-// row, eight wave-wide loads per 32 vectors and pass -- and folds what it read into one word per lane, written
-// once at the end.
+// row, eight wave-wide loads per 32 vectors and pass (32 lanes and sixteen loads in a pass of 256), lanes past N on the row's last
+// piece -- and folds what it read into one word per lane, written once at the end.
+template <int LPR>
 __global__ void __launch_bounds__(256) k_gather_probe(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk_desc,
                                                       const int32_t *__restrict__ vec_col, int nvec,
-                                                      const uint16_t *__restrict__ B, int64_t ldb, int N, int nbx, int slice, int n_swz,
+                                                      const uint16_t *__restrict__ B, int64_t ldb, int N, int first_col, int nbx, int slice, int n_swz,
                                                       uint32_t *__restrict__ sink)
 {
+    constexpr int RPI = 64 / LPR, NLD = 32 / RPI;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int pass = blockIdx.x / nbx, bx = blockIdx.x - pass * nbx;
     const int turn = fs_launch_turn<4>(bx, slice, n_swz) + wave;
     uint32_t x = 0;
     if (turn < n_items) {
         const int4 it = items[turn];
-        const int col = pass * 128 + (lane & 15) * 8;
-        const int64_t colb = col < N ? col : 0;
+        const int col = first_col + pass * LPR * 8 + (lane % LPR) * 8;
+        const int64_t colb = col < N ? col : N - 8;
         for (int b = 0; b < it.y; b++) {
             const int4 d = blk_desc[it.x + b];
             const int kb = d.y & 255;
             if (kb == 0) continue;
             const int my = vec_col[min(d.x + min(lane & 31, kb - 1), nvec - 1)];
-            fs_u4 v[8];
+            fs_u4 v[NLD];
 #pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const int r = __shfl(my, u * 4 + (lane >> 4), 64);
+            for (int u = 0; u < NLD; u++) {
+                const int r = __shfl(my, u * RPI + lane / LPR, 64);
                 v[u] = *reinterpret_cast<const fs_u4 *>(B + (int64_t)r * ldb + colb);
             }
 #pragma unroll
-            for (int u = 0; u < 8; u++) x ^= v[u].x ^ v[u].y ^ v[u].z ^ v[u].w;
+            for (int u = 0; u < NLD; u++) x ^= v[u].x ^ v[u].y ^ v[u].z ^ v[u].w;
         }
     }
     sink[((size_t)blockIdx.x * 256 + threadIdx.x) & (1024 * 256 - 1)] = x;  // any slot: the word only keeps the loads alive
@@ -121,13 +123,19 @@ extern "C" fs_status fs_gather_probe(const fs_format *fmt, const void *d_B, int6
     if (!d_B || !d_sink || N % 8 || ldb % 8 || !aligned(d_B, 16) || !aligned(d_sink, 4)) return FS_ERR_INVALID_ARG;
     if (sink_bytes < (size_t)1024 * 256 * sizeof(uint32_t)) return FS_ERR_BUFFER_TOO_SMALL;
     const fs_launch_geometry geo = fs_launch_geometry_for(fmt, 4);
-    const int64_t nblocks = (int64_t)geo.nbx * ((N + 127) / 128);
-    if (nblocks >= ((int64_t)1 << 31)) return FS_ERR_TOO_LARGE;
-    k_gather_probe<<<(unsigned)nblocks, 256, 0, (hipStream_t)stream>>>((const int4 *)fmt->items_by_cost, (int)fmt->n_items,
-                                                                        (const int4 *)fmt->blk_desc, fmt->vec_col, (int)fmt->nvec,
-                                                                        (const uint16_t *)d_B, ldb, (int)N, geo.nbx, geo.slice,
-                                                                        geo.n_swz, (uint32_t *)d_sink);
-    FS_LAUNCH_CHECK();
+    const bool wide = fs_spmm_wide(fmt, N);
+    const int64_t first = wide ? N - fs_spmm_rest(N) : 0;  // columns before it take passes of 256
+    const int64_t blocks256 = (int64_t)geo.nbx * ((first + 255) / 256), blocks128 = (int64_t)geo.nbx * ((N - first + 127) / 128);
+    if (blocks256 >= ((int64_t)1 << 31) || blocks128 >= ((int64_t)1 << 31)) return FS_ERR_TOO_LARGE;
+#define FS_PROBE(LPR, BLOCKS, FIRST)                                                                                                     \
+    k_gather_probe<LPR><<<(unsigned)(BLOCKS), 256, 0, (hipStream_t)stream>>>((const int4 *)fmt->items_by_cost, (int)fmt->n_items,         \
+                                                                            (const int4 *)fmt->blk_desc, fmt->vec_col, (int)fmt->nvec,   \
+                                                                            (const uint16_t *)d_B, ldb, (int)N, (int)(FIRST), geo.nbx,   \
+                                                                            geo.slice, geo.n_swz, (uint32_t *)d_sink);                   \
+    FS_LAUNCH_CHECK()
+    if (blocks256 > 0) { FS_PROBE(32, blocks256, 0); }
+    if (blocks128 > 0) { FS_PROBE(16, blocks128, first); }
+#undef FS_PROBE
     return FS_OK;
 }
 

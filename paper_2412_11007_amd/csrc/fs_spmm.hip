@@ -404,7 +404,6 @@ k_spmm_reduce(const int4 *__restrict__ split_windows, const float *__restrict__ 
 // time (615 items, N = 200: 11.7 / 14.1; from 2485 on 24.7 / 21.4).
 // Above 256 columns a rest of up to 128 has a launch of its own as wide as it is.
 // A tuning build (-DFS_TUNING_ENV) lets FS_SPMM_PASS=64|128|256 override the choice; the shipped library reads no environment.
-constexpr int kWidePassItems = 1024;
 int fs_spmm_pass_override()
 {
 #ifdef FS_TUNING_ENV
@@ -423,7 +422,7 @@ fs_status launch(const fs_format *f, const uint16_t *vals, const uint16_t *B, in
     if (f->n_items == 0) return FS_OK;
     const int4 *items = (const int4 *)f->items_by_cost;
     const int n_items = (int)f->n_items;
-    const bool wide = N > 128 && N % 64 && n_items >= kWidePassItems;
+    const bool wide = fs_spmm_wide(f, N);
     const auto width = [&](int64_t columns) -> int { return columns <= 32 && !blk_ofs ? 32 : columns <= 64 ? 64 : 128; };  // (packed values: 64 and up)
     int slice_len = 4096;  // launch positions per slice
 #ifdef FS_TUNING_ENV
@@ -448,7 +447,7 @@ fs_status launch(const fs_format *f, const uint16_t *vals, const uint16_t *B, in
         c.grid = (unsigned)nblocks;
         return nblocks < ((int64_t)1 << 31);
     };
-    const int64_t rest = wide && N > 256 && N % 256 <= 128 ? N % 256 : 0;
+    const int64_t rest = wide ? fs_spmm_rest(N) : 0;
     bool fits;
     if (N > 64 && (fs_spmm_pass_override() == 64 || fs_spmm_pass_override() == 128 || fs_spmm_pass_override() == 256)) fits = add(0, N, fs_spmm_pass_override());
     else fits = add(0, N - rest, wide ? 256 : width(N)) && (rest == 0 || add(N - rest, N, width(rest)));

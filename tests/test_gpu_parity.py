@@ -569,3 +569,41 @@ def test_gather_probe_runs_and_checks_arguments(fs):
     with pytest.raises(fs.FsError) as e:
         fs.fs_gather_probe(fmt, B, sink=torch.empty(1000, dtype=torch.int32, device="cuda"))
     assert e.value.code == 4
+
+
+@pytest.mark.parametrize("N", [8, 72, 128, 200, 256, 264, 400])
+def test_gather_probe_reads_what_spmm_reads(fs, N):
+    """One workgroup per row of the sink: every lane folds the words of its pieces of the gathered rows, in passes of 128 columns
+    or 256, lanes past N on the row's last piece."""
+    import torch
+    M, K = 8 * 4104, 500  # windows of one block, four an item: passes of 256 columns for widths that are no multiple of 64
+    rng = np.random.default_rng(N)
+    cols = np.stack([np.sort(rng.choice(K, size=32, replace=False)) for _ in range(M // 8)])
+    A = csr_from_coo(M, K, np.repeat(np.arange(0, M, 8), 32), cols.ravel(), "u01", "f16", rng)
+    fmt = convert(fs, A, 8, 32)
+    B = dense(K, N, "n01", "f16", stream(3, 96, N))
+    words = B.bits.view(np.uint32).reshape(K, N // 8, 4)
+    piece = np.bitwise_xor.reduce(words, axis=2)  # of a row and eight columns
+    sink = torch.zeros(1024 * 256, dtype=torch.int32, device="cuda")
+    fs.fs_gather_probe(fmt, to_dev(B.bits, "f16"), sink=sink)
+    got = sink.cpu().numpy().view(np.uint32)
+    items = fmt.items_by_cost_t().cpu().numpy()
+    assert fmt.n_items >= 1024 and fmt.n_cut_items == 0
+    wide = N > 128 and N % 64 != 0
+    rest = N % 256 if wide and N > 256 and N % 256 <= 128 else 0  # its launch comes last, and writes the same words
+    lpr = 32 if wide and not rest else 16
+    groups = (fmt.n_items + 3) // 4 + 7 & ~7
+    passes = -(-(rest or N) // (lpr * 8))
+    want = np.zeros(1024 * 256, dtype=np.uint32)
+    lane = np.arange(64)
+    for b in range(groups * passes):
+        for w in range(4):
+            t = (b % groups) * 4 + w
+            x = np.zeros(64, dtype=np.uint32)
+            if t < fmt.n_items:
+                for s in range(items[t, 0], items[t, 0] + items[t, 1]):
+                    p = np.minimum((N - rest if rest else 0) // 8 + (b // groups) * lpr + lane % lpr, N // 8 - 1)
+                    for u in range(lpr // 2):
+                        x ^= piece[cols[s][u * (64 // lpr) + lane // lpr], p]
+            want[(b * 256 + w * 64 + lane) & (1024 * 256 - 1)] = x
+    assert np.array_equal(got, want)
