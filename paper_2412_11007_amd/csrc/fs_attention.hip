@@ -5,8 +5,8 @@
 // writes the scores, reads and rewrites them, and reads them again; here a wavefront keeps them in
 // registers.  Per 32-vector block of its work item it
 //   * computes the V x 32 tile of scores on the matrix cores exactly as the SDDMM kernel does (gathered
-//     Y rows as the left operand, for d > 32 by way of LDS, the window's X rows as the right one), which leaves lane (j, g) with the scores of window row j and vectors
-//     8g .. 8g+7 -- the lane's piece of the SpMM sparse operand;
+//     Y rows as the left operand, longer ones mostly by way of LDS, the window's X rows as the right one), which leaves
+//     lane (j, g) with the scores of window row j and vectors 8g .. 8g+7 -- the lane's piece of the SpMM sparse operand;
 //   * masks them by the pattern, updates the running row maximum m and row sum l, turns them into
 //     p = 2^(t - m) (t = score * scale * log2 e) rounded to the element type, and scales the fp32
 //     accumulators of the window by 2^(m_old - m_new): the usual streaming form of a softmax-weighted sum;

@@ -17,7 +17,7 @@
 // vector-memory unit then takes a cycle per lane: 64-70 cycles per wave-wide load, 9 TB/s over the chip, however
 // often the rows hit a cache.  With neighbouring lanes on one row a load takes 18-24 cycles.  So for d > 32
 // the rows are gathered row by row like those of SpMM and turned into operand layout in LDS (R-MAT of 65 k rows,
-// d = 128: 38 -> 20 us; lognormal graph of 262 k rows, d = 256: 560 -> 421 us, 6.4 TB/s of rows that miss the
+// d = 128: 38 -> 20 us; lognormal graph of 262 k rows, d = 256: 560 -> 389 us, 7.0 TB/s of rows that miss the
 // L2s).  For d <= 32 a row is half a cache line at most, the loads are few and the L2s set the time; the detour
 // costs 2-5 % there and is left out.
 #include <algorithm>
@@ -110,8 +110,8 @@ __device__ __forceinline__ bool fs_sddmm_unit(const int4 *__restrict__ items, in
 // d > 32.  KS = 32-feature steps of the contraction per chunk of 32 * KS features (one chunk for d <= 32 * KS, else d is
 // walked in several); BB = blocks per step, BB * KS = 4: a step gathers its rows in eight wave-wide loads.  KS = 8 (BB = 1)
 // gathers whole rows of up to 512 bytes in sixteen: the two halves of a row are not fetched at different times, and blocks of
-// one window keep their rows of X, which chunks read anew (lognormal graph of 262 k rows, d = 256: 421 -> 382 us, 7.0 TB/s
-// of rows that miss the L2s; see the launch for where it is used).
+// one window keep their rows of X, which chunks read anew (lognormal graph of 262 k rows, four-row windows, d = 256: 424 -> 389 us; see
+// the launch for where it is used).
 // CSR: also (or only) write the scores in CSR order; kept out of the plain instantiation, whose registers it
 // would cost.  BIG: X or Y spans 4 GiB or more.
 template <int DT, int V, int KS, int BB, bool CHUNKS, bool BIG, bool CSR>
