@@ -223,7 +223,7 @@ int bits_of(int64_t n)  // of 0 .. n - 1
     while (b < 31 && ((n - 1) >> b) != 0) b++;
     return b;
 }
-TransposePlan plan_transpose(int64_t M, int64_t K, int64_t nnz)
+TransposePlan plan_transpose(int64_t M, int64_t K, int64_t nnz, bool any_size = false)
 {
     TransposePlan p;
     // as few passes as digits of ten bits take, evenly wide: 5.3 M entries, 18-bit columns, two passes of nine bits
@@ -235,9 +235,11 @@ TransposePlan plan_transpose(int64_t M, int64_t K, int64_t nnz)
     }
     p.row_shift = bits - p.bits[0];
     p.rows = p.passes <= 2 && p.row_shift + bits_of(std::max<int64_t>(M, 1)) <= 32;
-    // The room is that of the widest digits and of the most groups that so many entries or fewer make: its size depends on
-    // nnz alone and never goes down as nnz goes up, so that a buffer for the largest of several matrices serves them all.
-    const size_t e = fs_align_up((size_t)nnz, 64), counts = (size_t)sort_groups_bound(std::max<int64_t>(nnz, 1)) << kMaxDigitBits;
+    // any_size: the room that is asked for, of the widest digits and of the most groups that so many entries or fewer make.  It
+    // depends on nnz alone and never goes down as nnz goes up, so that a buffer for the largest of several matrices serves
+    // them all.  (A call takes less where it needs less.)
+    const int64_t n = std::max<int64_t>(nnz, 1);
+    const size_t e = fs_align_up((size_t)nnz, 64), counts = any_size ? (size_t)sort_groups_bound(n) << kMaxDigitBits : (size_t)sort_groups(n) << std::max(8, p.bits[0]);
     size_t o = 0;
     p.key0 = o; o += e;
     p.key1 = o; o += e;  // (not used where rows travel)
@@ -262,7 +264,7 @@ extern "C" fs_status fs_csr_transpose_bytes(int64_t M, int64_t K, int64_t nnz, s
 {
     if (!scratch_bytes || !sizes_ok(M, K, nnz)) return FS_ERR_INVALID_ARG;
     if (!sizes_fit(M, K, nnz)) return FS_ERR_TOO_LARGE;
-    *scratch_bytes = plan_transpose(M, K, nnz).total_ints * sizeof(int) + 256;
+    *scratch_bytes = plan_transpose(M, K, nnz, true).total_ints * sizeof(int) + 256;
     return FS_OK;
 }
 

@@ -239,7 +239,7 @@ def test_attention_on_a_matrix_without_entries(fs):
 @pytest.mark.parametrize("d", [8, 32, 40, 64, 72, 96, 128])
 def test_attention_pass_widths_and_feature_steps(fs, V, d):
     """Every width of a pass (32, 64, 128 and 256 columns) and every form of the score contraction (one step in operand
-    layout; two or four by way of LDS, whole and with features missing): against the fp64 definition on one width, and the
+    layout; two or four by way of LDS, four straight in a pass of 256, whole and with features missing): against the fp64 definition on one width, and the
     other widths' columns bit for bit those, because a column's sum does not depend on how many columns a pass takes.
     Hub windows cut across items and windows of several blocks, where a window's rows of X are kept."""
     import torch

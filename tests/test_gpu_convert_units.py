@@ -39,7 +39,8 @@ def pattern(kind, V, rng):
         rows = [np.arange(3000)] + [pick(2500, 10000) for _ in range(V - 1)]
     elif kind == "dense start":  # all rows hold the first columns, then thin out
         rows = [np.unique(np.concatenate([np.arange(700), pick(300 * (r % 3 + 1))])) for r in range(2 * V)]
-    elif kind == "runs":  # runs of 1, 2, 4 ... windows that just fit a unit or just do not, hubs between them, a last group cut short
+    elif kind == "runs":  # runs of 1, 2, 4 ... windows, hubs between them, a last group cut short (what just fits a unit depends on
+        # the matrix' entries: test_convert_units_of_so_many_entries)
         group = 64 // (1 << (V - 1).bit_length()) if V > 1 else 16
         sizes = [0] * group + [512 // group] * group + [512 // group + 1] * group      # a whole group fits, exactly and not
         sizes += [256, 256] * (group // 2) + [257, 256] * (group // 2)                 # pairs

@@ -71,7 +71,8 @@ def test_sddmm_block_order(fs, kind, V, dtype, d):  # noqa: F811
 @pytest.mark.parametrize("V", [4, 8, 16])
 @pytest.mark.parametrize("ordered", [False, True])
 def test_sddmm_whole_rows(fs, ordered, V, d):  # noqa: F811
-    """Enough blocks for rows of up to 512 bytes to be gathered whole: short windows, hubs of many blocks whose rows of X stay,
+    """Eight to ten thousand blocks, from which on windows of sixteen rows gather rows of up to 512 bytes whole and lower ones still
+    take chunks (test_sddmm_whole_rows_by_height has more): short windows, hubs of many blocks whose rows of X stay,
     empty windows between them, a last window of fewer than V rows; in slot order and in launch order."""
     import torch
     dtype = "bf16" if (d // 8 + V // 4) % 2 else "f16"

@@ -159,7 +159,7 @@ def test_gradient_wrt_dense_operand_full_size(fs):
 
 @pytest.mark.parametrize("n,source", [
     (5 << 19, 5 << 19), ((5 << 19) + 1, (5 << 19) + 1),        # plain, and the first banded size: a last workgroup of one element
-    (2621440 + 4097, 64), (2621440 + 4095, 40 << 20),           # everything in one band; most of it past the last one's start
+    (2621440 + 4097, 64), (2621440 + 4095, 40 << 20),           # all close together; most of it past the last band's start
     (8 << 20, 8 << 20), ((8 << 20) + 63, (8 << 20) + 63),       # bands of 1 MB and of 2
     ((1 << 25) + 1, 5 << 19),                                   # plain again
 ])
