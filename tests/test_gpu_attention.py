@@ -290,3 +290,30 @@ def test_attention_of_an_infinite_feature(fs, d, N):
         fmt = convert(fs, A, V, 32)
         got = fs.fs_attention(fmt, to_dev(X.bits, "f16"), to_dev(Y.bits, "f16"), to_dev(H.bits, "f16"), scale=0.2)
         assert scaled_error(from_dev_bits(got), ref, S, "f16") <= bar("f16"), V
+
+
+@pytest.mark.parametrize("V", [4, 8, 16])
+@pytest.mark.parametrize("d", [16, 40, 64, 96, 128])
+def test_attention_many_windows_of_one_block(fs, V, d):
+    """Large launches in which most windows are one block load a window's rows of X for every block: the columns of passes of 128
+    and 256 bit for bit those of passes of 64, which keep them, and sampled rows against the fp64 definition.  A few hubs
+    (windows of several blocks, cut ones), empty windows and a ragged last one among them."""
+    import torch
+    W, K = 66000, 3000
+    M = W * V - 3
+    rng = np.random.default_rng(V * d)
+    rows = np.concatenate([np.repeat(np.arange(0, M, 3), 2), np.full(2500, 5 * V), np.full(90, 9 * V + 1), np.full(2900, M - 1)])
+    key = np.unique(rows.astype(np.int64) * K + rng.integers(0, K, rows.shape[0]))
+    key = key[(key // K // V) % 50 != 7]
+    A = csr_from_coo(M, K, key // K, key % K, "u01", "f16", rng)
+    fmt = convert(fs, A, V)
+    assert fmt.n_items >= 16384 and 2 * fmt.n_blocks < 3 * fmt.W and fmt.n_split_items > 0
+    X, Y, H = (dense(n, w, "n01", "f16", stream(14, 60 + i, d)) for i, (n, w) in enumerate([(M, d), (K, d), (K, 264)]))
+    Xd, Yd, Hd = (to_dev(t.bits, "f16") for t in (X, Y, H))
+    for call in (fs.fs_attention, fs.fs_sddmm_spmm):
+        want = torch.cat([call(fmt, Xd, Yd, Hd[:, n:min(n + 64, 264)].contiguous(), scale=0.1) for n in range(0, 264, 64)], 1).view(torch.int16)
+        for N in (72, 128, 136, 264):
+            assert torch.equal(call(fmt, Xd, Yd, Hd[:, :N].contiguous(), scale=0.1).view(torch.int16), want[:, :N]), N
+    pick = np.unique(np.concatenate([rng.integers(0, M, 200), [0, 5 * V, 9 * V + 1, M - 1]]))
+    err, _ = run_and_check(fs, A, fmt, X, Y, H, 0.1, rows=pick)
+    assert err <= bar("f16")
