@@ -15,11 +15,13 @@
 //             is written once, whole), a descriptor per block and, for blocks of 32 vectors, the rows'
 //             occupancy and CSR positions and the bitmap-packed copy of the values.
 //   4. items  windows longer than one and a half times `chunk` vectors are cut into equal parts of about `chunk`
-//             vectors, shorter ones are packed whole into items of about four blocks (boundary candidates, scan,
-//             compact), and the items are put in launch order.
+//             vectors, shorter ones are packed whole into items of about four blocks (counted and then written window by
+//             window), and the items are put in launch order.
 //
 // A small matrix is bound by the number of launches, about 5 us each, and by the two times the host waits,
-// for the sizes and at the end (R-MAT of 65 k rows, 0.9 M entries: 35 launches, 292 us; now 19 and 214 us).
+// for the sizes and at the end.  So a kernel whose results are to be summed leaves the sum of every workgroup, and the next one adds
+// up those before its own: no launch only scans (R-MAT of 65 k rows, 0.9 M entries: 17 kernels and 192 us with scans between them
+// and a work list made candidate by candidate, now 11 and 166; of 1 M rows, 31 M entries 916 and 891).
 #include <algorithm>
 #include <cstdlib>
 
@@ -36,7 +38,6 @@ constexpr int kMaxItemBlocks = 32;  // a part of a cut window never has more blo
 // extra partial tiles (cfg 4: 702 us against 720 us per call; eight-block parts 752 us)
 constexpr int kDefaultMaxPartBlocks = 16;
 constexpr int kPackBlocks = 4;      // packing grain for short windows, in blocks
-constexpr int kMaxItemSlots = 64;   // the compute kernels hold an item's block descriptors one per lane
 
 // Step 4: work items.  Every window owns max(1, ceil(n_w / KB)) block slots, numbered window after
 // window.  Items are runs of consecutive slots.  A window with more than 1.5 T blocks is cut into
@@ -45,33 +46,42 @@ constexpr int kMaxItemSlots = 64;   // the compute kernels hold an item's block 
 // finer than T, because a block that ends its window (rounding, stores, a narrow operand) costs about
 // twice a block inside a long window, and because more, shorter wavefronts keep a CU's memory and LDS
 // pipelines busier than few that run in step.
-// Window that owns block slot x: the last w in [0, W) with blk_ptr[w] <= x.
-__device__ __forceinline__ int window_of_slot(const int *__restrict__ blk_ptr, int W, int x)
+//
+// Where items start follows from a window's own slots [lo, hi) and its neighbours', so the list is made window by window, without
+// a search (candidate by candidate it took one in the slot table each, 20 k candidates of a 65 k-row R-MAT 8 us, and four launches
+// more than a count and a scan of the windows).  Candidate x (a multiple of Ts) in a window that is cut starts the part it lies in;
+// in any other it starts an item at lo or, if that is nearer, at hi.  A part has at least Ts slots but for the last, so every part but
+// the last holds a candidate, the first one's is the window's first, and an item that begins before the window ends there.
+struct WindowCut {
+    int plen;   // slots of a part
+    int parts;  // items that hold a part of the window; 0: it is not cut
+};
+__device__ __forceinline__ uint32_t first_candidate(uint32_t lo, int Ts) { return (lo + Ts - 1) / Ts * Ts; }  // at lo or behind it
+__device__ __forceinline__ bool is_long(int lo, int hi, int T) { return hi - lo > T + T / 2; }
+__device__ __forceinline__ WindowCut window_cut(int lo, int hi, int T, int Ts)
 {
-    int lo = 0, hi = W;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (blk_ptr[mid] <= x) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-// Candidate i is the boundary for block slot i * Ts.  Candidates that fall on the same boundary are
-// merged afterwards.
-__device__ __forceinline__ int item_boundary(const int *__restrict__ blk_ptr, int W, int NB, int T, int Ts, int i)
-{
-    const int x = (int)min<int64_t>((int64_t)i * Ts, NB - 1);
-    const int w = window_of_slot(blk_ptr, W, x);
-    const int lo = blk_ptr[w], hi = blk_ptr[w + 1];
+    WindowCut c{0, 0};
     const int len = hi - lo;
-    if (len > T + T / 2) {
-        // long window: cut into round(len / T) parts of equal length (within one block), so that no part
-        // is a short tail -- a part costs an fp32 partial tile whatever its length
-        const int parts = (len + T / 2) / T;
-        const int plen = (len + parts - 1) / parts;
-        return lo + (x - lo) / plen * plen;
-    }
-    return (x - lo <= hi - x) ? lo : hi;  // up to one and a half part lengths: keep it whole
+    if (!is_long(lo, hi, T)) return c;
+    // round(len / T) parts of equal length (within one block), so that no part is a short tail -- a part costs an fp32 partial
+    // tile whatever its length
+    const int parts = (len + T / 2) / T;
+    c.plen = (len + parts - 1) / parts;
+    c.parts = (int)((uint32_t)(hi - 1) / Ts * Ts - lo) / c.plen + 1;  // up to the last candidate's
+    if (c.parts == 1) c.parts = 0;
+    return c;
+}
+// a candidate of window [lo, hi) starts an item at lo (a window of up to one and a half part lengths is kept whole)
+__device__ __forceinline__ bool starts_at_lo(int lo, int hi, int T, int Ts)
+{
+    const uint32_t x = first_candidate(lo, Ts);
+    return is_long(lo, hi, T) || (x < (uint32_t)hi && x - lo <= hi - x);
+}
+// ... at hi
+__device__ __forceinline__ bool starts_at_hi(int lo, int hi, int T, int Ts)
+{
+    const uint32_t x = (uint32_t)(hi - 1) / Ts * Ts;
+    return !is_long(lo, hi, T) && x >= (uint32_t)lo && x - lo > hi - x;
 }
 
 // T, the blocks per part of a long window, from the number of block slots NB: enough parts to put about 16
@@ -84,62 +94,57 @@ __host__ __device__ inline int part_blocks(int NB, int t_user)
     return t < 8 ? 8 : (t > kDefaultMaxPartBlocks ? kDefaultMaxPartBlocks : t);
 }
 
-// The number of block slots is still on the device when these two run (total[0], written by the scan of the
-// windows' block counts), so they are launched for the largest number of candidates there can be and work
-// out the real one themselves.
-// cand[i] = candidate i's boundary (cand[n_cand] = NB); flag[i] = 1 where it differs from its predecessor's
-__global__ void k_item_cand(const int *__restrict__ blk_ptr, int W, const int *__restrict__ total, int t_user, int Ts,
-                            int n_cand_max, int *__restrict__ cand, int *__restrict__ flag)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > n_cand_max) return;
-    const int NB = total[0], T = part_blocks(NB, t_user);
-    const int n_cand = (NB + Ts - 1) / Ts;
-    if (i >= n_cand) { cand[i] = NB; flag[i] = 0; return; }
-    const int st = item_boundary(blk_ptr, W, NB, T, Ts, i);
-    cand[i] = st;
-    flag[i] = (i == 0 || st != item_boundary(blk_ptr, W, NB, T, Ts, i - 1)) ? 1 : 0;
-}
+// The window tiles of k_win_ptr: its block slots so far come from its workgroups' sums.  Slots of window w, and of the one before.
+__device__ __forceinline__ int window_slots(const int32_t *__restrict__ win_ptr, int64_t w, int KB) { return max(1, (win_ptr[w + 1] - win_ptr[w] + KB - 1) / KB); }
 
-// pos = exclusive scan of the flags: the distinct boundaries, in order, are the item starts.  Candidate i makes the
-// record of the item that starts at its boundary, {first block slot, blocks, cost << 2 | head << 1 | tail, first
-// vector}: head / tail say that the item starts / ends inside a window.  n_part = its partial tiles; opens = 1 if the window
-// cut at its end begins in it (every cut window has one such item).  Both are cleared past the last item.
-constexpr int kItemMakeThreads = 1024;  // few workgroups, because each adds once to one counter
-__global__ void __launch_bounds__(kItemMakeThreads) k_item_make(const int *__restrict__ blk_ptr, int W, const int32_t *__restrict__ win_ptr, int KB, const int *__restrict__ cand,
-                            const int *__restrict__ pos, const int *__restrict__ total, int Ts, int n_cand_max, int4 *__restrict__ rec,
-                            int *__restrict__ n_part, int *__restrict__ opens, int *__restrict__ max_blocks, int *__restrict__ n_cut)
+// Per workgroup: items that start in its windows, partial tiles (one per part of a cut window), cut windows.
+struct ItemSums {
+    int *items, *tiles, *cuts;
+};
+
+// Block slots (blk_ptr[W]: their number) and, per workgroup, how many items, partial tiles and cut windows its windows make.
+__global__ void __launch_bounds__(kWindowThreads) k_win_slots(const int32_t *__restrict__ win_ptr, int64_t W, int KB, int tiles, const int *__restrict__ slots,
+                                                              int t_user, int Ts, int *__restrict__ blk_ptr, ItemSums sums, int *__restrict__ misc)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int NB = total[0];
-    const int n_cand = min((NB + Ts - 1) / Ts, n_cand_max);
-    bool cut = false;
-    if (i < n_cand && (i == 0 || cand[i] != cand[i - 1])) {
-        const int s0 = cand[i], k = pos[i];
-        int j = i + 1;
-        while (j < n_cand && cand[j] == s0) j++;  // at most the candidates inside one part
-        const int s1 = j < n_cand ? cand[j] : NB;
-        if (s1 - s0 > kMaxItemSlots) atomicMax(max_blocks, s1 - s0);  // never by construction; checked by the host
-        int4 r = make_int4(0, 0, 0, 0);
-        int parts = 0, first = 0;
-        if (s1 > s0) {
-            const int wf = window_of_slot(blk_ptr, W, s0), wl = window_of_slot(blk_ptr, W, s1 - 1);
-            const int bf = s0 - blk_ptr[wf];
-            const bool head = bf > 0, tail = s1 < blk_ptr[wl + 1];
-            first = tail && !(head && wl == wf);
-            parts = (head ? 1 : 0) + first;
-            cut = head || tail;
-            const int cost = s1 - s0 + wl - wf + (tail ? 0 : 1);  // blocks, and blocks that end a window
-            r = make_int4(s0, s1 - s0, cost << 2 | (head ? 2 : 0) | (tail ? 1 : 0), win_ptr[wf] + bf * KB);
-        }
-        rec[k] = r;
-        n_part[k] = parts;
-        opens[k] = first;
+    if (misc[0] & 1) return;  // malformed row pointers
+    const int64_t w0 = (int64_t)blockIdx.x * tiles * kWindowThreads, w1 = min(w0 + (int64_t)tiles * kWindowThreads, W);
+    int before[2] = {0, 0};  // the slots of the workgroups before this one, and of all
+    for (int k = threadIdx.x; k < (int)gridDim.x; k += kWindowThreads) {
+        before[1] += slots[k];
+        if (k < (int)blockIdx.x) before[0] = before[1];
     }
-    const int n_items = pos[n_cand_max];
-    if (i >= n_items && i <= n_cand_max) n_part[i] = opens[i] = 0;
-    const int cuts = __syncthreads_count(cut);
-    if (threadIdx.x == 0 && cuts) atomicAdd(n_cut, cuts);  // a count: the same whatever the order of the additions
+    block_sum<kWindowThreads>(before);
+    int ahead = before[0];
+    const int NB = before[1], T = part_blocks(NB, t_user);
+    int n[3] = {0, 0, 0};  // items, partial tiles, cut windows
+    for (int64_t wt = w0; wt < w1; wt += kWindowThreads) {
+        const int64_t w = wt + threadIdx.x;
+        const int mine = w < w1 ? window_slots(win_ptr, w, KB) : 0;
+        const int prev = w > 0 && w < w1 ? window_slots(win_ptr, w - 1, KB) : 0;
+        int here;
+        const int lo = ahead + block_exclusive_scan<kWindowThreads>(mine, &here), hi = lo + mine;
+        ahead += here;
+        if (w >= w1) continue;
+        blk_ptr[w] = lo;
+        const WindowCut c = window_cut(lo, hi, T, Ts);
+        n[0] += (starts_at_lo(lo, hi, T, Ts) || (w > 0 && starts_at_hi(lo - prev, lo, T, Ts)) ? 1 : 0) + max(c.parts - 1, 0);
+        if (w == W - 1) {
+            blk_ptr[W] = hi;
+            n[0] += starts_at_hi(lo, hi, T, Ts) ? 1 : 0;  // a record of no blocks, the last
+        }
+        n[1] += c.parts;
+        n[2] += c.parts > 0 ? 1 : 0;
+    }
+    block_sum<kWindowThreads>(n);
+    if (threadIdx.x == 0) {
+        sums.items[blockIdx.x] = n[0];
+        sums.tiles[blockIdx.x] = n[1];
+        sums.cuts[blockIdx.x] = n[2];
+        if (blockIdx.x == 0) misc[4] = NB;
+        // counts: the same whatever the order of the additions (one atomic operation for two of them, they are what the workgroups wait for)
+        atomicAdd(reinterpret_cast<unsigned long long *>(misc + 6), (unsigned long long)(uint32_t)n[1] << 32 | (uint32_t)n[0]);
+        if (n[2]) atomicAdd(&misc[5], n[2]);
+    }
 }
 
 // Launch order of the work list.  Parts of cut windows come first, ordered by the column of their first
@@ -152,41 +157,93 @@ __global__ void __launch_bounds__(kItemMakeThreads) k_item_make(const int *__res
 // the hubs.  Measured against the work list's own order: cfg 2 k_spmm 24.0 -> 21.5 us, cfg 4 (four-row
 // windows) 938 -> 827 us with the cost order alone.  The 24-bit key sorts ascending; equal keys keep the
 // work list's order (the sort is stable).
-// The item's record gets its first partial slot (slot_ptr); an item that a cut window begins in also fills that
-// window's entry of the cut-window table and tells every one of its partial slots the window's slot range (the window's
-// tiles are consecutive slots: the tail of this item, the items inside, the head of the window's last item).
-__global__ void __launch_bounds__(256) k_item_fill(const int4 *__restrict__ rec, int n_items, const int *__restrict__ slot_ptr, const int *__restrict__ cut_pos,
-                                                   const int *__restrict__ blk_ptr, const int4 *__restrict__ blk_desc, const int32_t *__restrict__ vec_col,
-                                                   int64_t nvec, int64_t K, int4 *__restrict__ items, int32_t *__restrict__ key,
+// The item records {first block slot, blocks, first partial slot, first vector} with their keys, the table of cut windows and, for
+// every partial slot, its window's slot range, again window by window.  An item that starts at a window's first slot, or with its last
+// part, ends where the next item of the windows behind it starts: at the first candidate from there on, which lies less than Ts windows
+// away.  With Ts <= T <= 32 no item exceeds the 64 block descriptors a wavefront holds: parts have at most 1.25 T + 1 blocks, whole
+// windows 1.5 T, and packing adds less than 3 Ts.  The parts of cut windows are dealt to the threads one by one, and in a
+// long list to the threads of several workgroups, because the hubs of a graph lie side by side (R-MAT of 1 M rows, 60 k parts: written by
+// the wavefront of their window 51 us, by one workgroup 30, by four 23).
+__global__ void __launch_bounds__(kWindowThreads) k_item_fill(const int *__restrict__ blk_ptr, int64_t W, int tiles, int t_user, int Ts, ItemSums sums,
+                                                   const int32_t *__restrict__ win_ptr, int KB, const int32_t *__restrict__ vec_col,
+                                                   int64_t nvec, int64_t K, int n_items, int4 *__restrict__ items, int32_t *__restrict__ key,
                                                    int4 *__restrict__ split_windows, int2 *__restrict__ slot_range)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_items) {
-        if (i < (n_items + 63) / 64 * 64) key[i] = INT32_MAX;  // (k_item_rank reads 64 keys at a time)
-        return;
+    // of the tile's cut windows, in order: parts before them, {first slot, slots a part, end of the last item, first vector}, {first item, parts}
+    __shared__ int part_of[kWindowThreads];
+    __shared__ int4 cut_at[kWindowThreads];
+    __shared__ int2 cut_items[kWindowThreads];
+    const int64_t w0 = (int64_t)blockIdx.x * tiles * kWindowThreads, w1 = min(w0 + (int64_t)tiles * kWindowThreads, W);
+    const int NB = blk_ptr[W], T = part_blocks(NB, t_user);
+    int ahead[3] = {0, 0, 0};  // items, partial tiles, cut windows of the workgroups before this one
+    for (int k = threadIdx.x; k < (int)blockIdx.x; k += kWindowThreads) {
+        ahead[0] += sums.items[k];
+        ahead[1] += sums.tiles[k];
+        ahead[2] += sums.cuts[k];
     }
-    const int4 r = rec[i];
-    const int slot = slot_ptr[i];
-    items[i] = make_int4(r.x, r.y, r.y ? slot : 0, r.w);
-    if (r.y == 0) {
-        key[i] = 0x00FFFFFF;  // empty record: last
-    } else if (r.z & 3) {
-        const int32_t c = nvec > 0 ? vec_col[min((int64_t)r.w, nvec - 1)] : 0;
-        key[i] = (int32_t)(((int64_t)c << 16) / max(K, (int64_t)1));  // column of the first vector, 16 bits
-    } else {
-        key[i] = (1 + 128 - min(r.z >> 2, 128)) << 16;
-    }
-    if (cut_pos[i + 1] != cut_pos[i]) {
-        const int w = blk_desc[r.x + r.y - 1].z, end = blk_ptr[w + 1];
-        int lo = i, hi = n_items;  // the last item that starts before the window's end
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            // (an empty record -- it can only be the last one -- lies past the end)
-            if (rec[mid].y > 0 && rec[mid].x < end) lo = mid; else hi = mid;
+    block_sum<kWindowThreads>(ahead);
+    const bool parts_only = blockIdx.y > 0;
+    if (!parts_only && blockIdx.x == 0 && threadIdx.x < 64 && n_items + (int)threadIdx.x < (n_items + 63) / 64 * 64)
+        key[n_items + threadIdx.x] = INT32_MAX;  // (k_item_rank reads 64 keys at a time)
+    for (int64_t wt = w0; wt < w1; wt += kWindowThreads) {
+        const int64_t w = wt + threadIdx.x;
+        const bool live = w < w1;
+        const int lo = live ? blk_ptr[w] : 0, hi = live ? blk_ptr[w + 1] : 0, lo_prev = live && w > 0 ? blk_ptr[w - 1] : 0;
+        const int q = live ? win_ptr[w] : 0;
+        const WindowCut c = live ? window_cut(lo, hi, T, Ts) : WindowCut{0, 0};
+        const bool begins = live && (starts_at_lo(lo, hi, T, Ts) || (w > 0 && starts_at_hi(lo_prev, lo, T, Ts)));
+        const bool nothing = live && w == W - 1 && starts_at_hi(lo, hi, T, Ts);  // a record of no blocks, the last
+        int n_i, n_t, n_c;
+        const int item = ahead[0] + block_exclusive_scan<kWindowThreads>((begins ? 1 : 0) + max(c.parts - 1, 0) + (nothing ? 1 : 0), &n_i);
+        const int part = block_exclusive_scan<kWindowThreads>(c.parts, &n_t), cut = block_exclusive_scan<kWindowThreads>(c.parts > 0 ? 1 : 0, &n_c);
+        // where the item ends that the window's first slot or last part begins, and the windows that end in it
+        int end = hi, ends = 1;
+        if ((c.parts > 0 || (begins && !parts_only)) && !starts_at_hi(lo, hi, T, Ts)) {
+            const uint32_t x = first_candidate(hi, Ts);  // the next candidate; it lies in the first window that ends behind it
+            end = NB;
+            int64_t v = w + 1;
+            int lo_v = hi;
+            for (; v < W; v++) {
+                const int hi_v = blk_ptr[v + 1];
+                if ((uint32_t)hi_v > x) {
+                    end = lo_v;
+                    if (!starts_at_lo(lo_v, hi_v, T, Ts)) { end = hi_v; v++; }
+                    break;
+                }
+                lo_v = hi_v;
+            }
+            ends = (int)(v - w);
         }
-        const int first = slot + (r.z & 2 ? 1 : 0), parts = lo - i + 1;
-        split_windows[cut_pos[i]] = make_int4(w, first, parts, 0);
-        for (int k = 0; k < parts; k++) slot_range[first + k] = make_int2(first, parts);
+        if (nothing && !parts_only) {
+            items[item + (begins ? 1 : 0)] = make_int4(0, 0, 0, 0);
+            key[item + (begins ? 1 : 0)] = 0x00FFFFFF;  // empty record: last
+        }
+        if (begins && c.parts == 0 && !parts_only) {
+            items[item] = make_int4(lo, end - lo, ahead[1] + part, q);
+            key[item] = (1 + 128 - min(end - lo + ends, 128)) << 16;  // blocks, and blocks that end a window
+        }
+        if (c.parts > 0) {
+            if (!parts_only) split_windows[ahead[2] + cut] = make_int4((int)w, ahead[1] + part, c.parts, 0);
+            part_of[cut] = part;
+            cut_at[cut] = make_int4(lo, c.plen, end, q);
+            cut_items[cut] = make_int2(item, c.parts);
+        }
+        __syncthreads();
+        for (int f = blockIdx.y * kWindowThreads + threadIdx.x; f < n_t; f += gridDim.y * kWindowThreads) {
+            int k = 0;  // the cut window of part f: the last that begins with it or before
+            for (int h = kWindowThreads >> 1; h > 0; h >>= 1) k += k + h < n_c && part_of[k + h] <= f ? h : 0;
+            const int4 at = cut_at[k];
+            const int2 its = cut_items[k];
+            const int m = f - part_of[k], s = at.x + m * at.y, v = at.w + m * at.y * KB, slot = ahead[1] + f;
+            const int32_t column = nvec > 0 ? vec_col[min((int64_t)v, nvec - 1)] : 0;
+            items[its.x + m] = make_int4(s, (m + 1 < its.y ? s + at.y : at.z) - s, slot, v);
+            key[its.x + m] = (int32_t)(((int64_t)column << 16) / max(K, (int64_t)1));  // column of the first vector, 16 bits
+            slot_range[slot] = make_int2(slot - m, its.y);
+        }
+        __syncthreads();
+        ahead[0] += n_i;
+        ahead[1] += n_t;
+        ahead[2] += n_c;
     }
 }
 
@@ -445,10 +502,10 @@ __global__ void __launch_bounds__(256) k_pack(const int4 *__restrict__ blk_desc,
 inline unsigned grid_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
 // Scratch layout (ints): [ranks: nnz 16-bit][scan tmp][err + totals: 64][units, 4 each][where they start in their rows, V each][their vector counts + 1]
-// [windows' places in them, 2 each][units per group + 1][blk_ptr: W+1][windows to cut again: W+1][cut windows that begin in an item][slot_ptr]
-// [item records, 4 each][boundary candidates][their flags / positions][digit counts of the work-list sort]
+// [their first vectors + 1][windows' places in them, 2 each][blk_ptr: W+1][windows to cut again: W+1][sums per workgroup, five times]
+// [keys of the work list, twice][its order][digit counts of its sort]
 struct ScratchPlan {
-    size_t info, tmp, misc, units, pieces, count, win_at, group, blk, redo, rec, start, slotp, cand, upos, hist, total_ints;
+    size_t info, tmp, misc, units, pieces, count, first, win_at, blk, redo, sums, key0, key1, order, hist, total_ints;
 };
 size_t items_bound(int64_t W, int64_t nnz, int KB) { return (size_t)(W + nnz / KB + 2); }
 ScratchPlan plan_scratch(int64_t nnz, int64_t W, int V, int KB)
@@ -462,15 +519,14 @@ ScratchPlan plan_scratch(int64_t nnz, int64_t W, int V, int KB)
     s.units = o; o += fs_align_up(4 * ub, 64);
     s.pieces = o; o += fs_align_up(ub * V, 64);
     s.count = o; o += fs_align_up(ub + 1, 64);
+    s.first = o; o += fs_align_up(ub + 1, 64);
     s.win_at = o; o += fs_align_up(2 * (size_t)W, 64);
-    s.group = o; o += fs_align_up((size_t)W + 1, 64);
     s.blk = o; o += fs_align_up((size_t)W + 1, 64);
     s.redo = o; o += fs_align_up((size_t)W + 1, 64);
-    s.rec = o; o += fs_align_up(4 * ib, 64);
-    s.start = o; o += fs_align_up(ib + 1, 64);
-    s.slotp = o; o += fs_align_up(ib + 1, 64);
-    s.cand = o; o += fs_align_up(ib + 1, 64);
-    s.upos = o; o += fs_align_up(ib + 1, 64);
+    s.sums = o; o += 5 * kScanDirect;
+    s.key0 = o; o += fs_align_up(ib, 64);
+    s.key1 = o; o += fs_align_up(ib, 64);
+    s.order = o; o += fs_align_up(ib, 64);
     s.hist = o; o += fs_align_up((size_t)kKeyDigits * sort_groups_bound((int64_t)ib) + 1, 64);  // digit counts of the work-list sort
     s.total_ints = std::max(o, (size_t)nnz);  // (never less than the four bytes per entry of earlier layouts)
     return s;
@@ -559,29 +615,35 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     const ScratchPlan sp = plan_scratch(nnz, W, V, KB);
     int *scr = (int *)d_scratch;
     int *misc = scr + sp.misc, *tmp = scr + sp.tmp;
-    int *blk_ptr = scr + sp.blk, *redo = scr + sp.redo, *cut_pos = scr + sp.start, *slot_ptr = scr + sp.slotp;
-    int *cand = scr + sp.cand, *upos = scr + sp.upos;
-    int4 *rec = (int4 *)(scr + sp.rec);
+    int *blk_ptr = scr + sp.blk, *redo = scr + sp.redo;
+    int32_t *key0 = scr + sp.key0, *key1 = scr + sp.key1, *order = scr + sp.order;
     uint16_t *info = (uint16_t *)(scr + sp.info);
     int4 *units = (int4 *)(scr + sp.units);
-    int *pieces = scr + sp.pieces, *first_vec = scr + sp.count, *group_pos = scr + sp.group;
+    int *pieces = scr + sp.pieces, *count = scr + sp.count, *first_vec = scr + sp.first;
     int2 *win_at = (int2 *)(scr + sp.win_at);
+    int *sums = scr + sp.sums;  // per workgroup: units, block slots, items, partial tiles, cut windows
+    const ItemSums item_sums{sums + 2 * kScanDirect, sums + 3 * kScanDirect, sums + 4 * kScanDirect};
     char *arena = (char *)d_arena;
     int32_t *win_ptr = (int32_t *)arena;
     CsrView a{d_rowptr, d_colidx, M, (int32_t)nnz};
 
-    // misc: [0] CSR error flags, [1] vectors, [2] longest item, [3] items with a part of a cut window,
-    // [4] block slots, [5] items, [6] partial tiles, [7] cut windows, [8] units -- what the host reads, in one copy
+    // misc: [0] CSR error flags, [1] vectors, [4] block slots, [5] cut windows, [6] items, [7] partial tiles (and items that hold a
+    // part of a cut window: one each), [8] units -- what the host reads, in one copy
     FS_HIP(hipMemsetAsync(misc, 0, 64 * sizeof(int), s));
     const UnitPlan up = unit_plan(nnz, V);
-    const int64_t n_groups = (W + up.group - 1) / up.group;
     const int64_t max_units = units_bound(up, W, nnz);
-    const int *n_units = misc + 8;
-    k_units_count<<<grid_for(std::max<int64_t>(n_groups, 1), 64), kCountThreads, 0, s>>>(a, up, W, group_pos, misc);
+    int *n_units = misc + 8;
+    // workgroups whose sums the next kernel adds up: at most kScanDirect, so each takes as many tiles of windows as that needs
+    auto tiles_for = [&](int64_t per_tile) -> int { return (int)std::max<int64_t>((W + per_tile * kScanDirect - 1) / (per_tile * kScanDirect), 1); };
+    auto groups_for = [&](int64_t per_tile, int tiles) -> unsigned { return grid_for(std::max<int64_t>(W, 1), (int)(per_tile * tiles)); };
+    const int unit_tiles = tiles_for(kCountGroups * up.group), tiles = tiles_for(kWindowThreads);
+    const unsigned unit_grid = groups_for(kCountGroups * up.group, unit_tiles), win_grid = groups_for(kWindowThreads, tiles);
+    k_units_count<<<unit_grid, kCountThreads, 0, s>>>(a, up, W, unit_tiles, sums, misc);
     FS_LAUNCH_CHECK();
+    const int *count_sums = nullptr;
+    bool scanned = false;
     if (W > 0) {
-        if ((st = scan_exclusive(group_pos, n_groups, tmp, s, misc + 8)) != FS_OK) return st;
-        k_units_fill<<<grid_for(n_groups * up.group, 256), 256, 0, s>>>(a, up, W, group_pos, units, redo, misc);
+        k_units_fill<<<unit_grid, kCountThreads, 0, s>>>(a, up, W, unit_tiles, sums, units, n_units, redo, misc);
         FS_LAUNCH_CHECK();
         if (nnz > kUnitEntries) {
             st = launch_units(V <= 8 ? (max_units + 6) / 7 : V <= 16 ? (max_units + 2) / 3 : max_units, [&](int first, unsigned grid) {
@@ -598,14 +660,22 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
             if (st != FS_OK) return st;
         }
         st = launch_units(max_units, [&](int first, unsigned grid) {
-            k_unit_rank<<<grid, 64, 0, s>>>(first, a, up, K, units, n_units, pieces, info, first_vec, win_at, misc);
+            k_unit_rank<<<grid, 64, 0, s>>>(first, a, up, K, units, n_units, pieces, info, count, win_at, misc);
         });
         if (st != FS_OK) return st;
-        if ((st = scan_exclusive(first_vec, max_units, tmp, s, misc + 1)) != FS_OK) return st;
+        // Up to 16 k units every workgroup of k_win_ptr adds up the counts before its own itself, 64 KB at most; more are summed
+        // beforehand, kScanTile at a time.
+        if (max_units > 16384) {
+            const int64_t n_sums = (max_units + kScanTile - 1) / kScanTile;
+            k_scan_reduce<<<(unsigned)n_sums, kScanThreads, 0, s>>>(count, max_units, tmp);
+            FS_LAUNCH_CHECK();
+            scanned = n_sums > kScanDirect;
+            if (scanned && (st = scan_exclusive(tmp, n_sums, tmp + fs_align_up((size_t)n_sums + 1, 64), s)) != FS_OK) return st;
+            count_sums = tmp;
+        }
     }
-    k_win_ptr<<<grid_for(W + 1, 256), 256, 0, s>>>(win_at, first_vec, n_units, W, KB, win_ptr, blk_ptr, misc);
+    k_win_ptr<<<win_grid, kWindowThreads, 0, s>>>(win_at, count, count_sums, scanned, n_units, W, KB, tiles, first_vec, win_ptr, sums + kScanDirect, misc + 1, misc);
     FS_LAUNCH_CHECK();
-    if ((st = scan_exclusive(blk_ptr, W, tmp, s, misc + 4)) != FS_OK) return st;
 
     // Work items (step 4), up to their count: the grain Ts is known here, T follows from the number of block
     // slots, which the kernels read from the device.
@@ -614,15 +684,9 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
 #ifdef FS_TUNING_ENV
     if (const char *e = getenv("FS_PACK_BLOCKS")) Ts = std::max(std::min(atoi(e), t_user > 0 ? t_user : 8), 1);
 #endif
-    const int n_cand_max = (int)((items_bound(W, nnz, KB) + Ts - 1) / Ts);  // block slots <= W + nnz / KB
     if (W > 0) {
-        k_item_cand<<<grid_for(n_cand_max + 1, 256), 256, 0, s>>>(blk_ptr, (int)W, misc + 4, t_user, Ts, n_cand_max, cand, upos);
+        k_win_slots<<<win_grid, kWindowThreads, 0, s>>>(win_ptr, W, KB, tiles, sums + kScanDirect, t_user, Ts, blk_ptr, item_sums, misc);
         FS_LAUNCH_CHECK();
-        if ((st = scan_exclusive(upos, n_cand_max, tmp, s, misc + 5)) != FS_OK) return st;
-        k_item_make<<<grid_for(n_cand_max + 1, kItemMakeThreads), kItemMakeThreads, 0, s>>>(blk_ptr, (int)W, win_ptr, KB, cand, upos, misc + 4, Ts, n_cand_max, rec, slot_ptr, cut_pos,
-                                                                  misc + 2, misc + 3);
-        FS_LAUNCH_CHECK();
-        if ((st = scan_exclusive(slot_ptr, n_cand_max, tmp, s, misc + 6, cut_pos, misc + 7)) != FS_OK) return st;
     }
 
     int h_misc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -636,10 +700,7 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         return fs_convert(M, K, nnz, d_rowptr, d_colidx, d_vals, dtype, 4, KB, chunk, d_arena, arena_bytes, d_scratch,
                           scratch_bytes, stream, out);
     if ((int64_t)V * nvec >= (int64_t)1 << 31) return FS_ERR_TOO_LARGE;
-    const int n_items = W > 0 ? h_misc[5] : 0;
-    // Uncut windows have at most 1.5 T <= 48 blocks and parts of cut windows at most 1.25 T + 1, so no item
-    // exceeds the 64 block descriptors a wavefront holds; a work list that did would be refused here.
-    if (h_misc[2] > kMaxItemSlots) return FS_ERR_UNSUPPORTED;
+    const int n_items = W > 0 ? h_misc[6] : 0;
     chunk = part_blocks(NB, t_user) * KB;
 
     // arena layout, now that the sizes are known.  The value array is followed by 256 zeroed bytes: with no
@@ -675,7 +736,7 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         po.packed_vals = (uint16_t *)(arena + o + pl.vals);
         o += pl.total;
     }
-    int4 *split_windows = (int4 *)(arena + o); o += fs_align_up((size_t)h_misc[7] * 16, 256);
+    int4 *split_windows = (int4 *)(arena + o); o += fs_align_up((size_t)h_misc[5] * 16, 256);
 
     if (!d_vals || W == 0) FS_HIP(hipMemsetAsync(vals_blk, 0, vals_padded, s));
     if (W > 0) {
@@ -706,18 +767,17 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     }
 
     if (n_items > 0) {
-        k_item_fill<<<grid_for(n_items, 256), 256, 0, s>>>(rec, n_items, slot_ptr, cut_pos, blk_ptr, blk_desc, vec_col, nvec, K, items, cand, split_windows,
-                                                           slot_range);
+        k_item_fill<<<dim3(win_grid, n_items > kRankItemsMax ? 4 : 1), kWindowThreads, 0, s>>>(blk_ptr, W, tiles, t_user, Ts, item_sums, win_ptr, KB, vec_col, nvec, K, n_items, items, key0, split_windows,
+                                                        slot_range);
         FS_LAUNCH_CHECK();
         // launch order: a stable sort by the keys
         if (n_items <= kRankItemsMax) {
-            k_item_rank<<<grid_for(n_items, kRankItems), 64 * kRankWaves, 0, s>>>(cand, n_items, items, item_order, items_by_cost);
+            k_item_rank<<<grid_for(n_items, kRankItems), 64 * kRankWaves, 0, s>>>(key0, n_items, items, item_order, items_by_cost);
             FS_LAUNCH_CHECK();
         } else {
-            // cand, upos and cut_pos are free again: keys alternate between cand and upos, the payload between cut_pos and item_order
             int *hist = scr + sp.hist;
-            int32_t *kbuf[2] = {upos, cand};              // pass p reads kbuf[(p + 1) & 1], writes kbuf[p & 1]
-            int32_t *vbuf[2] = {item_order, cut_pos};     // pass p writes vbuf[p & 1]; the last pass (2) writes item_order
+            int32_t *kbuf[2] = {key1, key0};            // pass p reads kbuf[(p + 1) & 1], writes kbuf[p & 1]
+            int32_t *vbuf[2] = {item_order, order};     // pass p writes vbuf[p & 1]; the last pass (2) writes item_order
             for (int p = 0; p < 3; p++) {
                 if ((st = sort_pass<kKeyDigitBits>((const uint32_t *)kbuf[(p + 1) & 1], p == 0 ? nullptr : vbuf[(p + 1) & 1], n_items, kKeyDigitBits * p,
                                                    kKeyDigitBits, hist, tmp, (uint32_t *)kbuf[p & 1], vbuf[p & 1], s)) != FS_OK)
@@ -731,8 +791,8 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
 
     out->M = M; out->K = K; out->nnz = nnz; out->nvec = nvec; out->W = W;
     out->V = V; out->KB = KB; out->dtype = (int32_t)dtype; out->chunk = chunk;
-    out->n_items = n_items; out->n_split_items = h_misc[6]; out->n_split_windows = h_misc[7];
-    out->n_cut_items = h_misc[3];
+    out->n_items = n_items; out->n_split_items = h_misc[7]; out->n_split_windows = h_misc[5];
+    out->n_cut_items = h_misc[7];
     out->win_ptr = win_ptr; out->vec_col = vec_col; out->vec_mask = vec_mask; out->csr_to_slot = csr_to_slot;
     out->vals_blk = vals_blk; out->blk_desc = (const int32_t *)blk_desc; out->n_blocks = NB;
     out->items = (const int32_t *)items; out->split_windows = (const int32_t *)split_windows;

@@ -43,6 +43,30 @@ __device__ __forceinline__ int block_exclusive_scan(int x, int *total)
     return ofs + inc - x;
 }
 
+// Sums over a block of THREADS threads, N at once, to every thread.
+template <int THREADS, int N>
+__device__ __forceinline__ void block_sum(int (&v)[N])
+{
+    __shared__ int of_wave[THREADS / 64][N];
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const int x = wave_inclusive_scan(v[i]);
+        if ((threadIdx.x & 63) == 63) of_wave[threadIdx.x >> 6][i] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        v[i] = 0;
+#pragma unroll
+        for (int w = 0; w < THREADS / 64; w++) v[i] += of_wave[w][i];
+    }
+    __syncthreads();
+}
+
+// A kernel's block sums, up to this many, are added up by every block of the next one: a few loads a thread, cheaper than the launch that
+// would scan them.
+constexpr int64_t kScanDirect = 2048;
+
 // Eight consecutive values of one thread (data is 16-byte aligned and base a multiple of eight): two 16-byte
 // accesses where all eight exist, element by element at the end of the array.
 __device__ __forceinline__ void scan_load8(const int *__restrict__ data, int64_t base, int64_t n, int (&v)[8])
@@ -84,7 +108,6 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const int *__restr
 // In place: data[i] <- sum of data[0..i); the last block also writes data[n] <- grand total.  before: what lies before each
 // block, or (SUMS) the blocks' sums, of which a block then adds up those before its own: up to kScanDirect of them,
 // two loads a thread and cheaper than the launch that would scan them.
-constexpr int64_t kScanDirect = 2048;
 template <bool SUMS>
 __global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ data, int64_t n, const int *__restrict__ before,
                                                              int *__restrict__ total_out)

@@ -123,71 +123,82 @@ __device__ __forceinline__ WindowUnits window_units(const UnitPlan &p, int k, in
     return x;
 }
 
-// How many units every group becomes, and a check of the row pointers.  Those of the workgroup's 64 groups pass through LDS,
-// so that they are read side by side (16 M rows: 155 us read by each thread for itself, now 36).
-constexpr int kCountThreads = 256;
-__global__ void __launch_bounds__(kCountThreads) k_units_count(CsrView a, UnitPlan p, int64_t W, int *__restrict__ pos, int *__restrict__ err)
+// How many units the windows of every workgroup of k_units_fill become, and a check of the row pointers.  A workgroup takes `tiles` tiles of
+// kCountGroups groups; the row pointers of a tile pass through LDS, so that they are read side by side (16 M rows: 155 us read by each
+// thread for itself, now 36).
+constexpr int kCountThreads = 256, kCountGroups = 32;
+__global__ void __launch_bounds__(kCountThreads) k_units_count(CsrView a, UnitPlan p, int64_t W, int tiles, int *__restrict__ made, int *__restrict__ err)
 {
-    constexpr int kMost = 64 * kUnitRows + 1;
+    constexpr int kMost = kCountGroups * kUnitRows + 1, kAhead = 8;
     __shared__ int32_t rp[kMost + kMost / 32 + 1];
     auto at = [](int i) -> int { return i + (i >> 5); };  // windows are often a power of two apart: spread them over the banks
-    const int64_t w0 = (int64_t)blockIdx.x * 64 * p.group, row0 = w0 * p.V;
-    const int here = (int)min((int64_t)64 * p.group * p.V, a.M - row0);
-    for (int i0 = threadIdx.x; i0 <= here; i0 += 4 * kCountThreads) {
-        int32_t v[4];
+    bool bad = false;
+    int n = 0;
+    for (int tile = 0; tile < tiles; tile++) {
+        const int64_t w0 = ((int64_t)blockIdx.x * tiles + tile) * kCountGroups * p.group, row0 = w0 * p.V;
+        if (w0 >= W && w0 > 0) break;
+        const int here = (int)min((int64_t)kCountGroups * p.group * p.V, a.M - row0);
+        if (tile > 0) __syncthreads();
+        for (int i0 = threadIdx.x; i0 <= here; i0 += kAhead * kCountThreads) {
+            int32_t v[kAhead];
 #pragma unroll
-        for (int k = 0; k < 4; k++) v[k] = a.rowptr[row0 + min(i0 + k * kCountThreads, here)];
+            for (int k = 0; k < kAhead; k++) v[k] = a.rowptr[row0 + min(i0 + k * kCountThreads, here)];
 #pragma unroll
-        for (int k = 0; k < 4; k++) rp[at(min(i0 + k * kCountThreads, here))] = v[k];
-    }
-    __syncthreads();
-    bool bad = w0 == 0 && threadIdx.x == 0 && rp[0] != 0;
-    if (threadIdx.x == 0 && row0 + here == a.M && rp[at(here)] != a.nnz) bad = true;
-    for (int i = threadIdx.x; i < 64 * p.group; i += kCountThreads) {  // (the same for the lanes of a wavefront)
-        const int lo = min(i * p.V, here), hi = min(lo + p.V, here);
-        for (int r = lo; r < hi; r++) bad |= rp[at(r + 1)] < rp[at(r)];
-        const WindowUnits x = window_units(p, i & (p.group - 1), rp[at(lo)], rp[at(hi)], w0 + i < W, [&]() -> int64_t {
-            int64_t n = 0;
-            for (int r = lo; r < hi; r++) n += max(rp[at(r + 1)] - rp[at(r)], 0) / p.stride;
-            return n;
-        });
-        int n = x.n;
-        for (int h = 1; h < p.group; h <<= 1) n += __shfl_xor(n, h, 64);
-        if (w0 + i < W && (i & (p.group - 1)) == 0) pos[(w0 + i) / p.group] = n;  // (of malformed row pointers any number: nothing is made of it)
+            for (int k = 0; k < kAhead; k++) rp[at(min(i0 + k * kCountThreads, here))] = v[k];
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) bad |= (w0 == 0 && rp[0] != 0) || (row0 + here == a.M && rp[at(here)] != a.nnz);
+        for (int i = threadIdx.x; i < kCountGroups * p.group; i += kCountThreads) {  // (the same for the lanes of a wavefront)
+            const int lo = min(i * p.V, here), hi = min(lo + p.V, here);
+            for (int r = lo; r < hi; r++) bad |= rp[at(r + 1)] < rp[at(r)];
+            n += window_units(p, i & (p.group - 1), rp[at(lo)], rp[at(hi)], w0 + i < W, [&]() -> int64_t {
+                int64_t samples = 0;
+                for (int r = lo; r < hi; r++) samples += max(rp[at(r + 1)] - rp[at(r)], 0) / p.stride;
+                return samples;
+            }).n;  // (of malformed row pointers any number: nothing is made of it)
+        }
     }
     if (bad) atomicOr(err, 1);
+    int total[1] = {n};
+    block_sum<kCountThreads>(total);
+    if (threadIdx.x == 0) made[blockIdx.x] = total[0];
 }
 
-// One window per thread again: the records {first window, windows, piece, pieces of the window} of the units that begin with it, from
-// position pos[group] on (pos = exclusive scan of the counts).  The many records of a hub window are written by the whole
-// wavefront (a row of 5 M entries, 16 k records: 346 us by one thread, now 10).
-__global__ void __launch_bounds__(256) k_units_fill(CsrView a, UnitPlan p, int64_t W, const int *__restrict__ pos, int4 *__restrict__ units, int *__restrict__ redo, const int *__restrict__ err)
+// One window per thread again: the records {first window, windows, piece, pieces of the window} of the units that begin with it, in
+// the order of the windows.  made = the workgroups' counts, of which each adds up those before its own: at most kScanDirect.  The many
+// records of a hub window are written by the whole wavefront (a row of 5 M entries, 16 k records: 346 us by one thread, now 10).
+__global__ void __launch_bounds__(kCountThreads) k_units_fill(CsrView a, UnitPlan p, int64_t W, int tiles, const int *__restrict__ made, int4 *__restrict__ units,
+                                                              int *__restrict__ n_units, int *__restrict__ redo, const int *__restrict__ err)
 {
     if (*err & 1) return;
-    const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63, k = lane & (p.group - 1);
-    const int64_t lo = min(w * p.V, a.M), hi = min(lo + p.V, a.M);
-    const int base = w - k < W ? pos[(w - k) / p.group] : 0;
-    const WindowUnits x = window_units(p, k, a.rowptr[lo], a.rowptr[hi], w < W, [&]() -> int64_t {
-        int64_t n = 0;
-        for (int64_t r = lo; r < hi; r++) n += (a.rowptr[r + 1] - a.rowptr[r]) / p.stride;
-        return n;
-    });
-    int upto = x.n;
-    for (int h = 1; h < p.group; h <<= 1) {
-        const int before = __shfl_up(upto, h, 64);
-        if (k >= h) upto += before;
+    const int lane = threadIdx.x & 63, per_tile = kCountGroups * p.group;
+    int before[1] = {0};
+    for (int k = threadIdx.x; k < (int)blockIdx.x; k += kCountThreads) before[0] += made[k];
+    block_sum<kCountThreads>(before);
+    int ahead = before[0];
+    for (int64_t i0 = 0; i0 < (int64_t)tiles * per_tile; i0 += kCountThreads) {
+        const int64_t w = (int64_t)blockIdx.x * tiles * per_tile + i0 + threadIdx.x;
+        const bool mine = i0 + threadIdx.x < (int64_t)tiles * per_tile && w < W;  // (few windows a group: a tile has fewer than threads)
+        const int64_t lo = min(w * p.V, a.M), hi = min(lo + p.V, a.M);
+        const WindowUnits x = window_units(p, lane & (p.group - 1), a.rowptr[lo], a.rowptr[hi], mine, [&]() -> int64_t {
+            int64_t n = 0;
+            for (int64_t r = lo; r < hi; r++) n += (a.rowptr[r + 1] - a.rowptr[r]) / p.stride;
+            return n;
+        });
+        int here;
+        const int u = ahead + block_exclusive_scan<kCountThreads>(x.n, &here);
+        ahead += here;
+        if (x.n == 1) units[u] = make_int4((int)w, (int)min((int64_t)x.run, W - w), 0, 1);
+        if (x.n > 1) redo[w] = 0;
+        constexpr int kFew = 16;
+        if (x.n > 1 && x.n <= kFew)
+            for (int q = 0; q < x.n; q++) units[u + q] = make_int4((int)w, 1, q, x.n);
+        for (uint64_t todo = __ballot(x.n > kFew); todo; todo &= todo - 1) {
+            const int l = __builtin_ctzll(todo), first = __shfl(u, l, 64), many = __shfl(x.n, l, 64), of = __shfl((int)w, l, 64);
+            for (int q = lane; q < many; q += 64) units[first + q] = make_int4(of, 1, q, many);
+        }
     }
-    const int u = base + upto - x.n;
-    if (x.n == 1) units[u] = make_int4((int)w, (int)min((int64_t)x.run, W - w), 0, 1);
-    if (x.n > 1) redo[w] = 0;
-    constexpr int kFew = 16;
-    if (x.n > 1 && x.n <= kFew)
-        for (int q = 0; q < x.n; q++) units[u + q] = make_int4((int)w, 1, q, x.n);
-    for (uint64_t todo = __ballot(x.n > kFew); todo; todo &= todo - 1) {
-        const int l = __builtin_ctzll(todo), first = __shfl(u, l, 64), many = __shfl(x.n, l, 64), of = __shfl((int)w, l, 64);
-        for (int q = lane; q < many; q += 64) units[first + q] = make_int4(of, 1, q, many);
-    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *n_units = ahead;
 }
 
 // First position in [lo, hi) whose column is >= c.
@@ -570,22 +581,66 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) k_
     }
 }
 
-// Window pointers from the units' first vectors, and every window's number of block slots.
-__global__ void __launch_bounds__(256) k_win_ptr(const int2 *__restrict__ win_at, const int *__restrict__ first_vec, const int *__restrict__ n_units, int64_t W,
-                                                 int KB, int32_t *__restrict__ win_ptr, int *__restrict__ nblk, const int *__restrict__ err)
+// Every unit's first vector (first_vec[n_units]: the number of vectors), the window pointers, and the block slots of every workgroup's
+// windows.  A workgroup takes `tiles` times kWindowThreads windows, which begin with a unit, and scans their units itself; what lies before them it
+// adds up from the units' counts, or from `sums`, the counts of kScanTile units each (as they are, or scanned, of which there may be any
+// number).  One launch instead of three: the scans of a small conversion were single workgroups, 4 us each and as much between them.
+constexpr int kWindowThreads = 1024;
+__global__ void __launch_bounds__(kWindowThreads) k_win_ptr(const int2 *__restrict__ win_at, const int *__restrict__ count, const int *__restrict__ sums, bool scanned,
+                                                            const int *__restrict__ n_units, int64_t W, int KB, int tiles, int *first_vec,
+                                                            int32_t *__restrict__ win_ptr, int *__restrict__ slots, int *__restrict__ n_vec, const int *__restrict__ err)
 {
-    const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (w > W) return;
-    const bool nothing = W == 0 || (*err & 1);  // no rows, or malformed row pointers: nothing was counted
-    auto ptr = [&](int64_t v) -> int32_t {
-        if (nothing) return 0;
-        if (v == W) return first_vec[*n_units];
-        const int2 at = win_at[v];
+    const int64_t w0 = (int64_t)blockIdx.x * tiles * kWindowThreads, w1 = min(w0 + (int64_t)tiles * kWindowThreads, W);
+    if (W == 0 || (*err & 1)) {  // no rows, or malformed row pointers: nothing was counted
+        for (int64_t w = w0 + threadIdx.x; w < w1; w += kWindowThreads) win_ptr[w] = 0;
+        if (w1 == W && threadIdx.x == 0) win_ptr[W] = 0;
+        if (threadIdx.x == 0) slots[blockIdx.x] = (int)(w1 - w0);
+        return;
+    }
+    const int u0 = win_at[w0].x, u1 = w1 < W ? win_at[w1].x : *n_units;
+    int from = 0, mine = 0;
+    if (sums) {
+        const int t = u0 / kScanTile;
+        from = t * kScanTile;
+        if (scanned) mine = threadIdx.x == 0 ? sums[t] : 0;
+        else
+            for (int k = threadIdx.x; k < t; k += kWindowThreads) mine += sums[k];
+    }
+    for (int i0 = from + threadIdx.x * 8; i0 < u0; i0 += 8 * kWindowThreads) {
+        int v[8];
+        scan_load8(count, i0, u0, v);
+#pragma unroll
+        for (int k = 0; k < 8; k++) mine += v[k];
+    }
+    int before[1] = {mine};
+    block_sum<kWindowThreads>(before);
+    int ahead = before[0];
+    for (int u = u0; u < u1; u += kWindowThreads) {
+        const int i = u + (int)threadIdx.x, c = i < u1 ? count[i] : 0;
+        int here;
+        const int first = ahead + block_exclusive_scan<kWindowThreads>(c, &here);
+        if (i < u1) first_vec[i] = first;
+        ahead += here;
+    }
+    if (w1 == W && threadIdx.x == 0) {
+        first_vec[u1] = ahead;
+        win_ptr[W] = ahead;
+        *n_vec = ahead;
+    }
+    __syncthreads();  // first_vec is read back by other threads than wrote it
+    auto ptr = [&](int64_t w) -> int32_t {
+        if (w >= w1) return ahead;
+        const int2 at = win_at[w];
         return first_vec[at.x] + at.y;
     };
-    const int32_t q = ptr(w);
-    win_ptr[w] = q;
-    if (w < W) nblk[w] = max(1, (ptr(w + 1) - q + KB - 1) / KB);
+    int made[1] = {0};
+    for (int64_t w = w0 + threadIdx.x; w < w1; w += kWindowThreads) {
+        const int32_t q = ptr(w);
+        win_ptr[w] = q;
+        made[0] += max(1, (ptr(w + 1) - q + KB - 1) / KB);
+    }
+    block_sum<kWindowThreads>(made);
+    if (threadIdx.x == 0) slots[blockIdx.x] = made[0];
 }
 
 // What the second kernel writes.  vals null: pattern only (the value array is cleared beforehand); packed_* null: not wanted.

@@ -163,3 +163,52 @@ def test_convert_more_units_than_one_launch_takes(fs):  # noqa: F811
     assert (fmt.vec_mask_t() == 1).all() and (fmt.vals_blk_t() == 1).all()
     del fmt, rp
     torch.cuda.empty_cache()
+
+
+def work_list(wp, KB, T):
+    """Item starts by their definition: every candidate (a multiple of Ts among the block slots) starts the part it lies in of
+    a window that is cut, or an item at the nearer end of one that is not."""
+    blk = np.concatenate([[0], np.cumsum(np.maximum(1, -(-np.diff(wp) // KB)))])
+    Ts, starts = min(T, 4), []
+    for x in range(0, blk[-1], Ts):
+        w = np.searchsorted(blk, x, side="right") - 1
+        lo, hi = blk[w], blk[w + 1]
+        if hi - lo > T + T // 2:
+            plen = -(-(hi - lo) // ((hi - lo + T // 2) // T))
+            starts.append(lo + (x - lo) // plen * plen)
+        else:
+            starts.append(lo if x - lo <= hi - x else hi)
+    return blk, np.unique(starts)
+
+
+@pytest.mark.parametrize("chunk", [0, 32, 64, 96, 128, 160, 224, 1024])
+@pytest.mark.parametrize("W", [1, 2, 1023, 1024, 1025, 2500])  # a workgroup takes 1024 windows
+def test_convert_work_list_is_what_the_candidates_make(fs, W, chunk):  # noqa: F811
+    V, K = 4, 30000
+    rng = np.random.default_rng(W + chunk)
+    sizes = rng.choice([0, 1, 20, 33, 90, 150, 260, 500, 2200, 9000], p=[.2, .3, .1, .1, .1, .08, .06, .04, .015, .005], size=W)
+    sizes[rng.integers(0, W, 2)] = (7000, 400)
+    rows = []
+    for n in sizes:
+        rows += [np.sort(rng.choice(K, size=(n + V - 1 - r) // V, replace=False)) for r in range(V)]
+    A = from_rows(rows, K)
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, A.M, A.K, V=V, KB=32, chunk=chunk)
+    assert_format_equal(fmt, A, V, 32)
+    assert_items_valid(fmt)
+    wp = fmt.win_ptr_t().cpu().numpy().astype(np.int64)
+    blk, starts = work_list(wp, 32, fmt.chunk // 32)
+    ends = np.append(starts[1:], blk[-1])
+    items, order = fmt.items_t().cpu().numpy().astype(np.int64), fmt.item_order_t().cpu().numpy()
+    real = starts < blk[-1]
+    assert len(items) == len(starts) and np.array_equal(items[real, 0], starts[real]) and np.array_equal(items[real, 1], (ends - starts)[real])
+    assert (items[~real] == 0).all()
+    # launch order: parts of cut windows by column, whole windows costliest first, stably
+    w_at = np.searchsorted(blk, items[:, 0], side="right") - 1
+    w_end = np.searchsorted(blk, items[:, 0] + items[:, 1] - 1, side="right") - 1
+    cut = real & ((items[:, 0] > blk[w_at]) | (items[:, 0] + items[:, 1] < blk[w_end + 1]))
+    cost = items[:, 1] + w_end - w_at + 1
+    col = fmt.vec_col_t().cpu().numpy().astype(np.int64)[np.minimum(items[:, 3], fmt.nvec - 1)]
+    key = np.where(~real, 0xFFFFFF, np.where(cut, (col << 16) // K, (129 - np.minimum(cost, 128)) << 16))
+    assert np.array_equal(order, np.argsort(key, kind="stable")) and fmt.n_cut_items == cut.sum()
+    assert np.array_equal(fmt.items_by_cost_t().cpu().numpy(), items[order])
