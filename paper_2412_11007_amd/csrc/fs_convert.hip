@@ -8,8 +8,8 @@
 //
 //   1. units  at most 512 stored entries each, one wavefront's work: a few windows, one window, or a range of
 //             columns of a hub window (fs_units.h).
-//   2. rank   a unit's rows are merged in LDS; an entry's rank is the number of distinct columns before its
-//             own.  Ranks stay per unit (two bytes per entry); a prefix sum over the units' vector counts gives
+//   2. rank   an entry's rank is the number of distinct columns of its unit's window before its own, counted
+//             in LDS.  Ranks stay per unit (two bytes per entry); a prefix sum over the units' vector counts gives
 //             every unit's first vector, and with it win_ptr.
 //   3. place  the same units write vec_col, vec_mask, csr_to_slot, the value array (put together in LDS, so that it
 //             is written once, whole), a descriptor per block and, for blocks of 32 vectors, the rows'
@@ -659,10 +659,8 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
             });
             if (st != FS_OK) return st;
         }
-        st = launch_units(max_units, [&](int first, unsigned grid) {
-            k_unit_rank<<<grid, 64, 0, s>>>(first, a, up, K, units, n_units, pieces, info, count, win_at, misc);
-        });
-        if (st != FS_OK) return st;
+        k_unit_rank<<<(unsigned)std::min<int64_t>(max_units, kRankGrid), 64, 0, s>>>(a, up, K, units, n_units, pieces, info, count, win_at, misc);
+        FS_LAUNCH_CHECK();
         // Up to 16 k units every workgroup of k_win_ptr adds up the counts before its own itself, 64 KB at most; more are summed
         // beforehand, kScanTile at a time.
         if (max_units > 16384) {
@@ -767,7 +765,9 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     }
 
     if (n_items > 0) {
-        k_item_fill<<<dim3(win_grid, n_items > kRankItemsMax ? 4 : 1), kWindowThreads, 0, s>>>(blk_ptr, W, tiles, t_user, Ts, item_sums, win_ptr, KB, vec_col, nvec, K, n_items, items, key0, split_windows,
+        // a list too long for one launch to rank may have its hubs in few workgroups; a grid that fills the chip has work enough
+        const unsigned part_grid = n_items > kRankItemsMax ? std::min(std::max(512 / win_grid, 1u), 4u) : 1;
+        k_item_fill<<<dim3(win_grid, part_grid), kWindowThreads, 0, s>>>(blk_ptr, W, tiles, t_user, Ts, item_sums, win_ptr, KB, vec_col, nvec, K, n_items, items, key0, split_windows,
                                                         slot_range);
         FS_LAUNCH_CHECK();
         // launch order: a stable sort by the keys

@@ -11,15 +11,25 @@ constexpr int kScanPerThread = 8;
 constexpr int kScanTile = kScanThreads * kScanPerThread;
 
 // ---------------------------------------------------------------- prefix sums
+// In lane order by DPP moves: inside the rows of sixteen lanes, then a row's last lane to the next row's and the second row's to the last
+// two.  Lanes that no move reaches get `none`, what combines to nothing.  (By cross-lane reads a step took eight instructions and a trip
+// through LDS.)
+template <typename F>
+__device__ __forceinline__ int wave_scan(int x, int none, F combine)
+{
+#define FS_SCAN_STEP(ctrl, rows) x = combine(x, __builtin_amdgcn_update_dpp(none, x, ctrl, rows, 0xF, false))
+    FS_SCAN_STEP(0x111, 0xF);  // row_shr:1
+    FS_SCAN_STEP(0x112, 0xF);  // row_shr:2
+    FS_SCAN_STEP(0x114, 0xF);  // row_shr:4
+    FS_SCAN_STEP(0x118, 0xF);  // row_shr:8
+    FS_SCAN_STEP(0x142, 0xA);  // row_bcast:15 into rows 1 and 3
+    FS_SCAN_STEP(0x143, 0xC);  // row_bcast:31 into rows 2 and 3
+#undef FS_SCAN_STEP
+    return x;
+}
 __device__ __forceinline__ int wave_inclusive_scan(int x)
 {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
-    return x;
+    return wave_scan(x, 0, [](int a, int b) { return a + b; });
 }
 
 // Exclusive scan of one int per thread across a block of THREADS threads; *total gets the block sum.

@@ -4,12 +4,9 @@
 // A unit is at most kUnitEntries stored entries, handled by one wavefront in LDS: a few consecutive windows, one
 // window, or -- of a hub window with more entries than that -- a range of columns.  What bounds the conversion
 // otherwise is searching: with one thread per entry and a binary search in each of the window's other rows, every
-// probe is a cache line (31.4 M entries in eight-row windows: 1.7 ms in two such kernels).  In LDS the V sorted rows of
-// a window are merged pairwise in log2(V) rounds, the neighbours of an entry in the merged
-// order tell which entries share a vector, and a prefix sum over the first ones of each vector is the rank.
-// Those entries (R-MAT of 1 M rows): the whole conversion 2.70 -> 0.92 ms, of which ranking takes 239 us (about thirty
-// instructions per entry and round: searching the merge paths bounds it, not memory: 260 MB are 50 us) and placing
-// 320 us (0.9 GB, most of it written, 170 us; the LDS tile and scattered two-byte accesses are the rest).
+// probe is a cache line (31.4 M entries in eight-row windows: 1.7 ms in two such kernels).  In LDS a unit's distinct columns are
+// counted in order by the bits of a trie (k_unit_rank).  Those entries (R-MAT of 1 M rows): the whole conversion 2.70 -> 0.77 ms, of which
+// ranking takes 119 us and placing 315 us (1.2 GB, most of it written, 260 us).
 #pragma once
 
 #include <algorithm>
@@ -373,20 +370,37 @@ struct UnitRows {
     int begin;            // its first entry among the unit's, row after row in lane order
     int total;            // entries of the unit
 };
-__device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &p, const int4 &un, int u, int wl, int r,
-                                              const int32_t *__restrict__ piece_start, bool &bad)
+// What has to be read for that, as it stands in memory.
+struct UnitRowLoads {
+    int32_t lo, hi, piece_lo, piece_hi;
+};
+__device__ __forceinline__ bool unit_row_live(const CsrView &a, const UnitPlan &p, const int4 &un, int wl, int r)
+{
+    return wl < un.y && r < p.V && ((int64_t)un.x + wl) * p.V + r < a.M;
+}
+__device__ __forceinline__ UnitRowLoads load_unit_rows(const CsrView &a, const UnitPlan &p, const int4 &un, int u, int wl, int r, const int32_t *__restrict__ piece_start)
+{
+    UnitRowLoads l{0, 0, 0, 0};
+    if (!unit_row_live(a, p, un, wl, r)) return l;
+    const int64_t row = ((int64_t)un.x + wl) * p.V + r;
+    l.lo = a.rowptr[row];
+    l.hi = a.rowptr[row + 1];
+    if (un.w > 1) {
+        if (un.z > 0) l.piece_lo = piece_start[(int64_t)u * p.V + r];
+        if (un.z + 1 < un.w) l.piece_hi = piece_start[((int64_t)u + 1) * p.V + r];
+    }
+    return l;
+}
+__device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &p, const int4 &un, const UnitRowLoads &l, int wl, int r, bool &bad)
 {
     UnitRows x;
-    const int64_t row = ((int64_t)un.x + wl) * p.V + r;
-    int32_t hi = 0;
-    x.row_lo = 0;
-    const bool live = wl < un.y && r < p.V && row < a.M;
-    if (live) row_range(a, row, x.row_lo, hi);
+    x.row_lo = min(max(l.lo, 0), a.nnz);  // (clamped as by row_range)
+    int32_t hi = min(max(l.hi, x.row_lo), a.nnz);
     x.lo = x.row_lo;
-    if (un.w > 1 && live) {
+    if (un.w > 1 && unit_row_live(a, p, un, wl, r)) {
         const int32_t end = hi;
-        if (un.z + 1 < un.w) hi = piece_start[((int64_t)u + 1) * p.V + r];
-        if (un.z > 0) x.lo = piece_start[(int64_t)u * p.V + r];
+        if (un.z + 1 < un.w) hi = l.piece_hi;
+        if (un.z > 0) x.lo = l.piece_lo;
         if (x.lo < x.row_lo || hi < x.lo || hi > end) {  // columns that do not ascend
             bad = true;
             x.lo = hi = x.row_lo;
@@ -394,7 +408,7 @@ __device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &
     }
     x.len = hi - x.lo;
     int upto = wave_inclusive_scan(x.len);
-    x.total = __shfl(upto, 63, 64);
+    x.total = __builtin_amdgcn_readlane(upto, 63);  // known to be the same for all lanes: what depends on it are branches, not masks
     if (x.total > kUnitEntries) {  // columns that do not ascend, again: nothing of this unit is used
         bad = true;
         x.len = x.total = upto = 0;
@@ -407,177 +421,181 @@ __device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &
 // wl: wl * 2^lv + r); count[u] = vectors of unit u; win_at[w] = {the unit window w begins in, vectors of that
 // unit before it}.  Checks the columns (err |= 2).
 //
-// The rows stand in LDS in bit-reversed order (rows 0 4 2 6 1 5 3 7 for V = 8, of each the unit's windows): a round
-// then merges the first half of the unit with the second, whatever rows it pairs, and leaves its output ready for
-// the next.  Every lane makes the same number of consecutive outputs: it finds where they begin in the two halves
-// with one binary search and then takes the smaller of two elements at a time -- a third of the instructions of a
-// search per element -- and when all lanes have theirs in registers they go back to the same place, so that LDS holds
-// the unit once and 28 wavefronts share a CU.  An element is {pair, column, place} in one 64-bit number, so that one
-// comparison orders it; an element larger than all ends each half, so that a merge needs no bounds.
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7))) k_unit_rank(int block0, CsrView a, UnitPlan p, int64_t K, const int4 *__restrict__ units, const int *__restrict__ n_units,
+// A vector is a number (window, column less the unit's smallest one), and its rank is how many different such numbers are smaller: what a
+// trie tells whose nodes are 32-bit masks.  The entries set the bits of the top level, up to 2^kTopBits of them; the number of set
+// bits before an entry's is its node on the next level, five bits further down, and on the last level it is the rank.  A level
+// costs an entry one LDS operation to set its bit and two to count, about twelve instructions whatever the rows are, and a prefix sum over its
+// at most 512 nodes.  Units of short windows of a matrix with 2^20 columns take three levels, pieces of hubs one or two.  What bounds it is
+// the issue of instructions (530 for the 314 entries of a unit on average of R-MAT of 1 M rows, 31 M entries; a merge of the rows
+// in log2(V) rounds of binary searches took 1450) and what a wavefront waits for, so the chip's wavefronts walk the units with the
+// next ones' records and row pointers under way: 238 -> 119 us, 190 MB; the vector units are busy 72 % of that, LDS 54 %.  (Nodes of
+// 64 bits, six bits a level: 770 instructions, 6 KB of LDS and 183 us.)
+constexpr int kTopBits = 14, kDigitBits = 5;
+constexpr int kFewEntries = 8;  // as many are compared one by one (16 M rows with 1 M entries, four a unit: by the trie 193 us, so 147)
+constexpr int kRankGrid = 32 * 256;  // wavefronts that the chip holds at once
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) k_unit_rank(CsrView a, UnitPlan p, int64_t K, const int4 *__restrict__ units, const int *__restrict__ n_units,
                                                   const int32_t *__restrict__ piece_start, uint16_t *__restrict__ info, int *__restrict__ count,
                                                   int2 *__restrict__ win_at, int *__restrict__ err)
 {
-    constexpr int NCH = kUnitEntries / 64;
-    constexpr int MOST = NCH + 1;  // outputs of a lane
-    __shared__ uint64_t buf[kUnitEntries + 2 + MOST];
-    __shared__ uint16_t rank_of[kUnitEntries];
-    __shared__ int begin[kUnitRows];
-    __shared__ int32_t sh_lo[kUnitRows];
+    constexpr int NCH = kUnitEntries / 64, PER = kUnitEntries / 64;  // entries and nodes of a lane
+    static_assert((1 << kTopBits) / 32 <= kUnitEntries && PER == 8, "nodes of the top level; sixteen-byte accesses");
+    __shared__ __attribute__((aligned(16))) uint32_t node[kUnitEntries];
+    __shared__ __attribute__((aligned(16))) uint16_t before[kUnitEntries];  // set bits of the level before a node's
+    __shared__ int2 row_of[kUnitRows];      // rows with entries, in order: {row, what to add to an entry's place in the unit}
+    __shared__ int32_t sh_lo[kUnitRows];    // the latter by row
+    __shared__ uint32_t opens[2 * NCH];     // a bit per entry that opens a row
     __shared__ int win_first[kMaxUnitWindows];
-    const int u = block0 + blockIdx.x, lane = threadIdx.x;
-    if (u >= *n_units || (*err & 1)) {  // (bit 1: malformed row pointers, set before; the records are not there)
-        if (lane == 0) count[u] = 0;
-        return;
-    }
-    const int4 un = units[u];
-    // lane = bit-reversed row * windows + window
-    const int lw = un.y == 1 ? 0 : 32 - __builtin_clz(un.y - 1);
-    const int lr = p.lv + lw;  // log2 of the unit's row slots
-    const int wl = lane & ((1 << lw) - 1);
-    const int r = p.lv ? (int)(__brev((uint32_t)lane >> lw) >> (32 - p.lv)) : 0;
-    bool bad = false;
-    const UnitRows x = unit_rows(a, p, un, u, lane < (1 << lr) ? wl : kMaxUnitWindows, r, piece_start, bad);
-    int E = x.total;
-    begin[lane] = x.begin;
-    sh_lo[lane] = x.lo - x.begin;  // element s of the unit in slot i is entry sh_lo[i] + s of the matrix
-    if (lane < kMaxUnitWindows) win_first[lane] = 0;
-    FS_WAVE_SYNC();
-    int32_t col[NCH];
-    int slot[NCH];
-    FS_EACH(h) {  // every load of the unit is on its way before the first use
-        col[h] = slot[h] = 0;
-        if (64 * h < E) {
-            const int e = min(64 * h + lane, E - 1);
-            int i = 0;  // the last slot with begin[i] <= e
-            for (int w = 1 << lr >> 1; w > 0; w >>= 1) i += begin[i + w] <= e ? w : 0;
-            slot[h] = i;
-            col[h] = a.colidx[sh_lo[i] + e];
-        }
-    } FS_EACH_END;
-    if (un.w > 1 && x.len > 0 && x.lo > x.row_lo && a.colidx[x.lo - 1] >= a.colidx[x.lo]) bad = true;  // across the cut
-    FS_WAIT_LOADS();
-    // elements of the slots whose bit lr - 1 - l is clear: the first half of round l
-    auto first_half = [&](int l) -> int {
-        int n = (lane >> (lr - 1 - l)) & 1 ? 0 : x.len;
-#pragma unroll
-        for (int h = 1; h < 64; h <<= 1) n += __shfl_xor(n, h, 64);
-        return n;
+    int lane = threadIdx.x;
+    const int wl = lane >> p.lv, r = lane & ((1 << p.lv) - 1);
+    if (*err & 1) return;  // malformed row pointers: the records are not there
+    const int n_all = *n_units;
+    // a unit's record, by a vector load (a scalar one under way would be waited for by every use of LDS)
+    auto record = [&](uint32_t u) -> int4 {
+        uint32_t at = min(u, (uint32_t)n_all - 1);
+        asm volatile("" : "+v"(at));
+        return units[at];
     };
-    int n_a = p.lv ? first_half(0) : E;
-    int32_t last = 0;  // the previous 64 entries' last column
-    FS_EACH(h) {
-        if (64 * h < E) {
-            const int e = 64 * h + lane, i = slot[h];
-            const int32_t c = col[h];
-            int32_t prev = __shfl_up(c, 1, 64);
-            if (lane == 0) prev = last;
-            last = __shfl(c, 63, 64);
-            if (e < E) {
-                if (e == begin[i]) prev = -1;  // the unit's first entry of the row
-                if (c < 0 || c >= K || prev >= c) bad = true;
-                const int half = p.lv ? (1 << lr >> 1) - 1 : ~0;  // the pair: the slot without its top bit
-                buf[e + (p.lv && e >= n_a ? 1 : 0)] = ((uint64_t)(uint32_t)(i & half) << 40) | ((uint64_t)(uint32_t)c << 9) | (uint32_t)e;
-            }
-        }
-    } FS_EACH_END;
-    if (__any(bad)) {  // what follows relies on ascending columns: nothing of this unit is used
-        if (lane == 0) atomicOr(err, 2);
-        E = n_a = 0;
-    }
-    const int per_lane = ((E + 63) / 64) | 1;  // odd, so that the lanes' outputs start in different banks
-    // Up to an entry per lane: its place is the number of smaller ones, and no rounds are needed (16 M rows, 1 M entries,
-    // four entries per unit: 280 -> 164 us).
-    const bool few = E <= 64;
-    if (few && p.lv) {
-        const uint64_t key = ((uint64_t)(uint32_t)(slot[0] & ((1 << lw) - 1)) << 40) | ((uint64_t)(uint32_t)col[0] << 9) | (uint32_t)lane;
-        int at = 0;
-        for (int j = 0; j < E; j++) {
-            const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)key, j), hi = __builtin_amdgcn_readlane((uint32_t)(key >> 32), j);
-            at += (((uint64_t)hi << 32) | lo) < key ? 1 : 0;
+    auto uniform = [](const int4 &v) -> int4 {
+        return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y), __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
+    };
+    // The record of the unit after next and the row pointers of the next one are read while a unit is ranked.
+    if ((int)blockIdx.x >= n_all) return;
+    int4 un = uniform(record(blockIdx.x)), coming = record(blockIdx.x + gridDim.x);
+    UnitRowLoads loads = load_unit_rows(a, p, un, blockIdx.x, wl, r, piece_start);
+    for (uint32_t u = blockIdx.x; u < (uint32_t)n_all; u += gridDim.x) {
+        bool bad = false;
+        asm volatile("" : "+v"(lane));  // (numbers that follow from it are not kept from unit to unit)
+        const UnitRows x = unit_rows(a, p, un, loads, wl, r, bad);
+        int E = x.total;
+        if (lane < 2 * NCH) opens[lane] = 0;
+        if (lane < kMaxUnitWindows) win_first[lane] = INT32_MAX;
+        FS_WAVE_SYNC();
+        sh_lo[lane] = x.lo - x.begin;
+        const uint64_t with = __ballot(x.len > 0);
+        if (x.len > 0) {
+            row_of[__builtin_amdgcn_mbcnt_hi((uint32_t)(with >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)with, 0))] = make_int2(lane, x.lo - x.begin);
+            atomicOr(&opens[x.begin >> 5], 1u << (x.begin & 31));
         }
         FS_WAVE_SYNC();
-        if (lane < E) buf[at] = key;
-    }
-    for (int l = few ? p.lv : 0; l < p.lv; l++) {
-        // in LDS: n_a elements, the largest, E - n_a elements, the largest
-        if (lane < 2) buf[lane ? E + 1 : n_a] = ~0ull;
-        FS_WAVE_SYNC();
-        const int n_b = E - n_a, d0 = min(lane * per_lane, E), d1 = min(d0 + per_lane, E);
-        int i = max(0, d0 - n_b), hi = min(d0, n_a);
-        while (__any(i < hi)) {
-            const int mid = (i + hi) >> 1;
-            const bool less = buf[mid] < buf[n_a + d0 - mid];  // (at i == hi: two elements of the unit, and nothing changes)
-            if (i < hi) {
-                if (less) i = mid + 1; else hi = mid;
+        uint32_t col[NCH];
+        int row[NCH];
+        uint64_t first_of[NCH];  // entries that open a row, the same for all lanes
+        int2 of[NCH];
+        const int opening_words = (int)opens[lane & (2 * NCH - 1)];
+        int rows_so_far = 0;
+        FS_EACH(h) {  // the reads of all of a lane's entries are under way together: no branches
+            first_of[h] = (uint32_t)__builtin_amdgcn_readlane(opening_words, 2 * h) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane(opening_words, 2 * h + 1) << 32;
+            // the row of entry e is the one that the last opening at e or before it begins
+            const uint64_t later = first_of[h] >> 1;
+            const int k = rows_so_far - 1 + (int)(first_of[h] & 1);
+            rows_so_far += __popcll(first_of[h]);
+            of[h] = row_of[max((int)__builtin_amdgcn_mbcnt_hi((uint32_t)(later >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)later, (uint32_t)k)), 0)];
+        } FS_EACH_END;
+        FS_EACH(h) {  // every load of the unit is on its way before the first use
+            row[h] = of[h].x;
+            col[h] = 0;
+            if (64 * h < E) col[h] = (uint32_t)a.colidx[of[h].y + 64 * h + min(lane, E - 1 - 64 * h)];
+        } FS_EACH_END;
+        if (un.w > 1 && x.len > 0 && x.lo > x.row_lo && a.colidx[x.lo - 1] >= a.colidx[x.lo]) bad = true;  // across the cut
+        FS_WAIT_LOADS();
+        const int4 next = uniform(coming);
+        loads = load_unit_rows(a, p, next, (int)min(u + gridDim.x, (uint32_t)n_all - 1), wl, r, piece_start);
+        coming = record(u + 2 * gridDim.x);
+        uint32_t last = 0, least = INT32_MAX, most = 0;  // last: the previous 64 entries' last column
+        FS_EACH(h) {
+            if (64 * h < E) {
+                // (lanes past the last entry hold its column once more, and are not looked at)
+                const uint32_t c = col[h], prev = (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)c, 0x138, 0xF, 0xF, false);  // wave_shr:1
+                last = (uint32_t)__builtin_amdgcn_readlane((int)c, 63);
+                const bool opening = __builtin_amdgcn_inverse_ballot_w64(first_of[h]);
+                if (lane < E - 64 * h && (c >= (uint32_t)K || (!opening && prev >= c))) bad = true;
+                least = min(least, c);
+                most = max(most, c);
             }
+        } FS_EACH_END;
+        if (__ballot(bad)) {  // what follows takes numbers from the columns: nothing of this unit is used
+            if (lane == 0) atomicOr(err, 2);
+            E = 0;
         }
-        int j = n_a + 1 + d0 - i;
-        uint64_t va = buf[i], vb = buf[j], got[MOST];
+        E = __builtin_amdgcn_readfirstlane(E);
+        int vectors = 0;
+        int at[NCH];  // an entry's node, at last its rank
+        FS_EACH(h) at[h] = 0; FS_EACH_END;
+        if (E <= kFewEntries) {  // one after the other
+            const uint64_t mine = (uint64_t)(uint32_t)(row[0] >> p.lv) << 32 | col[0];
+            auto number = [&](int j) -> uint64_t {
+                return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), j) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
+            };
+            bool leads = lane < E;  // no earlier entry of the same vector
+            for (int j = 0; j + 1 < E; j++) leads = leads && !(lane > j && number(j) == mine);
+            const uint64_t led = __ballot(leads);
+            vectors = __popcll(led);
+            for (uint64_t m = led; m; m &= m - 1) at[0] += number(__builtin_ctzll(m)) < mine ? 1 : 0;
+        } else {
+            // (columns are below 2^31: signed comparisons do)
+            least = (uint32_t)__builtin_amdgcn_readlane(wave_scan((int)least, INT32_MAX, [](int a, int b) { return min(a, b); }), 63);
+            const uint32_t span = (uint32_t)__builtin_amdgcn_readlane(wave_scan((int)most, 0, [](int a, int b) { return max(a, b); }), 63) - least;
+            const int col_bits = 32 - __builtin_clz(span | 1), win_bits = un.y == 1 ? 0 : 32 - __builtin_clz(un.y - 1);
+            const int below = max(col_bits + win_bits - kTopBits + kDigitBits - 1, 0) / kDigitBits;  // levels below the top one
+            const int top = col_bits - kDigitBits * below;                                          // a column's bits on the top level
+            // One level: bit(h) says which bit of its node an entry sets.  Returns how many are set.
+            auto walk = [&](auto bit) -> int {
+                fs_u4 *mine = reinterpret_cast<fs_u4 *>(node + lane * PER);
+                mine[0] = mine[1] = fs_u4{0u, 0u, 0u, 0u};
+                FS_WAVE_SYNC();
+                FS_EACH(h) {
+                    if (lane < E - 64 * h) atomicOr(node + at[h], 1u << (bit(h) & 31));
+                } FS_EACH_END;
+                FS_WAVE_SYNC();
+                int c[PER + 1];
+                c[0] = 0;
+                const fs_u4 m[2] = {mine[0], mine[1]};
 #pragma unroll
-        for (int t = 0; t < MOST; t++) {
-            got[t] = 0;
-            if (t < per_lane) {
-                const bool first = va < vb;
-                got[t] = first ? va : vb;
-                i += first ? 1 : 0;
-                j += first ? 0 : 1;
-                const uint64_t v = buf[first ? i : j];
-                va = first ? v : va;
-                vb = first ? vb : v;
+                for (int k = 0; k < PER; k++) c[k + 1] = c[k] + __popc(m[k / 4][k % 4]);
+                const int upto = wave_inclusive_scan(c[PER]), from = upto - c[PER];
+                fs_u4 o;
+#pragma unroll
+                for (int k = 0; k < PER / 2; k++) o[k] = (uint32_t)(from + c[2 * k]) | (uint32_t)(from + c[2 * k + 1]) << 16;
+                *reinterpret_cast<fs_u4 *>(before + lane * PER) = o;
+                FS_WAVE_SYNC();
+                FS_EACH(h) {
+                    if (64 * h < E) {
+                        asm volatile("" : "+v"(col[h]), "+v"(at[h]));  // worked out again, not kept from above
+                        at[h] = before[at[h]] + __popc(node[at[h]] & ((1u << (bit(h) & 31)) - 1));
+                    }
+                } FS_EACH_END;
+                FS_WAVE_SYNC();
+                return __builtin_amdgcn_readlane(upto, 63);
+            };
+            auto on_top = [&](int h) -> uint32_t { return ((uint32_t)(row[h] >> p.lv) << top) + (col[h] >> (kDigitBits * below)); };
+            FS_EACH(h) {
+                if (64 * h < E) {
+                    col[h] -= least;
+                    at[h] = (int)(on_top(h) >> 5);
+                }
+            } FS_EACH_END;
+            vectors = walk(on_top);
+            for (int shift = kDigitBits * (below - 1); shift >= 0; shift -= kDigitBits) vectors = walk([&](int h) -> uint32_t { return col[h] >> shift; });
+        }
+        FS_EACH(h) {
+            if (lane < E - 64 * h) {
+                asm volatile("" : "+v"(row[h]));  // read again, not kept
+                info[sh_lo[row[h]] + 64 * h + lane] = (uint16_t)(at[h] | (row[h] << 9));
+                if (__builtin_amdgcn_inverse_ballot_w64(first_of[h])) atomicMin(&win_first[row[h] >> p.lv], at[h]);  // a window's first vector is some row's first entry
+            }
+        } FS_EACH_END;
+        if (lane == 0) count[u] = vectors;
+        FS_WAVE_SYNC();
+        if (un.z == 0) {
+            const int mine = lane < kMaxUnitWindows ? win_first[lane] : INT32_MAX;
+            const uint64_t seen = __ballot(mine != INT32_MAX);  // windows with entries
+            if (lane < un.y) {
+                const uint64_t after = seen >> lane;  // an empty window begins where the next one with entries does
+                win_at[un.x + lane] = make_int2((int)u, after ? win_first[lane + __builtin_ctzll(after)] : vectors);
             }
         }
-        n_a = l + 1 < p.lv ? first_half(l + 1) : E;
-        const uint64_t keep = ((uint64_t)(l + 1 == p.lv ? (1 << lw) - 1 : (1 << lr >> (l + 2)) - 1) << 40) | (((uint64_t)1 << 40) - 1);
+        un = next;
         FS_WAVE_SYNC();
-#pragma unroll
-        for (int t = 0; t < MOST; t++) {
-            const int d = d0 + t;
-            if (t < per_lane && d < d1) buf[d + (d >= n_a ? 1 : 0)] = got[t] & keep;
-        }
-    }
-    FS_WAVE_SYNC();
-    // the first entry of every vector counts one
-    int vectors = 0;
-    uint64_t seen = 0;  // windows with entries
-    for (int e0 = 0; e0 < E; e0 += 64) {
-        const int s = e0 + lane;
-        bool leads = false;
-        uint64_t k1 = 0;
-        int w1 = 0, w0 = -1;
-        if (s < E) {
-            k1 = buf[s];
-            const uint64_t k0 = s > 0 ? buf[s - 1] : ~0ull;
-            leads = (k1 >> 9) != (k0 >> 9);
-            w1 = (int)(k1 >> 40);
-            w0 = s > 0 ? (int)(k0 >> 40) : -1;
-        }
-        const uint64_t mask = __ballot(leads);
-        const int rank = vectors + __popcll(mask & ((2ull << lane) - 1)) - 1;
-        if (s < E) {
-            rank_of[k1 & 511] = (uint16_t)rank;
-            if (w1 != w0) win_first[w1] = rank | 0x10000;
-        }
-        vectors += __popcll(mask);
-    }
-    FS_WAVE_SYNC();
-    FS_EACH(h) {
-        const int e = 64 * h + lane;
-        if (e < E) {
-            const int i = slot[h];
-            const int row = ((i & ((1 << lw) - 1)) << p.lv) | (p.lv ? (int)(__brev((uint32_t)i >> lw) >> (32 - p.lv)) : 0);
-            info[sh_lo[i] + e] = (uint16_t)(rank_of[e] | (row << 9));
-        }
-    } FS_EACH_END;
-    if (lane == 0) count[u] = vectors;
-    if (un.z == 0) {
-        const int mine = lane < kMaxUnitWindows ? win_first[lane] : 0;
-        seen = __ballot(mine != 0);
-        if (lane < un.y) {
-            const uint64_t after = seen >> lane;  // an empty window begins where the next one with entries does
-            const int at = after ? win_first[lane + __builtin_ctzll(after)] & 0xFFFF : vectors;
-            win_at[un.x + lane] = make_int2(u, at);
-        }
     }
 }
 
@@ -694,7 +712,7 @@ __global__ void __launch_bounds__(64) k_unit_place(int block0, CsrView a, UnitPl
     const int4 un = units[u];
     bool bad = false;
     const int my_wl = lane >> p.lv, my_r = lane & ((1 << p.lv) - 1);
-    const UnitRows x = unit_rows(a, p, un, u, my_wl, my_r, piece_start, bad);
+    const UnitRows x = unit_rows(a, p, un, load_unit_rows(a, p, un, u, my_wl, my_r, piece_start), my_wl, my_r, bad);
     const int E = x.total;
     const int f = first_vec[u], n = first_vec[u + 1] - f;
     begin[lane] = x.begin;

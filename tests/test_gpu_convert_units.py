@@ -212,3 +212,24 @@ def test_convert_work_list_is_what_the_candidates_make(fs, W, chunk):  # noqa: F
     key = np.where(~real, 0xFFFFFF, np.where(cut, (col << 16) // K, (129 - np.minimum(cost, 128)) << 16))
     assert np.array_equal(order, np.argsort(key, kind="stable")) and fmt.n_cut_items == cut.sum()
     assert np.array_equal(fmt.items_by_cost_t().cpu().numpy(), items[order])
+
+
+@pytest.mark.parametrize("V", [1, 4, 8, 32])  # units of sixteen, sixteen, eight and two windows
+@pytest.mark.parametrize("span", [1, 2, 31, 33, 1 << 9, (1 << 10) + 1, 1 << 14, (1 << 14) + 1, 1 << 19, (1 << 19) + 3, 1 << 24, (1 << 29) + 1, (1 << 31) - 2])
+def test_convert_columns_that_span_so_much(fs, V, span):  # noqa: F811
+    """Ranks where a level is added: the columns of a unit lie within `span`, both ends among them; short windows, a full unit, a hub."""
+    K = 2 ** 31 - 1
+    rng = np.random.default_rng(V + span % 1000)
+    base = int(rng.integers(0, K - span)) if K > span else 0
+    rows = []
+    for n in [3] * 16 + [500] + [2000] + [0, 7, 1]:
+        for r in range(V):
+            c = np.unique(rng.integers(0, span, (n + V - 1 - r) // V))
+            if r == V - 1 and n:
+                c = np.unique(np.concatenate([c, [0, span - 1]]))
+            rows.append(base + c)
+    A = from_rows(rows, K)
+    rp, ci, va = upload_csr(A)
+    fmt = fs.fs_convert(rp, ci, va, A.M, A.K, V=V)
+    assert_format_equal(fmt, A, V, 32)
+    assert_row_base_valid(fmt, A)
