@@ -20,8 +20,8 @@
 //
 // A small matrix is bound by the number of launches, about 5 us each, and by the two times the host waits,
 // for the sizes and at the end.  So a kernel whose results are to be summed leaves the sum of every workgroup, and the next one adds
-// up those before its own: no launch only scans (R-MAT of 65 k rows, 0.9 M entries: 17 kernels and 192 us with scans between them
-// and a work list made candidate by candidate, now 11 and 166; of 1 M rows, 31 M entries 916 and 891).
+// up those before its own: no launch only scans (R-MAT of 65 k rows, 0.9 M entries: 17 kernels and 192 us with scans between them,
+// ranks by merging and a work list made candidate by candidate, now ten and 149; of 1 M rows, 31 M entries 920 and 752).
 #include <algorithm>
 #include <cstdlib>
 
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(kWindowThreads) k_win_slots(const int32_t *__r
 // windows 1.5 T, and packing adds less than 3 Ts.  The parts of cut windows are dealt to the threads one by one, and in a
 // long list to the threads of several workgroups, because the hubs of a graph lie side by side (R-MAT of 1 M rows, 60 k parts: written by
 // the wavefront of their window 51 us, by one workgroup 30, by four 23).
-__global__ void __launch_bounds__(kWindowThreads) k_item_fill(const int *__restrict__ blk_ptr, int64_t W, int tiles, int t_user, int Ts, ItemSums sums,
+__device__ __forceinline__ void fill_items(int group, int share, int shares, const int *__restrict__ blk_ptr, int64_t W, int tiles, int t_user, int Ts, ItemSums sums,
                                                    const int32_t *__restrict__ win_ptr, int KB, const int32_t *__restrict__ vec_col,
                                                    int64_t nvec, int64_t K, int n_items, int4 *__restrict__ items, int32_t *__restrict__ key,
                                                    int4 *__restrict__ split_windows, int2 *__restrict__ slot_range)
@@ -173,17 +173,17 @@ __global__ void __launch_bounds__(kWindowThreads) k_item_fill(const int *__restr
     __shared__ int part_of[kWindowThreads];
     __shared__ int4 cut_at[kWindowThreads];
     __shared__ int2 cut_items[kWindowThreads];
-    const int64_t w0 = (int64_t)blockIdx.x * tiles * kWindowThreads, w1 = min(w0 + (int64_t)tiles * kWindowThreads, W);
+    const int64_t w0 = (int64_t)group * tiles * kWindowThreads, w1 = min(w0 + (int64_t)tiles * kWindowThreads, W);
     const int NB = blk_ptr[W], T = part_blocks(NB, t_user);
     int ahead[3] = {0, 0, 0};  // items, partial tiles, cut windows of the workgroups before this one
-    for (int k = threadIdx.x; k < (int)blockIdx.x; k += kWindowThreads) {
+    for (int k = threadIdx.x; k < group; k += kWindowThreads) {
         ahead[0] += sums.items[k];
         ahead[1] += sums.tiles[k];
         ahead[2] += sums.cuts[k];
     }
     block_sum<kWindowThreads>(ahead);
-    const bool parts_only = blockIdx.y > 0;
-    if (!parts_only && blockIdx.x == 0 && threadIdx.x < 64 && n_items + (int)threadIdx.x < (n_items + 63) / 64 * 64)
+    const bool parts_only = share > 0;
+    if (!parts_only && group == 0 && threadIdx.x < 64 && n_items + (int)threadIdx.x < (n_items + 63) / 64 * 64)
         key[n_items + threadIdx.x] = INT32_MAX;  // (k_item_rank reads 64 keys at a time)
     for (int64_t wt = w0; wt < w1; wt += kWindowThreads) {
         const int64_t w = wt + threadIdx.x;
@@ -229,7 +229,7 @@ __global__ void __launch_bounds__(kWindowThreads) k_item_fill(const int *__restr
             cut_items[cut] = make_int2(item, c.parts);
         }
         __syncthreads();
-        for (int f = blockIdx.y * kWindowThreads + threadIdx.x; f < n_t; f += gridDim.y * kWindowThreads) {
+        for (int f = share * kWindowThreads + threadIdx.x; f < n_t; f += shares * kWindowThreads) {
             int k = 0;  // the cut window of part f: the last that begins with it or before
             for (int h = kWindowThreads >> 1; h > 0; h >>= 1) k += k + h < n_c && part_of[k + h] <= f ? h : 0;
             const int4 at = cut_at[k];
@@ -245,6 +245,31 @@ __global__ void __launch_bounds__(kWindowThreads) k_item_fill(const int *__restr
         ahead[1] += n_t;
         ahead[2] += n_c;
     }
+}
+
+// What is left when the units are placed: the work list, by the first groups * shares workgroups, and, where they are few, the blocks that
+// pieces of hub windows share, by the others: a launch less where launches are the time (R-MAT of 65 k rows 9 and 5 us, now 9).
+struct ItemFill {
+    int groups, shares, tiles, t_user, Ts, n_items;
+    ItemSums sums;
+    int4 *items;
+    int32_t *key;
+    int4 *split_windows;
+    int2 *slot_range;
+};
+__global__ void __launch_bounds__(kWindowThreads) __attribute__((amdgpu_waves_per_eu(4))) k_finish(ItemFill fill, const int *__restrict__ blk_ptr, int64_t W, const int32_t *__restrict__ win_ptr, int KB, int64_t nvec, int64_t K,
+                                                           int V, const int4 *__restrict__ units, int n_units, const int *__restrict__ first_vec,
+                                                           const uint16_t *__restrict__ vals, PlaceOut out)
+{
+    const int first = fill.groups * fill.shares;
+    if ((int)blockIdx.x < first) {
+        fill_items(blockIdx.x % fill.groups, blockIdx.x / fill.groups, fill.shares, blk_ptr, W, fill.tiles, fill.t_user, fill.Ts, fill.sums, win_ptr, KB, out.vec_col, nvec, K,
+                   fill.n_items, fill.items, fill.key, fill.split_windows, fill.slot_range);
+        return;
+    }
+    constexpr int kWaves = kWindowThreads / 64;
+    __shared__ __attribute__((aligned(16))) uint16_t stage[kWaves * 2][2 * kSharedStage];
+    finish_shared_blocks((int64_t)(((int)blockIdx.x - first) * kWaves + (threadIdx.x >> 6)) * kSharedPerWave, n_units, V, units, first_vec, win_ptr, blk_ptr, vals, out, stage[threadIdx.x >> 5]);
 }
 
 // The work list in launch order: by_cost[t] = items[order[t]], so that a wavefront finds its item with one load.
@@ -755,21 +780,26 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
             k_block_row_base<<<grid_for((int64_t)NB * V, 256), 256, 0, s>>>(a, V, blk_desc, NB, vec_col, nvec, blk_row_base);
             FS_LAUNCH_CHECK();
         }
-        if (nnz > kUnitEntries) {
-            st = launch_units((units_made + kSharedPerWave - 1) / kSharedPerWave, [&](int first, unsigned grid) {
-                if (KB == 32) k_shared_blocks<<<grid, 64, 0, s>>>(first, V, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
+        // With the work list only up to 16 k units, a workgroup a CU: its registers leave half the wavefronts that the shared blocks
+        // wait with by themselves (R-MAT of 1 M rows, 100 k units: 72 us together, 45 and 20 apart).
+        const bool together = KB == 32 && units_made <= 512 * kSharedPerWave * (kWindowThreads / 64);
+        if (nnz > kUnitEntries && !together) {
+            const int each = KB == 32 ? kSharedPerWave * kSharedWaves : kSharedPerWave;
+            st = launch_units((units_made + each - 1) / each, [&](int first, unsigned grid) {
+                if (KB == 32) k_shared_blocks<<<grid, 64 * kSharedWaves, 0, s>>>(first, V, units, units_made, first_vec, win_ptr, blk_ptr, va, po);
                 else k_shared_blocks_any<<<grid, 64, 0, s>>>(first, V, KB, units, n_units, first_vec, win_ptr, blk_ptr, va, po);
-            });
+            }, kSharedWaves);
             if (st != FS_OK) return st;
         }
+        // a list too long for one launch to rank may have its hubs in few workgroups; a grid that fills the chip has work enough
+        const unsigned shares = n_items > kRankItemsMax ? std::min(std::max(512 / win_grid, 1u), 4u) : 1;
+        const ItemFill fill{(int)win_grid, (int)shares, tiles, t_user, Ts, n_items, item_sums, items, key0, split_windows, slot_range};
+        const int shared = nnz > kUnitEntries && together ? grid_for(units_made, kSharedPerWave * (kWindowThreads / 64)) : 0;
+        k_finish<<<win_grid * shares + shared, kWindowThreads, 0, s>>>(fill, blk_ptr, W, win_ptr, KB, nvec, K, V, units, units_made, first_vec, va, po);
+        FS_LAUNCH_CHECK();
     }
 
     if (n_items > 0) {
-        // a list too long for one launch to rank may have its hubs in few workgroups; a grid that fills the chip has work enough
-        const unsigned part_grid = n_items > kRankItemsMax ? std::min(std::max(512 / win_grid, 1u), 4u) : 1;
-        k_item_fill<<<dim3(win_grid, part_grid), kWindowThreads, 0, s>>>(blk_ptr, W, tiles, t_user, Ts, item_sums, win_ptr, KB, vec_col, nvec, K, n_items, items, key0, split_windows,
-                                                        slot_range);
-        FS_LAUNCH_CHECK();
         // launch order: a stable sort by the keys
         if (n_items <= kRankItemsMax) {
             k_item_rank<<<grid_for(n_items, kRankItems), 64 * kRankWaves, 0, s>>>(key0, n_items, items, item_order, items_by_cost);

@@ -84,13 +84,13 @@ inline int64_t units_bound(const UnitPlan &p, int64_t W, int64_t nnz)
     const int64_t groups = (W + p.group - 1) / p.group;
     return std::min(groups + (p.group - 1) * (nnz / (p.fill + 1)), W) + nnz / (p.per * p.stride) + 2;
 }
-// Wavefronts per launch: a launch has fewer than 2^32 threads, so a larger number takes several.
-constexpr int64_t kUnitLaunch = (int64_t)1 << 24;
+// Workgroups per launch: a launch has fewer than 2^32 threads, so a larger number takes several.
 template <typename Launch>
-fs_status launch_units(int64_t n, Launch launch)
+fs_status launch_units(int64_t n, Launch launch, int waves = 1)
 {
-    for (int64_t first = 0; first < n; first += kUnitLaunch) {
-        launch((int)first, (unsigned)std::min(n - first, kUnitLaunch));
+    const int64_t most = ((int64_t)1 << 24) / waves;
+    for (int64_t first = 0; first < n; first += most) {
+        launch((int)first, (unsigned)std::min(n - first, most));
         FS_LAUNCH_CHECK();
     }
     return FS_OK;
@@ -211,7 +211,9 @@ __device__ __forceinline__ int32_t first_at_least(const int32_t *__restrict__ co
 // Where the pieces of hub windows start: start[u * V + r] = the first entry of row r that belongs to piece u or a later
 // one.  Piece k should start where k / pieces of the window's entries lie before; that column is looked for among
 // those of the window's longest row, by interpolation between the two nearest ones known (a guess from the longest
-// row alone is off by a factor where the hot columns saturate all rows).  A few steps are enough for a graph; a window
+// row alone is off by a factor where the hot columns saturate all rows).  A search in a row is a probe a lane, and the probes are the
+// time; so a step ends the search as soon as a piece that is off at both ends still fits a unit, and later steps look
+// near by first (R-MAT of 1 M rows 68 -> 61 us, of 65 k rows 13 -> 10).  A few steps are enough for a graph; a window
 // one of whose pieces came out too large for a unit is noted in redo[] for k_pieces_exact.  64 / ROWS pieces per
 // wavefront, one row per lane; the last one of a wavefront is only there for the size of the one before.
 template <int ROWS>  // a power of two, at least V
@@ -219,7 +221,7 @@ __global__ void __launch_bounds__(64) k_pieces(int block0, CsrView a, UnitPlan p
                                                int32_t *__restrict__ start, int *__restrict__ redo, const int *__restrict__ err)
 {
     constexpr int PER = 64 / ROWS;
-    constexpr int CLOSE = kUnitEntries / 12;  // near enough: pieces are planned at most five sixths full
+    const int close = (kUnitEntries - p.per * p.stride) / 2;  // near enough: a piece too long at both ends still fits
     const int lane = threadIdx.x, k = lane / ROWS, r = lane % ROWS;
     const int u0 = (block0 + blockIdx.x) * (PER - 1), u = u0 + k, n = *n_units;
     if (u0 >= n || (*err & 1)) return;
@@ -246,6 +248,7 @@ __global__ void __launch_bounds__(64) k_pieces(int block0, CsrView a, UnitPlan p
     // between which places of the longest row the column lies, and what of this row and of all lies before them
     int i_lo = 0, i_hi = long_len, f_lo = 0, f_hi = all;
     int32_t at_lo = lo, at_hi = hi, at = lo;
+    int off = 0;  // entries by which the last column was off
     bool done = !hub || un.z == 0;
     for (int step = 0; step < 6 && !__all(done); step++) {
         int i = i_lo + (int)((int64_t)(want - f_lo) * (i_hi - i_lo) / max(f_hi - f_lo, 1));
@@ -253,11 +256,20 @@ __global__ void __launch_bounds__(64) k_pieces(int block0, CsrView a, UnitPlan p
         i = min(max(i, i_lo), long_len - 1);
         if (!done) {
             const int32_t c = a.colidx[long_lo + i];
-            at = first_at_least(a.colidx, at_lo, at_hi, c);
+            int32_t from = at_lo, to = at_hi;
+            if (off != 0) {  // the row's share of what is missing, twice over, is mostly more than enough
+                const int reach = 2 * (int)((int64_t)abs(off) * (hi - lo) / max(all, 1)) + 8;
+                const int32_t q = off < 0 ? from + reach : to - 1 - reach;
+                if (q >= from && q < to) {
+                    if (a.colidx[q] < c) from = q + 1; else to = q;
+                }
+            }
+            at = first_at_least(a.colidx, from, to, c);
         }
         const int f = over_rows(at - lo);
         if (!done) {
-            if (abs(f - want) <= CLOSE || i_hi - i_lo <= 1) done = true;
+            off = f - want;
+            if (abs(off) <= close || i_hi - i_lo <= 1) done = true;
             if (f < want) { i_lo = i + 1; f_lo = f; at_lo = at; }
             else { i_hi = i; f_hi = f; at_hi = at; }
             if (i_lo >= i_hi) done = true;
@@ -894,61 +906,85 @@ __global__ void __launch_bounds__(64) k_unit_place(int block0, CsrView a, UnitPl
 }
 
 // A block that more than one piece of a hub window reaches into is finished by the first piece that begins inside it.  Its
-// vectors, and the CSR position of each row's first entry in it, are in place.  Returns the block slot, or -1: none.
-constexpr int kSharedPerWave = 2;  // units a wavefront looks at
-__device__ __forceinline__ int shared_block(int u, int n, int KB, const int4 *__restrict__ units, const int *__restrict__ first_vec,
-                                            const int32_t *__restrict__ win_ptr, const int *__restrict__ blk_ptr, int &s, int &kb)
+// vectors, and the CSR position of each row's first entry in it, are in place.  A unit's record, its first vector and the one of the unit
+// before it; from them the block, its first vector and its width; xb: the block slot, or -1 (none).
+struct SharedBlock {
+    int xb, s, kb;
+};
+__device__ __forceinline__ SharedBlock shared_block(bool live, int KB, const int4 &un, int first, int first_before, int f_w, int f_next, int slot0)
 {
-    if (u >= n) return -1;
-    const int4 un = units[u];
-    if (un.w <= 1 || un.z == 0) return -1;
-    const int f_w = win_ptr[un.x], n_w = win_ptr[un.x + 1] - f_w;
-    const int o = first_vec[u] - f_w, b = o / KB;
-    if (o <= b * KB || o >= n_w || first_vec[u - 1] - f_w > b * KB) return -1;
-    s = f_w + b * KB;
-    kb = min(KB, n_w - b * KB);
-    return blk_ptr[un.x] + b;
+    const int n_w = f_next - f_w, o = first - f_w, b = o / KB;
+    const bool shared = live && un.w > 1 && un.z > 0 && o > b * KB && o < n_w && first_before - f_w <= b * KB;
+    return SharedBlock{shared ? slot0 + b : -1, f_w + b * KB, shared ? min(KB, n_w - b * KB) : 0};
 }
 
-// Blocks of 32 vectors: half a wavefront per unit, so that its two blocks wait for memory together (R-MAT of 1 M rows, 31 M
-// entries: 86 us one after the other, now 59).
-__global__ void __launch_bounds__(64) k_shared_blocks(int block0, int V, const int4 *__restrict__ units, const int *__restrict__ n_units, const int *__restrict__ first_vec,
-                                                      const int32_t *__restrict__ win_ptr, const int *__restrict__ blk_ptr,
-                                                      const uint16_t *__restrict__ vals, PlaceOut out)
+// Blocks of 32 vectors: half a wavefront per unit, so that its two blocks wait for memory together (four of them need the registers of
+// the other wavefronts: 51 us).  A block's values pass through LDS, eight rows at a time, and leave in sixteen-byte pieces.  What bounds it is
+// the chain record -> window -> masks -> values of short wavefronts: R-MAT of 1 M rows, 100 k units, values stored row by row and one by
+// one 51 us, now 45.
+constexpr int kSharedPerWave = 2;  // units a wavefront looks at
+constexpr int kSharedStage = 8 * 32;  // elements of eight rows of a block
+__device__ __forceinline__ void finish_shared_blocks(int64_t u0, int n_units, int V, const int4 *__restrict__ units, const int *__restrict__ first_vec,
+                                                     const int32_t *__restrict__ win_ptr, const int *__restrict__ blk_ptr,
+                                                     const uint16_t *__restrict__ vals, const PlaceOut &out, uint16_t *stage /* 2 * kSharedStage of this half */)
 {
-    static_assert(kSharedPerWave == 2, "half a wavefront per unit");
-    const int half = threadIdx.x & 32, c = threadIdx.x & 31;
-    int s = 0, kb = 0;
-    const int xb = shared_block((block0 + blockIdx.x) * kSharedPerWave + (half >> 5), *n_units, 32, units, first_vec, win_ptr, blk_ptr, s, kb);
-    if (!__any(xb >= 0)) return;
-    const uint32_t m = c < kb ? out.vec_mask[s + c] : 0u;  // (nothing stored where there is no block)
-    const int32_t base = xb >= 0 && c < V ? out.row_base[(int64_t)xb * V + c] : 0;
-    int32_t packed = xb >= 0 && out.packed_vals ? out.packed_ofs[xb] : 0;
+    const int lane = threadIdx.x & 63, half = lane & 32, c = lane & 31;
+    const int u = (int)min(u0 + (half >> 5), (int64_t)n_units - 1);
+    const int4 un = units[u];
+    const SharedBlock sb = shared_block(u0 + (half >> 5) < n_units, 32, un, first_vec[u], first_vec[max(u - 1, 0)], win_ptr[un.x], win_ptr[un.x + 1], blk_ptr[un.x]);
+    if (!__ballot(sb.xb >= 0)) return;
+    const uint32_t m = c < sb.kb ? out.vec_mask[sb.s + c] : 0u;  // (nothing stored where there is no block)
+    const int32_t base = sb.xb >= 0 && c < V ? out.row_base[(int64_t)sb.xb * V + c] : 0;
+    int32_t packed = sb.xb >= 0 && out.packed_vals ? out.packed_ofs[sb.xb] : 0;
     const uint32_t below = (1u << c) - 1;
     for (int r0 = 0; r0 < V; r0 += 8) {  // eight rows' loads together
         uint16_t v[8];
-        uint32_t row[8];
+        uint32_t mine = 0;  // occupancy of row r0 + c, in the first eight lanes
 #pragma unroll
         for (int g = 0; g < 8; g++) {
             const int r = r0 + g;
             const bool has = r < V && ((m >> r) & 1u);
             const uint64_t both = __ballot(has);
-            row[g] = (uint32_t)(half ? both >> 32 : both);
-            const int32_t q = __shfl(base, half + min(r, 31), 64) + __popc(row[g] & below);
+            const uint32_t row = (uint32_t)(half ? both >> 32 : both);
+            if (c == g) mine = row;
+            const int32_t q = __shfl(base, half + min(r, 31), 64) + __popc(row & below);
             v[g] = has && vals ? vals[q] : (uint16_t)0;
         }
+        const int rows = min(V - r0, 8);
+        if (sb.xb >= 0 && c < rows) out.row_bits[(int64_t)sb.xb * V + r0 + c] = mine;
+        if (!vals) continue;
+        int n = 0;  // stored values so far
 #pragma unroll
         for (int g = 0; g < 8; g++) {
-            const int r = r0 + g;
-            if (r >= V) break;
-            if (c == 0 && xb >= 0) out.row_bits[(int64_t)xb * V + r] = row[g];
-            if (vals && c < kb) {
-                out.vals_blk[(int64_t)V * s + r * kb + c] = v[g];
-                if (out.packed_vals && ((m >> r) & 1u)) out.packed_vals[packed + __popc(row[g] & below)] = v[g];
-            }
-            packed += __popc(row[g]);
+            const uint32_t row = __shfl(mine, half + g, 64);
+            if (g < rows && c < sb.kb) stage[g * sb.kb + c] = v[g];
+            if ((row >> c) & 1u) stage[kSharedStage + n + __popc(row & below)] = v[g];
+            n += __popc(row);
         }
+        FS_WAVE_SYNC();
+        uint16_t *dst = out.vals_blk + (int64_t)V * sb.s + r0 * sb.kb;
+        if (V % 8 == 0) {
+            if (c * 8 < rows * sb.kb) *reinterpret_cast<fs_u4 *>(dst + c * 8) = *reinterpret_cast<const fs_u4 *>(stage + c * 8);
+        } else if (V % 4 == 0) {
+            for (int i = c * 4; i < rows * sb.kb; i += 128) *reinterpret_cast<uint2 *>(dst + i) = *reinterpret_cast<const uint2 *>(stage + i);
+        } else {
+            for (int i = c; i < rows * sb.kb; i += 32) dst[i] = stage[i];
+        }
+        if (out.packed_vals)
+            for (int i = c; i < n; i += 32) out.packed_vals[packed + i] = stage[kSharedStage + i];
+        packed += n;
+        FS_WAVE_SYNC();
     }
+}
+
+constexpr int kSharedWaves = 4;  // per workgroup: they share nothing, but there are a quarter as many to start
+__global__ void __launch_bounds__(64 * kSharedWaves) __attribute__((amdgpu_waves_per_eu(8))) k_shared_blocks(int block0, int V, const int4 *__restrict__ units, int n_units, const int *__restrict__ first_vec,
+                                                      const int32_t *__restrict__ win_ptr, const int *__restrict__ blk_ptr,
+                                                      const uint16_t *__restrict__ vals, PlaceOut out)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t stage[2 * kSharedWaves][2 * kSharedStage];
+    finish_shared_blocks((((int64_t)block0 + blockIdx.x) * kSharedWaves + (threadIdx.x >> 6)) * kSharedPerWave, n_units, V, units, first_vec, win_ptr, blk_ptr, vals, out,
+                         stage[threadIdx.x >> 5]);
 }
 
 // Other block widths: one block after the other by the whole wavefront.
@@ -958,7 +994,12 @@ __global__ void __launch_bounds__(64) k_shared_blocks_any(int block0, int V, int
 {
     const int lane = threadIdx.x;
     int my_s = 0, my_kb = 0, my_x = -1;
-    if (lane < kSharedPerWave) my_x = shared_block((block0 + blockIdx.x) * kSharedPerWave + lane, *n_units, KB, units, first_vec, win_ptr, blk_ptr, my_s, my_kb);
+    const int u = (block0 + blockIdx.x) * kSharedPerWave + lane;
+    if (lane < kSharedPerWave && u < *n_units) {
+        const int4 un = units[u];
+        const SharedBlock sb = shared_block(true, KB, un, first_vec[u], first_vec[max(u - 1, 0)], win_ptr[un.x], win_ptr[un.x + 1], blk_ptr[un.x]);
+        my_x = sb.xb; my_s = sb.s; my_kb = sb.kb;
+    }
     if (!vals) return;
     for (uint64_t todo = __ballot(my_x >= 0); todo; todo &= todo - 1) {
         const int k = __builtin_ctzll(todo);
