@@ -12,10 +12,14 @@
 // first merges the pairs of all parts of its window in a fixed order.  No atomics: results are
 // bit-reproducible.
 //
-// Lane (j, q) = (lane % V, lane / V) handles row j and the E = V/2 vectors q*E .. q*E+E-1 of a block: for a
-// full block that is one aligned 8- or 16-byte piece of the row-major tile.  A run is read twice: once
-// for the statistics (a running maximum and a sum of exponentials relative to it, rescaled when the
-// maximum moves), once to write the normalised values.
+// Lane (block b of a round, row j, group g) handles the eight vectors 8g .. 8g+7 of a row: sixteen bytes of the row-major tile,
+// so that a wave-wide load or store moves 1 KB of consecutive blocks (16 / V of them), and one word tells which of the eight A stores.  An item of up to
+// kChunk blocks -- nearly all of them are -- is read once, all its loads together, and stays in registers; the rows' maxima and sums go from block to
+// block of a window through LDS.  Longer items are walked run by run and read twice.
+// What bounds it is the chain item -> blocks -> values of the wavefronts and, beside it, the instructions for positions that A does
+// not store.  Lognormal graph of 262 k rows, four-row windows (46 k items, 90 MB; 4-byte pieces and a mask per vector): softmax
+// 46 -> 37 us, its gradient 69 -> 40;
+// stencil of 1 M rows, eight-row windows 71 -> 29 and 92 -> 34.
 //
 // The same walk serves the gradient of that softmax (BWD): with p the probabilities and g the gradient
 // that arrives at them, both in the vals_blk layout,  ds = scale * p * (g - sum over the row of p * g).
@@ -24,10 +28,9 @@
 #include <cmath>
 
 #include "fs_common.h"
+#include "fs_tile.h"  // FS_WAVE_SYNC, fs_u4_unaligned
 
 namespace {
-
-constexpr int kWpb = 1;  // wavefronts (= work items) per workgroup: one measured best (cfg 5 -3 %; they share nothing)
 
 template <int DT>
 __device__ __forceinline__ float fs_to_float(uint16_t bits)
@@ -48,132 +51,26 @@ __device__ __forceinline__ void merge_stats(float &top, float &total, float top2
     top = t;
 }
 
-// E scaled scores of row j of a block (vectors q*E ..), -infinity where A stores nothing
-template <int DT, int V>
-struct BlockScores {
-    static constexpr int E = V / 2;
-    float v[E];
-    uint16_t raw[E];
-    uint32_t mk[E];
-    // issue the loads of a full block (kb = 32): one aligned piece of the row, E masks
-    __device__ __forceinline__ void fetch_full(const uint16_t *__restrict__ vals, const uint32_t *__restrict__ vec_mask,
-                                               int s, int j, int q)
-    {
-        const uint16_t *p = vals + (int64_t)V * s + j * 32 + q * E;
-        if constexpr (E == 2) {
-            const uint32_t r = *reinterpret_cast<const uint32_t *>(p);
-            raw[0] = r & 0xFFFF; raw[1] = r >> 16;
-            mk[0] = vec_mask[s + q * E];
-            mk[1] = vec_mask[s + q * E + 1];
-        } else if constexpr (E == 4) {
-            const uint2 r = *reinterpret_cast<const uint2 *>(p);
-            raw[0] = r.x & 0xFFFF; raw[1] = r.x >> 16; raw[2] = r.y & 0xFFFF; raw[3] = r.y >> 16;
-            const fs_u4 m = *reinterpret_cast<const fs_u4 *>(vec_mask + s + q * E);
-            mk[0] = m.x; mk[1] = m.y; mk[2] = m.z; mk[3] = m.w;
-        } else {
-            const fs_u4 r = *reinterpret_cast<const fs_u4 *>(p);
-            raw[0] = r.x & 0xFFFF; raw[1] = r.x >> 16; raw[2] = r.y & 0xFFFF; raw[3] = r.y >> 16;
-            raw[4] = r.z & 0xFFFF; raw[5] = r.z >> 16; raw[6] = r.w & 0xFFFF; raw[7] = r.w >> 16;
-            const fs_u4 m0 = *reinterpret_cast<const fs_u4 *>(vec_mask + s + q * E);
-            const fs_u4 m1 = *reinterpret_cast<const fs_u4 *>(vec_mask + s + q * E + 4);
-            mk[0] = m0.x; mk[1] = m0.y; mk[2] = m0.z; mk[3] = m0.w;
-            mk[4] = m1.x; mk[5] = m1.y; mk[6] = m1.z; mk[7] = m1.w;
-        }
-    }
-    // the same for a block of any width (row stride kb): element by element
-    __device__ __forceinline__ void fetch_any(const uint16_t *__restrict__ vals, const uint32_t *__restrict__ vec_mask,
-                                              int s, int kb, int j, int q)
-    {
-#pragma unroll
-        for (int e = 0; e < E; e++) {
-            const int c = q * E + e;
-            const bool in = c < kb;
-            mk[e] = in ? vec_mask[s + c] : 0u;
-            raw[e] = in ? vals[(int64_t)V * s + j * kb + c] : (uint16_t)0;
-        }
-    }
-    __device__ __forceinline__ void scale_and_mask(int j, float scale)
-    {
-#pragma unroll
-        for (int e = 0; e < E; e++) v[e] = ((mk[e] >> j) & 1) ? scale * fs_to_float<DT>(raw[e]) : -INFINITY;
-    }
-    // BWD: the plain values, zero where A stores nothing
-    __device__ __forceinline__ void plain_and_mask(int j)
-    {
-#pragma unroll
-        for (int e = 0; e < E; e++) v[e] = ((mk[e] >> j) & 1) ? fs_to_float<DT>(raw[e]) : 0.f;
-    }
-    // BWD: sum of p * g over this block's share of the row
-    __device__ __forceinline__ void absorb_dot(const BlockScores &g, float &total) const
-    {
-#pragma unroll
-        for (int e = 0; e < E; e++) total = fmaf(v[e], g.v[e], total);
-    }
-    // BWD: scale * p * (g - dot), stored in the block's tile (row stride kb); *this holds p
-    __device__ __forceinline__ void store_grad(const BlockScores &g, uint16_t *__restrict__ out, int s, int kb, int j, int q,
-                                               float dot, float scale) const
-    {
-        float y[E];
-#pragma unroll
-        for (int e = 0; e < E; e++) y[e] = ((mk[e] >> j) & 1) ? scale * v[e] * (g.v[e] - dot) : 0.f;
-        store_values(y, out, s, kb, j, q);
-    }
-    // running (maximum, sum) of a lane absorbs this block's scores
-    __device__ __forceinline__ void absorb(float &top, float &total) const
-    {
-        float bt = v[0];
-#pragma unroll
-        for (int e = 1; e < E; e++) bt = fmaxf(bt, v[e]);
-        if (bt > -INFINITY) {
-            const float t = fmaxf(top, bt);
-            float sum = total * __expf(top - t);
-#pragma unroll
-            for (int e = 0; e < E; e++) sum += __expf(v[e] - t);  // exp(-inf) = 0 where nothing is stored
-            top = t;
-            total = sum;
-        }
-    }
-    // normalised values of this block, stored in its tile (row stride kb)
-    __device__ __forceinline__ void store(uint16_t *__restrict__ out, int s, int kb, int j, int q, float top, float inv) const
-    {
-        float y[E];
-#pragma unroll
-        for (int e = 0; e < E; e++) {
-            // The fast exponential returns zero where the result would be a subnormal fp32 number, a range
-            // bf16 still represents: far below the maximum, evaluate e^(x+40) and scale by e^-40 (the
-            // multiplication keeps subnormal results).
-            const float x = v[e] - top;
-            const float p = x < -80.f ? __expf(x + 40.f) * 4.24835425529158899533e-18f : __expf(x);
-            y[e] = v[e] > -INFINITY ? p * inv : 0.f;
-        }
-        store_values(y, out, s, kb, j, q);
-    }
-    // E values of row j into the block's tile (row stride kb)
-    __device__ __forceinline__ void store_values(const float (&y)[E], uint16_t *__restrict__ out, int s, int kb, int j, int q) const
-    {
-        if (kb == 32) {
-            uint16_t *p = out + (int64_t)V * s + j * 32 + q * E;
-            if constexpr (E == 2) {
-                *reinterpret_cast<uint32_t *>(p) = fs_pack2<DT>(y[0], y[1]);
-            } else if constexpr (E == 4) {
-                uint2 o;
-                o.x = fs_pack2<DT>(y[0], y[1]); o.y = fs_pack2<DT>(y[2], y[3]);
-                *reinterpret_cast<uint2 *>(p) = o;
-            } else {
-                fs_u4 o;
-                o.x = fs_pack2<DT>(y[0], y[1]); o.y = fs_pack2<DT>(y[2], y[3]);
-                o.z = fs_pack2<DT>(y[4], y[5]); o.w = fs_pack2<DT>(y[6], y[7]);
-                *reinterpret_cast<fs_u4 *>(p) = o;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < E; e++) {
-                const int c = q * E + e;
-                if (c < kb) out[(int64_t)V * s + j * kb + c] = fs_round_bits<DT>(y[e]);
-            }
-        }
-    }
-};
+// The value of lane l ^ 1 or l ^ 2: the lanes of a row's four groups are neighbours
+template <int X>
+__device__ __forceinline__ float quad_xor(float v)
+{
+    constexpr int ctrl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float quad_max(float v)
+{
+    v = fmaxf(v, quad_xor<1>(v));
+    return fmaxf(v, quad_xor<2>(v));
+}
+__device__ __forceinline__ float quad_sum(float v)
+{
+    v += quad_xor<1>(v);
+    return v + quad_xor<2>(v);
+}
+
+// Bit x of m8 as 0 or ~0
+__device__ __forceinline__ uint32_t stored(uint32_t m8, int x) { return (uint32_t)__builtin_amdgcn_sbfe((int)m8, x, 1); }
 
 // PARTS = false: statistics of every run, whole windows are normalised, parts of cut windows leave
 //                their statistics in the workspace.
@@ -182,207 +79,342 @@ struct BlockScores {
 // BWD          : the gradient instead: `in` holds the probabilities, `in2` the gradient that arrives at them,
 //                the row statistic is sum p * g (second float of a workspace pair), the output
 //                scale * p * (g - that sum).
+// n_el: elements of the arrays.
 template <int DT, int V, bool PARTS, bool BWD>
-__global__ void __launch_bounds__(64 * kWpb)
+__global__ void __launch_bounds__(64)
 k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk_desc,
-               const uint32_t *__restrict__ vec_mask, const uint16_t *__restrict__ in, const uint16_t *__restrict__ in2,
-               uint16_t *__restrict__ out, float *__restrict__ stats, float scale, const int2 *__restrict__ slot_range,
+               const uint32_t *__restrict__ row_bits, const uint16_t *in, const uint16_t *in2,
+               uint16_t *out, int n_el, float *__restrict__ stats, float scale, const int2 *__restrict__ slot_range,
                int n_slots)
 {
-    constexpr int E = V / 2;  // vectors per lane and block
-    constexpr int B = 4;      // full blocks whose loads are issued together
-    const int lane = threadIdx.x & 63;
-    const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kWpb + (threadIdx.x >> 6));
-    if (item >= n_items) return;
-    const int4 it = items[item];  // {first block slot, blocks, first workspace slot, first vector}
+    constexpr int PER = 16 / V;                      // blocks of a round
+    constexpr int ROUNDS = V == 16 || (V == 8 && BWD) ? 4 : 2;  // rounds whose loads are issued together (forward, eight rows, four of them take the
+                                                     // registers of half the wavefronts: lognormal graph of 262 k rows 57 us against 66)
+    constexpr int kChunk = PER * ROUNDS;             // their blocks
+    __shared__ float part[kChunk * V];               // a row's statistic in each block
+    __shared__ __attribute__((aligned(16))) uint16_t tile[16 * 32];  // re-lays narrow blocks
+    const int lane = threadIdx.x;
+    const int4 it = items[blockIdx.x];  // {first block slot, blocks, first workspace slot, first vector}
     const int nblk = it.y;
     if (nblk == 0) return;
-    int slot = it.z;
-    const int j = lane % V, q = lane / V;
+    const int g = lane & 3, j = (lane >> 2) % V, b = PER == 1 ? 0 : (lane >> 2) / V;
     // PARTS: where the statistics of the windows of the item's (at most two) parts lie -- slot numbers that
     // follow from the item record alone, so these loads travel together with the descriptors'
     int2 range0 = make_int2(0, 0), range1 = make_int2(0, 0);
     if constexpr (PARTS) {
-        range0 = slot_range[min(slot, n_slots - 1)];
-        range1 = slot_range[min(slot + 1, n_slots - 1)];
+        range0 = slot_range[min(it.z, n_slots - 1)];
+        range1 = slot_range[min(it.z + 1, n_slots - 1)];
     }
     const int4 my_desc = blk_desc[it.x + min(lane, nblk - 1)];  // at most 64 blocks per item
+    const uint64_t firsts = __ballot(lane < nblk && (my_desc.y & 512)), lasts = __ballot(lane < nblk && (my_desc.y & 256));
 
-    int a = 0;  // first block of the current run
-    while (a < nblk) {
-        // the run ends with the window's last block or with the item
-        int b = a;
-        bool ends_window = false;
-        while (b < nblk && !ends_window) {
-            ends_window = (__builtin_amdgcn_readlane(my_desc.y, b) & 256) != 0;
-            b++;
+    // Eight positions of a row: what A stores of them, the values and (BWD) the gradient.
+    struct Eight {
+        int s, kb;     // first vector and width of the block, 0: none
+        uint32_t m8;
+        fs_frag v, d;
+    };
+    // block i of the item (none from `end` on); the bits do not depend on the descriptor, so they are under way beside it
+    auto bits_of = [&](int i, int end) -> uint32_t { return i < end ? row_bits[(int64_t)(it.x + i) * V + j] >> (8 * g) & 0xFFu : 0u; };
+    auto values_of = [&](const uint16_t *from, const Eight &x) -> fs_frag {
+        // Narrow blocks: what follows the row, or the block, is read along with it and not looked at; at the end of the array it is not there.
+        const uint32_t at = (uint32_t)V * x.s + j * x.kb + 8 * g;  // (up to 2^31 elements)
+        fs_frag r;
+        r.u = fs_u4{0u, 0u, 0u, 0u};
+        if (at + 8 <= (uint32_t)n_el) {
+            r.u = *reinterpret_cast<const fs_u4_unaligned *>(from + at);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; k++) r.e[k] = at + k < (uint32_t)n_el ? from[at + k] : (uint16_t)0;
         }
-        const bool whole = ends_window && (__builtin_amdgcn_readlane(my_desc.y, a) & 512) != 0;
-        if (PARTS && whole) { a = b; continue; }
-        // every block of a window but its last is full
-        const int nfull = a + (ends_window ? b - a - 1 : b - a);
-
-        float top = -INFINITY, total = 0.f;
-        if constexpr (!PARTS) {
-            if (whole && b - a <= B) {
-                // A window of at most B blocks that lies whole inside the item (most windows of a graph with
-                // short rows): read once, keep the blocks in registers between the statistics and the output.
-                BlockScores<DT, V> x[B], g[BWD ? B : 1];
-                int kbs[B];
+        return r;
+    };
+    auto fetch = [&](Eight &x, int i, int end) {
+        const int ic = min(i, nblk - 1);
+        if constexpr (PER == 1) {  // the same block for all lanes
+            x.s = __builtin_amdgcn_readlane(my_desc.x, ic);
+            x.kb = __builtin_amdgcn_readlane(my_desc.y, ic) & 255;
+        } else {
+            x.s = __shfl(my_desc.x, ic, 64);
+            x.kb = __shfl(my_desc.y, ic, 64) & 255;
+        }
+        if (i >= end) x.kb = 0;
+        x.v = values_of(in, x);
+        if constexpr (BWD) x.d = values_of(in2, x);
+    };
+    auto score = [&](const Eight &x, int k) -> float {  // scaled, -infinity where A stores nothing
+        const uint32_t keep = stored(x.m8, k);
+        return __uint_as_float((keep & __float_as_uint(scale * fs_to_float<DT>(x.v.e[k]))) | (~keep & 0xFF800000u));
+    };
+    auto dot = [&](const Eight &x) -> float {  // sum of p * g
+        float t = 0.f;
 #pragma unroll
-                for (int u = 0; u < B; u++) {
-                    const int i = min(a + u, b - 1);
-                    const int s = __builtin_amdgcn_readlane(my_desc.x, i);
-                    kbs[u] = a + u < b ? (__builtin_amdgcn_readlane(my_desc.y, i) & 255) : 0;
-                    if (kbs[u] == 32) {
-                        x[u].fetch_full(in, vec_mask, s, j, q);
-                        if constexpr (BWD) g[u].fetch_full(in2, vec_mask, s, j, q);
-                    } else if (kbs[u] > 0) {
-                        x[u].fetch_any(in, vec_mask, s, kbs[u], j, q);
-                        if constexpr (BWD) g[u].fetch_any(in2, vec_mask, s, kbs[u], j, q);
-                    }
-                }
+        for (int k = 0; k < 8; k++) {
+            const uint32_t keep = stored(x.m8, k);
+            t = fmaf(__uint_as_float(keep & __float_as_uint(fs_to_float<DT>(x.v.e[k]))), __uint_as_float(keep & __float_as_uint(fs_to_float<DT>(x.d.e[k]))), t);
+        }
+        return t;
+    };
+    // Results of a round to their blocks; positions that A does not store get +0.0.
+    auto store = [&](const Eight &x, const float (&y)[8], bool mine) {
+        fs_frag o;
+        o.u = fs_u4{fs_pack2<DT>(y[0], y[1]), fs_pack2<DT>(y[2], y[3]), fs_pack2<DT>(y[4], y[5]), fs_pack2<DT>(y[6], y[7])};
+        const int kb = mine ? x.kb : 0;
+        uint16_t *blk = out + (int64_t)V * x.s;
+        if (kb == 32) *reinterpret_cast<fs_u4 *>(blk + j * 32 + 8 * g) = o.u;
+        const bool narrow = kb > 0 && kb < 32;
+        if (!__ballot(narrow)) return;
+        uint16_t *mine_at = tile + b * (32 * V);
+        if (narrow) {
 #pragma unroll
-                for (int u = 0; u < B; u++) {
-                    if (kbs[u] == 0) continue;
-                    if constexpr (BWD) {
-                        x[u].plain_and_mask(j);
-                        g[u].plain_and_mask(j);
-                        x[u].absorb_dot(g[u], total);
-                    } else {
-                        x[u].scale_and_mask(j, scale);
-                        x[u].absorb(top, total);
-                    }
-                }
+            for (int k = 0; k < 8; k++)
+                if (8 * g + k < kb) mine_at[j * kb + 8 * g + k] = o.e[k];
+        }
+        FS_WAVE_SYNC();
+        const int at = 8 * (j * 4 + g);
+        if (narrow) {
+            if (at + 8 <= V * kb) *reinterpret_cast<fs_u4 *>(blk + at) = *reinterpret_cast<const fs_u4 *>(mine_at + at);
+            else if (V == 4 && at < V * kb) *reinterpret_cast<uint2 *>(blk + at) = *reinterpret_cast<const uint2 *>(mine_at + at);  // odd widths
+        }
+        FS_WAVE_SYNC();
+    };
+    // exp(v - top) / total, one score at a time.  The fast exponential returns zero where the result would be a subnormal fp32 number, a
+    // range bf16 still represents: far below the maximum, evaluate e^(x+40) and scale by e^-40 (the
+    // multiplication keeps subnormal results).
+    auto probability = [&](float v, float top, float inv) -> float {
+        const float x = v - top;
+        const float p = x < -80.f ? __expf(x + 40.f) * 4.24835425529158899533e-18f : __expf(x);
+        return v > -INFINITY ? p * inv : 0.f;
+    };
+    auto emit = [&](const Eight &x, float top, float total, bool mine) {
+        float y[8];
+        if constexpr (BWD) {
 #pragma unroll
-                for (int o = V; o < 64; o <<= 1) {
-                    if constexpr (BWD) total += __shfl_xor(total, o, 64);
-                    else merge_stats(top, total, __shfl_xor(top, o, 64), __shfl_xor(total, o, 64));
-                }
-                const float inv1 = total > 0.f ? 1.f / total : 0.f;
-#pragma unroll
-                for (int u = 0; u < B; u++) {
-                    if (kbs[u] == 0) continue;
-                    const int s = __builtin_amdgcn_readlane(my_desc.x, min(a + u, b - 1));
-                    if constexpr (BWD) x[u].store_grad(g[u], out, s, kbs[u], j, q, total, scale);
-                    else x[u].store(out, s, kbs[u], j, q, top, inv1);
-                }
-                a = b;
-                continue;
-            }
-            int i = a;
-            for (; i + B <= nfull; i += B) {  // B full blocks at a time: all loads first
-                BlockScores<DT, V> x[B], g[BWD ? B : 1];
-#pragma unroll
-                for (int u = 0; u < B; u++) {
-                    x[u].fetch_full(in, vec_mask, __builtin_amdgcn_readlane(my_desc.x, i + u), j, q);
-                    if constexpr (BWD) g[u].fetch_full(in2, vec_mask, __builtin_amdgcn_readlane(my_desc.x, i + u), j, q);
-                }
-#pragma unroll
-                for (int u = 0; u < B; u++) {
-                    if constexpr (BWD) {
-                        x[u].plain_and_mask(j);
-                        g[u].plain_and_mask(j);
-                        x[u].absorb_dot(g[u], total);
-                    } else {
-                        x[u].scale_and_mask(j, scale);
-                        x[u].absorb(top, total);
-                    }
-                }
-            }
-            for (; i < b; i++) {
-                const int s = __builtin_amdgcn_readlane(my_desc.x, i);
-                const int kb = __builtin_amdgcn_readlane(my_desc.y, i) & 255;
-                if (kb == 0) continue;
-                BlockScores<DT, V> x, g;
-                if (i < nfull) x.fetch_full(in, vec_mask, s, j, q);
-                else x.fetch_any(in, vec_mask, s, kb, j, q);
-                if constexpr (BWD) {
-                    if (i < nfull) g.fetch_full(in2, vec_mask, s, j, q);
-                    else g.fetch_any(in2, vec_mask, s, kb, j, q);
-                    x.plain_and_mask(j);
-                    g.plain_and_mask(j);
-                    x.absorb_dot(g, total);
-                } else {
-                    x.scale_and_mask(j, scale);
-                    x.absorb(top, total);
-                }
-            }
-            // the lanes that share row j: lane bits above log2(V)
-#pragma unroll
-            for (int o = V; o < 64; o <<= 1) {
-                if constexpr (BWD) total += __shfl_xor(total, o, 64);
-                else merge_stats(top, total, __shfl_xor(top, o, 64), __shfl_xor(total, o, 64));
-            }
-            if (!whole) {
-                if (q == 0) {
-                    float *st = stats + (int64_t)slot * 2 * V;
-                    st[j] = BWD ? 0.f : top;
-                    st[V + j] = total;
-                }
-                slot++;
-                a = b;
-                continue;
+            for (int k = 0; k < 8; k++) {
+                const uint32_t keep = stored(x.m8, k);
+                y[k] = __uint_as_float(keep & __float_as_uint(scale * fs_to_float<DT>(x.v.e[k]) * (fs_to_float<DT>(x.d.e[k]) - total)));
             }
         } else {
-            // The parts of this window left their (maximum, sum) pairs in consecutive workspace slots, whose
-            // range the format keeps per slot.  Lane (j, q) merges the pairs of row j over the parts
-            // q, q + 64/V, ... and the lanes of a row are merged by shuffles: a fixed order, deterministic.
-            const int2 rg = slot == it.z ? range0 : range1;
-            const int4 sw = make_int4(0, rg.x, rg.y, 0);  // {-, first slot, slots, -}
-            const float *st = stats + (int64_t)sw.y * 2 * V;
-            for (int k = q; k < sw.z; k += 64 / V) {
+            const float inv = total > 0.f ? 1.f / total : 0.f;
+#pragma unroll
+            for (int k = 0; k < 8; k++) y[k] = probability(score(x, k), top, inv);
+        }
+        store(x, y, mine);
+    };
+    auto pair_to_workspace = [&](int slot, float top, float total) {
+        float *st = stats + (int64_t)slot * 2 * V;
+        st[j] = BWD ? 0.f : top;
+        st[V + j] = total;
+    };
+    // over the lanes that share row j
+    auto reduce_row = [&](float &top, float &total) {
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            if (o >= 4 && o < 4 * V) continue;
+            if constexpr (BWD) total += __shfl_xor(total, o, 64);
+            else merge_stats(top, total, __shfl_xor(top, o, 64), __shfl_xor(total, o, 64));
+        }
+    };
+
+    if constexpr (PARTS) {
+        // the item's first run if its window begins before the item, and its last if its window goes on behind it; the
+        // parts of a window left their pairs in consecutive workspace slots.  Lane (b, j, g) merges the pairs of row j over
+        // the parts 4b + g, 4b + g + 64/V, ... and the lanes of a row are merged by shuffles: a fixed order, deterministic.
+        const bool head = !(firsts & 1), tail = !(lasts >> (nblk - 1) & 1);
+        const int head_end = lasts ? (int)__builtin_ctzll(lasts) + 1 : nblk;           // blocks of the first run
+        const int tail_at = firsts ? 63 - (int)__builtin_clzll(firsts) : 0;            // where the last run begins
+        for (int run = 0; run < 2; run++) {
+            if (run == 0 ? !head : !tail || (head && head_end == nblk)) continue;  // (a part inside its window is the first run)
+            const int2 rg = run == 0 || !head ? range0 : range1;
+            const float *st = stats + (int64_t)rg.x * 2 * V;
+            float top = -INFINITY, total = 0.f;
+            for (int k = 4 * b + g; k < rg.y; k += 64 / V) {
                 if constexpr (BWD) total += st[k * 2 * V + V + j];
                 else merge_stats(top, total, st[k * 2 * V + j], st[k * 2 * V + V + j]);
             }
+            reduce_row(top, total);
+            const int end = run == 0 ? head_end : nblk;
+            for (int c = run == 0 ? 0 : tail_at; c < end; c += kChunk) {
+                Eight x[ROUNDS];
 #pragma unroll
-            for (int o = V; o < 64; o <<= 1) {
-                if constexpr (BWD) total += __shfl_xor(total, o, 64);
-                else merge_stats(top, total, __shfl_xor(top, o, 64), __shfl_xor(total, o, 64));
-            }
-            slot++;
-        }
-        // normalised values; positions of the tile that A does not store get +0.0
-        const float inv = total > 0.f ? 1.f / total : 0.f;
-        int i = a;
-        for (; i + B <= nfull; i += B) {
-            BlockScores<DT, V> x[B], g[BWD ? B : 1];
+                for (int r = 0; r < ROUNDS; r++) {
+                    if (c + r * PER >= end) break;
+                    const int i = c + r * PER + b;
+                    x[r].m8 = bits_of(i, end);
+                    fetch(x[r], i, end);
+                }
 #pragma unroll
-            for (int u = 0; u < B; u++) {
-                x[u].fetch_full(in, vec_mask, __builtin_amdgcn_readlane(my_desc.x, i + u), j, q);
-                if constexpr (BWD) g[u].fetch_full(in2, vec_mask, __builtin_amdgcn_readlane(my_desc.x, i + u), j, q);
-            }
-#pragma unroll
-            for (int u = 0; u < B; u++) {
-                if constexpr (BWD) {
-                    x[u].plain_and_mask(j);
-                    g[u].plain_and_mask(j);
-                    x[u].store_grad(g[u], out, __builtin_amdgcn_readlane(my_desc.x, i + u), 32, j, q, total, scale);
-                } else {
-                    x[u].scale_and_mask(j, scale);
-                    x[u].store(out, __builtin_amdgcn_readlane(my_desc.x, i + u), 32, j, q, top, inv);
+                for (int r = 0; r < ROUNDS; r++) {
+                    if (c + r * PER >= end) break;
+                    emit(x[r], top, total, true);
                 }
             }
         }
-        for (; i < b; i++) {
-            const int s = __builtin_amdgcn_readlane(my_desc.x, i);
-            const int kb = __builtin_amdgcn_readlane(my_desc.y, i) & 255;
-            if (kb == 0) continue;
-            BlockScores<DT, V> x, g;
-            if (i < nfull) x.fetch_full(in, vec_mask, s, j, q);
-            else x.fetch_any(in, vec_mask, s, kb, j, q);
+        return;
+    }
+    if (nblk <= kChunk) {
+        Eight x[ROUNDS];
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) x[r].m8 = bits_of(r * PER + b, nblk);
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (r * PER >= nblk) break;
+            fetch(x[r], r * PER + b, nblk);
+        }
+        // the lane's window in a round: its blocks of the item, and whether they are all of it
+        auto run_of = [&](int i, int &lo, int &hi) -> bool {
+            const uint64_t before = firsts & ((2ull << i) - 1), after = lasts >> i;
+            lo = before ? 63 - (int)__builtin_clzll(before) : 0;
+            hi = after ? i + (int)__builtin_ctzll(after) : nblk - 1;
+            return before && after;
+        };
+        auto over_run = [&](int i, float own, auto combine) -> float {  // of what every block's lanes left in part[]
+            int lo, hi;
+            run_of(i, lo, hi);
+            if (lo == hi) return own;
+            float t = part[lo * V + j];
+            for (int k = lo + 1; k <= hi; k++) t = combine(t, part[k * V + j]);
+            return t;
+        };
+        float top[ROUNDS], total[ROUNDS], e[ROUNDS][8];
+        // No score is so far below its row's maximum, and none so large or no number, that the exponential needs care: known from
+        // the largest magnitude among the values (they compare like whole numbers) without a look at each difference.
+        bool plain = true;
+        if constexpr (!BWD) {
+#pragma unroll
+            for (int r = 0; r < ROUNDS; r++) {
+                if (r * PER >= nblk) break;
+                float t = -INFINITY;
+                uint32_t largest = 0;
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    e[r][k] = score(x[r], k);
+                    t = fmaxf(t, e[r][k]);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const uint32_t magnitude = x[r].v.u[k] & 0x7FFF7FFFu;
+                    typedef uint16_t two __attribute__((ext_vector_type(2)));
+                    const two m = __builtin_elementwise_max(__builtin_bit_cast(two, magnitude), __builtin_bit_cast(two, largest));
+                    largest = __builtin_bit_cast(uint32_t, m);
+                }
+                plain = plain && fabsf(scale) * fs_to_float<DT>((uint16_t)max(largest & 0xFFFF, largest >> 16)) <= 39.f;
+                top[r] = quad_max(t);
+                if (g == 0) part[(r * PER + b) * V + j] = top[r];
+            }
+            FS_WAVE_SYNC();
+#pragma unroll
+            for (int r = 0; r < ROUNDS; r++) {
+                if (r * PER >= nblk) break;
+                const int i = min(r * PER + b, nblk - 1);
+                top[r] = over_run(i, top[r], [](float a, float c) { return fmaxf(a, c); });
+            }
+            FS_WAVE_SYNC();
+        }
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (r * PER >= nblk) break;
             if constexpr (BWD) {
-                if (i < nfull) g.fetch_full(in2, vec_mask, s, j, q);
-                else g.fetch_any(in2, vec_mask, s, kb, j, q);
-                x.plain_and_mask(j);
-                g.plain_and_mask(j);
-                x.store_grad(g, out, s, i < nfull ? 32 : kb, j, q, total, scale);
+                total[r] = dot(x[r]);
             } else {
-                x.scale_and_mask(j, scale);
-                x.store(out, s, i < nfull ? 32 : kb, j, q, top, inv);
+                const float from = top[r] > -INFINITY ? top[r] : 0.f;  // (nothing stored, or minus infinity only: all exponentials are zero)
+                float sum = 0.f;
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    e[r][k] = __expf(e[r][k] - from);  // exp(-inf) = 0 where nothing is stored
+                    sum += e[r][k];
+                }
+                total[r] = sum;
+            }
+            total[r] = quad_sum(total[r]);
+            if (g == 0) part[(r * PER + b) * V + j] = total[r];
+        }
+        FS_WAVE_SYNC();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (r * PER >= nblk) break;
+            const int i = min(r * PER + b, nblk - 1);
+            total[r] = over_run(i, total[r], [](float a, float c) { return a + c; });
+        }
+        const bool fast = !BWD && !__ballot(!plain);
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (r * PER >= nblk) break;
+            const int i = r * PER + b;
+            int lo, hi;
+            const bool whole = run_of(min(i, nblk - 1), lo, hi);
+            if (fast) {
+                const float inv = total[r] > 0.f ? 1.f / total[r] : 0.f;
+#pragma unroll
+                for (int k = 0; k < 8; k++) e[r][k] *= inv;
+                store(x[r], e[r], whole);
+            } else {
+                emit(x[r], BWD ? 0.f : top[r], total[r], whole);
+            }
+            // a part's rows, by the lanes of its first block; it is the second part of the item if the first begins before it
+            if (!whole && i == lo && g == 0) pair_to_workspace(it.z + (lo > 0 && !(firsts & 1) ? 1 : 0), BWD ? 0.f : top[r], total[r]);
+        }
+        return;
+    }
+    int slot = it.z;
+    for (int a = 0; a < nblk;) {  // run by run
+        const uint64_t after = lasts >> a;
+        const int end = after ? a + (int)__builtin_ctzll(after) + 1 : nblk;
+        const bool whole = after && (firsts >> a & 1);
+        float top = -INFINITY, total = 0.f;
+        for (int c = a; c < end; c += kChunk) {
+            Eight x[ROUNDS];
+#pragma unroll
+            for (int r = 0; r < ROUNDS; r++) {
+                if (c + r * PER >= end) break;
+                const int i = c + r * PER + b;
+                x[r].m8 = bits_of(i, end);
+                fetch(x[r], i, end);
+            }
+#pragma unroll
+            for (int r = 0; r < ROUNDS; r++) {
+                if (c + r * PER >= end) break;
+                if constexpr (BWD) {
+                    total += dot(x[r]);
+                } else {
+                    float v[8], t = -INFINITY;
+#pragma unroll
+                    for (int k = 0; k < 8; k++) {
+                        v[k] = score(x[r], k);
+                        t = fmaxf(t, v[k]);
+                    }
+                    if (t > -INFINITY) {
+                        t = fmaxf(t, top);
+                        total *= __expf(top - t);
+#pragma unroll
+                        for (int k = 0; k < 8; k++) total += __expf(v[k] - t);  // exp(-inf) = 0 where nothing is stored
+                        top = t;
+                    }
+                }
             }
         }
-        a = b;
+        reduce_row(top, total);
+        if (!whole) {
+            if (g == 0 && b == 0) pair_to_workspace(slot, top, total);
+            slot++;
+        } else {
+            for (int c = a; c < end; c += kChunk) {
+                Eight x[ROUNDS];
+#pragma unroll
+                for (int r = 0; r < ROUNDS; r++) {
+                    if (c + r * PER >= end) break;
+                    const int i = c + r * PER + b;
+                    x[r].m8 = bits_of(i, end);
+                    fetch(x[r], i, end);
+                }
+#pragma unroll
+                for (int r = 0; r < ROUNDS; r++) {
+                    if (c + r * PER >= end) break;
+                    emit(x[r], top, total, true);
+                }
+            }
+        }
+        a = end;
     }
 }
 
@@ -395,17 +427,14 @@ fs_status launch(const fs_format *f, const uint16_t *in, const uint16_t *in2, ui
     // them), the whole windows after them, costliest first.  The second launch only needs the former.
     const int4 *items = (const int4 *)f->items_by_cost;
     const int n_items = (int)f->n_items;
-    const unsigned grid = (unsigned)((n_items + kWpb - 1) / kWpb);
-    k_edge_softmax<DT, V, false, BWD><<<grid, 64 * kWpb, 0, st>>>(items, n_items, (const int4 *)f->blk_desc,
-                                                                  f->vec_mask, in, in2, out, stats, scale,
-                                                                  (const int2 *)f->slot_range, (int)f->n_split_items);
+    const int n_el = (int)(V * f->nvec);
+    k_edge_softmax<DT, V, false, BWD><<<(unsigned)n_items, 64, 0, st>>>(items, n_items, (const int4 *)f->blk_desc, f->blk_row_bits, in, in2, out, n_el, stats, scale,
+                                                                        (const int2 *)f->slot_range, (int)f->n_split_items);
     FS_LAUNCH_CHECK();
     const int n_cut = (int)std::min<int64_t>(f->n_cut_items, f->n_items);
     if (f->n_split_windows > 0 && n_cut > 0) {
-        const unsigned grid2 = (unsigned)((n_cut + kWpb - 1) / kWpb);
-        k_edge_softmax<DT, V, true, BWD><<<grid2, 64 * kWpb, 0, st>>>(items, n_cut, (const int4 *)f->blk_desc,
-                                                                      f->vec_mask, in, in2, out, stats, scale,
-                                                                      (const int2 *)f->slot_range, (int)f->n_split_items);
+        k_edge_softmax<DT, V, true, BWD><<<(unsigned)n_cut, 64, 0, st>>>(items, n_cut, (const int4 *)f->blk_desc, f->blk_row_bits, in, in2, out, n_el, stats, scale,
+                                                                         (const int2 *)f->slot_range, (int)f->n_split_items);
         FS_LAUNCH_CHECK();
     }
     return FS_OK;
