@@ -74,7 +74,7 @@ typedef enum { FS_F16 = 0, FS_BF16 = 1 } fs_dtype;
  *                  an item is a run of consecutive block slots.  With T = chunk / KB: a window with more than 1.5 T blocks is cut into
  *                  round(blocks / T) parts of equal length (within one block), from its start;
  *                  shorter windows are never cut and are packed whole into items of about
- *                  min(T, 4) blocks.  No item has more than 2 * T + 4 blocks (at most 64).  n_items records of four int32
+ *                  min(T, 4) blocks (two or three in a small matrix with chunk = 0).  No item has more than 2 * T + 4 blocks (at most 64).  n_items records of four int32
  *                  {first block slot, number of blocks, first partial slot, first vector}; a
  *                  record with 0 blocks is empty.  An item whose first or last window is only
  *                  partly inside it adds that part into an fp32 partial tile (slots are handed
@@ -166,8 +166,8 @@ fs_status fs_format_bytes(int64_t M, int64_t nnz, int32_t V, int32_t KB, fs_dtyp
  * For a matrix with at least 4 Mi stored entries and 12 per row on average (bound by memory traffic), values
  * given and KB = 32, V <= 16, the conversion also stores the values bitmap-packed (fs_format.packed, see
  * fs_pack_values); fs_spmm then reads those instead of vals_blk.  Same results bit for bit.
- * Synchronises `stream` twice (the vector, block and work-item counts come back to the host, then the
- * counts of the cut windows).  On FS_ERR_INVALID_CSR the arena content is unspecified.
+ * Synchronises `stream` twice (the counts of vectors, blocks, items and cut windows come back to the host; the scratch
+ * buffer is the caller's again).  On FS_ERR_INVALID_CSR the arena content is unspecified.
  * The CSR check is always on (it costs one comparison per entry).
  * Errors: FS_ERR_INVALID_ARG (a NULL pointer, a misaligned buffer, a chunk that is no multiple of KB or too
  * long, stored entries in a matrix without rows), FS_ERR_BUFFER_TOO_SMALL, FS_ERR_TOO_LARGE (a size or

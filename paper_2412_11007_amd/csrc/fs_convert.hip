@@ -84,14 +84,33 @@ __device__ __forceinline__ bool starts_at_hi(int lo, int hi, int T, int Ts)
     return !is_long(lo, hi, T) && x >= (uint32_t)lo && x - lo > hi - x;
 }
 
-// T, the blocks per part of a long window, from the number of block slots NB: enough parts to put about 16
-// wavefronts on each of the 256 CUs, long enough to amortise an item's fixed cost, short enough that one
-// item is a small part of the run time.  A caller's own choice (t_user > 0) wins.
-__host__ __device__ inline int part_blocks(int NB, int t_user)
+// T, the blocks per part of a long window, and Ts, the slots between candidates, from the number of block slots NB and those of the longest
+// window: enough items to put about 16 wavefronts on each of the 256 CUs, long enough to amortise an item's fixed cost,
+// short enough that one item is a small part of the run time.  A caller's own choice of T (t_user > 0) wins; Ts is then as ever, four or T.
+// In a small matrix the chain of one item is the time, and shorter items shorten it, but a window cut into parts costs a launch that adds
+// them up; so parts are shorter than eight blocks only where some window is cut anyway.  T, Ts = 8, 4 / here, us, SpMM with
+// 64 and 128 columns and attention with d = 64, N = 128: lognormal graph of 4 k rows 9.2 / 7.2, 10.5 / 8.3, 16.8 / 12.3; R-MAT of 8 k rows, eight entries a
+// row, 9.1 / 7.2, 10.5 / 8.2, 17.1 / 11.9, of 16 k, six, 9.8 / 7.7, 11.6 / 9.1, 18.1 / 14.4; of 32 k, sixteen, where parts stay, 12.1 / 11.2, 15.1 / 14.4, 24.3 / 21.1;
+// uniform, 20 k rows, no window cut 6.2 / 5.3, 9.1 / 9.1, 14.0 / 13.5; stencil of 170^2 points 5.6 / 4.7, 6.9 / 5.7, 10.6 / 7.8.  Four blocks a part for
+// 6 k blocks cost R-MAT of 16 k rows, twelve a row, 3 to 9 %, six for 10 k blocks one of 32 k, eight a row, up to 5; 256 columns lose 5 % at 3.4 k
+// blocks (R-MAT of 8 k rows, sixteen a row 10.9 / 11.5).
+struct Grain {
+    int T, Ts;
+};
+__host__ __device__ inline Grain item_grain(int NB, int longest, int t_user, int ts_user)
 {
-    if (t_user > 0) return t_user;
-    const int t = (NB + 4095) / 4096;
-    return t < 8 ? 8 : (t > kDefaultMaxPartBlocks ? kDefaultMaxPartBlocks : t);
+    Grain g;
+    if (t_user > 0) {
+        g.T = t_user;
+        g.Ts = t_user < kPackBlocks ? t_user : kPackBlocks;
+    } else {
+        const int t = (NB + 4095) / 4096;
+        g.T = t < 8 ? 8 : (t > kDefaultMaxPartBlocks ? kDefaultMaxPartBlocks : t);
+        g.Ts = NB < 4096 ? 2 : NB < 16384 ? 3 : kPackBlocks;
+        if (longest > g.T + g.T / 2 && NB < 8192) g.T = NB < 5120 ? 4 : 6;
+    }
+    if (ts_user > 0) g.Ts = ts_user;
+    return g;
 }
 
 // The window tiles of k_win_ptr: its block slots so far come from its workgroups' sums.  Slots of window w, and of the one before.
@@ -104,7 +123,7 @@ struct ItemSums {
 
 // Block slots (blk_ptr[W]: their number) and, per workgroup, how many items, partial tiles and cut windows its windows make.
 __global__ void __launch_bounds__(kWindowThreads) k_win_slots(const int32_t *__restrict__ win_ptr, int64_t W, int KB, int tiles, const int *__restrict__ slots,
-                                                              int t_user, int Ts, int *__restrict__ blk_ptr, ItemSums sums, int *__restrict__ misc)
+                                                              int t_user, int ts_user, int *__restrict__ blk_ptr, ItemSums sums, int *__restrict__ misc)
 {
     if (misc[0] & 1) return;  // malformed row pointers
     const int64_t w0 = (int64_t)blockIdx.x * tiles * kWindowThreads, w1 = min(w0 + (int64_t)tiles * kWindowThreads, W);
@@ -115,7 +134,9 @@ __global__ void __launch_bounds__(kWindowThreads) k_win_slots(const int32_t *__r
     }
     block_sum<kWindowThreads>(before);
     int ahead = before[0];
-    const int NB = before[1], T = part_blocks(NB, t_user);
+    const int NB = before[1];
+    const Grain grain = item_grain(NB, misc[2], t_user, ts_user);
+    const int T = grain.T, Ts = grain.Ts;
     int n[3] = {0, 0, 0};  // items, partial tiles, cut windows
     for (int64_t wt = w0; wt < w1; wt += kWindowThreads) {
         const int64_t w = wt + threadIdx.x;
@@ -164,7 +185,7 @@ __global__ void __launch_bounds__(kWindowThreads) k_win_slots(const int32_t *__r
 // windows 1.5 T, and packing adds less than 3 Ts.  The parts of cut windows are dealt to the threads one by one, and in a
 // long list to the threads of several workgroups, because the hubs of a graph lie side by side (R-MAT of 1 M rows, 60 k parts: written by
 // the wavefront of their window 51 us, by one workgroup 30, by four 23).
-__device__ __forceinline__ void fill_items(int group, int share, int shares, const int *__restrict__ blk_ptr, int64_t W, int tiles, int t_user, int Ts, ItemSums sums,
+__device__ __forceinline__ void fill_items(int group, int share, int shares, const int *__restrict__ blk_ptr, int64_t W, int tiles, Grain grain, ItemSums sums,
                                                    const int32_t *__restrict__ win_ptr, int KB, const int32_t *__restrict__ vec_col,
                                                    int64_t nvec, int64_t K, int n_items, int4 *__restrict__ items, int32_t *__restrict__ key,
                                                    int4 *__restrict__ split_windows, int2 *__restrict__ slot_range)
@@ -174,7 +195,7 @@ __device__ __forceinline__ void fill_items(int group, int share, int shares, con
     __shared__ int4 cut_at[kWindowThreads];
     __shared__ int2 cut_items[kWindowThreads];
     const int64_t w0 = (int64_t)group * tiles * kWindowThreads, w1 = min(w0 + (int64_t)tiles * kWindowThreads, W);
-    const int NB = blk_ptr[W], T = part_blocks(NB, t_user);
+    const int NB = blk_ptr[W], T = grain.T, Ts = grain.Ts;
     int ahead[3] = {0, 0, 0};  // items, partial tiles, cut windows of the workgroups before this one
     for (int k = threadIdx.x; k < group; k += kWindowThreads) {
         ahead[0] += sums.items[k];
@@ -250,7 +271,8 @@ __device__ __forceinline__ void fill_items(int group, int share, int shares, con
 // What is left when the units are placed: the work list, by the first groups * shares workgroups, and, where they are few, the blocks that
 // pieces of hub windows share, by the others: a launch less where launches are the time (R-MAT of 65 k rows 9 and 5 us, now 9).
 struct ItemFill {
-    int groups, shares, tiles, t_user, Ts, n_items;
+    int groups, shares, tiles, n_items;
+    Grain grain;
     ItemSums sums;
     int4 *items;
     int32_t *key;
@@ -263,7 +285,7 @@ __global__ void __launch_bounds__(kWindowThreads) __attribute__((amdgpu_waves_pe
 {
     const int first = fill.groups * fill.shares;
     if ((int)blockIdx.x < first) {
-        fill_items(blockIdx.x % fill.groups, blockIdx.x / fill.groups, fill.shares, blk_ptr, W, fill.tiles, fill.t_user, fill.Ts, fill.sums, win_ptr, KB, out.vec_col, nvec, K,
+        fill_items(blockIdx.x % fill.groups, blockIdx.x / fill.groups, fill.shares, blk_ptr, W, fill.tiles, fill.grain, fill.sums, win_ptr, KB, out.vec_col, nvec, K,
                    fill.n_items, fill.items, fill.key, fill.split_windows, fill.slot_range);
         return;
     }
@@ -652,7 +674,7 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
     int32_t *win_ptr = (int32_t *)arena;
     CsrView a{d_rowptr, d_colidx, M, (int32_t)nnz};
 
-    // misc: [0] CSR error flags, [1] vectors, [4] block slots, [5] cut windows, [6] items, [7] partial tiles (and items that hold a
+    // misc: [0] CSR error flags, [1] vectors, [2] block slots of the longest window, [4] block slots, [5] cut windows, [6] items, [7] partial tiles (and items that hold a
     // part of a cut window: one each), [8] units -- what the host reads, in one copy
     FS_HIP(hipMemsetAsync(misc, 0, 64 * sizeof(int), s));
     const UnitPlan up = unit_plan(nnz, V);
@@ -697,18 +719,18 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
             count_sums = tmp;
         }
     }
-    k_win_ptr<<<win_grid, kWindowThreads, 0, s>>>(win_at, count, count_sums, scanned, n_units, W, KB, tiles, first_vec, win_ptr, sums + kScanDirect, misc + 1, misc);
+    k_win_ptr<<<win_grid, kWindowThreads, 0, s>>>(win_at, count, count_sums, scanned, n_units, W, KB, tiles, first_vec, win_ptr, sums + kScanDirect, misc);
     FS_LAUNCH_CHECK();
 
-    // Work items (step 4), up to their count: the grain Ts is known here, T follows from the number of block
-    // slots, which the kernels read from the device.
+    // Work items (step 4), up to their count: their grain follows from the number of block slots and the longest window, which the
+    // kernels read from the device.
     const int t_user = chunk > 0 ? chunk / KB : 0;
-    int Ts = std::min(t_user > 0 ? t_user : kPackBlocks, kPackBlocks);
+    int ts_user = 0;
 #ifdef FS_TUNING_ENV
-    if (const char *e = getenv("FS_PACK_BLOCKS")) Ts = std::max(std::min(atoi(e), t_user > 0 ? t_user : 8), 1);
+    if (const char *e = getenv("FS_PACK_BLOCKS")) ts_user = std::max(std::min(atoi(e), t_user > 0 ? t_user : 4), 1);
 #endif
     if (W > 0) {
-        k_win_slots<<<win_grid, kWindowThreads, 0, s>>>(win_ptr, W, KB, tiles, sums + kScanDirect, t_user, Ts, blk_ptr, item_sums, misc);
+        k_win_slots<<<win_grid, kWindowThreads, 0, s>>>(win_ptr, W, KB, tiles, sums + kScanDirect, t_user, ts_user, blk_ptr, item_sums, misc);
         FS_LAUNCH_CHECK();
     }
 
@@ -724,7 +746,8 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
                           scratch_bytes, stream, out);
     if ((int64_t)V * nvec >= (int64_t)1 << 31) return FS_ERR_TOO_LARGE;
     const int n_items = W > 0 ? h_misc[6] : 0;
-    chunk = part_blocks(NB, t_user) * KB;
+    const Grain grain = item_grain(NB, h_misc[2], t_user, ts_user);
+    chunk = grain.T * KB;
 
     // arena layout, now that the sizes are known.  The value array is followed by 256 zeroed bytes: with no
     // vectors at all every per-vector array has size zero and starts there, so that the kernels' clamped
@@ -793,7 +816,7 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
         }
         // a list too long for one launch to rank may have its hubs in few workgroups; a grid that fills the chip has work enough
         const unsigned shares = n_items > kRankItemsMax ? std::min(std::max(512 / win_grid, 1u), 4u) : 1;
-        const ItemFill fill{(int)win_grid, (int)shares, tiles, t_user, Ts, n_items, item_sums, items, key0, split_windows, slot_range};
+        const ItemFill fill{(int)win_grid, (int)shares, tiles, n_items, grain, item_sums, items, key0, split_windows, slot_range};
         const int shared = nnz > kUnitEntries && together ? grid_for(units_made, kSharedPerWave * (kWindowThreads / 64)) : 0;
         k_finish<<<win_grid * shares + shared, kWindowThreads, 0, s>>>(fill, blk_ptr, W, win_ptr, KB, nvec, K, V, units, units_made, first_vec, va, po);
         FS_LAUNCH_CHECK();

@@ -140,8 +140,8 @@ inline fs_launch_geometry fs_launch_geometry_for(const fs_format *f, int wpb, in
 
 // Whether fs_spmm takes passes of 256 columns for a product that wide (the reasons stand at its launch), and the columns after
 // them that have a narrower launch of their own.
-constexpr int kWidePassItems = 1024;
-inline bool fs_spmm_wide(const fs_format *f, int64_t N) { return N > 128 && N % 64 && f->n_items >= kWidePassItems; }
+constexpr int kWidePassItems = 1024, kWidePassBlocks = 4096;  // (small matrices make more, shorter items)
+inline bool fs_spmm_wide(const fs_format *f, int64_t N) { return N > 128 && N % 64 && f->n_items >= kWidePassItems && f->n_blocks >= kWidePassBlocks; }
 inline int64_t fs_spmm_rest(int64_t N) { return N > 256 && N % 256 <= 128 ? N % 256 : 0; }
 
 // Accumulators -> rounded V x NC tile, row-major in the wavefront's LDS tile (the gathered rows in it have

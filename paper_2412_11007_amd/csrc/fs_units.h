@@ -618,10 +618,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) k_
 constexpr int kWindowThreads = 1024;
 __global__ void __launch_bounds__(kWindowThreads) k_win_ptr(const int2 *__restrict__ win_at, const int *__restrict__ count, const int *__restrict__ sums, bool scanned,
                                                             const int *__restrict__ n_units, int64_t W, int KB, int tiles, int *first_vec,
-                                                            int32_t *__restrict__ win_ptr, int *__restrict__ slots, int *__restrict__ n_vec, const int *__restrict__ err)
+                                                            int32_t *__restrict__ win_ptr, int *__restrict__ slots, int *__restrict__ misc)
 {
     const int64_t w0 = (int64_t)blockIdx.x * tiles * kWindowThreads, w1 = min(w0 + (int64_t)tiles * kWindowThreads, W);
-    if (W == 0 || (*err & 1)) {  // no rows, or malformed row pointers: nothing was counted
+    if (W == 0 || (misc[0] & 1)) {  // no rows, or malformed row pointers: nothing was counted
         for (int64_t w = w0 + threadIdx.x; w < w1; w += kWindowThreads) win_ptr[w] = 0;
         if (w1 == W && threadIdx.x == 0) win_ptr[W] = 0;
         if (threadIdx.x == 0) slots[blockIdx.x] = (int)(w1 - w0);
@@ -655,7 +655,7 @@ __global__ void __launch_bounds__(kWindowThreads) k_win_ptr(const int2 *__restri
     if (w1 == W && threadIdx.x == 0) {
         first_vec[u1] = ahead;
         win_ptr[W] = ahead;
-        *n_vec = ahead;
+        misc[1] = ahead;
     }
     __syncthreads();  // first_vec is read back by other threads than wrote it
     auto ptr = [&](int64_t w) -> int32_t {
@@ -663,14 +663,23 @@ __global__ void __launch_bounds__(kWindowThreads) k_win_ptr(const int2 *__restri
         const int2 at = win_at[w];
         return first_vec[at.x] + at.y;
     };
-    int made[1] = {0};
+    int made[1] = {0}, longest = 0;
     for (int64_t w = w0 + threadIdx.x; w < w1; w += kWindowThreads) {
         const int32_t q = ptr(w);
         win_ptr[w] = q;
-        made[0] += max(1, (ptr(w + 1) - q + KB - 1) / KB);
+        const int n = max(1, (ptr(w + 1) - q + KB - 1) / KB);
+        made[0] += n;
+        longest = max(longest, n);
     }
-    block_sum<kWindowThreads>(made);
-    if (threadIdx.x == 0) slots[blockIdx.x] = made[0];
+    longest = wave_scan(longest, 0, [](int a, int b) { return max(a, b); });
+    __shared__ int most[kWindowThreads / 64];
+    if ((threadIdx.x & 63) == 63) most[threadIdx.x >> 6] = longest;
+    block_sum<kWindowThreads>(made);  // (with its barriers)
+    if (threadIdx.x == 0) {
+        slots[blockIdx.x] = made[0];
+        for (int k = 0; k < kWindowThreads / 64; k++) longest = max(longest, most[k]);
+        atomicMax(&misc[2], longest);
+    }
 }
 
 // What the second kernel writes.  vals null: pattern only (the value array is cleared beforehand); packed_* null: not wanted.

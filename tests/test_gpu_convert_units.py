@@ -165,11 +165,15 @@ def test_convert_more_units_than_one_launch_takes(fs):  # noqa: F811
     torch.cuda.empty_cache()
 
 
-def work_list(wp, KB, T):
+def work_list(wp, KB, T, chunk):
     """Item starts by their definition: every candidate (a multiple of Ts among the block slots) starts the part it lies in of
     a window that is cut, or an item at the nearer end of one that is not."""
     blk = np.concatenate([[0], np.cumsum(np.maximum(1, -(-np.diff(wp) // KB)))])
+    NB, longest = blk[-1], np.diff(blk).max()
     Ts, starts = min(T, 4), []
+    if chunk == 0:
+        Ts = 2 if NB < 4096 else 3 if NB < 16384 else 4
+        assert T == (4 if longest > 12 and NB < 5120 else 6 if longest > 12 and NB < 8192 else min(max(-(-NB // 4096), 8), 16))
     for x in range(0, blk[-1], Ts):
         w = np.searchsorted(blk, x, side="right") - 1
         lo, hi = blk[w], blk[w + 1]
@@ -182,7 +186,7 @@ def work_list(wp, KB, T):
 
 
 @pytest.mark.parametrize("chunk", [0, 32, 64, 96, 128, 160, 224, 1024])
-@pytest.mark.parametrize("W", [1, 2, 1023, 1024, 1025, 2500])  # a workgroup takes 1024 windows
+@pytest.mark.parametrize("W", [1, 2, 1023, 1024, 1025, 2500, 5000])  # a workgroup takes 1024 windows; all grains of chunk 0
 def test_convert_work_list_is_what_the_candidates_make(fs, W, chunk):  # noqa: F811
     V, K = 4, 30000
     rng = np.random.default_rng(W + chunk)
@@ -197,7 +201,7 @@ def test_convert_work_list_is_what_the_candidates_make(fs, W, chunk):  # noqa: F
     assert_format_equal(fmt, A, V, 32)
     assert_items_valid(fmt)
     wp = fmt.win_ptr_t().cpu().numpy().astype(np.int64)
-    blk, starts = work_list(wp, 32, fmt.chunk // 32)
+    blk, starts = work_list(wp, 32, fmt.chunk // 32, chunk)
     ends = np.append(starts[1:], blk[-1])
     items, order = fmt.items_t().cpu().numpy().astype(np.int64), fmt.item_order_t().cpu().numpy()
     real = starts < blk[-1]
