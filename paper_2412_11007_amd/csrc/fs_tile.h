@@ -117,13 +117,14 @@ __device__ __forceinline__ int fs_launch_turn(int bx, int slice, int n_swz)
 // contiguous eighth of the rows.  Such a matrix has a few entries a row, and one that gains from any order is a mesh, whose rows gather what
 // their neighbours in the other dimensions gather as well: in one L2, or, items dealt out, in several, as the grid's width happens
 // to fall on the XCDs.  us, dealt out / in eighths: SpMM on a stencil of 450^2 points, N = 128 34 / 22, 256 65 / 40; 700^2, N = 64 42 / 28, 128
-// 77 / 46; attention, d = 64, N = 128, 300^2 24 / 17, 550^2 72 / 47; SDDMM, d = 128, 700^2 80 / 58.  Only grids whose width is near
-// a multiple of 256 were dealt out well, a row's neighbours next to it on one XCD, and lose with wide rows: 1024^2, N = 64 54 / 53, 128 124 / 126; 512^2,
-// attention, d = 64, N = 128 37 / 38, d = 128 50 / 60.  Without a mesh it is the same (200 k rows with three entries at random 1.00).
+// 77 / 46; attention, d = 64, N = 128, 300^2 24 / 17, 550^2 72 / 47; SDDMM, d = 128, 700^2 80 / 58; on arrays that no cache holds yet 700^2,
+// N = 64 42 / 37, 128 76 / 63, attention 112 / 88.  A grid whose sides are multiples of 256 is dealt out well, a row's neighbours side by side on one
+// XCD, and better than in eighths (new arrays, 1024^2, N = 64 68 / 78; 512^2, N = 128 34 / 40), so numbers of rows that are multiples of 256^2
+// are left as they are (widths a few off such a multiple lose up to 15 %).  Without a mesh it is the same (200 k rows with three entries at random 1.00).
 struct fs_launch_geometry {
     int nbx, slice, n_swz;
 };
-inline bool fs_rows_alike(const fs_format *f) { return f->n_blocks == f->W && f->n_cut_items == 0; }
+inline bool fs_rows_alike(const fs_format *f) { return f->n_blocks == f->W && f->n_cut_items == 0 && f->M % (256 * 256) != 0; }
 inline fs_launch_geometry fs_launch_geometry_for(const fs_format *f, int wpb, int slice = 4096)
 {
     fs_launch_geometry g;
