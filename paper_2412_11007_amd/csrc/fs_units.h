@@ -440,7 +440,7 @@ __device__ __forceinline__ UnitRows unit_rows(const CsrView &a, const UnitPlan &
 // at most 512 nodes.  Units of short windows of a matrix with 2^20 columns take three levels, pieces of hubs one or two.  What bounds it is
 // the issue of instructions (530 for the 314 entries of a unit on average of R-MAT of 1 M rows, 31 M entries; a merge of the rows
 // in log2(V) rounds of binary searches took 1450) and what a wavefront waits for, so the chip's wavefronts walk the units with the
-// next ones' records and row pointers under way: 238 -> 119 us, 190 MB; the vector units are busy 72 % of that, LDS 54 %.  (Nodes of
+// next ones' records and row pointers under way: 238 -> 119 us, 190 MB; the vector units are busy 70 % of that, LDS 51 %.  (Nodes of
 // 64 bits, six bits a level: 770 instructions, 6 KB of LDS and 183 us.)
 constexpr int kTopBits = 14, kDigitBits = 5;
 constexpr int kFewEntries = 8;  // as many are compared one by one (16 M rows with 1 M entries, four a unit: by the trie 193 us, so 147)
