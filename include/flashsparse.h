@@ -213,7 +213,9 @@ fs_status fs_spmm(const fs_format *fmt, const void *d_vals,
  * library's device image (one copy per GPU, held until the process ends) instead of d_work.  The call
  * allocates and frees nothing.
  *   Needs fs_spmm_workspace_bytes(fmt, N) <= 32 MiB (33 554 432), else FS_ERR_TOO_LARGE and nothing is
- *   queued.  The current device must be the one `stream` and the buffers belong to; the array's address on
+ *   queued; but where fs_convert chose parts of four or six blocks (chunk = 0, less than 8192 block slots: more partial
+ *   tiles than parts of eight make), a product that needs more is multiplied in passes of columns that fit.
+ *   The current device must be the one `stream` and the buffers belong to; the array's address on
  *   that device is looked up on the first call there (at most 64 devices, else FS_ERR_UNSUPPORTED).
  *   All calls on one GPU share the array, which keeps the previous call's contents (every partial tile
  *   is written before it is read, so nothing needs clearing): two calls whose work overlaps in time on

@@ -147,9 +147,8 @@ extern "C" fs_status fs_spmm_workspace_bytes(const fs_format *fmt, int64_t N, si
     return FS_OK;
 }
 
-extern "C" fs_status fs_spmm_timed(const fs_format *fmt, const void *d_vals, const void *d_B, int64_t N, int64_t ldb,
-                                   void *d_C, int64_t ldc, void *d_work, size_t work_bytes, void *stream,
-                                   void *ev_before_main, void *ev_after_main)
+// The arguments of a product, but for its workspace.
+static fs_status spmm_arguments(const fs_format *fmt, const void *d_vals, const void *d_B, int64_t N, int64_t ldb, const void *d_C, int64_t ldc)
 {
     if (!format_ok(fmt) || N < 0 || ldb < N || ldc < N) return FS_ERR_INVALID_ARG;
     if (!kernels_support(fmt)) return FS_ERR_UNSUPPORTED;
@@ -159,6 +158,15 @@ extern "C" fs_status fs_spmm_timed(const fs_format *fmt, const void *d_vals, con
     if (N >= ((int64_t)1 << 24) || ldc >= ((int64_t)1 << 24) || ldb >= ((int64_t)1 << 30)) return FS_ERR_TOO_LARGE;
     const void *vals = d_vals ? d_vals : fmt->vals_blk;
     if (fmt->nvec > 0 && (!vals || !aligned(vals, 16))) return FS_ERR_INVALID_ARG;
+    return FS_OK;
+}
+
+extern "C" fs_status fs_spmm_timed(const fs_format *fmt, const void *d_vals, const void *d_B, int64_t N, int64_t ldb,
+                                   void *d_C, int64_t ldc, void *d_work, size_t work_bytes, void *stream,
+                                   void *ev_before_main, void *ev_after_main)
+{
+    const fs_status st = spmm_arguments(fmt, d_vals, d_B, N, ldb, d_C, ldc);
+    if (st != FS_OK || N == 0 || fmt->M == 0) return st;
     size_t need = 0;
     fs_spmm_workspace_bytes(fmt, N, &need);
     if (need > 0 && (!d_work || !aligned(d_work, 16))) return FS_ERR_INVALID_ARG;
@@ -189,19 +197,38 @@ extern "C" fs_status fs_spmm(const fs_format *fmt, const void *d_vals, const voi
     return fs_spmm_timed(fmt, d_vals, d_B, N, ldb, d_C, ldc, d_work, work_bytes, stream, nullptr, nullptr);
 }
 
+// Columns per call of a product whose partial tiles go to the fixed array: all N where they fit.  Parts of less than eight blocks are
+// the conversion's choice, made without knowing N, and parts of eight would make fewer tiles (windows of 7 to 12 blocks none at
+// all); so a product that needs more goes in passes.  0: the tiles do not fit.
+static int64_t static_columns(const fs_format *fmt, int64_t N, size_t need)
+{
+    if (need <= FS_STATIC_WORK_BYTES) return N;
+    if (fmt->n_blocks >= kShortPartsBelow || fmt->chunk != fs_short_part_blocks(fmt->n_blocks) * fmt->KB) return 0;
+    const int64_t fit = (int64_t)(FS_STATIC_WORK_BYTES / ((size_t)fmt->n_split_items * fmt->V * sizeof(float)));
+    return fit >= 128 ? fit / 128 * 128 : fit / 8 * 8;  // whole passes of the kernels
+}
+
 extern "C" fs_status fs_spmm_static(const fs_format *fmt, const void *d_vals, const void *d_B, int64_t N, int64_t ldb,
                                     void *d_C, int64_t ldc, void *stream)
 {
     size_t need = 0;
     const fs_status s = fs_spmm_workspace_bytes(fmt, N, &need);
     if (s != FS_OK) return s;
-    if (need > FS_STATIC_WORK_BYTES) return FS_ERR_TOO_LARGE;
+    const int64_t columns = static_columns(fmt, N, need);
+    if (columns == 0 && N > 0) return FS_ERR_TOO_LARGE;
+    const fs_status a = spmm_arguments(fmt, d_vals, d_B, N, ldb, d_C, ldc);
+    if (a != FS_OK || N == 0) return a;
     void *work = nullptr;
     if (need > 0) {  // partial tiles are written whole before they are read: nothing to clear
-        const fs_status a = static_workspace(&work);
-        if (a != FS_OK) return a;
+        const fs_status w = static_workspace(&work);
+        if (w != FS_OK) return w;
     }
-    return fs_spmm_timed(fmt, d_vals, d_B, N, ldb, d_C, ldc, work, need, stream, nullptr, nullptr);
+    for (int64_t n0 = 0; n0 < N; n0 += columns) {
+        const fs_status p = fs_spmm_timed(fmt, d_vals, (const uint16_t *)d_B + n0, std::min(columns, N - n0), ldb, (uint16_t *)d_C + n0, ldc, work,
+                                          std::min(need, FS_STATIC_WORK_BYTES), stream, nullptr, nullptr);
+        if (p != FS_OK) return p;
+    }
+    return FS_OK;
 }
 
 extern "C" fs_status fs_sddmm(const fs_format *fmt, const void *d_X, int64_t ldx, const void *d_Y, int64_t ldy,

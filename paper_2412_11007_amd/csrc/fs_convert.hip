@@ -107,7 +107,7 @@ __host__ __device__ inline Grain item_grain(int NB, int longest, int t_user, int
         const int t = (NB + 4095) / 4096;
         g.T = t < 8 ? 8 : (t > kDefaultMaxPartBlocks ? kDefaultMaxPartBlocks : t);
         g.Ts = NB < 4096 ? 2 : NB < 16384 ? 3 : kPackBlocks;
-        if (longest > g.T + g.T / 2 && NB < 8192) g.T = NB < 5120 ? 4 : 6;
+        if (longest > g.T + g.T / 2 && NB < kShortPartsBelow) g.T = fs_short_part_blocks(NB);
     }
     if (ts_user > 0) g.Ts = ts_user;
     return g;

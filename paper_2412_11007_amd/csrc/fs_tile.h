@@ -139,6 +139,11 @@ inline fs_launch_geometry fs_launch_geometry_for(const fs_format *f, int wpb, in
     return g;
 }
 
+// Blocks per part of a cut window that fs_convert takes by itself (chunk = 0) in a matrix of so many block slots; from
+// kShortPartsBelow on they are eight or more.  The reasons stand at the conversion's grain.
+constexpr int64_t kShortPartsBelow = 8192;
+__host__ __device__ inline int fs_short_part_blocks(int64_t n_blocks) { return n_blocks < 5120 ? 4 : 6; }
+
 // Whether fs_spmm takes passes of 256 columns for a product that wide (the reasons stand at its launch), and the columns after
 // them that have a narrower launch of their own.
 constexpr int kWidePassItems = 1024, kWidePassBlocks = 4096;  // (small matrices make more, shorter items)

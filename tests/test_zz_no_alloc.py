@@ -76,3 +76,30 @@ def test_static_workspace_limit_is_an_error(fs):
     assert (out == 3.0).all()
     del Bd, out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("windows,V,N", [(500, 8, 1024), (500, 8, 1000), (700, 4, 1664), (300, 16, 808)])
+def test_static_workspace_holds_the_short_parts_of_small_matrices(fs, windows, V, N):
+    """Windows of ten blocks, which parts of eight leave whole, in parts of four or six because one window is longer: the tiles of a
+    wide product exceed the fixed array, and the call multiplies in passes."""
+    import torch
+    g = np.random.default_rng(3)
+    K, M = 4096, windows * V
+    A = torch.zeros((M, K), dtype=torch.bool)
+    for w in range(windows):  # 10 blocks a window (the first: 16), every vector in one or two rows
+        cols = g.choice(K, 512 if w == 0 else 310, replace=False)
+        A[w * V + np.arange(cols.size) % V, cols] = True
+        A[w * V, cols[:40]] = True
+    rows, cols = A.nonzero(as_tuple=True)
+    rp = torch.zeros(M + 1, dtype=torch.int32)
+    rp[1:] = torch.cumsum(torch.bincount(rows, minlength=M), 0)
+    va = torch.from_numpy(g.standard_normal(rows.numel())).half().cuda()
+    fmt = fs.fs_convert(rp.cuda(), cols.int().cuda(), va, M, K, V=V)
+    assert fs.fs_spmm_workspace_bytes(fmt, N) > STATIC_BYTES
+    B = torch.from_numpy(g.standard_normal((K, N + 8))).half().cuda()[:, :N]
+    want = fs.fs_spmm(fmt, B)
+    got = torch.full((M, N + 8), 3.0, dtype=torch.float16, device="cuda")
+    fs.fs_spmm_static(fmt, B, got[:, :N])
+    assert torch.equal(got[:, :N], want) and (got[:, N:] == 3.0).all()
+    # arguments are checked for the whole product, not for a pass of it
+    assert fs.load_library().fs_spmm_static(ctypes.byref(fmt.c), 0, B.data_ptr(), N, N - 8, got.data_ptr(), N + 8, None) == 1
