@@ -109,8 +109,7 @@ __global__ void __launch_bounds__(256) k_gather_probe(const int4 *__restrict__ i
             for (int u = 0; u < NLD; u++) x ^= v[u].x ^ v[u].y ^ v[u].z ^ v[u].w;
         }
     }
-    // any slot: the word only keeps the loads alive (here that of the launch position, wherever it ran)
-    sink[((size_t)(pass * nbx + turn / 4) * 256 + threadIdx.x) & (1024 * 256 - 1)] = x;
+    sink[((size_t)blockIdx.x * 256 + threadIdx.x) & (1024 * 256 - 1)] = x;  // any slot: the word only keeps the loads alive
 }
 
 }  // namespace

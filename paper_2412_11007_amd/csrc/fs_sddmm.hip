@@ -102,7 +102,7 @@ __device__ __forceinline__ bool fs_sddmm_unit(const int4 *__restrict__ items, in
         nblk = it.y;
         return nblk > 0;
     }
-    first = fs_launch_turn<1>(blockIdx.x, slice, n_swz) * G;
+    first = blockIdx.x * G;
     nblk = min(G, n_blocks - first);
     return nblk > 0;
 }
@@ -388,12 +388,7 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
     const bool big = f->K >= ((int64_t)1 << 24) || f->M >= ((int64_t)1 << 24) || ldx * 2 >= ((int64_t)1 << 24) ||
                      ldy * 2 >= ((int64_t)1 << 24) || f->K * ldy * 2 >= ((int64_t)1 << 32) ||
                      (f->M + 32) * ldx * 2 >= ((int64_t)1 << 32);
-    const int64_t groups = ((int64_t)n_blocks + G - 1) / G;
-    fs_launch_geometry geo = fs_launch_geometry_for(f, 1);
-    if (!ordered) {  // (rows alike: contiguous eighths of the slots, one per XCD, as for the items)
-        geo.n_swz = fs_rows_alike(f) ? (int)(groups / 8 * 8) : 0;
-        geo.slice = std::max(geo.n_swz, 8);
-    }
+    const fs_launch_geometry geo = fs_launch_geometry_for(f, 1);
     // 128 < d <= 256: whole rows at a time, or chunks of 128 features.  Whole rows are fetched once, and keep a window's rows of X, by
     // half the wavefronts; so they gain where rows of Y miss the L2s and windows are tall, and lose where rows hit.  Chunks / whole rows,
     // us, d = 136, 168, 200, 256, blocks in brackets, "in order" in launch order:
@@ -414,7 +409,7 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
                       : V == 8 ? n_blocks >= 12800 && (ordered ? d >= 200 || y_bytes >= ((int64_t)64 << 20) : n_cut * 4 < n_items)
                                : f->nvec >= 18 * f->n_blocks && n_blocks >= (n_cut * 16 < n_items ? 1 << 15 : d >= 240 ? 1 << 16 : 1 << 19);
     const bool wide = tall && (d > 160 || (!ordered && y_bytes > ((int64_t)8 << 20)));
-    const dim3 grid(ordered ? (unsigned)geo.nbx : (unsigned)groups), block(64);
+    const dim3 grid(ordered ? (unsigned)geo.nbx : (unsigned)(((int64_t)n_blocks + G - 1) / G)), block(64);
 #define FS_SDDMM_ARGS items, (int)f->n_items, geo.slice, geo.n_swz, n_blocks, G, (const int4 *)f->blk_desc, f->vec_col, f->blk_row_bits, (int)f->nvec, X, ldx, Y, ldy, (int)d, out, f->M, out_csr, f->blk_row_base
 #define FS_SDDMM_LAUNCH(...)  /* the kernel and its first template arguments */                         \
     {                                                                                                     \

@@ -100,7 +100,7 @@ __device__ __forceinline__ void fs_for_each_index(F &&f, std::integer_sequence<i
 // once -- XCD x takes the x-th eighth, a contiguous run: parts of different hub windows that sweep the same
 // columns meet in one L2.  n_swz and slice are multiples of 8 * WPB, the workgroups per pass of 8.
 template <int WPB>
-__device__ __forceinline__ int fs_launch_turn(int bx, int slice, int n_swz)
+__host__ __device__ __forceinline__ int fs_launch_turn(int bx, int slice, int n_swz)
 {
     int u = bx * WPB;
     if (u < n_swz) {
@@ -113,27 +113,18 @@ __device__ __forceinline__ int fs_launch_turn(int bx, int slice, int n_swz)
 }
 
 // Host side of the same: workgroups per pass, slice length and swizzled prefix for wpb items per workgroup.
-// Where every window is one block, all items are alike, their order is that of the rows, and the whole launch is one slice: an XCD takes a
-// contiguous eighth of the rows.  Such a matrix has a few entries a row, and one that gains from any order is a mesh, whose rows gather what
-// their neighbours in the other dimensions gather as well: in one L2, or, items dealt out, in several, as the grid's width happens
-// to fall on the XCDs.  us, dealt out / in eighths: SpMM on a stencil of 450^2 points, N = 128 34 / 22, 256 65 / 40; 700^2, N = 64 42 / 28, 128
-// 77 / 46; attention, d = 64, N = 128, 300^2 24 / 17, 550^2 72 / 47; SDDMM, d = 128, 700^2 80 / 58; on arrays that no cache holds yet 700^2,
-// N = 64 42 / 37, 128 76 / 63, attention 112 / 88.  A grid whose sides are multiples of 256 is dealt out well, a row's neighbours side by side on one
-// XCD, and better than in eighths (new arrays, 1024^2, N = 64 68 / 78; 512^2, N = 128 34 / 40), so numbers of rows that are multiples of 256^2
-// are left as they are (widths a few off such a multiple lose up to 15 %).  Without a mesh it is the same (200 k rows with three entries at random 1.00).
+// Whole windows keep the list's order and go to the XCDs one by one, whatever the matrix: that deals out the work evenly however it
+// is spread over the rows.  (A contiguous eighth of the rows for every XCD, where every window is one block, suits meshes whose
+// width is far from a multiple of what eight workgroups take: 896^2 points, SpMM with 128 columns 120 us, in eighths 101, attention 174 and 138.  But the
+// order is chosen without the width, and at 1020^2 it costs 10 to 14 %; and a block holds 0 to 32 vectors: 262 k rows,
+// four-row windows, all entries in the first eighth of the rows, SpMM with 128 columns 28 and 44.)
 struct fs_launch_geometry {
     int nbx, slice, n_swz;
 };
-inline bool fs_rows_alike(const fs_format *f) { return f->n_blocks == f->W && f->n_cut_items == 0 && f->M % (256 * 256) != 0; }
 inline fs_launch_geometry fs_launch_geometry_for(const fs_format *f, int wpb, int slice = 4096)
 {
     fs_launch_geometry g;
     g.nbx = (int)((((int64_t)f->n_items + wpb - 1) / wpb + 7) / 8 * 8);
-    if (fs_rows_alike(f)) {
-        g.n_swz = (int)(f->n_items / (8 * wpb) * (8 * wpb));
-        g.slice = std::max(g.n_swz, 8 * wpb);
-        return g;
-    }
     g.slice = slice / 32 * 32;  // a multiple of 8 * wpb for wpb = 1, 2, 4
     g.n_swz = g.slice > 0 ? (int)(std::min<int64_t>(f->n_cut_items, f->n_items) / (8 * wpb) * (8 * wpb)) : 0;
     return g;
