@@ -74,7 +74,7 @@ typedef enum { FS_F16 = 0, FS_BF16 = 1 } fs_dtype;
  *                  an item is a run of consecutive block slots.  With T = chunk / KB: a window with more than 1.5 T blocks is cut into
  *                  round(blocks / T) parts of equal length (within one block), from its start;
  *                  shorter windows are never cut and are packed whole into items of about
- *                  min(T, 4) blocks (two or three in a small matrix with chunk = 0).  No item has more than 2 * T + 4 blocks (at most 64).  n_items records of four int32
+ *                  min(T, 4) blocks (two to four in a small matrix with chunk = 0).  No item has more than 2 * T + 4 blocks (at most 64).  n_items records of four int32
  *                  {first block slot, number of blocks, first partial slot, first vector}; a
  *                  record with 0 blocks is empty.  An item whose first or last window is only
  *                  partly inside it adds that part into an fp32 partial tile (slots are handed

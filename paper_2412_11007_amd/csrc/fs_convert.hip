@@ -88,16 +88,22 @@ __device__ __forceinline__ bool starts_at_hi(int lo, int hi, int T, int Ts)
 // window: enough items to put about 16 wavefronts on each of the 256 CUs, long enough to amortise an item's fixed cost,
 // short enough that one item is a small part of the run time.  A caller's own choice of T (t_user > 0) wins; Ts is then as ever, four or T.
 // In a small matrix the chain of one item is the time, and shorter items shorten it, but a window cut into parts costs a launch that adds
-// them up; so parts are shorter than eight blocks only where some window is cut anyway.  T, Ts = 8, 4 / here, us, SpMM with
+// them up; so parts are shorter than eight blocks only where some window is cut anyway.  T, Ts = 8, 4 / 4 or 6, 2, us, SpMM with
 // 64 and 128 columns and attention with d = 64, N = 128: lognormal graph of 4 k rows 9.2 / 7.2, 10.5 / 8.3, 16.8 / 12.3; R-MAT of 8 k rows, eight entries a
-// row, 9.1 / 7.2, 10.5 / 8.2, 17.1 / 11.9, of 16 k, six, 9.8 / 7.7, 11.6 / 9.1, 18.1 / 14.4; of 32 k, sixteen, where parts stay, 12.1 / 11.2, 15.1 / 14.4, 24.3 / 21.1;
-// uniform, 20 k rows, no window cut 6.2 / 5.3, 9.1 / 9.1, 14.0 / 13.5; stencil of 170^2 points 5.6 / 4.7, 6.9 / 5.7, 10.6 / 7.8.  Four blocks a part for
-// 6 k blocks cost R-MAT of 16 k rows, twelve a row, 3 to 9 %, six for 10 k blocks one of 32 k, eight a row, up to 5; 256 columns lose 5 % at 3.4 k
-// blocks (R-MAT of 8 k rows, sixteen a row 10.9 / 11.5).
+// row, 9.1 / 7.2, 10.5 / 8.2, 17.1 / 11.9, of 16 k, six, 9.8 / 7.6, 11.6 / 9.1, 17.8 / 13.9; stencil of 170^2 points, Ts alone, 6.2 / 5.7, 7.7 / 7.4, 11.0 / 10.3.  Four blocks a
+// part for 6 k blocks cost R-MAT of 16 k rows, twelve a row, 3 to 9 %, six for 10 k blocks one of 32 k, eight a row, up to 5.  The conversion does not know
+// the width of the products, and wide ones pay for the partial tiles of short parts where hubs hold many of the blocks: R-MAT of 8 k rows, sixteen a row (524 tiles
+// of 3.4 k blocks), 128 columns 9.8 / 9.4, 256 10.8 / 11.5, 512 13.4 / 15.2, 1024 20.0 / 22.4; with fewer tiles, R-MAT of 16 k rows, six a row (269 of 4.0 k), 512 15.8 / 15.3.
+// From 4 k blocks on three block slots an item pay where windows are long (Ts = 4 / 3: uniform, 20 k rows, twelve a row, three blocks a window, 64 columns
+// 7.2 / 6.3, softmax 8.9 / 6.7; lognormal graph of 20 k rows, attention 22.0 / 21.0).  Windows of a block or two may be those of a mesh, whose rows share
+// operands with rows a width of the mesh away: items of 32 rows meet them on one XCD where the width is a multiple of 256, and so do
+// items of 16, but not of 24 (256^2 points, Ts = 2 / 3 / 4, SpMM with 128 columns 10.5 / 13.6 / 11.2, attention 16.8 / 19.8 / 15.5; with a row of 4000 entries, which
+// is cut, 13.7 / 16.6 / 14.9, 21.0 / 24.9 / 21.1).  So there an item has two, where hubs may be the reason that windows are short on
+// average (R-MAT of 32 k rows, four a row, 10.5 / 10.5 / 12.6, 15.0 / 14.9 / 19.4), and else four.
 struct Grain {
     int T, Ts;
 };
-__host__ __device__ inline Grain item_grain(int NB, int longest, int t_user, int ts_user)
+__host__ __device__ inline Grain item_grain(int NB, int64_t W, int longest, int t_user, int ts_user)
 {
     Grain g;
     if (t_user > 0) {
@@ -106,7 +112,10 @@ __host__ __device__ inline Grain item_grain(int NB, int longest, int t_user, int
     } else {
         const int t = (NB + 4095) / 4096;
         g.T = t < 8 ? 8 : (t > kDefaultMaxPartBlocks ? kDefaultMaxPartBlocks : t);
-        g.Ts = NB < 4096 ? 2 : NB < 16384 ? 3 : kPackBlocks;
+        if (NB < 4096) g.Ts = 2;
+        else if (NB >= 16384) g.Ts = kPackBlocks;
+        else if (2 * (int64_t)NB >= 5 * W) g.Ts = 3;
+        else g.Ts = longest > g.T + g.T / 2 ? 2 : kPackBlocks;
         if (longest > g.T + g.T / 2 && NB < kShortPartsBelow) g.T = fs_short_part_blocks(NB);
     }
     if (ts_user > 0) g.Ts = ts_user;
@@ -135,7 +144,7 @@ __global__ void __launch_bounds__(kWindowThreads) k_win_slots(const int32_t *__r
     block_sum<kWindowThreads>(before);
     int ahead = before[0];
     const int NB = before[1];
-    const Grain grain = item_grain(NB, misc[2], t_user, ts_user);
+    const Grain grain = item_grain(NB, W, misc[2], t_user, ts_user);
     const int T = grain.T, Ts = grain.Ts;
     int n[3] = {0, 0, 0};  // items, partial tiles, cut windows
     for (int64_t wt = w0; wt < w1; wt += kWindowThreads) {
@@ -746,7 +755,7 @@ extern "C" fs_status fs_convert(int64_t M, int64_t K, int64_t nnz, const int32_t
                           scratch_bytes, stream, out);
     if ((int64_t)V * nvec >= (int64_t)1 << 31) return FS_ERR_TOO_LARGE;
     const int n_items = W > 0 ? h_misc[6] : 0;
-    const Grain grain = item_grain(NB, h_misc[2], t_user, ts_user);
+    const Grain grain = item_grain(NB, W, h_misc[2], t_user, ts_user);
     chunk = grain.T * KB;
 
     // arena layout, now that the sizes are known.  The value array is followed by 256 zeroed bytes: with no

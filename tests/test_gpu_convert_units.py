@@ -237,3 +237,27 @@ def test_convert_columns_that_span_so_much(fs, V, span):  # noqa: F811
     fmt = fs.fs_convert(rp, ci, va, A.M, A.K, V=V)
     assert_format_equal(fmt, A, V, 32)
     assert_row_base_valid(fmt, A)
+
+
+@pytest.mark.parametrize("width,height,dense_row,blocks_an_item", [(64, 64, False, 2), (128, 128, False, 2), (256, 256, False, 4), (256, 130, False, 4),
+                                                                   (512, 300, False, 4), (256, 256, True, 2), (400, 400, True, 4)])
+def test_whole_items_of_a_mesh_have_a_power_of_two_blocks(fs, width, height, dense_row, blocks_an_item):
+    """Windows of one block: items of three would take 24 rows, and the rows that share operands, a width of the mesh apart, would meet in
+    no L2 where the width is a power of two."""
+    import torch
+    n = width * height
+    i = np.arange(n)
+    x, y = i % width, i // width
+    rows = np.concatenate([i, i[x > 0], i[x < width - 1], i[y > 0], i[y < height - 1]])
+    cols = np.concatenate([i, i[x > 0] - 1, i[x < width - 1] + 1, i[y > 0] - width, i[y < height - 1] + width])
+    if dense_row:  # one window of more than 12 blocks, which is cut
+        rows, cols = np.concatenate([rows, np.full(n // 64, 77)]), np.concatenate([cols, np.arange(n // 64) * 64])
+    key = np.unique(rows * n + cols)
+    rp = np.concatenate([[0], np.cumsum(np.bincount(key // n, minlength=n))])
+    fmt = fs.fs_convert(torch.from_numpy(rp).int().cuda(), torch.from_numpy(key % n).int().cuda(), None, n, n, torch_dtype=torch.float16, V=8)
+    items = fmt.items_t().cpu().numpy()
+    cut = fmt.n_cut_items
+    assert (cut > 0) == dense_row
+    whole = items[np.sort(fmt.item_order_t().cpu().numpy()[cut:])]
+    # the one next to a cut window and the last may be shorter or longer
+    assert (whole[:, 1] == blocks_an_item).sum() >= len(whole) - 3, np.bincount(whole[:, 1])
