@@ -93,7 +93,8 @@ typedef enum { FS_F16 = 0, FS_BF16 = 1 } fs_dtype;
  *                  the row if there is none).  With the occupancy masks this locates every entry of a
  *                  block in CSR order: fs_sddmm writes CSR-order output with it
  *   blk_row_bits   V uint32 per block slot (KB = 32 only, else NULL): [x * V + r] = the vectors of block x that window
- *                  row r stores, bit c for the block's vector c (the occupancy masks, seen from a row)
+ *                  row r stores, bit c for the block's vector c (the occupancy masks, seen from a row).  fs_sddmm and the fused calls need it;
+ *                  fs_edge_softmax and its gradient do without, from vec_mask, a little slower
  *   split_windows  n_split_windows records of four int32
  *                  {window, first partial slot, number of slots, 0}: the partial
  *                  tiles of a cut window are consecutive slots

@@ -258,7 +258,7 @@ extern "C" fs_status fs_edge_softmax(const fs_format *fmt, const void *d_in_blk,
     if (!format_ok(fmt) || !(scale == scale) || scale - scale != 0.f) return FS_ERR_INVALID_ARG;  // NaN, infinity
     if (!kernels_support(fmt)) return FS_ERR_UNSUPPORTED;
     if (fmt->nvec == 0) return FS_OK;
-    if (!d_in_blk || !d_out_blk || !fmt->blk_row_bits) return FS_ERR_INVALID_ARG;
+    if (!d_in_blk || !d_out_blk) return FS_ERR_INVALID_ARG;
     size_t need = 0;
     fs_edge_softmax_workspace_bytes(fmt, &need);
     if (need > 0 && (!d_work || !aligned(d_work, 4))) return FS_ERR_INVALID_ARG;
@@ -272,7 +272,7 @@ extern "C" fs_status fs_edge_softmax_backward(const fs_format *fmt, const void *
     if (!format_ok(fmt) || !(scale == scale) || scale - scale != 0.f) return FS_ERR_INVALID_ARG;  // NaN, infinity
     if (!kernels_support(fmt)) return FS_ERR_UNSUPPORTED;
     if (fmt->nvec == 0) return FS_OK;
-    if (!d_p_blk || !d_g_blk || !d_out_blk || !fmt->blk_row_bits) return FS_ERR_INVALID_ARG;
+    if (!d_p_blk || !d_g_blk || !d_out_blk) return FS_ERR_INVALID_ARG;
     size_t need = 0;
     fs_edge_softmax_workspace_bytes(fmt, &need);
     if (need > 0 && (!d_work || !aligned(d_work, 4))) return FS_ERR_INVALID_ARG;

@@ -79,11 +79,13 @@ __device__ __forceinline__ uint32_t stored(uint32_t m8, int x) { return (uint32_
 // BWD          : the gradient instead: `in` holds the probabilities, `in2` the gradient that arrives at them,
 //                the row statistic is sum p * g (second float of a workspace pair), the output
 //                scale * p * (g - that sum).
+// BITS = false : a format without blk_row_bits; which positions A stores is put together from vec_mask.  (Asked for at run time, the
+//                question alone cost sixteen-row windows up to a quarter: their loads no longer travelled together.)
 // n_el: elements of the arrays.
-template <int DT, int V, bool PARTS, bool BWD>
+template <int DT, int V, bool PARTS, bool BWD, bool BITS>
 __global__ void __launch_bounds__(64)
 k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk_desc,
-               const uint32_t *__restrict__ row_bits, const uint16_t *in, const uint16_t *in2,
+               const uint32_t *__restrict__ row_bits, const uint32_t *__restrict__ vec_mask, const uint16_t *in, const uint16_t *in2,
                uint16_t *out, int n_el, float *__restrict__ stats, float scale, const int2 *__restrict__ slot_range,
                int n_slots)
 {
@@ -115,7 +117,7 @@ k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restri
         fs_frag v, d;
     };
     // block i of the item (none from `end` on); the bits do not depend on the descriptor, so they are under way beside it
-    auto bits_of = [&](int i, int end) -> uint32_t { return i < end ? row_bits[(int64_t)(it.x + i) * V + j] >> (8 * g) & 0xFFu : 0u; };
+    auto bits_of = [&](int i, int end) -> uint32_t { return BITS && i < end ? row_bits[(int64_t)(it.x + i) * V + j] >> (8 * g) & 0xFFu : 0u; };
     auto values_of = [&](const uint16_t *from, const Eight &x) -> fs_frag {
         // Narrow blocks: what follows the row, or the block, is read along with it and not looked at; at the end of the array it is not there.
         const uint32_t at = (uint32_t)V * x.s + j * x.kb + 8 * g;  // (up to 2^31 elements)
@@ -139,6 +141,10 @@ k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restri
             x.kb = __shfl(my_desc.y, ic, 64) & 255;
         }
         if (i >= end) x.kb = 0;
+        if constexpr (!BITS) {
+#pragma unroll
+            for (int k = 0; k < 8; k++) x.m8 |= 8 * g + k < x.kb ? (vec_mask[x.s + 8 * g + k] >> j & 1u) << k : 0u;
+        }
         x.v = values_of(in, x);
         if constexpr (BWD) x.d = values_of(in2, x);
     };
@@ -418,8 +424,8 @@ k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restri
     }
 }
 
-template <int DT, int V, bool BWD>
-fs_status launch(const fs_format *f, const uint16_t *in, const uint16_t *in2, uint16_t *out, float scale, float *stats,
+template <int DT, int V, bool BWD, bool BITS>
+fs_status launch_with(const fs_format *f, const uint16_t *in, const uint16_t *in2, uint16_t *out, float scale, float *stats,
                  hipStream_t st)
 {
     if (f->n_items == 0) return FS_OK;
@@ -428,16 +434,24 @@ fs_status launch(const fs_format *f, const uint16_t *in, const uint16_t *in2, ui
     const int4 *items = (const int4 *)f->items_by_cost;
     const int n_items = (int)f->n_items;
     const int n_el = (int)(V * f->nvec);
-    k_edge_softmax<DT, V, false, BWD><<<(unsigned)n_items, 64, 0, st>>>(items, n_items, (const int4 *)f->blk_desc, f->blk_row_bits, in, in2, out, n_el, stats, scale,
+    k_edge_softmax<DT, V, false, BWD, BITS><<<(unsigned)n_items, 64, 0, st>>>(items, n_items, (const int4 *)f->blk_desc, f->blk_row_bits, f->vec_mask, in, in2, out, n_el, stats, scale,
                                                                         (const int2 *)f->slot_range, (int)f->n_split_items);
     FS_LAUNCH_CHECK();
     const int n_cut = (int)std::min<int64_t>(f->n_cut_items, f->n_items);
     if (f->n_split_windows > 0 && n_cut > 0) {
-        k_edge_softmax<DT, V, true, BWD><<<(unsigned)n_cut, 64, 0, st>>>(items, n_cut, (const int4 *)f->blk_desc, f->blk_row_bits, in, in2, out, n_el, stats, scale,
+        k_edge_softmax<DT, V, true, BWD, BITS><<<(unsigned)n_cut, 64, 0, st>>>(items, n_cut, (const int4 *)f->blk_desc, f->blk_row_bits, f->vec_mask, in, in2, out, n_el, stats, scale,
                                                                          (const int2 *)f->slot_range, (int)f->n_split_items);
         FS_LAUNCH_CHECK();
     }
     return FS_OK;
+}
+
+template <int DT, int V, bool BWD>
+fs_status launch(const fs_format *f, const uint16_t *in, const uint16_t *in2, uint16_t *out, float scale, float *stats,
+                 hipStream_t st)
+{
+    return f->blk_row_bits ? launch_with<DT, V, BWD, true>(f, in, in2, out, scale, stats, st)
+                           : launch_with<DT, V, BWD, false>(f, in, in2, out, scale, stats, st);
 }
 
 template <bool BWD>

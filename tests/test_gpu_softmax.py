@@ -312,3 +312,21 @@ def test_attention_backward_chain_matches_finite_differences(fs):
             fdH[k, t] = (loss_yh(Yf, Hf + E) - loss_yh(Yf, Hf - E)) / (2 * h)
     assert np.abs(dY - fdY).max() <= 2e-2 * np.abs(fdY).max(), (np.abs(dY - fdY).max(), np.abs(fdY).max())
     assert np.abs(dH - fdH).max() <= 2e-2 * np.abs(fdH).max(), (np.abs(dH - fdH).max(), np.abs(fdH).max())
+
+
+@pytest.mark.parametrize("V,chunk", [(4, 0), (8, 0), (8, 32), (16, 64)])
+def test_softmax_of_a_format_without_row_occupancies(fs, V, chunk):
+    """A format that somebody put together with the vectors' masks alone: the same bits as with the rows' occupancies."""
+    import torch
+    M, K, dtype = 180, 5000, "f16"
+    A = hub_csr(M, K, dtype, 77 + V)
+    fmt = convert(fs, A, V, chunk)
+    assert fmt.n_split_items > 0
+    vals, g = fmt.vals_blk_t(), torch.randn(V * fmt.nvec, generator=torch.Generator("cuda").manual_seed(V), device="cuda").half()
+    p = fs.fs_edge_softmax(fmt, vals, scale=0.5)
+    d = fs.fs_edge_softmax_backward(fmt, p, g, scale=0.5)
+    bare = fs.FsFormat(type(fmt.c).from_buffer_copy(fmt.c), fmt.arena, fmt.torch_dtype)
+    bare.c.blk_row_bits = None
+    for out in (torch.full_like(vals, 3.0), None):
+        assert torch.equal(fs.fs_edge_softmax(bare, vals, out=out, scale=0.5).view(torch.int16), p.view(torch.int16))
+    assert torch.equal(fs.fs_edge_softmax_backward(bare, p, g, scale=0.5).view(torch.int16), d.view(torch.int16))
