@@ -280,7 +280,7 @@ fs_status fs_edge_softmax_workspace_bytes(const fs_format *fmt, size_t *work_byt
  * attention GNN (the softmax layer of the paper's Section 4.4 end-to-end model; the paper gives
  * no kernel for it, this is the textbook definition, evaluated in fp32 with the row maximum
  * subtracted first and rounded once to the element type).
- *   d_in_blk, d_out_blk : V*nvec elements each; may be the same buffer.  Positions of d_out_blk
+ *   d_in_blk, d_out_blk : V*nvec elements each, 2-byte aligned; may be the same buffer.  Positions of d_out_blk
  *                         outside the pattern get +0.0; a row without stored entries gets zeros.
  *   scale               : finite.
  *   d_work              : workspace of fs_edge_softmax_workspace_bytes(fmt) bytes, 4-byte aligned
@@ -298,7 +298,7 @@ fs_status fs_edge_softmax(const fs_format *fmt, const void *d_in_blk, void *d_ou
  * all three in the vals_blk layout (g is what fs_sddmm(dOut, H) writes; out is what fs_spmm takes as values
  * for the gradients of X and, on the transposed format, of Y).  fp32 arithmetic, one rounding to the element
  * type; positions outside the pattern get +0.0.
- *   d_p_blk, d_g_blk, d_out_blk : V*nvec elements each; d_out_blk may be either input buffer.
+ *   d_p_blk, d_g_blk, d_out_blk : V*nvec elements each, 2-byte aligned; d_out_blk may be either input buffer.
  *   scale                       : the scale of the forward call; finite.
  *   d_work                      : workspace of fs_edge_softmax_workspace_bytes(fmt) bytes, 4-byte aligned
  *                                 (may be NULL when that size is 0).

@@ -167,7 +167,7 @@ k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restri
         o.u = fs_u4{fs_pack2<DT>(y[0], y[1]), fs_pack2<DT>(y[2], y[3]), fs_pack2<DT>(y[4], y[5]), fs_pack2<DT>(y[6], y[7])};
         const int kb = mine ? x.kb : 0;
         uint16_t *blk = out + (int64_t)V * x.s;
-        if (kb == 32) *reinterpret_cast<fs_u4 *>(blk + j * 32 + 8 * g) = o.u;
+        if (kb == 32) *reinterpret_cast<fs_u4_unaligned *>(blk + j * 32 + 8 * g) = o.u;  // (four rows: blocks begin on eight bytes; the array on any element)
         const bool narrow = kb > 0 && kb < 32;
         if (!__ballot(narrow)) return;
         uint16_t *mine_at = tile + b * (32 * V);
@@ -179,8 +179,8 @@ k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restri
         FS_WAVE_SYNC();
         const int at = 8 * (j * 4 + g);
         if (narrow) {
-            if (at + 8 <= V * kb) *reinterpret_cast<fs_u4 *>(blk + at) = *reinterpret_cast<const fs_u4 *>(mine_at + at);
-            else if (V == 4 && at < V * kb) *reinterpret_cast<uint2 *>(blk + at) = *reinterpret_cast<const uint2 *>(mine_at + at);  // odd widths
+            if (at + 8 <= V * kb) *reinterpret_cast<fs_u4_unaligned *>(blk + at) = *reinterpret_cast<const fs_u4 *>(mine_at + at);
+            else if (V == 4 && at < V * kb) *reinterpret_cast<fs_u2_unaligned *>(blk + at) = *reinterpret_cast<const fs_u2 *>(mine_at + at);  // odd widths
         }
         FS_WAVE_SYNC();
     };

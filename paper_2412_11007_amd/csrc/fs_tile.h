@@ -30,8 +30,10 @@ __device__ __forceinline__ constexpr int lds_row(int r)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");      \
     } while (0)
 
-// 16 bytes at a 2-byte-aligned address, read with one load instruction
+// 16 and 8 bytes at a 2-byte-aligned address, read or written with one instruction
 typedef fs_u4 fs_u4_unaligned __attribute__((aligned(2)));
+typedef uint32_t fs_u2 __attribute__((ext_vector_type(2)));
+typedef fs_u2 fs_u2_unaligned __attribute__((aligned(2)));
 
 // A lane's stored values -> eight positions of its row.  `raw` holds the values back to back (halfword 0 first), bit x of m8
 // says whether position x is stored: stored positions take the next halfword, the others +0.0.  Entry m of sel[16], a table in

@@ -330,3 +330,30 @@ def test_softmax_of_a_format_without_row_occupancies(fs, V, chunk):
     for out in (torch.full_like(vals, 3.0), None):
         assert torch.equal(fs.fs_edge_softmax(bare, vals, out=out, scale=0.5).view(torch.int16), p.view(torch.int16))
     assert torch.equal(fs.fs_edge_softmax_backward(bare, p, g, scale=0.5).view(torch.int16), d.view(torch.int16))
+
+
+@pytest.mark.parametrize("V", [4, 8, 16])
+@pytest.mark.parametrize("offset", [0, 1, 2, 3, 5])
+def test_softmax_arrays_begin_on_any_element(fs, V, offset):
+    """Value arrays that are part of a larger buffer, and with four rows blocks that begin eight bytes past a line: sixteen bytes
+    are moved at a time wherever they lie, and nothing beside the array is written."""
+    import torch
+    fmt = convert(fs, random_csr(303, 170, 0.2, "f16", seed=V, empty_rows=0.1), V, 0)
+    n = V * fmt.nvec
+    gen = torch.Generator("cuda").manual_seed(offset)
+    vals, g = (torch.randn(n, generator=gen, device="cuda").half() for _ in range(2))
+    p = fs.fs_edge_softmax(fmt, vals)
+    d = fs.fs_edge_softmax_backward(fmt, p, g)
+
+    def moved(t):
+        buf = torch.full((n + 16,), 7.0, dtype=torch.float16, device="cuda")
+        buf[offset:offset + n] = t
+        return buf
+
+    a, b, out = moved(vals), moved(g), moved(torch.zeros_like(vals))
+    fs.fs_edge_softmax(fmt, a[offset:offset + n], out=out[offset:offset + n])
+    assert torch.equal(out.view(torch.int16), moved(p).view(torch.int16))
+    fs.fs_edge_softmax(fmt, a[offset:offset + n], out=a[offset:offset + n])
+    assert torch.equal(a.view(torch.int16), moved(p).view(torch.int16))
+    fs.fs_edge_softmax_backward(fmt, a[offset:offset + n], b[offset:offset + n], out=b[offset:offset + n])
+    assert torch.equal(b.view(torch.int16), moved(d).view(torch.int16))
