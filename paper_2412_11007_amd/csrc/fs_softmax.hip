@@ -13,9 +13,12 @@
 // bit-reproducible.
 //
 // Lane (block b of a round, row j, group g) handles the eight vectors 8g .. 8g+7 of a row: sixteen bytes of the row-major tile,
-// so that a wave-wide load or store moves 1 KB of consecutive blocks (16 / V of them), and one word tells which of the eight A stores.  An item of up to
-// kChunk blocks -- nearly all of them are -- is read once, all its loads together, and stays in registers; the rows' maxima and sums go from block to
-// block of a window through LDS.  Longer items are walked run by run and read twice.
+// so that a wave-wide load or store moves 1 KB of consecutive blocks (16 / V of them), and one word tells which of the eight A stores.
+// kChunk blocks are loaded together: eight with four rows and, for the gradient, with eight, else four.  An item of up to as many is
+// read once and stays in registers, its windows side by side; the rows' maxima and sums go from block to block of a window through LDS.  Longer
+// items (of R-MAT graphs a fifth of the items with four rows a window, half with eight, 60 % with sixteen) are walked window by window; a window of up to kChunk
+// blocks stays in registers between its statistics and its results, a longer one is read twice.  (Steps of whole windows in one loop
+// for all items: twice the registers.)
 // What bounds it is the chain item -> blocks -> values of the wavefronts and, beside it, the instructions for positions that A does
 // not store.  Lognormal graph of 262 k rows, four-row windows (46 k items, 90 MB; 4-byte pieces and a mask per vector): softmax
 // 46 -> 37 us, its gradient 69 -> 40;
@@ -368,8 +371,8 @@ k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restri
         const int end = after ? a + (int)__builtin_ctzll(after) + 1 : nblk;
         const bool whole = after && (firsts >> a & 1);
         float top = -INFINITY, total = 0.f;
+        Eight x[ROUNDS];
         for (int c = a; c < end; c += kChunk) {
-            Eight x[ROUNDS];
 #pragma unroll
             for (int r = 0; r < ROUNDS; r++) {
                 if (c + r * PER >= end) break;
@@ -405,10 +408,9 @@ k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restri
             slot++;
         } else {
             for (int c = a; c < end; c += kChunk) {
-                Eight x[ROUNDS];
 #pragma unroll
                 for (int r = 0; r < ROUNDS; r++) {
-                    if (c + r * PER >= end) break;
+                    if (c + r * PER >= end || end - a <= kChunk) break;
                     const int i = c + r * PER + b;
                     x[r].m8 = bits_of(i, end);
                     fetch(x[r], i, end);

@@ -357,3 +357,54 @@ def test_softmax_arrays_begin_on_any_element(fs, V, offset):
     assert torch.equal(a.view(torch.int16), moved(p).view(torch.int16))
     fs.fs_edge_softmax_backward(fmt, a[offset:offset + n], b[offset:offset + n], out=b[offset:offset + n])
     assert torch.equal(b.view(torch.int16), moved(d).view(torch.int16))
+
+
+def ragged_windows(V, dtype, seed, large):
+    """Windows of 0 to 10 blocks in every order, the last block of most of them narrow, and a few long enough to be cut; `large` windows
+    have scores so far apart that the exponential needs care (a range of +-60 after scaling by one), beside others that have not."""
+    rng = np.random.default_rng(seed)
+    K, blocks = 6000, np.concatenate([np.repeat(np.arange(11), 9), [14, 20, 60, 13]])
+    rng.shuffle(blocks)
+    rows, cols, span = [], [], []
+    for w, n_b in enumerate(blocks):
+        n = 0 if n_b == 0 else 32 * (n_b - 1) + int(rng.choice([1, 7, 8, 9, 31, 32]))
+        c = rng.choice(K, size=n, replace=False)
+        r = np.concatenate([rng.integers(0, V, n), rng.integers(0, V, n // 3)])  # every vector in one or two rows
+        rows.append(w * V + r)
+        cols.append(np.concatenate([c, c[:n // 3]]))
+        span.append(np.full(r.size, 60.0 if large and w % 3 == 0 else 1.0))
+    rows, cols, span = (np.concatenate(x) for x in (rows, cols, span))
+    keep = np.unique(rows * K + cols, return_index=True)[1]  # in CSR order
+    A = csr_from_coo(len(blocks) * V, K, rows[keep], cols[keep], "n01", dtype, rng)
+    A.vals[:] = round_to_bits((rng.uniform(-1, 1, keep.size) * span[keep]).astype(np.float32), dtype)
+    return A
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("V", [4, 8, 16])
+@pytest.mark.parametrize("chunk,large", [(0, False), (0, True), (128, True), (256, False), (1024, True)])
+def test_softmax_items_around_a_register_load(fs, V, dtype, chunk, large):
+    """Items with whole windows and parts of cut ones, as long as one load of blocks holds, shorter and longer: both walks and both
+    exponentials, in place as well as not."""
+    import torch
+    A = ragged_windows(V, dtype, V + chunk, large)
+    fmt = convert(fs, A, V, chunk)
+    n = fmt.items_t()[:, 1].cpu().numpy()
+    for at in (4, 8) if chunk >= 256 else (4,):  # (shorter parts make no items of eight)
+        assert (n < at).any() and (n == at).any() and (n > at).any(), np.bincount(n)
+    assert fmt.n_split_items > 0
+    vals = fmt.vals_blk_t().clone()
+    out = fs.fs_edge_softmax(fmt, vals)
+    assert check(fs, A, fmt, out, 1.0) <= BAR[dtype]
+    assert torch.equal(fs.fs_edge_softmax(fmt, vals, out=vals).view(torch.int16), out.view(torch.int16))
+
+    # the gradient, against the definition in 64 bits on the same probabilities
+    p_bits = from_dev_bits(fs.fs_blk_to_csr(fmt, out))
+    g_bits = A.vals
+    got = bits_to_f64(run_backward(fs, A, fmt, p_bits, g_bits, 0.5, inplace=True), dtype)
+    p, g = bits_to_f64(p_bits, dtype), bits_to_f64(g_bits, dtype)
+    row = np.repeat(np.arange(A.M), np.diff(A.rowptr))
+    dot, size = (np.bincount(row, weights=x, minlength=A.M)[row] for x in (p * g, np.abs(p * g)))
+    # one rounding of the result, and fp32 sums whose terms are no larger than `size`: 2^-20 holds some hundred of them
+    bound = 0.5 * p * (np.abs(g - dot) * BAR[dtype] + (size + np.abs(g)) * 2.0 ** -20) + {"f16": 2.0 ** -24, "bf16": 2.0 ** -133}[dtype]
+    assert (np.abs(got - 0.5 * p * (g - dot)) <= bound).all()
