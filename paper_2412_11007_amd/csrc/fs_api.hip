@@ -202,7 +202,7 @@ extern "C" fs_status fs_spmm(const fs_format *fmt, const void *d_vals, const voi
 static int64_t static_columns(const fs_format *fmt, int64_t N, size_t need)
 {
     if (need <= FS_STATIC_WORK_BYTES) return N;
-    if (fmt->n_blocks >= kShortPartsBelow || fmt->chunk != fs_short_part_blocks(fmt->n_blocks) * fmt->KB) return 0;
+    if (!fs_short_parts(fmt)) return 0;
     const int64_t fit = (int64_t)(FS_STATIC_WORK_BYTES / ((size_t)fmt->n_split_items * fmt->V * sizeof(float)));
     return fit >= 128 ? fit / 128 * 128 : fit / 8 * 8;  // whole passes of the kernels
 }

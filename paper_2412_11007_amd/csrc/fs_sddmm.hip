@@ -371,10 +371,8 @@ fs_status launch(const fs_format *f, const uint16_t *X, int64_t ldx, const uint1
     // 5 k, 1.2 k items: 12 and 13, at d = 64 9 and 7).  For d <= 32 the rows are short and the L2s set the time:
     // only where hubs hold most of the work (500 rows of 4 k entries among 30 k short ones: 22 and 25; R-MAT of 131 k
     // rows: 21 and 20).
-    // (Blocks are asked for as well because matrices of less than 16 k blocks are cut into shorter items.)
     const int64_t n_cut = f->n_cut_items, n_items = f->n_items;
-    const bool many = n_items >= 4096 && n_blocks >= 16384 && n_cut * (d <= 32 ? 2 : 8) >= n_items;
-    const bool ordered = f->K * d * 2 > ((int64_t)4 << 20) && (many || (d > 32 && n_items >= 1536 && n_blocks >= 12288 && n_cut * 4 >= n_items * 3));
+    const bool ordered = fs_sddmm_in_order(f, d);
     // Otherwise up to four block slots per wavefront (4 to 8 measured best from 11 thousand to 200 thousand blocks, 16 and
     // more lose 5-15 %), fewer where that leaves less than eight wavefronts per CU: then a wavefront's own chain of steps
     // is the whole time (R-MAT of 8 k rows, 3 k blocks, d = 248: 14.1 us with four slots, 8.5 us with one).

@@ -137,11 +137,28 @@ inline fs_launch_geometry fs_launch_geometry_for(const fs_format *f, int wpb, in
 constexpr int64_t kShortPartsBelow = 8192;
 __host__ __device__ inline int fs_short_part_blocks(int64_t n_blocks) { return n_blocks < 5120 ? 4 : 6; }
 
+// The rules below are in items of four slots, or of T where a caller's chunk makes parts of T < 4 blocks: what the conversion always makes
+// but by itself in small matrices, whose shorter items count as the fours they would have been at most.
+inline int64_t fs_items_of_four(const fs_format *f)
+{
+    return f->chunk < 4 * f->KB ? f->n_items : std::min(f->n_items, (f->n_blocks + 3) / 4);
+}
+inline bool fs_short_parts(const fs_format *f) { return f->n_blocks < kShortPartsBelow && f->chunk == fs_short_part_blocks(f->n_blocks) * f->KB; }
+
 // Whether fs_spmm takes passes of 256 columns for a product that wide (the reasons stand at its launch), and the columns after
 // them that have a narrower launch of their own.
-constexpr int kWidePassItems = 1024, kWidePassBlocks = 4096;  // (small matrices make more, shorter items)
-inline bool fs_spmm_wide(const fs_format *f, int64_t N) { return N > 128 && N % 64 && f->n_items >= kWidePassItems && f->n_blocks >= kWidePassBlocks; }
+constexpr int kWidePassItems = 1024;
+inline bool fs_spmm_wide(const fs_format *f, int64_t N) { return N > 128 && N % 64 && fs_items_of_four(f) >= kWidePassItems; }
 inline int64_t fs_spmm_rest(int64_t N) { return N > 256 && N % 256 <= 128 ? N % 256 : 0; }
+
+// Whether fs_sddmm takes the items in launch order (the reasons stand at its launch).
+inline bool fs_sddmm_in_order(const fs_format *f, int64_t d)
+{
+    const int64_t n_cut = f->n_cut_items, n_items = f->n_items, usual = fs_items_of_four(f);
+    const bool many = usual >= 4096 && n_cut * (d <= 32 ? 2 : 8) >= n_items;
+    const bool alike = d > 32 && usual >= 1536 && n_cut * 4 >= n_items * 3 && !fs_short_parts(f);
+    return f->K * d * 2 > ((int64_t)4 << 20) && (many || alike);
+}
 
 // Accumulators -> rounded V x NC tile, row-major in the wavefront's LDS tile (the gathered rows in it have
 // been consumed).  Lane (j, g) holds C[w*V + j][n0 + 16t + 4g .. +3] in acc[t]; `scale` multiplies on the way.
