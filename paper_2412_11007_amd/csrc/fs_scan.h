@@ -119,8 +119,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const int *__restr
 // block, or (SUMS) the blocks' sums, of which a block then adds up those before its own: up to kScanDirect of them,
 // two loads a thread and cheaper than the launch that would scan them.
 template <bool SUMS>
-__global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ data, int64_t n, const int *__restrict__ before,
-                                                             int *__restrict__ total_out)
+__global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ data, int64_t n, const int *__restrict__ before)
 {
     int ahead = 0;
     if constexpr (SUMS) {
@@ -150,10 +149,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ d
         ofs += v[i];
     }
     scan_store8(data, base, n, o);
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) {
-        data[n] = ofs;
-        if (total_out) *total_out = ofs;
-    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) data[n] = ofs;
 }
 
 // Up to 65536 values in one launch: a single workgroup of 1024 threads walks tiles of 8192 values, every
@@ -162,11 +158,8 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(int *__restrict__ d
 // latency is exposed.
 constexpr int kSmallScanThreads = 1024;
 constexpr int kSmallScanMax = 65536;
-// A second array of the same length may go along (workgroup 1).
-__global__ void __launch_bounds__(kSmallScanThreads) k_scan_small(int *__restrict__ data0, int n, int *__restrict__ total0, int *__restrict__ data1,
-                                                                  int *__restrict__ total1)
+__global__ void __launch_bounds__(kSmallScanThreads) k_scan_small(int *__restrict__ data, int n)
 {
-    int *data = blockIdx.x ? data1 : data0, *total_out = blockIdx.x ? total1 : total0;
     __shared__ int wave_sum[2][kSmallScanThreads / 64];
     constexpr int kTile = kSmallScanThreads * 8;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -203,10 +196,7 @@ __global__ void __launch_bounds__(kSmallScanThreads) k_scan_small(int *__restric
 #pragma unroll
         for (int i = 0; i < 8; i++) v[i] = nv[i];
     }
-    if (threadIdx.x == 0) {
-        data[n] = carry;
-        if (total_out) *total_out = carry;
-    }
+    if (threadIdx.x == 0) data[n] = carry;
 }
 
 size_t scan_tmp_ints(int64_t n)
@@ -220,37 +210,31 @@ size_t scan_tmp_ints(int64_t n)
     return tot + 64;
 }
 
-// data has n+1 ints; tmp has scan_tmp_ints(n) ints.  total_out (optional) also receives the grand total.  `also`, a second
-// array of the same length with a total of its own, shares the launch where one is enough.
-fs_status scan_exclusive(int *data, int64_t n, int *tmp, hipStream_t st, int *total_out = nullptr, int *also = nullptr, int *also_total = nullptr)
+// data has n+1 ints; tmp has scan_tmp_ints(n) ints.
+fs_status scan_exclusive(int *data, int64_t n, int *tmp, hipStream_t st)
 {
     int64_t nb = n <= 0 ? 1 : (n + kScanTile - 1) / kScanTile;
-    if ((nb > 1 || also) && n > 0 && n <= kSmallScanMax) {
-        k_scan_small<<<also ? 2 : 1, kSmallScanThreads, 0, st>>>(data, (int)n, total_out, also, also_total);
+    if (nb > 1 && n <= kSmallScanMax) {
+        k_scan_small<<<1, kSmallScanThreads, 0, st>>>(data, (int)n);
         FS_LAUNCH_CHECK();
         return FS_OK;
     }
-    if (also) {
-        const fs_status s = scan_exclusive(also, n, tmp, st, also_total);
-        if (s != FS_OK) return s;
-    }
     if (nb == 1) {
-        k_scan_apply<false><<<1, kScanThreads, 0, st>>>(data, n < 0 ? 0 : n, nullptr, total_out);
+        k_scan_apply<false><<<1, kScanThreads, 0, st>>>(data, n < 0 ? 0 : n, nullptr);
         FS_LAUNCH_CHECK();
         return FS_OK;
     }
     k_scan_reduce<<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp);
     FS_LAUNCH_CHECK();
     if (nb <= kScanDirect) {
-        k_scan_apply<true><<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp, total_out);
+        k_scan_apply<true><<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp);
     } else {
         fs_status s = scan_exclusive(tmp, nb, tmp + fs_align_up((size_t)nb + 1, 64), st);
         if (s != FS_OK) return s;
-        k_scan_apply<false><<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp, total_out);
+        k_scan_apply<false><<<(unsigned)nb, kScanThreads, 0, st>>>(data, n, tmp);
     }
     FS_LAUNCH_CHECK();
     return FS_OK;
 }
-
 
 }  // namespace

@@ -87,7 +87,7 @@ __device__ __forceinline__ uint32_t stored(uint32_t m8, int x) { return (uint32_
 // n_el: elements of the arrays.
 template <int DT, int V, bool PARTS, bool BWD, bool BITS>
 __global__ void __launch_bounds__(64)
-k_edge_softmax(const int4 *__restrict__ items, int n_items, const int4 *__restrict__ blk_desc,
+k_edge_softmax(const int4 *__restrict__ items, const int4 *__restrict__ blk_desc,
                const uint32_t *__restrict__ row_bits, const uint32_t *__restrict__ vec_mask, const uint16_t *in, const uint16_t *in2,
                uint16_t *out, int n_el, float *__restrict__ stats, float scale, const int2 *__restrict__ slot_range,
                int n_slots)
@@ -436,12 +436,12 @@ fs_status launch_with(const fs_format *f, const uint16_t *in, const uint16_t *in
     const int4 *items = (const int4 *)f->items_by_cost;
     const int n_items = (int)f->n_items;
     const int n_el = (int)(V * f->nvec);
-    k_edge_softmax<DT, V, false, BWD, BITS><<<(unsigned)n_items, 64, 0, st>>>(items, n_items, (const int4 *)f->blk_desc, f->blk_row_bits, f->vec_mask, in, in2, out, n_el, stats, scale,
+    k_edge_softmax<DT, V, false, BWD, BITS><<<(unsigned)n_items, 64, 0, st>>>(items, (const int4 *)f->blk_desc, f->blk_row_bits, f->vec_mask, in, in2, out, n_el, stats, scale,
                                                                         (const int2 *)f->slot_range, (int)f->n_split_items);
     FS_LAUNCH_CHECK();
     const int n_cut = (int)std::min<int64_t>(f->n_cut_items, f->n_items);
     if (f->n_split_windows > 0 && n_cut > 0) {
-        k_edge_softmax<DT, V, true, BWD, BITS><<<(unsigned)n_cut, 64, 0, st>>>(items, n_cut, (const int4 *)f->blk_desc, f->blk_row_bits, f->vec_mask, in, in2, out, n_el, stats, scale,
+        k_edge_softmax<DT, V, true, BWD, BITS><<<(unsigned)n_cut, 64, 0, st>>>(items, (const int4 *)f->blk_desc, f->blk_row_bits, f->vec_mask, in, in2, out, n_el, stats, scale,
                                                                          (const int2 *)f->slot_range, (int)f->n_split_items);
         FS_LAUNCH_CHECK();
     }
