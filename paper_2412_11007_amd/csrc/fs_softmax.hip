@@ -21,7 +21,7 @@
 // for all items: twice the registers.)
 // What bounds it is the chain item -> blocks -> values of the wavefronts and, beside it, the instructions for positions that A does
 // not store.  Lognormal graph of 262 k rows, four-row windows (46 k items, 90 MB; 4-byte pieces and a mask per vector): softmax
-// 46 -> 37 us, its gradient 69 -> 40;
+// 46 -> 37 us, its gradient 69 -> 37;
 // stencil of 1 M rows, eight-row windows 71 -> 29 and 92 -> 34.
 //
 // The same walk serves the gradient of that softmax (BWD): with p the probabilities and g the gradient
