@@ -281,7 +281,8 @@ fs_status fs_edge_softmax_workspace_bytes(const fs_format *fmt, size_t *work_byt
  * no kernel for it, this is the textbook definition, evaluated in fp32 with the row maximum
  * subtracted first and rounded once to the element type).
  *   d_in_blk, d_out_blk : V*nvec elements each, 2-byte aligned; may be the same buffer.  Positions of d_out_blk
- *                         outside the pattern get +0.0; a row without stored entries gets zeros.
+ *                         outside the pattern get +0.0; a row without stored entries gets zeros, and so does one with a
+ *                         NaN among them.
  *   scale               : finite.
  *   d_work              : workspace of fs_edge_softmax_workspace_bytes(fmt) bytes, 4-byte aligned
  *                         (may be NULL when that size is 0).

@@ -50,7 +50,7 @@ __device__ __forceinline__ float fs_to_float(uint16_t bits)
 __device__ __forceinline__ void merge_stats(float &top, float &total, float top2, float total2)
 {
     const float t = fmaxf(top, top2);
-    if (t > -INFINITY) total = total * __expf(top - t) + total2 * __expf(top2 - t);
+    total = t > -INFINITY ? total * __expf(top - t) + total2 * __expf(top2 - t) : total + total2;  // (zeros, or a NaN)
     top = t;
 }
 
@@ -387,18 +387,18 @@ k_edge_softmax(const int4 *__restrict__ items, const int4 *__restrict__ blk_desc
                     total += dot(x[r]);
                 } else {
                     float v[8], t = -INFINITY;
+                    const float was = top;
 #pragma unroll
                     for (int k = 0; k < 8; k++) {
                         v[k] = score(x[r], k);
                         t = fmaxf(t, v[k]);
                     }
-                    if (t > -INFINITY) {
-                        t = fmaxf(t, top);
-                        total *= __expf(top - t);
+                    // (a NaN, which no maximum shows, has to reach the sum even where it is all that the lane holds)
+                    top = fmaxf(t, top);
+                    const float from = top > -INFINITY ? top : 0.f;
+                    total *= __expf(was - from);
 #pragma unroll
-                        for (int k = 0; k < 8; k++) total += __expf(v[k] - t);  // exp(-inf) = 0 where nothing is stored
-                        top = t;
-                    }
+                    for (int k = 0; k < 8; k++) total += __expf(v[k] - from);  // exp(-inf) = 0 where nothing is stored
                 }
             }
         }

@@ -408,3 +408,22 @@ def test_softmax_items_around_a_register_load(fs, V, dtype, chunk, large):
     # one rounding of the result, and fp32 sums whose terms are no larger than `size`: 2^-20 holds some hundred of them
     bound = 0.5 * p * (np.abs(g - dot) * BAR[dtype] + (size + np.abs(g)) * 2.0 ** -20) + {"f16": 2.0 ** -24, "bf16": 2.0 ** -133}[dtype]
     assert (np.abs(got - 0.5 * p * (g - dot)) <= bound).all()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("V", [4, 8, 16])
+def test_softmax_of_scores_that_are_no_numbers(fs, V, dtype):
+    """A NaN makes its row zeros and touches no other, however the work list is cut and whatever else its lane holds."""
+    import torch
+    A = ragged_windows(V, dtype, 5 + V, False)
+    rng = np.random.default_rng(V)
+    row = np.repeat(np.arange(A.M), np.diff(A.rowptr))
+    bad = rng.choice(A.nnz, 60, replace=False)
+    fine = ~np.isin(row, row[bad])
+    nan = A.vals.copy()
+    nan[bad] = 0x7E00 if dtype == "f16" else 0x7FC0
+    for chunk in (0, 32, 256, 1024):
+        fmt = convert(fs, A, V, chunk)
+        want = from_dev_bits(fs.fs_blk_to_csr(fmt, fs.fs_edge_softmax(fmt, fmt.vals_blk_t())))
+        got = from_dev_bits(fs.fs_blk_to_csr(fmt, fs.fs_edge_softmax(fmt, fs.fs_csr_to_blk(fmt, to_dev(nan, dtype)))))
+        assert np.array_equal(got[fine], want[fine]) and not got[~fine].any(), chunk
